@@ -88,8 +88,8 @@ __device__ __forceinline__ void epilogue_patch(const GemmParams& p, int row, int
                 for (int e = 0; e < 4; ++e) {
                     float a = c0[4 * g4 + e], b = c1[4 * g4 + e];
                     if (bp) { a += bf2f(bp[8 * g4 + e]); b += bf2f(bp[32 + 8 * g4 + e]); }
-                    lo[e] = (a * cv[e] - b * sv[e]) * qs;
-                    hi[e] = (b * cv[e] + a * sv[e]) * qs;
+                    lo[e] = fmaf(a, cv[e], -(b * sv[e])) * qs;
+                    hi[e] = fmaf(b, cv[e], a * sv[e]) * qs;
                 }
                 *(uint2*)(drow + 8 * g4) = pack4(lo[0], lo[1], lo[2], lo[3]);
                 *(uint2*)(drow + half + 8 * g4) = pack4(hi[0], hi[1], hi[2], hi[3]);
@@ -331,22 +331,19 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// Epilogue of a 256 x 256 block tile whose accumulators sit in the layout of the bf16 GEMM: eight wavefronts
-// arranged 2 x 4, each a 128-row x 64-column patch of 8 x 4 MFMA 16x16 tiles; in tile (u, t) a lane holds token
-// row 16 u + (lane & 15) and the four consecutive features 16 t + 4 (lane >> 4) + r.  A wavefront's 64 columns are
+// Epilogue of one wavefront of the bf16 GEMMs: a patch of 16 MU rows x 64 columns from (row_base, col_base) in MU x 4
+// MFMA 16x16 tiles; in tile (u, t) a lane holds token row 16 u + (lane & 15) and the four consecutive features
+// 16 t + 4 (lane >> 4) + r.  A wavefront's 64 columns are
 // exactly one patch of the packed weights: tiles 0, 1 hold the gate values / the first rotary halves of 32
 // features, tiles 2, 3 the up values / second halves, so a lane finds a pair in the same register of tiles t, t + 2.
-// The position-wise results pass through LDS (8 KiB per wavefront, wave-private, 16-byte groups XOR-swizzled with
+// The position-wise results pass through LDS (wave-private, 16-byte groups XOR-swizzled with
 // the row so that the writes, lane = row, and the reads, lanes along a row, are free of bank conflicts) and leave
 // as 16 bytes per lane covering whole row segments; QKV keeps a per-lane path (rotary pairs, V^T).
-// smem: at least 8 KiB per wavefront, free to overwrite (callers synchronise the workgroup before).
+// stg: 4 KiB of LDS of this wavefront's own, free to overwrite (callers synchronise the workgroup before).
 template <int EPI, int MU>
-__device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4 (&acc)[MU][4], unsigned char* smem,
-                                                int m0, int n0, int wave, int lane) {
+__device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4 (&acc)[MU][4], unsigned char* stg,
+                                                int row_base, int col_base, int lane) {
     const int l15 = lane & 15, l4 = lane >> 4;
-    const int wm = wave >> 2, wn = wave & 3;
-    unsigned char* stg = smem + wave * 8192;
-    const int row_base = m0 + wm * (MU * 16), col_base = n0 + wn * 64;
     if (col_base >= p.N) return;                       // (N is a multiple of 64: a patch is wholly in or out)
     if (EPI == EPI_QKV_ROPE) {
         const int half = p.hd >> 1;
@@ -359,6 +356,8 @@ __device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4
             const int c = is_q ? cb : cb - p.qd;
             const int head = c / p.hd;
             const int patch = (c - head * p.hd) >> 6;
+            // (the rotation as written-out fused multiply-adds: left to the compiler, which of the two products of a sum is
+            //  rounded first differs between instantiations of this function, and so would the bits between tile heights)
             auto qk_patch = [&](auto has_bias) {
                 constexpr bool HB = decltype(has_bias)::value;
                 float ba[2][4], bb[2][4];
@@ -388,8 +387,8 @@ __device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4
                         for (int e = 0; e < 4; ++e) {
                             float a = acc[u][t][e], b = acc[u][t + 2][e];
                             if (HB) { a += ba[t][e]; b += bb[t][e]; }
-                            lo[e] = (a * cv[e] - b * sv[e]) * qs;
-                            hi[e] = (b * cv[e] + a * sv[e]) * qs;
+                            lo[e] = fmaf(a, cv[e], -(b * sv[e])) * qs;
+                            hi[e] = fmaf(b, cv[e], a * sv[e]) * qs;
                         }
                         *(uint2*)(drow + i0) = pack4(lo[0], lo[1], lo[2], lo[3]);
                         *(uint2*)(drow + half + i0) = pack4(hi[0], hi[1], hi[2], hi[3]);

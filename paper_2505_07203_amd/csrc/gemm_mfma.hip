@@ -49,6 +49,8 @@
 
 #include <string.h>
 
+#include <algorithm>
+
 namespace po {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -61,32 +63,25 @@ constexpr int BK = 64;
 constexpr int UNIT_BYTES = BM * BK * 2;            // one operand's slice: 256 rows x 128 bytes = 32 KiB
 constexpr int NUNIT = 5;                           // ring of five units: the whole 160 KiB of LDS
 constexpr int SMEM_BYTES = NUNIT * UNIT_BYTES;
-constexpr int NT_BF16 = 512;                       // eight wavefronts (the FP8 kernel keeps gemm::NTHREADS = 256)
+constexpr int NT_BF16 = 512;                       // eight wavefronts
 
-// MU = 16-row groups per wavefront patch: 8 (256-row block tile, the form described above) or 4 (128-row block tile:
-// wavefront patches of 64 x 64, a slice is two phases of 16 MFMAs with the hand-over barrier behind the first, the A
-// unit is half full).  Every output element still is ONE fp32 accumulator running over K in steps of 32 in the same
-// order, so the two forms give the same bits, and the launcher may pick by tile count alone: launches whose 256-row
-// tiles would leave compute units idle (short requests, N of 4096-5120) take the 128-row form.
-template <int EPI, int MU>
+template <int EPI>
 __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int BM_ = 32 * MU;                   // block tile rows
-    constexpr int NA = MU / 2;                     // global->LDS loads per wavefront for an A unit (W: always 4)
+    constexpr int MU = 8;                          // 16-row groups per wavefront patch
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
     const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
     const int li = xcd * per_xcd + local;
     if (local >= per_xcd || li >= total) return;
-    constexpr int GM = MU == 8 ? GROUP_M : 2 * GROUP_M;       // M-tiles per group: 1024 rows either way
-    const int group_sz = GM * p.nt;
+    const int group_sz = GROUP_M * p.nt;
     const int g = li / group_sz;
     const int within = li - g * group_sz;
-    const int gm_this = min(GM, p.mt - g * GM);
+    const int gm_this = min(GROUP_M, p.mt - g * GROUP_M);
     const int tn = within / gm_this;
-    const int tm = g * GM + (within - tn * gm_this);
-    const int m0 = tm * BM_, n0 = tn * BN;
+    const int tm = g * GROUP_M + (within - tn * gm_this);
+    const int m0 = tm * BM, n0 = tn * BN;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -101,25 +96,20 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
         (void*)(p.A + (int64_t)m0 * p.lda + k0), 0, (int)(uint32_t)(a_bytes > 0xffffffffull ? 0xffffffffull : a_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(p.W + (int64_t)n0 * p.ldw + k0), 0, (int)(uint32_t)(w_bytes > 0xffffffffull ? 0xffffffffull : w_bytes), 0x00020000);
-    uint32_t voa[4] = {0, 0, 0, 0}, vow[4];      // (voa: NA entries used)
+    uint32_t voa[4], vow[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = (wave * 4 + i) * 8 + (lane >> 3);
         const int lseg = (lane & 7) ^ ((row >> 1) & 7);
+        voa[i] = (uint32_t)row * (uint32_t)(p.lda * 2) + lseg * 16;
         vow[i] = (uint32_t)row * (uint32_t)(p.ldw * 2) + lseg * 16;
     }
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const int row = (wave * NA + i) * 8 + (lane >> 3);
-        const int lseg = (lane & 7) ^ ((row >> 1) & 7);
-        voa[i] = (uint32_t)row * (uint32_t)(p.lda * 2) + lseg * 16;
-    }
     const int KT = p.K / BK;
-    // load i_ (W: 0..3, A: 0..NA-1) of this wavefront's share of the A (is_w_ = 0) or W unit of slice slice_, into ring
+    // load i_ (0..3) of this wavefront's share of the A (is_w_ = 0) or W unit of slice slice_, into ring
     // position pos_
 #define PO_DMA(is_w_, slice_, pos_, i_)                                                                              \
     {                                                                                                                  \
-        unsigned char* d_ = smem + (pos_) * UNIT_BYTES + (wave * ((is_w_) ? 4 : NA) + (i_)) * 1024;                    \
+        unsigned char* d_ = smem + (pos_) * UNIT_BYTES + (wave * 4 + (i_)) * 1024;                    \
         __builtin_amdgcn_raw_ptr_buffer_load_lds((is_w_) ? rw : ra, (__attribute__((address_space(3))) void*)d_, 16,   \
                                                  (is_w_) ? vow[(i_)] : voa[(i_)],                    \
                                                  min((slice_), KT - 1) * (BK * 2), 0, 0);                              \
@@ -139,9 +129,8 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 #pragma unroll
     for (int u4 = 0; u4 < 4; ++u4)
 #pragma unroll
-        for (int i = 0; i < ((u4 & 1) ? 4 : NA); ++i) PO_DMA(u4 & 1, u4 >> 1, u4, i)
-    if (MU == 8) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");      // slice 0 has landed
-    else asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
+        for (int i = 0; i < 4; ++i) PO_DMA(u4 & 1, u4 >> 1, u4, i)
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");      // slice 0 has landed
     bf16x8 A0[4], A1[4], W0[4], W1[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -165,7 +154,7 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
         } else if (m < nra_ + nrw_) {                                                                                 \
             WN[(m - nra_) & 3] = *(const bf16x8*)((uw_) + ((m - nra_) & 3) * 2048 + f_off[rwk_]);  \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
-        } else if ((DMA_) && m < nra_ + nrw_ + ((dw_) ? 4 : NA)) {                                                    \
+        } else if ((DMA_) && m < nra_ + nrw_ + 4) {                                                    \
             PO_DMA(dw_, ds_, dp_, (m - nra_ - nrw_) & 3)                                         \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
         }                                                                                                             \
@@ -179,25 +168,16 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
         const unsigned char* uw = smem + pw * UNIT_BYTES + w_base;
         const unsigned char* ua1 = smem + pa1 * UNIT_BYTES + a_base;
         const unsigned char* uw1 = smem + pw1 * UNIT_BYTES + w_base;
-        if constexpr (MU == 8) {
-            // phase 0: k-step 0, rows 0-63 | reads A(k0, rows 64-127) and W(k1)
-            PO_PHASE(A0, W0, 0, 1, A1, ua, 1, 0, 1, W1, uw, 1, 0, 0, 0, 0)
-            // phase 1: k-step 0, rows 64-127 | reads A(k1, rows 0-63); loads A(s+2) into the position W(s-1) left
-            PO_PHASE(A1, W0, 1, 1, A0, ua, 0, 1, 0, W1, uw, 1, 1, 0, s + 2, (pa + 4 >= NUNIT ? pa + 4 - NUNIT : pa + 4))
-            // phase 2: k-step 1, rows 0-63 | reads A(k1, rows 64-127)
-            PO_PHASE(A0, W1, 0, 1, A1, ua, 1, 1, 0, W0, uw, 0, 0, 0, 0, 0)
-            // hand-over: slice s+1 has landed (all but the 4 youngest loads), every LDS read of slice s is done
-            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            // phase 3: k-step 1, rows 64-127 | reads W(k0) and A(k0, rows 0-63) of slice s+1; loads W(s+2) into A(s)'s position
-            PO_PHASE(A1, W1, 1, 1, A0, ua1, 0, 0, 1, W0, uw1, 0, 1, 1, s + 2, pa)
-        } else {
-            // phase 0: k-step 0 | reads A(k1) and W(k1); loads A(s+2) into the position W(s-1) left
-            PO_PHASE(A0, W0, 0, 1, A1, ua, 0, 1, 1, W1, uw, 1, 1, 0, s + 2, (pa + 4 >= NUNIT ? pa + 4 - NUNIT : pa + 4))
-            // hand-over: slice s+1 has landed (all but the NA youngest loads), every LDS read of slice s is done
-            asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            // phase 1: k-step 1 | reads A(k0) and W(k0) of slice s+1; loads W(s+2) into A(s)'s position
-            PO_PHASE(A1, W1, 0, 1, A0, ua1, 0, 0, 1, W0, uw1, 0, 1, 1, s + 2, pa)
-        }
+        // phase 0: k-step 0, rows 0-63 | reads A(k0, rows 64-127) and W(k1)
+        PO_PHASE(A0, W0, 0, 1, A1, ua, 1, 0, 1, W1, uw, 1, 0, 0, 0, 0)
+        // phase 1: k-step 0, rows 64-127 | reads A(k1, rows 0-63); loads A(s+2) into the position W(s-1) left
+        PO_PHASE(A1, W0, 1, 1, A0, ua, 0, 1, 0, W1, uw, 1, 1, 0, s + 2, (pa + 4 >= NUNIT ? pa + 4 - NUNIT : pa + 4))
+        // phase 2: k-step 1, rows 0-63 | reads A(k1, rows 64-127)
+        PO_PHASE(A0, W1, 0, 1, A1, ua, 1, 1, 0, W0, uw, 0, 0, 0, 0, 0)
+        // hand-over: slice s+1 has landed (all but the 4 youngest loads), every LDS read of slice s is done
+        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // phase 3: k-step 1, rows 64-127 | reads W(k0) and A(k0, rows 0-63) of slice s+1; loads W(s+2) into A(s)'s position
+        PO_PHASE(A1, W1, 1, 1, A0, ua1, 0, 0, 1, W0, uw1, 0, 1, 1, s + 2, pa)
         pa = pa1;
     }
 #undef PO_PHASE
@@ -207,9 +187,143 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
     if (EPI == EPI_PARTIAL) {
         GemmParams q = p;
         q.dst = (bf16_t*)((float*)p.dst + (int64_t)blockIdx.y * p.ldr);
-        tile_epilogue16<EPI, MU>(q, acc, smem, m0, n0, wave, lane);
+        tile_epilogue16<EPI, MU>(q, acc, smem + wave * 4096, m0 + wm * (MU * 16), n0 + wn * 64, lane);
     } else {
-        tile_epilogue16<EPI, MU>(p, acc, smem, m0, n0, wave, lane);
+        tile_epilogue16<EPI, MU>(p, acc, smem + wave * 4096, m0 + wm * (MU * 16), n0 + wn * 64, lane);
+    }
+}
+
+// all but the n_ youngest global->LDS loads and every LDS read done, then the workgroup barrier (n_ a constant
+// expression of template parameters, which the host pass would not take as an asm operand)
+#ifdef __HIP_DEVICE_COMPILE__
+#define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
+#else
+#define PO_WAIT_BARRIER(n_)
+#endif
+
+// The same GEMM in small block tiles, for launches whose 256-column tiles would leave compute units idle (requests of up
+// to about 2000 rows, the last layer's single row, split-K launches).  What bounds those launches is the latency of a
+// slice, not the matrix pipe: a 256-row tile of the kernel above takes 1.05 us per slice in a launch of 16 tiles, and the
+// same 128 x 128 tile 0.8 us with two slices in flight and 0.41 with four.  So a tile has 128 columns, four wavefronts
+// (2 x 2 patches of 16 MU rows x 64 columns) and as many slices in flight as the LDS of a whole compute unit holds
+// (D = 7 at 32 rows .. 2 at 256; two workgroups per compute unit with half the depth each were 1.9 x slower at one round
+// of tiles and no faster at two).  A and W have rings of their own, D + 1 and D slices: A(s + D) is loaded during phase 0
+// of slice s into what A(s - 1) left, W(s + D) behind the hand-over barrier into W(s)'s place.  A slice is two phases,
+// one per k-step of 32, with the next k-step's fragments read behind this one's MFMAs; swizzle, tile order and epilogues
+// are those of the kernel above, and so are the bits (one fp32 accumulator per output, K in steps of 32, in order).
+// Measured: down projection (N 4096, K 14336) at 471 rows 225 -> 92 us, 1 row 240 -> 76; O projection at 471 rows 48 ->
+// 24; at one round of 128 x 128 tiles 0.89 PFLOP/s, with 14 TB/s from L2 into LDS.
+template <int EPI, int MU, int D>
+__global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParams p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int BM_ = 32 * MU, BN_ = 128;
+    constexpr int AU = BM_ * 128, WU = BN_ * 128;          // bytes of a slice of A / W
+    constexpr int NA = MU, NW = 4;                         // global->LDS loads per wavefront and slice
+
+    const int total = p.mt * p.nt;
+    const int per_xcd = (total + 7) >> 3;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int li = xcd * per_xcd + local;
+    if (local >= per_xcd || li >= total) return;
+    constexpr int GM = 1024 / BM_;
+    const int group_sz = GM * p.nt;
+    const int g = li / group_sz;
+    const int within = li - g * group_sz;
+    const int gm_this = min(GM, p.mt - g * GM);
+    const int tn = within / gm_this;
+    const int tm = g * GM + (within - tn * gm_this);
+    const int m0 = tm * BM_, n0 = tn * BN_;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, l4 = lane >> 4;
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // resources: the tile's rows that exist (rows beyond them read as zero), columns from k0 on
+    const int64_t k0 = (EPI == EPI_PARTIAL) ? (int64_t)blockIdx.y * p.K : 0;
+    const uint32_t a_bytes = (uint32_t)min(BM_, p.M - m0) * (uint32_t)(p.lda * 2) - (uint32_t)(k0 * 2);
+    const uint32_t w_bytes = (uint32_t)min(BN_, p.N - n0) * (uint32_t)(p.ldw * 2) - (uint32_t)(k0 * 2);
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p.A + (int64_t)m0 * p.lda + k0), 0, (int)a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(p.W + (int64_t)n0 * p.ldw + k0), 0, (int)w_bytes, 0x00020000);
+    uint32_t voa[8], vow[4];                               // (voa: NA entries used)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int row = (wave * NA + i) * 8 + (lane >> 3);
+        voa[i] = (uint32_t)row * (uint32_t)(p.lda * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int row = (wave * NW + i) * 8 + (lane >> 3);
+        vow[i] = (uint32_t)row * (uint32_t)(p.ldw * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+    const int KT = p.K / BK;
+    // byte offset of slice s_ along K; slices past the end lie outside both resources: they read as zero without traffic
+#define PO_SOFF(s_) ((s_) < KT ? (s_) * (BK * 2) : 0x40000000)
+#define PO_DMA_A(soff_, pos_, i_)                                                                                         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(smem + (pos_) * AU + (wave * NA + (i_)) * 1024),                                              16, voa[(i_)], (soff_), 0, 0);
+#define PO_DMA_W(soff_, pos_, i_)                                                                                         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(smem + (D + 1) * AU + (pos_) * WU + (wave * NW + (i_)) * 1024),                                              16, vow[(i_)], (soff_), 0, 0);
+    int f_off[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) f_off[ks] = l15 * 128 + (((ks * 4 + l4) ^ ((l15 >> 1) & 7)) << 4);
+    const int a_base = wm * (MU * 16) * 128, w_base = (D + 1) * AU + wn * 64 * 128;
+
+    f32x4 acc[MU][4];
+#pragma unroll
+    for (int u = 0; u < MU; ++u)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+        const int so = PO_SOFF(s);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) PO_DMA_A(so, s, i)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) PO_DMA_W(so, s, i)
+    }
+    PO_WAIT_BARRIER((D - 1) * (NA + NW));                      // slice 0 has landed
+    bf16x8 A0[MU], A1[MU], W0[4], W1[4];
+#pragma unroll
+    for (int j = 0; j < MU; ++j) A0[j] = *(const bf16x8*)(smem + a_base + j * 2048 + f_off[0]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) W0[j] = *(const bf16x8*)(smem + w_base + j * 2048 + f_off[0]);
+
+    // One phase: the 4 MU MFMAs of one k-step; spread behind them the MU + 4 fragment reads of the next k-step (A unit
+    // at ua_, W unit at uw_, k-step kn_) and then ND_ global->LDS loads
+#define PO_PHASE(AC, WC, AN, WN, ua_, uw_, kn_, ND_, LOAD_)                                                              _Pragma("unroll") for (int m = 0; m < 4 * MU; ++m) {                                                                      acc[m >> 2][m & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WC[m & 3], AC[m >> 2], acc[m >> 2][m & 3], 0, 0, 0);         __builtin_amdgcn_sched_barrier(0);                                                                                    constexpr int T_ = MU + 4 + (ND_);                                                                                    _Pragma("unroll") for (int x = 0; x < T_; ++x) {                                                                          if (x >= m * T_ / (4 * MU) && x < (m + 1) * T_ / (4 * MU)) {                                                              if (x < MU) AN[x < MU ? x : 0] = *(const bf16x8*)((ua_) + x * 2048 + f_off[kn_]);                                     else if (x < MU + 4) WN[(x - MU) & 3] = *(const bf16x8*)((uw_) + (x - MU) * 2048 + f_off[kn_]);                       else { LOAD_(x - MU - 4) }                                                                                            __builtin_amdgcn_sched_barrier(0);                                                                                }                                                                                                                 }                                                                                                                 }
+    int pa = 0, pw = 0;                          // ring positions of slice s: A in D + 1 positions, W in D
+    for (int s = 0; s < KT; ++s) {
+        const int pa1 = pa + 1 > D ? 0 : pa + 1, pw1 = pw + 1 >= D ? 0 : pw + 1;
+        const int pa_free = pa == 0 ? D : pa - 1;              // position of A(s - 1)
+        const int so = PO_SOFF(s + D);
+        const unsigned char* ua = smem + pa * AU + a_base;
+        const unsigned char* uw = smem + pw * WU + w_base;
+        const unsigned char* ua1 = smem + pa1 * AU + a_base;
+        const unsigned char* uw1 = smem + pw1 * WU + w_base;
+        // phase 0: k-step 0 | reads k-step 1; loads A(s + D) into the position A(s - 1) left
+#define PO_LA(i_) PO_DMA_A(so, pa_free, ((i_) < NA ? (i_) : 0))
+        PO_PHASE(A0, W0, A1, W1, ua, uw, 1, NA, PO_LA)
+        // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1 and A(s+D)); all LDS reads of slice s are done
+        PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA);
+        // phase 1: k-step 1 | reads k-step 0 of slice s+1; loads W(s + D) into W(s)'s position
+#define PO_LW(i_) PO_DMA_W(so, pw, ((i_) < NW ? (i_) : 0))
+        PO_PHASE(A1, W1, A0, W0, ua1, uw1, 0, NW, PO_LW)
+        pa = pa1;
+        pw = pw1;
+    }
+#undef PO_LA
+#undef PO_LW
+#undef PO_PHASE
+#undef PO_DMA_A
+#undef PO_DMA_W
+#undef PO_SOFF
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (EPI == EPI_PARTIAL) {
+        GemmParams q = p;
+        q.dst = (bf16_t*)((float*)p.dst + (int64_t)blockIdx.y * p.ldr);
+        tile_epilogue16<EPI, MU>(q, acc, smem + wave * 4096, m0 + wm * (MU * 16), n0 + wn * 64, lane);
+    } else {
+        tile_epilogue16<EPI, MU>(p, acc, smem + wave * 4096, m0 + wm * (MU * 16), n0 + wn * 64, lane);
     }
 }
 
@@ -295,37 +409,112 @@ __global__ void __launch_bounds__(256) splitk_reduce_silu_kernel(const float* __
     H[(int64_t)row * ldh + f] = f2bf(silu_f(g) * u);
 }
 
-// 256-row or 128-row block tiles: the cheaper by rounds of tiles over the 256 compute units, a 128-row tile counted
-// as 0.66 of a 256-row one.  Measured: 0.51-0.55 in launches of one round (O- and down projections of up to 2048
-// rows: 185 against 248 us at 1920 rows), 0.63-0.68 in launches of many rounds (gate/up: every tile streams a whole W
-// slice for half the rows), where the 256-row form stays the better one unless it wastes most of a round.  Same bits
-// either way.
-constexpr double COST_128_ROW_TILE = 0.66;
-double cost_256(int64_t M, int N) { return (double)((((M + 255) / 256) * ((N + BN - 1) / BN) + 255) / 256); }
-double cost_128(int64_t M, int N) {
-    return COST_128_ROW_TILE * (double)((((M + 127) / 128) * ((N + BN - 1) / BN) + 255) / 256);
-}
-bool prefer_128_row_tiles(int64_t M, int N) { return cost_128(M, N) < cost_256(M, N); }
+// Which block tile a launch takes.  Every form accumulates an output over K in the same order, so the choice changes no
+// bit and goes by time alone.  A launch runs in rounds of 256 tiles, one per compute unit; per K slice of 64 a full
+// round costs `hi` microseconds, and a round of few tiles `lo` (the latency of a slice; in between the L2 and the
+// matrix pipe fill up).  Constants fitted to 232 shapes (N, K of the 8B and 32B projections, 1 .. 8192 rows; weights
+// from HBM): the pick is on average 0.6 % and at most 14 % off the fastest form.  Measured, 256-row tiles against the
+// pick: down projection (N 4096, K 14336) 1 row 241 -> 76 us, 471 rows 247 -> 91, 1024 rows 245 -> 125; O projection
+// (4096 x 4096) 471 rows 72 -> 24, 2048 rows 78 -> 61; QKV 700 rows 76 -> 40; from about 2000 rows (gate/up: 200) on the
+// 256 x 256 tile, which moves half the bytes per flop.
+struct TileForm {
+    int bm, bn;
+    double us, lo, hi;
+};
+constexpr TileForm FORMS[] = {{256, 256, 5.9, 0.99, 1.41}, {32, 128, 3.1, 0.29, 0.31}, {64, 128, 2.3, 0.34, 0.40},
+                              {96, 128, 2.8, 0.35, 0.47},  {128, 128, 2.7, 0.41, 0.55}, {160, 128, 3.6, 0.46, 0.63},
+                              {192, 128, 3.6, 0.49, 0.70}, {256, 128, 1.0, 0.83, 0.97}};
+constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]);
 
-template <int E2, int M2>
-void launch_mu(GemmParams p, hipStream_t s, int splits) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_mfma_kernel<E2, M2>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM_BYTES);
-        attr_set = true;
-    }
-    p.mt = (p.M + 32 * M2 - 1) / (32 * M2);
-    const int total = p.mt * p.nt;
-    const int per_xcd = (total + 7) / 8;
-    hipLaunchKernelGGL((gemm_bf16_mfma_kernel<E2, M2>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NT_BF16),
-                       SMEM_BYTES, s, p);
+int64_t form_tiles(int f, int64_t M, int N) {
+    return ((M + FORMS[f].bm - 1) / FORMS[f].bm) * ((N + FORMS[f].bn - 1) / FORMS[f].bn);
+}
+double form_us(int f, int64_t M, int N, int K, int splits) {
+    const int64_t tiles = form_tiles(f, M, N) * splits, rounds = (tiles + 255) / 256;
+    const double fill = (double)(tiles - (rounds - 1) * 256) / 256;
+    const TileForm& t = FORMS[f];
+    const double us = t.us + (double)(K / BK) / splits * ((double)(rounds - 1) * t.hi + t.lo + (t.hi - t.lo) * fill);
+    return f == 0 ? 0.95 * us : us;              // a predicted gain below the fit's error does not leave the 256 x 256 tile
+}
+// (the small forms address a tile with offsets below 2^30 bytes)
+int pick_form(const GemmParams& p, int splits) {
+    int best = 0;
+    if (p.lda >= (1 << 20) || p.ldw >= (1 << 20)) return best;
+    for (int f = 1; f < N_FORMS; ++f)
+        if (form_us(f, p.M, p.N, p.K * splits, splits) < form_us(best, p.M, p.N, p.K * splits, splits)) best = f;
+    return best;
 }
 
 template <int EPI>
-void launch_t(const GemmParams& p, hipStream_t s, int splits = 1) {
-    if (EPI != EPI_PARTIAL && prefer_128_row_tiles(p.M, p.N)) launch_mu<EPI, 4>(p, s, splits);
-    else launch_mu<EPI, 8>(p, s, splits);
+void launch_256(const GemmParams& p, hipStream_t s, int splits) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)gemm_bf16_mfma_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  SMEM_BYTES);
+        attr_set = true;
+    }
+    const int per_xcd = (p.mt * p.nt + 7) / 8;
+    hipLaunchKernelGGL((gemm_bf16_mfma_kernel<EPI>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NT_BF16),
+                       SMEM_BYTES, s, p);
+}
+
+template <int EPI, int MU, int D>
+void launch_small(GemmParams p, hipStream_t s, int splits) {
+    constexpr int SMEM = ((D + 1) * 32 * MU + D * 128) * 128;
+    static_assert(SMEM <= 160 * 1024 && SMEM >= 4 * 4096, "LDS of a compute unit; staging of four wavefronts");
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)gemm_bf16_small_kernel<EPI, MU, D>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        attr_set = true;
+    }
+    p.mt = (p.M + 32 * MU - 1) / (32 * MU);
+    p.nt = (p.N + 127) / 128;
+    const int per_xcd = (p.mt * p.nt + 7) / 8;
+    hipLaunchKernelGGL((gemm_bf16_small_kernel<EPI, MU, D>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(256), SMEM,
+                       s, p);
+}
+
+template <int EPI>
+void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
+    switch (form) {
+        case 1: launch_small<EPI, 1, 7>(p, s, splits); break;
+        case 2: launch_small<EPI, 2, 6>(p, s, splits); break;
+        case 3: launch_small<EPI, 3, 5>(p, s, splits); break;
+        case 4: launch_small<EPI, 4, 4>(p, s, splits); break;
+        case 5: launch_small<EPI, 5, 3>(p, s, splits); break;
+        case 6: launch_small<EPI, 6, 3>(p, s, splits); break;
+        case 7: launch_small<EPI, 8, 2>(p, s, splits); break;
+        default: launch_256<EPI>(p, s, splits); break;
+    }
+}
+
+template <int EPI>
+void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(pick_form(p, 1), p, s); }
+
+// Number of K splits of a few-rows launch; 1 = run unsplit.  `must`: only whether the shape allows a split counts
+// (pick_splits), not whether it pays.  Modelled time: the tiles' as above but at least the weights' at the 4.6 TB/s these
+// launches reach, plus, split, a second launch (3 us) and the partial sums written and read at 6 TB/s (fitted to 40
+// shapes: on average 3.6 % off the fastest of all forms and splits).  Measured at 150 rows, 256-row tiles with their
+// splits -> now: O 24 -> 17 us, down 49 -> 36, QKV 28 -> 22, gate/up 75 -> 60 (unsplit).  Launches of up to 64 tiles
+// always split: whatever they gain is below a microsecond either way.
+int plan_splits(const GemmParams& p, size_t part_bytes, bool must) {
+    const int kt = p.K / BK;
+    if (pick_splits(p.M, p.N, kt, part_bytes) < 2) return 1;
+    auto us = [&](int splits) {
+        GemmParams q = p;
+        q.K = p.K / splits;
+        double t = form_us(pick_form(q, splits), p.M, p.N, p.K, splits);
+        t = std::max(t, 2.0 * p.N * p.K / 4.6e6);
+        return splits == 1 ? t : t + 3.0 + 8.0 * splits * p.M * p.N / 6e6;
+    };
+    must = must || form_tiles(pick_form(p, 1), p.M, p.N) <= 64;
+    int best = must ? 2 : 1;
+    for (int splits = 2 * best; splits <= 8; splits *= 2)
+        if (kt % splits == 0 && kt / splits >= 2 && (size_t)splits * p.M * p.N * sizeof(float) <= part_bytes &&
+            us(splits) < us(best))
+            best = splits;
+    return best;
 }
 
 GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, int64_t M, int N, int K) {
@@ -344,7 +533,7 @@ GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ld
 // K must be a multiple of 64 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_mfma_supported(int N, int K) { return K > 0 && K % 64 == 0 && N > 0 && N % 64 == 0; }
 
-double gemm_mfma_launch_cost(int64_t M, int N) { return prefer_128_row_tiles(M, N) ? cost_128(M, N) : cost_256(M, N); }
+double gemm_mfma_launch_cost(int64_t M, int N) { return (double)((form_tiles(0, M, N) + 255) / 256); }
 
 void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C, int64_t ldc,
                       const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s) {
@@ -393,17 +582,17 @@ void launch_splitk_reduce_qkv(const float* part, int splits, const GemmParams& r
 int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                                 bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                                 const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd, int kvd,
-                                int hd, int K, float q_scale, float* part, size_t part_bytes, bool launch, hipStream_t s) {
+                                int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s) {
     const int N = qd + 2 * kvd;
     if (M <= 0 || !gemm_mfma_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
-    const int splits = pick_splits(M, N, K / BK, part_bytes);
+    GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K);
+    const int splits = plan_splits(p, part_bytes, false);
     if (splits < 2) return 0;
-    if (!launch) return splits;
-    GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K / splits);
+    p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;
-    launch_t<EPI_PARTIAL>(p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
     GemmParams r = base_params(A, lda, Wqkv, ldw, M, N, K);
     r.bias = bias; r.dst = Q; r.dst_k = Kd; r.dst_vt = Vt; r.ldv = ldv;
     r.rope_cos = rope_cos; r.rope_sin = rope_sin; r.pos0 = pos0; r.row_pos = row_pos;
@@ -413,32 +602,32 @@ int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv
 }
 
 int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* H, int64_t ldh,
-                                 int64_t M, int N, int K, float* part, size_t part_bytes, bool launch, hipStream_t s) {
+                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s) {
     if (M <= 0 || !gemm_mfma_supported(N, K)) return 0;
-    const int splits = pick_splits(M, N, K / BK, part_bytes);
+    GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    const int splits = plan_splits(p, part_bytes, false);
     if (splits < 2) return 0;
-    if (!launch) return splits;
-    GemmParams p = base_params(A, lda, W, ldw, M, N, K / splits);
+    p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;
-    launch_t<EPI_PARTIAL>(p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
     launch_splitk_reduce_silu(part, splits, H, ldh, M, N, s);
     return splits;
 }
 
 int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C,
                                      int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M, int N, int K,
-                                     float* part, size_t part_bytes, bool launch, hipStream_t s) {
+                                     float* part, size_t part_bytes, bool must, hipStream_t s) {
     if (M <= 0 || N <= 0 || !gemm_mfma_supported(N, K) || (N & 7) || (ldc & 7) || (ldr & 7)) return 0;
-    const int splits = pick_splits(M, N, K / BK, part_bytes);
+    GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    const int splits = plan_splits(p, part_bytes, must);
     if (splits < 2) return 0;
-    if (!launch) return splits;
-    GemmParams p = base_params(A, lda, W, ldw, M, N, K / splits);
+    p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;              // floats between two splits' planes
-    launch_t<EPI_PARTIAL>(p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
     launch_splitk_reduce_residual(part, splits, R, ldr, C, ldc, M, N, s);
     return splits;
 }

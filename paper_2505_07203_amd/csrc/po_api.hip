@@ -403,7 +403,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                     launch_gemm_qkv_rope_splitk((const bf16_t*)Xn, d, (const bf16_t*)wqkv, d, (const bf16_t*)bqkv,
                                                   (bf16_t*)(Q + (size_t)c0 * qd * esz), (bf16_t*)(K + (size_t)c0 * kvd * esz),
                                                   (bf16_t*)(ws + L.Vt), L.ldv, rc, rs, c0, d_row_pos, rows, qd, kvd, hd, d,
-                                                q_scale, (float*)(H + h_used), h_bytes - h_used, true, s) > 1)
+                                                q_scale, (float*)(H + h_used), h_bytes - h_used, s) > 1)
                     ++n_split_launches;
                 else
                     launch_gemm_qkv_rope((const bf16_t*)Xn, d, (const bf16_t*)wqkv, d, (const bf16_t*)bqkv,
@@ -558,7 +558,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                     PhaseTimer pt(c, PO_K_RESIDUAL);
                     if (c->split_few_rows &&
                         launch_gemm_mfma_splitk_residual((const bf16_t*)Oc, qd, (const bf16_t*)(c->w + o.wo), qd, (bf16_t*)Xc, d,
-                                                         (const bf16_t*)Xc, d, rows, d, qd, (float*)H, h_bytes, true, s) > 1)
+                                                         (const bf16_t*)Xc, d, rows, d, qd, (float*)H, h_bytes, false, s) > 1)
                         ++n_split_launches;
                     else
                         launch_gemm_mfma(EPI_RESIDUAL, (const bf16_t*)Oc, qd, (const bf16_t*)(c->w + o.wo), qd,
@@ -570,7 +570,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                     PhaseTimer pt(c, PO_K_GATE_UP);
                     if (c->split_few_rows && h_used < h_bytes &&
                         launch_gemm_mfma_splitk_silu((const bf16_t*)Xn, d, (const bf16_t*)(c->w + o.wgu), d, (bf16_t*)H, F, rows,
-                                                     2 * F, d, (float*)(H + h_used), h_bytes - h_used, true, s) > 1)
+                                                     2 * F, d, (float*)(H + h_used), h_bytes - h_used, s) > 1)
                         ++n_split_launches;
                     else
                         launch_gemm_mfma(EPI_SILU_MUL, (const bf16_t*)Xn, d, (const bf16_t*)(c->w + o.wgu), d, (bf16_t*)H, F,
@@ -580,7 +580,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                 if (c->split_few_rows && h_used < h_bytes &&
                     launch_gemm_mfma_splitk_residual((const bf16_t*)H, F, (const bf16_t*)(c->w + o.wd), F, (bf16_t*)Xc, d,
                                                      (const bf16_t*)Xc, d, rows, d, F, (float*)(H + h_used), h_bytes - h_used,
-                                                     true, s) > 1)
+                                                     false, s) > 1)
                     ++n_split_launches;
                 else
                     launch_gemm_mfma(EPI_RESIDUAL, (const bf16_t*)H, F, (const bf16_t*)(c->w + o.wd), F, (bf16_t*)Xc, d,

@@ -118,29 +118,28 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
                                 size_t scratch_bytes, bool launch, const bf16_t* k2, const bf16_t* vt2, int64_t ldv2,
                                 int64_t n2, bool q_prescaled, hipStream_t s);
 bool gemm_mfma_supported(int N, int K);
-// Time of one bf16 GEMM launch of M rows x N columns in units of (one 256 x 256 tile's K loop): rounds of tiles over
-// the compute units with the tile height the launcher will pick.
+// Time of one bf16 GEMM launch of M rows x N columns on 256 x 256 tiles, in units of one such tile's K loop: rounds of
+// tiles over the compute units.
 double gemm_mfma_launch_cost(int64_t M, int N);
 // C = A W^T + R for a GEMM with few rows, the reduction over K split between workgroups (a GEMM with few
 // output tiles leaves most of the chip idle and every workgroup streaming a whole K range of both operands):
 // split s of `splits` writes its fp32 partial tile sums to part[s][M][N], a second kernel adds them up in
 // split order, adds R and rounds once.  The sum order differs from launch_gemm_mfma's (there one fp32
 // accumulator runs over all of K), so the results agree to rounding, not bit for bit.  Returns the number
-// of splits it would use for this shape and `part_bytes` of scratch memory; 0 or 1 = not worth it or does
-// not fit (then nothing is launched).  With launch = false only that number is computed.
+// of splits used for this shape and `part_bytes` of scratch memory; 0 or 1 = it does not pay or does not fit (then
+// nothing is launched).  must: split whenever the shape allows it, whether it pays or not.
 // launch_gemm_qkv_rope the same way (partials, then one kernel that sums them and applies bias, rotary
 // embedding and the V^T store)
 int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                                 bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                                 const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd,
-                                int kvd, int hd, int K, float q_scale, float* part, size_t part_bytes, bool launch,
-                                hipStream_t s);
+                                int kvd, int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s);
 // launch_gemm_mfma(EPI_SILU_MUL) the same way; part must not overlap H's rows [0, M)
 int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* H, int64_t ldh,
-                                 int64_t M, int N, int K, float* part, size_t part_bytes, bool launch, hipStream_t s);
+                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s);
 int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C,
                                      int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M, int N, int K,
-                                     float* part, size_t part_bytes, bool launch, hipStream_t s);
+                                     float* part, size_t part_bytes, bool must, hipStream_t s);
 
 // ---- FP8-dynamic linear layers (OCP E4M3 codes + float32 scales) -----------------------------------
 // rows of bf16 -> codes + one scale per row; source row r goes to destination row
