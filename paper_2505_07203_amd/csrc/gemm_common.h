@@ -144,34 +144,31 @@ __device__ __forceinline__ void epilogue_patch(const GemmParams& p, int row, int
     }
 }
 
-// Epilogue of a 256 x 256 block tile whose accumulators sit in the 2 x 2 wavefront layout of both GEMM
-// kernels (wavefront = 128 x 128 patch of 4 x 4 MFMA 32x32 tiles; a lane holds one token row and runs of
-// four consecutive features).  smem: at least 8 KiB per wavefront, free to overwrite (callers synchronise
-// the workgroup before).
+// Epilogue of one wavefront of the FP8 GEMMs: a patch of 32 MI rows x 32 NI columns (NI = 4 or 2) from
+// (row_base, col_base) in MI x NI MFMA 32x32 tiles; a lane holds one token row and runs of four consecutive
+// features.  stg: 8 KiB of LDS of this wavefront's own, free to overwrite (callers synchronise the workgroup
+// before).
 // In an accumulator tile a lane holds one token row and runs of four consecutive
 // features, so storing from there puts 8 bytes per lane into 32 different rows: partial cache lines,
 // which the memory side handles several times slower than whole ones.  The position-wise epilogues
-// therefore pass their results through LDS (the ring is free now; every wavefront uses 8 KiB of its
-// own, so no further workgroup barrier is needed) one 32-row tile row at a time and store 16 bytes per
+// therefore pass their results through LDS (the ring is free now; no further workgroup barrier is needed) one
+// 32-row tile row at a time and store 16 bytes per
 // lane, a wavefront covering whole row segments.  16-byte groups of a staged row are XOR-swizzled with
 // the row number so that both the writes (lane = row) and the reads (lanes along a row) are free of
 // bank conflicts.  The arithmetic (fp32 bias / residual add / SiLU-multiply, one round-to-nearest-even
 // conversion) is the per-lane one.  QKV keeps the per-lane path (rotary pairs, V^T).
-template <int EPI>
-__device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 (&acc)[4][4], unsigned char* smem,
-                                              int m0, int n0, int wave, int elane) {
+template <int EPI, int MI, int NI>
+__device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 (&acc)[MI][NI], unsigned char* stg,
+                                              int row_base, int col_base, int elane) {
     const int e31 = elane & 31, ehi = elane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
-    unsigned char* stg = smem + wave * 8192;
-    const int row_base = m0 + wm * 128, col_base = n0 + wn * 128;
     if (EPI == EPI_QKV_ROPE) {
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
+        for (int mi = 0; mi < MI; ++mi) {
             const int row = row_base + mi * 32 + e31;
             if (row >= p.M) continue;
             const int64_t pos = p.row_pos ? (int64_t)p.row_pos[p.pos0 + row] : p.pos0 + row;
 #pragma unroll
-            for (int pt = 0; pt < 2; ++pt) {
+            for (int pt = 0; pt < NI / 2; ++pt) {
                 const int cb = col_base + pt * 64;
                 if (cb >= p.N) continue;
                 epilogue_patch<EPI>(p, row, pos, cb, ehi, acc[mi][2 * pt], acc[mi][2 * pt + 1]);
@@ -182,9 +179,9 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
         // 32 rows x 64 features at a time as fp32 (256-byte rows, 16 groups), then 8 consecutive features
         // per lane: + residual (read 16 bytes per lane; it may alias the destination), convert, store
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
+            for (int hf = 0; hf < NI / 2; ++hf) {
 #pragma unroll
                 for (int n2 = 0; n2 < 2; ++n2)
 #pragma unroll
@@ -228,9 +225,9 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
         // wavefront covering 8 rows x 256 bytes); p.dst is the split's float plane, p.ld its row pitch in floats
         float* part = (float*)p.dst;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
+            for (int hf = 0; hf < NI / 2; ++hf) {
 #pragma unroll
                 for (int n2 = 0; n2 < 2; ++n2)
 #pragma unroll
@@ -261,11 +258,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
                 __builtin_amdgcn_sched_barrier(0);
             }
     } else if (EPI == EPI_STORE) {
-        // 32 rows x 128 features at a time as bf16 (256-byte rows, 16 groups)
+        // 32 rows x 32 NI features at a time as bf16 (rows of G = 16 or 8 groups)
+        constexpr int G = 4 * NI, SH = NI == 4 ? 0 : 1;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
+        for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
+            for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
                     const f32x16& cc = acc[mi][ni];
@@ -277,17 +275,17 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
                         v[2] += __uint_as_float(bw.y << 16); v[3] += __uint_as_float(bw.y & 0xffff0000u);
                     }
                     const int grp = ni * 4 + g4;                           // 8 features = one 16-byte group
-                    *(uint2*)(stg + e31 * 256 + ((grp ^ (e31 & 15)) << 4) + ehi * 8) = pack4(v[0], v[1], v[2], v[3]);
+                    *(uint2*)(stg + e31 * (G * 16) + ((grp ^ ((e31 >> SH) & (G - 1))) << 4) + ehi * 8) = pack4(v[0], v[1], v[2], v[3]);
                 }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            const int col = col_base + (elane & 15) * 8;
+            const int col = col_base + (elane & (G - 1)) * 8;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int rl = i * 4 + (elane >> 4);
+            for (int i = 0; i < G / 2; ++i) {
+                const int rl = i * (64 / G) + elane / G;
                 const int row = row_base + mi * 32 + rl;
-                const uint4 o = *(const uint4*)(stg + rl * 256 + (((elane & 15) ^ (rl & 15)) << 4));
+                const uint4 o = *(const uint4*)(stg + rl * (G * 16) + (((elane & (G - 1)) ^ ((rl >> SH) & (G - 1))) << 4));
                 if (row < p.M && col < p.N) *(uint4*)(p.dst + (int64_t)row * p.ld + col) = o;
             }
             asm volatile("" ::: "memory");
@@ -295,31 +293,32 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& p, const f32x16 
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        // SiLU-multiply: a 64-column patch (32 gate, 32 up) gives 32 features; 32 rows x 64 features at a
-        // time as bf16 (128-byte rows, 8 groups, two rows per 256 bytes of banks: swizzle with row / 2);
-        // a wavefront then stores 8 rows x 128 bytes per instruction
+        // SiLU-multiply: a 64-column patch (32 gate, 32 up) gives 32 features; 32 rows x 16 NI features at a
+        // time as bf16 (rows of G = 8 or 4 groups, two or four rows per 256 bytes of banks: swizzle with row / 2 or
+        // row / 4); a wavefront then stores whole row segments of 128 or 64 bytes
+        constexpr int G = 2 * NI, SH = NI == 4 ? 1 : 2;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
+        for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
-            for (int pt = 0; pt < 2; ++pt)
+            for (int pt = 0; pt < NI / 2; ++pt)
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
                     const f32x16& c0 = acc[mi][2 * pt];
                     const f32x16& c1 = acc[mi][2 * pt + 1];
                     const int grp = pt * 4 + g4;
-                    *(uint2*)(stg + e31 * 128 + ((grp ^ ((e31 >> 1) & 7)) << 4) + ehi * 8) =
+                    *(uint2*)(stg + e31 * (G * 16) + ((grp ^ ((e31 >> SH) & (G - 1))) << 4) + ehi * 8) =
                         pack4(silu_f(c0[4 * g4]) * c1[4 * g4], silu_f(c0[4 * g4 + 1]) * c1[4 * g4 + 1],
                               silu_f(c0[4 * g4 + 2]) * c1[4 * g4 + 2], silu_f(c0[4 * g4 + 3]) * c1[4 * g4 + 3]);
                 }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            const int col = col_base / 2 + (elane & 7) * 8;
+            const int col = col_base / 2 + (elane & (G - 1)) * 8;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int rl = i * 8 + (elane >> 3);
+            for (int i = 0; i < G / 2; ++i) {
+                const int rl = i * (64 / G) + elane / G;
                 const int row = row_base + mi * 32 + rl;
-                const uint4 o = *(const uint4*)(stg + rl * 128 + (((elane & 7) ^ ((rl >> 1) & 7)) << 4));
+                const uint4 o = *(const uint4*)(stg + rl * (G * 16) + (((elane & (G - 1)) ^ ((rl >> SH) & (G - 1))) << 4));
                 if (row < p.M && col < p.N / 2) *(uint4*)(p.dst + (int64_t)row * p.ld + col) = o;
             }
             asm volatile("" ::: "memory");
@@ -539,10 +538,26 @@ __device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4
     }
 }
 
-// ---- split-K support shared by the bf16 and the FP8 GEMM (defined with the bf16 kernel)
-// splits of the reduction for a GEMM with few output tiles whose K range has kt slices: enough workgroups for
-// the chip's 256 compute units, whole slices, at least two per split, fp32 partials within part_bytes; 1 = none
-int pick_splits(int64_t M, int N, int kt, size_t part_bytes);
+// ---- block tiles and K splits, shared by the bf16 and the FP8 GEMM (defined with the bf16 kernels)
+// Which block tile a launch takes.  Every form accumulates an output over K in the same order, so the choice changes no
+// bit and goes by time alone.  A launch runs in rounds of 256 tiles, one per compute unit; per K slice a full round
+// costs `hi` microseconds and a round of few tiles `lo` (the latency of a slice; in between the L2 and the matrix pipe
+// fill up); `us` is what is left of a launch.
+struct TileForm {
+    int bm, bn;
+    double us, lo, hi;
+};
+struct TileForms {
+    const TileForm* form;        // form[0]: the 256 x 256 tile
+    int n, slice;                // slice: elements of K
+    int weight_bytes;            // per element
+};
+int64_t form_tiles(const TileForm& t, int64_t M, int N);
+// the form for a launch of `splits` workgroup rows that work on p.K of K each
+int pick_form(const TileForms& f, const GemmParams& p, int splits);
+// Number of K splits of a few-rows launch, 1 = run unsplit: at most half a round of 256 x 256 tiles, whole slices and at
+// least two per split, fp32 partials within part_bytes, and a shorter time expected.  must: the last does not count.
+int plan_splits(const TileForms& f, const GemmParams& p, size_t part_bytes, bool must);
 // the kernels that add up part[split][M][N] in split order and apply an epilogue
 void launch_splitk_reduce_residual(const float* part, int splits, const bf16_t* R, int64_t ldr, bf16_t* C, int64_t ldc,
                                    int64_t M, int N, hipStream_t s);

@@ -409,41 +409,15 @@ __global__ void __launch_bounds__(256) splitk_reduce_silu_kernel(const float* __
     H[(int64_t)row * ldh + f] = f2bf(silu_f(g) * u);
 }
 
-// Which block tile a launch takes.  Every form accumulates an output over K in the same order, so the choice changes no
-// bit and goes by time alone.  A launch runs in rounds of 256 tiles, one per compute unit; per K slice of 64 a full
-// round costs `hi` microseconds, and a round of few tiles `lo` (the latency of a slice; in between the L2 and the
-// matrix pipe fill up).  Constants fitted to 232 shapes (N, K of the 8B and 32B projections, 1 .. 8192 rows; weights
-// from HBM): the pick is on average 0.6 % and at most 14 % off the fastest form.  Measured, 256-row tiles against the
-// pick: down projection (N 4096, K 14336) 1 row 241 -> 76 us, 471 rows 247 -> 91, 1024 rows 245 -> 125; O projection
-// (4096 x 4096) 471 rows 72 -> 24, 2048 rows 78 -> 61; QKV 700 rows 76 -> 40; from about 2000 rows (gate/up: 200) on the
-// 256 x 256 tile, which moves half the bytes per flop.
-struct TileForm {
-    int bm, bn;
-    double us, lo, hi;
-};
+// Block tiles of the bf16 launches (see TileForm), fitted to 232 shapes: N, K of the 8B and 32B projections, 1 .. 8192
+// rows, weights from HBM; the pick is on average 0.6 % and at most 14 % off the fastest form.  Measured, 256-row tiles
+// against the pick: down projection (N 4096, K 14336) 1 row 241 -> 76 us, 471 rows 247 -> 91, 1024 rows 245 -> 125; O
+// projection (4096 x 4096) 471 rows 72 -> 24, 2048 rows 78 -> 61; QKV 700 rows 76 -> 40; from about 2000 rows (gate/up:
+// 200) on the 256 x 256 tile, which moves half the bytes per flop.
 constexpr TileForm FORMS[] = {{256, 256, 5.9, 0.99, 1.41}, {32, 128, 3.1, 0.29, 0.31}, {64, 128, 2.3, 0.34, 0.40},
                               {96, 128, 2.8, 0.35, 0.47},  {128, 128, 2.7, 0.41, 0.55}, {160, 128, 3.6, 0.46, 0.63},
                               {192, 128, 3.6, 0.49, 0.70}, {256, 128, 1.0, 0.83, 0.97}};
-constexpr int N_FORMS = sizeof(FORMS) / sizeof(FORMS[0]);
-
-int64_t form_tiles(int f, int64_t M, int N) {
-    return ((M + FORMS[f].bm - 1) / FORMS[f].bm) * ((N + FORMS[f].bn - 1) / FORMS[f].bn);
-}
-double form_us(int f, int64_t M, int N, int K, int splits) {
-    const int64_t tiles = form_tiles(f, M, N) * splits, rounds = (tiles + 255) / 256;
-    const double fill = (double)(tiles - (rounds - 1) * 256) / 256;
-    const TileForm& t = FORMS[f];
-    const double us = t.us + (double)(K / BK) / splits * ((double)(rounds - 1) * t.hi + t.lo + (t.hi - t.lo) * fill);
-    return f == 0 ? 0.95 * us : us;              // a predicted gain below the fit's error does not leave the 256 x 256 tile
-}
-// (the small forms address a tile with offsets below 2^30 bytes)
-int pick_form(const GemmParams& p, int splits) {
-    int best = 0;
-    if (p.lda >= (1 << 20) || p.ldw >= (1 << 20)) return best;
-    for (int f = 1; f < N_FORMS; ++f)
-        if (form_us(f, p.M, p.N, p.K * splits, splits) < form_us(best, p.M, p.N, p.K * splits, splits)) best = f;
-    return best;
-}
+constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BK, 2};
 
 template <int EPI>
 void launch_256(const GemmParams& p, hipStream_t s, int splits) {
@@ -490,32 +464,7 @@ void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
 }
 
 template <int EPI>
-void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(pick_form(p, 1), p, s); }
-
-// Number of K splits of a few-rows launch; 1 = run unsplit.  `must`: only whether the shape allows a split counts
-// (pick_splits), not whether it pays.  Modelled time: the tiles' as above but at least the weights' at the 4.6 TB/s these
-// launches reach, plus, split, a second launch (3 us) and the partial sums written and read at 6 TB/s (fitted to 40
-// shapes: on average 3.6 % off the fastest of all forms and splits).  Measured at 150 rows, 256-row tiles with their
-// splits -> now: O 24 -> 17 us, down 49 -> 36, QKV 28 -> 22, gate/up 75 -> 60 (unsplit).  Launches of up to 64 tiles
-// always split: whatever they gain is below a microsecond either way.
-int plan_splits(const GemmParams& p, size_t part_bytes, bool must) {
-    const int kt = p.K / BK;
-    if (pick_splits(p.M, p.N, kt, part_bytes) < 2) return 1;
-    auto us = [&](int splits) {
-        GemmParams q = p;
-        q.K = p.K / splits;
-        double t = form_us(pick_form(q, splits), p.M, p.N, p.K, splits);
-        t = std::max(t, 2.0 * p.N * p.K / 4.6e6);
-        return splits == 1 ? t : t + 3.0 + 8.0 * splits * p.M * p.N / 6e6;
-    };
-    must = must || form_tiles(pick_form(p, 1), p.M, p.N) <= 64;
-    int best = must ? 2 : 1;
-    for (int splits = 2 * best; splits <= 8; splits *= 2)
-        if (kt % splits == 0 && kt / splits >= 2 && (size_t)splits * p.M * p.N * sizeof(float) <= part_bytes &&
-            us(splits) < us(best))
-            best = splits;
-    return best;
-}
+void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(pick_form(TILES, p, 1), p, s); }
 
 GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, int64_t M, int N, int K) {
     GemmParams p;
@@ -533,7 +482,7 @@ GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ld
 // K must be a multiple of 64 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_mfma_supported(int N, int K) { return K > 0 && K % 64 == 0 && N > 0 && N % 64 == 0; }
 
-double gemm_mfma_launch_cost(int64_t M, int N) { return (double)((form_tiles(0, M, N) + 255) / 256); }
+double gemm_mfma_launch_cost(int64_t M, int N) { return (double)((form_tiles(FORMS[0], M, N) + 255) / 256); }
 
 void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C, int64_t ldc,
                       const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s) {
@@ -550,13 +499,49 @@ void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, in
 
 namespace gemm {
 
-int pick_splits(int64_t M, int N, int kt, size_t part_bytes) {
-    const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    int splits = 1;
-    // (8 against 16 splits measured equal on the 8B shape's O / down projections at 150 rows, 4 a quarter slower)
-    while (splits < 8 && tiles * splits * 2 <= 256 && kt % (splits * 2) == 0 && kt / (splits * 2) >= 2) splits *= 2;
-    while (splits > 1 && (size_t)splits * (size_t)M * (size_t)N * sizeof(float) > part_bytes) splits /= 2;
-    return splits;
+int64_t form_tiles(const TileForm& t, int64_t M, int N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+// whole_k: the launch's K over all splits
+static double form_us(const TileForms& f, int form, int64_t M, int N, int whole_k, int splits) {
+    const TileForm& t = f.form[form];
+    const int64_t tiles = form_tiles(t, M, N) * splits, rounds = (tiles + 255) / 256;
+    const double fill = (double)(tiles - (rounds - 1) * 256) / 256;
+    const double us = t.us + (double)(whole_k / f.slice) / splits * ((double)(rounds - 1) * t.hi + t.lo + (t.hi - t.lo) * fill);
+    return form == 0 ? 0.95 * us : us;           // a predicted gain below the fit's error does not leave the 256 x 256 tile
+}
+
+int pick_form(const TileForms& f, const GemmParams& p, int splits) {
+    int best = 0;
+    // (the small forms address a tile with offsets below 2^30 bytes)
+    if (p.lda >= (1 << 20) || p.ldw >= (1 << 20)) return best;
+    for (int i = 1; i < f.n; ++i)
+        if (form_us(f, i, p.M, p.N, p.K * splits, splits) < form_us(f, best, p.M, p.N, p.K * splits, splits)) best = i;
+    return best;
+}
+
+// Modelled time: the tiles' as in pick_form but at least the weights' at the 4.6 TB/s these launches reach, plus, split, a
+// second launch (3 us) and the partial sums written and read at 6 TB/s (fitted to 40 bf16 shapes, 1 .. 1000 rows: on
+// average 3.6 % off the fastest of all forms and splits).  Measured at 150 rows of the 8B shape, 256-row tiles with their
+// splits -> now: O 24 -> 17 us, down 49 -> 36, QKV 28 -> 22, gate/up 75 -> 60 (unsplit).  Launches of up to 64 tiles
+// always split where they can: nearly the whole chip is idle without.
+int plan_splits(const TileForms& f, const GemmParams& p, size_t part_bytes, bool must) {
+    const int kt = p.K / f.slice;
+    auto allowed = [&](int splits) {
+        return kt % splits == 0 && kt / splits >= 2 && (size_t)splits * (size_t)p.M * (size_t)p.N * sizeof(float) <= part_bytes;
+    };
+    if (form_tiles(f.form[0], p.M, p.N) * 2 > 256 || !allowed(2)) return 1;
+    auto us = [&](int splits) {
+        GemmParams q = p;
+        q.K = p.K / splits;
+        const double t = std::max(form_us(f, pick_form(f, q, splits), p.M, p.N, p.K, splits),
+                                  (double)f.weight_bytes * p.N * p.K / 4.6e6);
+        return splits == 1 ? t : t + 3.0 + 8.0 * splits * p.M * p.N / 6e6;
+    };
+    must = must || form_tiles(f.form[pick_form(f, p, 1)], p.M, p.N) <= 64;
+    int best = must ? 2 : 1;
+    for (int splits = 2 * best; splits <= 8; splits *= 2)
+        if (allowed(splits) && us(splits) < us(best)) best = splits;
+    return best;
 }
 
 void launch_splitk_reduce_residual(const float* part, int splits, const bf16_t* R, int64_t ldr, bf16_t* C, int64_t ldc,
@@ -586,13 +571,13 @@ int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv
     const int N = qd + 2 * kvd;
     if (M <= 0 || !gemm_mfma_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
     GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K);
-    const int splits = plan_splits(p, part_bytes, false);
+    const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;
-    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(TILES, p, splits), p, s, splits);
     GemmParams r = base_params(A, lda, Wqkv, ldw, M, N, K);
     r.bias = bias; r.dst = Q; r.dst_k = Kd; r.dst_vt = Vt; r.ldv = ldv;
     r.rope_cos = rope_cos; r.rope_sin = rope_sin; r.pos0 = pos0; r.row_pos = row_pos;
@@ -605,13 +590,13 @@ int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, 
                                  int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s) {
     if (M <= 0 || !gemm_mfma_supported(N, K)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
-    const int splits = plan_splits(p, part_bytes, false);
+    const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;
-    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(TILES, p, splits), p, s, splits);
     launch_splitk_reduce_silu(part, splits, H, ldh, M, N, s);
     return splits;
 }
@@ -621,13 +606,13 @@ int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t*
                                      float* part, size_t part_bytes, bool must, hipStream_t s) {
     if (M <= 0 || N <= 0 || !gemm_mfma_supported(N, K) || (N & 7) || (ldc & 7) || (ldr & 7)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
-    const int splits = plan_splits(p, part_bytes, must);
+    const int splits = plan_splits(TILES, p, part_bytes, must);
     if (splits < 2) return 0;
     p.K = K / splits;
     p.dst = (bf16_t*)part;
     p.ld = N;
     p.ldr = M * (int64_t)N;              // floats between two splits' planes
-    launch_form<EPI_PARTIAL>(pick_form(p, splits), p, s, splits);
+    launch_form<EPI_PARTIAL>(pick_form(TILES, p, splits), p, s, splits);
     launch_splitk_reduce_residual(part, splits, R, ldr, C, ldc, M, N, s);
     return splits;
 }

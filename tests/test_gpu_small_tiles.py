@@ -45,3 +45,42 @@ def test_qkv_rows_are_the_same_bits_in_launches_of_every_height(cfg, K, bias):
     for m in ROWS:
         q1, k1, vt1 = B.po_op_qkv_rope(a[:m].contiguous(), w, b, cos, sin, hq, hkv, hd)
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("N,K", [(4096, 128), (4096, 896), (6144, 2048), (320, 640), (64, 1024)])
+def test_fp8_rows_are_the_same_bits_in_launches_of_every_height(N, K):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    top = 4300
+    r = rnd(top, N)
+    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(top, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
+    whole = {"store": B.po_op_linear_fp8(qa, sa, qw, sw), "residual": B.po_op_linear_fp8(qa, sa, qw, sw, residual=r),
+             "silu": B.po_op_linear_fp8(qa, sa, qw, sw, silu_mul=True)}
+    val = lambda q, s: q.view(torch.float8_e4m3fn).double() * s.double()[:, None]
+    ref = (val(qa, sa) @ val(qw, sw).t()).cpu().numpy()
+    tol = 2.0 ** -8 * np.abs(ref) + K * 2.0 ** -22 * (val(qa, sa).abs() @ val(qw, sw).abs().t()).cpu().numpy()
+    assert np.all(np.abs(whole["store"].double().cpu().numpy() - ref) <= tol)
+    for m in ROWS + (2100,):
+        x, s = qa[:m].contiguous(), sa[:m].contiguous()
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw), whole["store"][:m]), m
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole["residual"][:m]), m
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, silu_mul=True), whole["silu"][:m]), m
+
+
+@pytest.mark.parametrize("bias", [True, False])
+def test_fp8_qkv_rows_are_the_same_bits_in_launches_of_every_height(bias):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    hq, hkv, hd, K = 32, 8, 128, 1024
+    g = torch.Generator(device="cuda").manual_seed(7)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    top = 4300
+    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(top, K)), B.po_op_quantize_rows(rnd((hq + 2 * hkv) * hd, K) * 0.05)
+    b = rnd((hq + 2 * hkv) * hd) if bias else None
+    cos, sin = B.po_op_rope_table(top, hd, 500000.0)
+    q, k, vt = B.po_op_qkv_rope_fp8(qa, sa, qw, sw, b, cos, sin, hq, hkv, hd)
+    for m in ROWS + (2100,):
+        q1, k1, vt1 = B.po_op_qkv_rope_fp8(qa[:m].contiguous(), sa[:m].contiguous(), qw, sw, b, cos, sin, hq, hkv, hd)
+        assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
