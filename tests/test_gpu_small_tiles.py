@@ -84,3 +84,20 @@ def test_fp8_qkv_rows_are_the_same_bits_in_launches_of_every_height(bias):
     for m in ROWS + (2100,):
         q1, k1, vt1 = B.po_op_qkv_rope_fp8(qa[:m].contiguous(), sa[:m].contiguous(), qw, sw, b, cos, sin, hq, hkv, hd)
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("N,K", [(4096, 64), (4096, 100), (1030, 688), (256, 4), (33, 1000)])
+def test_f32_rows_are_the_same_bits_in_launches_of_every_height(N, K):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    top = 4300
+    a, r, w = (torch.randn(*s, generator=g, device="cuda") for s in ((top, K), (top, N), (N, K)))
+    whole, whole_r = B.po_op_linear(a, w), B.po_op_linear(a, w, residual=r)
+    ref = (a.double() @ w.double().t()).cpu().numpy()
+    tol = K * 2.0 ** -24 * (a.double().abs() @ w.double().abs().t()).cpu().numpy()      # K sequential float32 additions
+    assert np.all(np.abs(whole.double().cpu().numpy() - ref) <= tol + 2.0 ** -24 * np.abs(ref))
+    for m in ROWS + (2100,):
+        x = a[:m].contiguous()
+        assert torch.equal(B.po_op_linear(x, w), whole[:m]), m
+        assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole_r[:m]), m
