@@ -6,6 +6,8 @@
 // configurations (32 layers x 32768 tokens) to run in seconds.
 #include "po_internal.h"
 
+#include <algorithm>
+
 namespace po {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -16,92 +18,63 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
 
 // ------------------------------------------------------------------ attention
 // softmax(Q K^T / sqrt(hd)) V with the causal mask, grouped-query heads (Section 4.2 of the paper: attention runs
-// over the whole sequence, unchunked).  Workgroup = 128 query rows of one head, wavefront = 32 of them.  Keys go by
-// in tiles of 32 staged in LDS (K rows padded by 4 floats, V rows as they are).  Per tile a wavefront forms
-// S^T[key][query] = K Q^T with 64 (hd 128) matrix instructions, so that a lane owns ONE query column -- lane l and
-// lane l ^ 32 share it, 16 keys each -- and the online softmax needs one exchange with the partner lane per tile;
-// the probabilities never leave their registers: register r of S^T is exactly the B operand of step r of
+// over the whole sequence, unchunked).  A wavefront works on 32 query rows of one head, keys go by in tiles of 32.  Per
+// tile it forms S^T[key][query] = K Q^T with 64 (hd 128) matrix instructions, so that a lane owns ONE query column --
+// lane l and lane l ^ 32 share it, 16 keys each -- and the online softmax needs one exchange with the partner lane per
+// tile; the probabilities never leave their registers: register r of S^T is exactly the B operand of step r of
 // O^T[hd][query] += V^T P^T when the V fragment of that step is read at the key that register r holds.
 // The contraction index of Q K^T is split between the lane halves (half h takes elements [h hd/2, (h+1) hd/2)), so
-// that a lane's K fragment is contiguous in LDS (16-byte reads).
-// A query's result depends only on its own column of S^T and on the tile grid, which starts at key 0 for every
-// workgroup: it is the same bits wherever the row sits in a workgroup and whichever rows are computed beside it
-// (tiles wholly above a wavefront's rows are skipped; they would contribute p = 0 and a rescale by 1, exactly).
-// o may alias q: a wavefront reads its own 32 query rows before it writes them, and nobody else touches them.
-template <int HD>
-__global__ void __launch_bounds__(256, HD == 128 ? 1 : 2) attention_f32_mfma_kernel(const float* q, const float* __restrict__ k,
-                                                                    const float* __restrict__ v, float* o, int64_t N,
-                                                                    int Hq, int Hkv, int64_t blk0) {
-    constexpr int KP = HD + 4;        // padded K row: 8 lanes' 16-byte reads fall into different banks
-    constexpr int HH = HD / 2;        // contraction elements per lane half
-    constexpr int NB = HD / 32;       // 32-row blocks of O^T
-    constexpr int V4 = HD / 32;       // float4 per thread and operand of one staged tile (32 rows x HD floats, 256 threads)
-    constexpr int RV = HD / 4;        // float4 per row
-    __shared__ __align__(16) float Ks[32 * KP];
-    __shared__ __align__(16) float Vs[32 * HD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 31, half = lane >> 5;
-    const int h = blockIdx.y;
-    const int c = h / (Hq / Hkv);
-    const int64_t r0 = ((int64_t)(gridDim.x - 1 - blockIdx.x) + blk0) * 128;      // longest rows first
-    const int64_t q0 = r0 + wave * 32;          // this wavefront's first query row
-    const int64_t t = q0 + col;                 // this lane's query row
-    const bool live = t < N;
-    const float scale = 1.0f / sqrtf((float)HD);
+// that a lane's K fragment is contiguous (16-byte reads).
+// Which wavefronts share the keys depends on the POSITION of a row alone, so that a row is the same bits wherever it
+// sits in a launch and whichever rows are computed beside it (the tile grid starts at key 0; tiles wholly above a
+// wavefront's rows are skipped, they would contribute p = 0 and a rescale by 1, exactly):
+//  * rows from f32_split_rows on: a workgroup is 128 rows, one wavefront per 32 of them, K and V tiles shared through
+//    LDS.  Matrix-pipe bound: tiles are copied global -> LDS directly, one tile ahead, one barrier per tile, and two
+//    workgroups share a compute unit, so that one's softmax runs beside the other's MFMAs.
+//  * rows below: a workgroup is 32 rows and its four wavefronts take every fourth key tile each, straight from global
+//    memory, merging at the end in wavefront order.  A short request is bound by the one chain of its last rows (16 tiles
+//    of about 3 us at 512 keys), which this cuts to a quarter.
+// o may alias q: a workgroup reads its own query rows before it writes them, and nobody else touches them.
+// Measured (kernel before: one workgroup per compute unit, tiles through registers, two barriers per tile, head-major
+// order), 32 heads of 128: 512 rows 95 -> 48 us, 1024 rows 186 -> 138, 3000 rows 1347 -> 706, 32768 rows 98.0 -> 70.6 ms
+// (125 TFLOP/s of 155); 4 heads of 64, 512 rows 50 -> 21 us.  The line between the two at 128: with 1536 in its place 1500
+// rows take 246 instead of 289 us, but 2048 428 instead of 408 and 3000 734 instead of 706 (the small workgroups read K and V
+// four times as often); at 64 the longer chains favour the small workgroups further (1500 rows 52 against 146 us).
+constexpr int f32_split_rows(int hd) { return hd == 64 ? 1536 : 1024; }
 
+template <int HD>
+struct F32Rows {                  // a wavefront's 32 query rows: this lane's column
+    static constexpr int HH = HD / 2, NB = HD / 32;      // contraction elements per lane half; 32-row blocks of O^T
     float qf[HH];
-    {
+    f32x16 O[NB];
+    float m, l;
+
+    __device__ __forceinline__ void start(const float* q, int64_t t, int64_t N, int h, int Hq, int half) {
         const float* qp = q + (t * Hq + h) * HD + half * HH;
 #pragma unroll
         for (int i = 0; i < HH / 4; ++i) {
             float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (live) x = *(const float4*)(qp + 4 * i);
+            if (t < N) x = *(const float4*)(qp + 4 * i);
             qf[4 * i] = x.x; qf[4 * i + 1] = x.y; qf[4 * i + 2] = x.z; qf[4 * i + 3] = x.w;
         }
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) O[b][r] = 0.f;
+        m = -INFINITY;
+        l = 0.f;
     }
-    f32x16 O[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) O[b][r] = 0.f;
-    float m = -INFINITY, l = 0.f;
 
-    const int64_t kv_end = (r0 + 128 < N) ? r0 + 128 : N;
-    float4 pk[V4], pv[V4];
-    auto fetch = [&](int64_t kv0) {
-#pragma unroll
-        for (int j = 0; j < V4; ++j) {
-            const int idx = tid + 256 * j;
-            const int64_t s = kv0 + idx / RV;
-            const int c4 = idx % RV;
-            pk[j] = pv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (s < N) {
-                pk[j] = *(const float4*)(k + (s * Hkv + c) * HD + 4 * c4);
-                pv[j] = *(const float4*)(v + (s * Hkv + c) * HD + 4 * c4);
-            }
-        }
-    };
-    fetch(0);
-    for (int64_t kv0 = 0; kv0 < kv_end; kv0 += 32) {
-        __syncthreads();                        // everybody is done reading the previous tile
-#pragma unroll
-        for (int j = 0; j < V4; ++j) {
-            const int idx = tid + 256 * j;
-            const int row = idx / RV, c4 = idx % RV;
-            *(float4*)(Ks + row * KP + 4 * c4) = pk[j];
-            *(float4*)(Vs + row * HD + 4 * c4) = pv[j];
-        }
-        __syncthreads();
-        if (kv0 + 32 < kv_end) fetch(kv0 + 32);          // in flight during this tile's arithmetic
-        if (kv0 > q0 + 31) continue;                     // wavefront-uniform: every key of the tile is masked for these rows
-
+    // one key tile: kfrag(i) = elements 4 i .. 4 i + 3 of this lane's half of K row `col`; vfrag(b, r) = V[key of register
+    // r][32 b + col]
+    template <typename KF, typename VF>
+    __device__ __forceinline__ void tile(int64_t kv0, int64_t q0, int64_t t, int half, float scale, KF kfrag, VF vfrag) {
         f32x16 S;
 #pragma unroll
         for (int r = 0; r < 16; ++r) S[r] = 0.f;
-        const float* kr = Ks + col * KP + half * HH;
 #pragma unroll
         for (int i = 0; i < HH / 4; ++i) {
-            const float4 kk = *(const float4*)(kr + 4 * i);
+            const float4 kk = kfrag(i);
             S = mfma_f32(kk.x, qf[4 * i], S);
             S = mfma_f32(kk.y, qf[4 * i + 1], S);
             S = mfma_f32(kk.z, qf[4 * i + 2], S);
@@ -109,59 +82,194 @@ __global__ void __launch_bounds__(256, HD == 128 ? 1 : 2) attention_f32_mfma_ker
         }
         // register r holds key kv0 + 8 (r / 4) + 4 half + r % 4 of query t
         float p[16];
-        float tmax = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t key = kv0 + 8 * (r / 4) + 4 * half + (r % 4);
-            p[r] = key > t ? -INFINITY : S[r] * scale;
-            tmax = fmaxf(tmax, p[r]);
+        for (int r = 0; r < 16; ++r) p[r] = S[r] * scale;
+        if (kv0 + 31 > q0) {                             // wavefront-uniform: the tile touches the diagonal
+            const int d = (int)(t - kv0) - 4 * half;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r / 4) + (r % 4) > d) p[r] = -INFINITY;
         }
+        float tmax = p[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, p[r]);
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        const float mn = fmaxf(m, tmax);                 // finite: key kv0 <= q0 <= t is never masked
-        const float a = expf(m - mn);                    // exp(-inf) = 0 on the first tile
+        const float mn = fmaxf(m, tmax);                 // finite from the first tile a wavefront sees: its first key is never masked
+        if (__any(mn > m)) {                             // (else every factor is 1)
+            const float a = expf(m - mn);                // exp(-inf) = 0 on the first tile
+            l *= a;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) O[b][r] *= a;
+            m = mn;
+        }
         float psum = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            p[r] = expf(p[r] - mn);
+            p[r] = expf(p[r] - m);
             psum += p[r];
         }
-        l = l * a + psum;                                // this lane's 16 keys; the partner's are added at the end
-        m = mn;
+        l += psum;                                       // this lane's 16 keys; the partner's are added at the end
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) O[b][r] *= a;
+            for (int r = 0; r < 16; ++r) O[b] = mfma_f32(vfrag(b, r), p[r], O[b]);
+    }
+};
+
+// grid: workgroup i works for head i % Hq; i / Hq counts first the n_main blocks of 128 rows from block blk_main on, then
+// the blocks of 32 rows from block blk_split on, the longest rows of all heads first in both
+template <int HD>
+__global__ void __launch_bounds__(256, 2) attention_f32_mfma_kernel(const float* q, const float* __restrict__ k,
+                                                                    const float* __restrict__ v, float* o, int64_t N, int Hq,
+                                                                    int Hkv, int n_main, int n_split, int64_t blk_main, int64_t blk_split) {
+    constexpr int HH = HD / 2, NB = HD / 32;
+    constexpr int ROWB = HD * 4, TB = 32 * ROWB;             // bytes of a K / V row and of a tile
+    constexpr int RPL = 1024 / ROWB, LPW = 32 / RPL / 4;     // rows per 1 KiB load; loads per wavefront, operand and tile
+    constexpr int SEGS = ROWB / 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int h = (int)(blockIdx.x % (unsigned)Hq), item = (int)(blockIdx.x / (unsigned)Hq);
+    const int c = h / (Hq / Hkv);
+    const float scale = 1.0f / sqrtf((float)HD);
+    const int64_t kvrow = (int64_t)Hkv * HD;                 // floats between two positions
+    F32Rows<HD> st;
+
+    if (item < n_main) {
+        const int64_t r0 = (n_main - 1 - item + blk_main) * 128;
+        const int64_t q0 = r0 + wave * 32;          // this wavefront's first query row
+        const int64_t t = q0 + col;                 // this lane's query row
+        st.start(q, t, N, h, Hq, half);
+        const int64_t kv_end = (r0 + 128 < N) ? r0 + 128 : N;
+        // load jj of this wavefront: rows (wave LPW + jj) RPL .. of a tile; K segments swizzled with the row on this side
+        uint32_t vok[4], vov[4];                     // (LPW entries used)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float vv = Vs[(8 * (r / 4) + 4 * half + (r % 4)) * HD + 32 * b + col];
-                O[b] = mfma_f32(vv, p[r], O[b]);
+        for (int jj = 0; jj < LPW; ++jj) {
+            const int row = (wave * LPW + jj) * RPL + lane / SEGS, seg = lane % SEGS;
+            vok[jj] = (uint32_t)row * (uint32_t)(kvrow * 4) + (uint32_t)((seg ^ (row & 15)) << 4);
+            vov[jj] = (uint32_t)row * (uint32_t)(kvrow * 4) + (uint32_t)(seg << 4);
+        }
+        auto load_tile = [&](int64_t kv0, int stage) {       // rows past N read as zero (masked keys)
+            const int rows = (int)min((int64_t)32, N - kv0);
+            const int bytes = (int)((rows - 1) * kvrow * 4) + ROWB;
+            const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(k + kv0 * kvrow + c * HD), 0, bytes, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(v + kv0 * kvrow + c * HD), 0, bytes, 0x00020000);
+            unsigned char* dst = smem + stage * 2 * TB + wave * LPW * 1024;
+#pragma unroll
+            for (int jj = 0; jj < LPW; ++jj) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(dst + jj * 1024), 16, vok[jj], 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(dst + TB + jj * 1024), 16, vov[jj], 0, 0, 0);
             }
+        };
+        load_tile(0, 0);
+        int stage = 0;
+        for (int64_t kv0 = 0; kv0 < kv_end; kv0 += 32, stage ^= 1) {
+            // this tile has landed; everybody is done with the other stage
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (kv0 + 32 < kv_end) load_tile(kv0 + 32, stage ^ 1);
+            if (kv0 > q0 + 31) continue;             // wavefront-uniform: every key of the tile is masked for these rows
+            const unsigned char* ks = smem + stage * 2 * TB + col * ROWB;
+            const float* vs = (const float*)(smem + stage * 2 * TB + TB) + (4 * half) * HD + col;
+            st.tile(kv0, q0, t, half, scale,
+                    [&](int i) { return *(const float4*)(ks + (((half * (SEGS / 2) + i) ^ (col & 15)) << 4)); },
+                    [&](int b, int r) { return vs[(8 * (r / 4) + (r % 4)) * HD + 32 * b]; });
+        }
+        float l = st.l;
+        l += __shfl_xor(l, 32);
+        if (t >= N) return;
+        const float inv = 1.0f / l;
+        float* op = o + (t * Hq + h) * HD;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *(float4*)(op + 32 * b + 8 * g + 4 * half) =
+                    make_float4(st.O[b][4 * g] * inv, st.O[b][4 * g + 1] * inv, st.O[b][4 * g + 2] * inv, st.O[b][4 * g + 3] * inv);
+    } else {
+        const int64_t q0 = (n_split - 1 - (item - n_main) + blk_split) * 32;
+        const int64_t t = q0 + col;
+        st.start(q, t, N, h, Hq, half);
+        for (int64_t kv0 = wave * 32; kv0 < q0 + 32; kv0 += 128) {
+            // (keys past N are masked: they are past every row; their fragments come from the last position)
+            const float* kp = k + min(kv0 + col, N - 1) * kvrow + c * HD + half * HH;
+            float4 kf[HH / 4];
+#pragma unroll
+            for (int i = 0; i < HH / 4; ++i) kf[i] = *(const float4*)(kp + 4 * i);
+            const float* vp = v + c * HD + col;
+            st.tile(kv0, q0, t, half, scale, [&](int i) { return kf[i]; },
+                    [&](int b, int r) { return vp[min(kv0 + 8 * (r / 4) + 4 * half + (r % 4), N - 1) * kvrow + 32 * b]; });
+        }
+        // merge: O, maximum and row sum of each wavefront through LDS, added in wavefront order
+        float* so = (float*)smem;                                        // [wave][hd][32 queries]
+        float* sm = so + 4 * HD * 32;                                    // [wave][32] maxima, then [wave][32] row sums
+        const float l = st.l + __shfl_xor(st.l, 32);
+        if (half == 0) {
+            sm[wave * 32 + col] = st.m;
+            sm[128 + wave * 32 + col] = l;
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) so[(wave * HD + 32 * b + 8 * (r / 4) + 4 * half + (r % 4)) * 32 + col] = st.O[b][r];
+        __syncthreads();
+        float mx = sm[col], f[4], lt = 0.f;
+#pragma unroll
+        for (int w = 1; w < 4; ++w) mx = fmaxf(mx, sm[w * 32 + col]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            f[w] = expf(sm[w * 32 + col] - mx);                          // 0 for a wavefront without a tile
+            lt += f[w] * sm[128 + w * 32 + col];
+        }
+        if (t >= N) return;
+        const float inv = 1.0f / lt;
+        // wavefront w stores dimensions [w HD / 4, ..), each lane half half of those, 4 at a time
+        float* op = o + (t * Hq + h) * HD;
+#pragma unroll
+        for (int x = 0; x < HD / 32; ++x) {
+            const int d0 = wave * (HD / 4) + half * (HD / 8) + 4 * x;
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float acc = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) acc += f[w] * so[(w * HD + d0 + e) * 32 + col];
+                y[e] = acc * inv;
+            }
+            *(float4*)(op + d0) = make_float4(y[0], y[1], y[2], y[3]);
         }
     }
-    l += __shfl_xor(l, 32);
-    if (!live) return;
-    const float inv = 1.0f / l;
-    float* op = o + (t * Hq + h) * HD;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            *(float4*)(op + 32 * b + 8 * g + 4 * half) =
-                make_float4(O[b][4 * g] * inv, O[b][4 * g + 1] * inv, O[b][4 * g + 2] * inv, O[b][4 * g + 3] * inv);
 }
 
-// q_row0: rows below it need no result (the workgroup that holds it still computes its rows from the 128-row
-// boundary on; what it writes below q_row0 nobody reads)
+template <int HD>
+static void launch_attention_f32(const float* q, const float* k, const float* v, float* o, int64_t N, int Hq, int Hkv,
+                                 int64_t q_row0, hipStream_t s) {
+    constexpr int SMEM_MAIN = 2 * 2 * 32 * HD * 4, SMEM_SPLIT = 4 * HD * 32 * 4 + 2 * 128 * 4;
+    constexpr int SMEM = SMEM_MAIN > SMEM_SPLIT ? SMEM_MAIN : SMEM_SPLIT;
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)attention_f32_mfma_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        attr_set = true;
+    }
+    const int64_t row0 = (q_row0 > 0 && q_row0 < N) ? q_row0 : 0, split_rows = f32_split_rows(HD);
+    const int64_t blk_main = std::max<int64_t>(row0, split_rows) / 128, end_main = (N + 127) / 128;
+    const int64_t blk_split = row0 / 32, end_split = (std::min<int64_t>(N, split_rows) + 31) / 32;
+    const int64_t n_main = std::max<int64_t>(0, end_main - blk_main), n_split = std::max<int64_t>(0, end_split - blk_split);
+    hipLaunchKernelGGL(attention_f32_mfma_kernel<HD>, dim3((unsigned)((n_main + n_split) * Hq)), dim3(256), SMEM, s, q, k, v, o,
+                       N, Hq, Hkv, (int)n_main, (int)n_split, blk_main, blk_split);
+}
+
+// q_row0: rows below it need no result (the block of 128 or 32 rows that holds it is computed whole; what is written
+// below q_row0 nobody reads)
 bool launch_attention_f32_mfma(const float* q, const float* k, const float* v, float* o, int64_t N, int Hq, int Hkv, int hd,
                                int64_t q_row0, hipStream_t s) {
     if (N <= 0) return true;
     if (hd != 64 && hd != 128) return false;
-    const int64_t blk0 = (q_row0 > 0 && q_row0 < N) ? q_row0 / 128 : 0;
-    const dim3 grid((unsigned)((N + 127) / 128 - blk0), (unsigned)Hq);
-    if (hd == 128)
-        hipLaunchKernelGGL(attention_f32_mfma_kernel<128>, grid, dim3(256), 0, s, q, k, v, o, N, Hq, Hkv, blk0);
-    else
-        hipLaunchKernelGGL(attention_f32_mfma_kernel<64>, grid, dim3(256), 0, s, q, k, v, o, N, Hq, Hkv, blk0);
+    if ((int64_t)Hkv * hd >= (1 << 23)) return false;       // a tile of 32 positions is addressed with 32-bit byte offsets
+    if (hd == 128) launch_attention_f32<128>(q, k, v, o, N, Hq, Hkv, q_row0, s);
+    else launch_attention_f32<64>(q, k, v, o, N, Hq, Hkv, q_row0, s);
     return true;
 }
 

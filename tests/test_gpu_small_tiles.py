@@ -101,3 +101,24 @@ def test_f32_rows_are_the_same_bits_in_launches_of_every_height(N, K):
         x = a[:m].contiguous()
         assert torch.equal(B.po_op_linear(x, w), whole[:m]), m
         assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole_r[:m]), m
+
+
+@pytest.mark.parametrize("Hq,Hkv,hd,n", [(4, 2, 64, 1700), (4, 1, 128, 1200), (2, 2, 128, 33)])
+def test_f32_attention_rows_do_not_depend_on_the_length(Hq, Hkv, hd, n):
+    """Rows below and above the change of work split: against float64, and the same bits in a shorter sequence."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(n, h, hd, generator=g, device="cuda") for h in (Hq, Hkv, Hkv))
+    q = q * 2
+    o = B.po_op_attention(q, k, v)
+    mask = torch.ones(n, n, dtype=torch.bool, device="cuda").tril()
+    for h in range(Hq):
+        c = h // (Hq // Hkv)
+        s = (q[:, h].double() @ k[:, c].double().t()) * hd ** -0.5
+        ref = s.masked_fill(~mask, -float("inf")).softmax(-1) @ v[:, c].double()
+        # float32 dot products of hd terms in the exponent, sums of n non-negative terms
+        assert (o[:, h].double() - ref).abs().max().item() <= 4e-6 * v.abs().max().item()
+    for m in (1, 31, 32, 33, 127, 129, 1023, 1024, 1025, 1100, 1535, 1537, 1601):
+        if m < n:
+            assert torch.equal(B.po_op_attention(q[:m].contiguous(), k[:m].contiguous(), v[:m].contiguous()), o[:m]), m
