@@ -407,16 +407,50 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 // 2^-126 .. 2^127, attention scores of ordinary size are within +-40, and a row whose sum of p leaves 2^-60 .. 2^100
 // (scores far above or far below that) gives up and is recomputed by the running-maximum kernel, like an overflow
 // in the other form.
-template <bool PRE>
+//
+// SPLIT (with PRE; few query rows against many keys): rows q_row0 .. N-1 of ALL query heads of a KV head are the rows of
+// a workgroup, since they share its keys (a 150-row suffix of 4 heads per KV head is 600 rows: 3 workgroups that are
+// nearly full instead of 4 with 59 % of their rows), and the key tiles are divided into pieces of `per` tiles: pieces 0
+// .. n2 - 1 cover tiles [0, tiles2) of a second K / V^T pair (a prefix-cache entry read in place), the rest what follows
+// in the first.  A piece writes its unnormalised fp32 accumulators and row sums; without a reference exponent the sums of
+// the pieces simply add, in attn_combine_kernel, which also looks at the total.  Measured (32 heads on 8 KV heads, 150
+// rows behind 14 000 keys, per layer): 67 us with the 32-row kernel above, 45 us here; one row 43 us and 17.
+struct SplitArgs {
+    const bf16_t *k2, *vt2;
+    int64_t ldv2;
+    float *opart, *mlpart;        // [piece][row - q_row0][head][HD], [..][2]
+    int q_row0, tiles2, n2, n, per;       // n: pieces
+};
+template <bool PRE, bool SPLIT>
 __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ vt, int64_t ldv, bf16_t* o, int N,
-                                                         int Hq, int Hkv, float sc_log2e, int nqt, int hpx, int* redo) {
+                                                         int Hq, int Hkv, float sc_log2e, int nqt, int hpx, int* redo,
+                                                         const SplitArgs sp) {
     constexpr int HD = 128, KS = 8, HT = 4;
     constexpr int TILE_BYTES = 64 * HD * 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-    int qtile, head;
-    if (hpx > 0) {
+    int qtile, head, kvh, piece = 0, tile0 = 0, piece_tiles = 0;
+    const int group = Hq / Hkv;
+    if (SPLIT) {
+        kvh = blockIdx.x % Hkv;
+        const int rest = blockIdx.x / Hkv;
+        piece = rest % sp.n;
+        qtile = rest / sp.n;
+        head = kvh * group;
+        const int n_all = (N + 63) / 64;
+        const bool second = piece < sp.n2;
+        tile0 = second ? piece * sp.per : sp.tiles2 + (piece - sp.n2) * sp.per;
+        piece_tiles = min(sp.per, (second ? sp.tiles2 : n_all) - tile0);
+        if (second) {
+            k = sp.k2;
+            vt = sp.vt2;
+            ldv = sp.ldv2;
+        }
+        // everything below counts keys from this piece's first one
+        k += (int64_t)tile0 * 64 * Hkv * HD;
+        vt += tile0 * 64;
+    } else if (hpx > 0) {
         const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
         qtile = nqt - 1 - j / hpx;
         head = xcd * hpx + j % hpx;
@@ -424,22 +458,34 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         qtile = nqt - 1 - (int)(blockIdx.x / Hq);
         head = blockIdx.x % Hq;
     }
-    const int kvh = head / (Hq / Hkv);
+    if (!SPLIT) kvh = head / group;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l31 = lane & 31, lhi = lane >> 5;
     const int qb = qtile * 256;
     const int qw = qb + wave * 64;
     const int blk_last = min(N, qb + 256) - 1;
-    const int n_tiles = blk_last / 64 + 1;                       // 64-key tiles the workgroup streams
+    const int n_tiles = SPLIT ? piece_tiles : blk_last / 64 + 1;       // 64-key tiles the workgroup streams
     const int nkb_w = (qw < N) ? (min(N, qw + 64) - 1) / 32 + 1 : 0;   // 32-key blocks this wavefront needs
+    // SPLIT: this lane's query rows (position and head), clamped to the last one, and their positions in keys of this piece
+    const int n_virtual = SPLIT ? (N - sp.q_row0) * group : 0;
+    int vrow[2], vhead[2], vpos[2];
+    if (SPLIT) {
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            const int vr = min(qw + qt * 32 + l31, n_virtual - 1);
+            vrow[qt] = vr / group;
+            vhead[qt] = head + vr - vrow[qt] * group;
+            vpos[qt] = sp.q_row0 + vrow[qt] - tile0 * 64;
+        }
+    }
 
     // ---- Q fragments (B operand: lane = query column, 8 consecutive head-dim values)
     bf16x8 qf[2][KS];
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-        const int qrow = min(qw + qt * 32 + l31, N - 1);
-        const bf16_t* qp = q + ((int64_t)qrow * Hq + head) * HD + lhi * 8;
+        const int qrow = SPLIT ? sp.q_row0 + vrow[qt] : min(qw + qt * 32 + l31, N - 1);
+        const bf16_t* qp = q + ((int64_t)qrow * Hq + (SPLIT ? vhead[qt] : head)) * HD + lhi * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const uint4 t = *(const uint4*)(qp + ks * 16);
@@ -460,10 +506,11 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // K goes through a buffer resource that ends with the last position: rows of the last, ragged tile
     // beyond it read as zero (they are masked keys) instead of needing a clamp per load.
     const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(k + (int64_t)kvh * HD), 0, (int)((uint32_t)(N - 1) * krs2 + 256u), 0x00020000);
+        (void*)(k + (int64_t)kvh * HD), 0,
+        (int)((SPLIT ? (uint32_t)((piece < sp.n2 ? sp.tiles2 * 64 : N) - tile0 * 64 - 1) : (uint32_t)(N - 1)) * krs2 + 256u), 0x00020000);
     // (V^T of this KV head: 128 rows of ldv positions; its columns are always inside the row)
     const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(vt + (int64_t)kvh * HD * ldv), 0, (int)((uint32_t)HD * (uint32_t)(ldv * 2)), 0x00020000);
+        (void*)(vt + (int64_t)kvh * HD * ldv), 0, (int)((uint32_t)HD * (uint32_t)(ldv * 2) - (uint32_t)(tile0 * 128)), 0x00020000);
     const uint32_t vrow32 = (uint32_t)(32 * ldv * 2);
     // load jj_ (0..3: K rows, 4..7: V^T rows) of tile tile_ into stage stg_
 #define PO_DMA(tile_, stg_, jj_)                                                                               \
@@ -493,6 +540,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         for (int j2 = 0; j2 < 2; ++j2)      // (the V^T half of LDS starts at 64 KiB: in the register, so that what is left is an immediate)
             vofs[a][j2] = A64_VBASE + l31 * 128 + (((a * 4 + j2 * 2 + lhi) ^ swz8(l31)) << 4);
 
+    // the lowest position among this wavefront's rows (rows ascend with the lane and the tile)
+    const int pos_min = SPLIT ? __builtin_amdgcn_readfirstlane(vpos[0]) : 0;
+
     f32x16 oacc[HT][2];
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
@@ -510,7 +560,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // causal mask of a 32-key block on the accumulators of one query tile
 #define PO_MASK(S, kb_, qt_)                                                                     \
     {                                                                                            \
-        const int qidx_ = qw + (qt_) * 32 + l31;                                                 \
+        const int qidx_ = SPLIT ? vpos[qt_] : qw + (qt_) * 32 + l31;                             \
         _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                         \
             const int key_ = (kb_) * 32 + (r & 7) + 8 * lhi + 16 * (r >> 3);                     \
             if (key_ > qidx_) S[qt_][r] = -INFINITY;                                             \
@@ -550,7 +600,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                 }
             }
         }
-        if (31 > qw) { PO_MASK(sa, 0, 0); PO_MASK(sa, 0, 1); }
+        if (31 > (SPLIT ? pos_min : qw)) { PO_MASK(sa, 0, 0); PO_MASK(sa, 0, 1); }
         float m0 = 0.f, m1 = 0.f;
         if (!PRE) {
             PO_BLOCKMAX(sa, 0, m0);
@@ -708,7 +758,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         PO_ITER(2 * j + 1, sb, sa, kstn, 0, vst, 1, kstn, 1, 0, j + 3, ((s_) + 3) & 3, 4, M1_);    \
     }
     const int wt = qw >> 6;                      // pair that holds this wavefront's first query row
-    const int j_last = (nkb_w > 0) ? wt : -1;    // last pair with work
+    // last pair with work.  SPLIT: pairs j with 64 j + 95 <= pos_min touch no masked key, all others take both masks
+    const int j_free = pos_min < 95 ? 0 : min((pos_min - 95) / 64 + 1, n_tiles);
+    const int j_last = SPLIT ? j_free + 1 : (nkb_w > 0) ? wt : -1;
     fr[0] = *(const bf16x8*)(smem + 8192 + koff[0]);      // K fragments 0, 1, 2 of block 1
     fr[1] = *(const bf16x8*)(smem + 8192 + koff[1]);
     fr[2] = *(const bf16x8*)(smem + 8192 + koff[2]);
@@ -724,8 +776,12 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         j -= 3;
     }
     for (; j < j_last - 1; ++j) PO_PAIR(j & 3, 0, 0);
-    if (j == j_last - 1) { PO_PAIR(j & 3, 0, 1); ++j; }
-    if (j == j_last) { PO_PAIR(j & 3, 1, 1); ++j; }
+    if (SPLIT) {
+        for (; j < n_tiles; ++j) PO_PAIR(j & 3, 1, 1);
+    } else {
+        if (j == j_last - 1) { PO_PAIR(j & 3, 0, 1); ++j; }
+        if (j == j_last) { PO_PAIR(j & 3, 1, 1); ++j; }
+    }
     for (; j < n_tiles; ++j) {
         asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
         _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(j + 3, (j + 3) & 3, jj);
@@ -745,6 +801,25 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #undef PO_MFMA_ACC
 #undef PO_MFMA_DRAIN
 
+    if (SPLIT) {
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            const float ltot = half_swap_sum((lsum[qt][0] + lsum[qt][1]) + (lsum[qt][2] + lsum[qt][3]));
+            if (qw + qt * 32 + l31 >= n_virtual) continue;
+            const int64_t slot = ((int64_t)piece * (N - sp.q_row0) + vrow[qt]) * Hq + vhead[qt];
+            float* op = sp.opart + slot * HD + 4 * lhi;
+#pragma unroll
+            for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    const float4 v = {oacc[ht][qt][rg * 4 + 0], oacc[ht][qt][rg * 4 + 1], oacc[ht][qt][rg * 4 + 2],
+                                      oacc[ht][qt][rg * 4 + 3]};
+                    *(float4*)(op + ht * 32 + rg * 8) = v;
+                }
+            if (lhi == 0) *(float2*)(sp.mlpart + slot * 2) = make_float2(0.f, ltot);
+        }
+        return;
+    }
     if (PRE) {
         lrow[0] = (lsum[0][0] + lsum[0][1]) + (lsum[0][2] + lsum[0][3]);
         lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
@@ -782,30 +857,63 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 }
 
 // o[row][head][:] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^((m_s - max m) sc_log2e); one thread per 4 values.
-template <int HD>
+// PRE64 (pieces of attn_fwd64_kernel: Q prescaled, every m_s 0, so every w_s 1): a total that left [2^-60, 2^100) means
+// probabilities near an end of the float range; the threads of that row and head then form it again with a running
+// maximum, key by key (q still holds the row: o may alias q, and nobody else writes it).
+template <int HD, bool PRE64>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ opart, const float* __restrict__ mlpart,
                                                            int n_split, int nq, int Hq, float sc_log2e, bf16_t* o,
-                                                           int q_row0) {
+                                                           int q_row0, const bf16_t* q, const bf16_t* __restrict__ k,
+                                                           const bf16_t* __restrict__ vt, int64_t ldv, int Hkv, SplitArgs sp) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     constexpr int PER = HD / 4;
     if (i >= (int64_t)nq * Hq * PER) return;
     const int64_t rh = i / PER;                       // (row - q_row0) * Hq + head
     const int f = (int)(i - rh * PER) * 4;
     const int64_t plane = (int64_t)nq * Hq;
+    const int64_t row = q_row0 + rh / Hq;
+    const int head = (int)(rh % Hq);
     float mx = -1.0e30f;
-    for (int sp = 0; sp < n_split; ++sp) mx = fmaxf(mx, mlpart[(sp * plane + rh) * 2]);
+    if (PRE64) mx = 0.f;
+    else
+        for (int sp = 0; sp < n_split; ++sp) mx = fmaxf(mx, mlpart[(sp * plane + rh) * 2]);
     float4 acc = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
+#pragma unroll 4
     for (int sp = 0; sp < n_split; ++sp) {
         const float2 ml = *(const float2*)(mlpart + (sp * plane + rh) * 2);
-        const float w = __builtin_amdgcn_exp2f((ml.x - mx) * sc_log2e);
+        const float w = PRE64 ? 1.0f : __builtin_amdgcn_exp2f((ml.x - mx) * sc_log2e);
         const float4 v = *(const float4*)(opart + (sp * plane + rh) * HD + f);
         acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
         l += w * ml.y;
     }
+    if (PRE64 && (!(l >= 0x1p-60f) || !(l < 0x1p100f))) {
+        const int kvh = head / (Hq / Hkv);
+        const uint2 qv = *(const uint2*)(q + (row * Hq + head) * HD + f);
+        const float q0 = __uint_as_float(qv.x << 16), q1 = __uint_as_float(qv.x & 0xffff0000u),
+                    q2 = __uint_as_float(qv.y << 16), q3 = __uint_as_float(qv.y & 0xffff0000u);
+        float m = -1.0e30f;
+        acc = {0.f, 0.f, 0.f, 0.f};
+        l = 0.f;
+        for (int64_t key = 0; key <= row; ++key) {
+            const bool second = key < (int64_t)sp.tiles2 * 64;
+            const bf16_t* kr = (second ? sp.k2 : k) + (key * Hkv + kvh) * HD + f;
+            const bf16_t* vr = (second ? sp.vt2 : vt) + key;
+            const int64_t ld = second ? sp.ldv2 : ldv;
+            float d = q0 * bf2f(kr[0]) + q1 * bf2f(kr[1]) + q2 * bf2f(kr[2]) + q3 * bf2f(kr[3]);
+            for (int off = PER / 2; off > 0; off >>= 1) d += __shfl_xor(d, off);      // the PER threads of this row and head
+            const float mn = fmaxf(m, d);
+            const float a = __builtin_amdgcn_exp2f(m - mn), pv = __builtin_amdgcn_exp2f(d - mn);
+            const int64_t fr = (int64_t)kvh * HD + f;
+            acc.x = acc.x * a + pv * bf2f(vr[fr * ld]);
+            acc.y = acc.y * a + pv * bf2f(vr[(fr + 1) * ld]);
+            acc.z = acc.z * a + pv * bf2f(vr[(fr + 2) * ld]);
+            acc.w = acc.w * a + pv * bf2f(vr[(fr + 3) * ld]);
+            l = l * a + pv;
+            m = mn;
+        }
+    }
     const float inv = 1.0f / l;
-    const int64_t row = q_row0 + rh / Hq;
-    const int head = (int)(rh % Hq);
     uint2 w2;
     w2.x = (uint32_t)f2bf(acc.x * inv) | ((uint32_t)f2bf(acc.y * inv) << 16);
     w2.y = (uint32_t)f2bf(acc.z * inv) | ((uint32_t)f2bf(acc.w * inv) << 16);
@@ -818,8 +926,8 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     constexpr int SMEM_REDO = 2 * 2 * BNK * 128 * 2;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)attn_fwd64_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        (void)hipFuncSetAttribute((const void*)attn_fwd64_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, false>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, false>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         (void)hipFuncSetAttribute((const void*)attn_fwd_kernel<128, 1, 8, false>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, SMEM_REDO);
         attr_set = true;
@@ -830,11 +938,11 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     // workgroups enumerate query tiles from the last one down: fewer of them = only the last tiles
     const int nsel = nqt - (int)((q_row0 > 0 && q_row0 < N) ? q_row0 / 256 : 0);
     if (q_prescaled)
-        hipLaunchKernelGGL(attn_fwd64_kernel<true>, dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
-                           Hq, Hkv, sc_log2e, nqt, hpx, redo);
+        hipLaunchKernelGGL((attn_fwd64_kernel<true, false>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+                           Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
     else
-        hipLaunchKernelGGL(attn_fwd64_kernel<false>, dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
-                           Hq, Hkv, sc_log2e, nqt, hpx, redo);
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, false>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+                           Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
     // the (query tile, head) pairs given up above, by the running-maximum kernel with the same 256-row tiles
     // (8 wavefronts x 32 rows); item b = query tile * Hq + head
     hipLaunchKernelGGL((attn_fwd_kernel<128, 1, 8, false>), dim3((unsigned)std::min(nqt * Hq, 256)), dim3(512), SMEM_REDO, s, q, k, vt, ldv,
@@ -891,9 +999,50 @@ int launch_split_t(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t l
                        k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt, 0, (int)q_row0, n_split, opart, mlpart,
                        k2 ? k2 : k, vt2 ? vt2 : vt, vt2 ? ldv2 : ldv, (k2 && vt2) ? (int)(n2 / BNK) : 0, nullptr);
     const int64_t n = nq * Hq * (HD / 4);
-    hipLaunchKernelGGL(attn_combine_kernel<HD>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, opart, mlpart, n_split,
-                       (int)nq, Hq, sc_log2e, o, (int)q_row0);
+    hipLaunchKernelGGL((attn_combine_kernel<HD, false>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, opart, mlpart,
+                       n_split, (int)nq, Hq, sc_log2e, o, (int)q_row0, q, k, vt, ldv, Hkv, SplitArgs{});
     return n_split;
+}
+
+// The prescaled-Q form for head dimension 128: pieces of key tiles sized so that the workgroups (KV heads x blocks of
+// 256 rows of all a KV head's query heads x pieces) are one round of the 256 compute units, at least two tiles each.
+// 0 = nothing launched: too many rows for two pieces, fewer than four tiles, or the scratch too small.
+int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o, int64_t N, int Hq, int Hkv,
+                       int64_t q_row0, float* scratch, size_t scratch_bytes, bool launch, const bf16_t* k2, const bf16_t* vt2,
+                       int64_t ldv2, int64_t n2, hipStream_t s) {
+    constexpr int SMEM = 2 * A64_NSTAGE * A64_TILE + 16;
+    const int64_t nq = N - q_row0;
+    const int group = Hq / Hkv;
+    if (nq <= 0 || nq > 1024 || nq * group > (1 << 20)) return 0;
+    const int nqt = (int)((nq * group + 255) / 256);
+    const int tiles = (int)((N + 63) / 64), tiles2 = (k2 && vt2) ? (int)(n2 / 64) : 0;
+    const int max_pieces = 256 / (nqt * Hkv);
+    if (max_pieces < 2 || tiles < 4) return 0;
+    SplitArgs sp{};
+    for (sp.per = std::max(2, (tiles + max_pieces - 1) / max_pieces);; ++sp.per) {
+        sp.n2 = (tiles2 + sp.per - 1) / sp.per;
+        sp.n = sp.n2 + (tiles - tiles2 + sp.per - 1) / sp.per;
+        if (sp.n < 2) return 0;
+        const size_t floats = (size_t)sp.n * (size_t)nq * (size_t)Hq * (128 + 2);
+        if (sp.n <= max_pieces && floats * sizeof(float) <= scratch_bytes) break;
+    }
+    if (!launch) return sp.n;
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        attr_set = true;
+    }
+    sp.k2 = k2; sp.vt2 = vt2; sp.ldv2 = ldv2;
+    sp.q_row0 = (int)q_row0;
+    sp.tiles2 = tiles2;
+    sp.opart = scratch;
+    sp.mlpart = scratch + (size_t)sp.n * (size_t)nq * (size_t)Hq * 128;
+    hipLaunchKernelGGL((attn_fwd64_kernel<true, true>), dim3((unsigned)(Hkv * sp.n * nqt)), dim3(256), SMEM, s, q, k, vt, ldv, o,
+                       (int)N, Hq, Hkv, 1.0f, nqt, 0, nullptr, sp);
+    const int64_t n = nq * Hq * 32;
+    hipLaunchKernelGGL((attn_combine_kernel<128, true>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sp.opart, sp.mlpart,
+                       sp.n, (int)nq, Hq, 1.0f, o, (int)q_row0, q, k, vt, ldv, Hkv, sp);
+    return sp.n;
 }
 
 }  // namespace
@@ -906,6 +1055,10 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
                                 int Hq, int Hkv, int hd, int64_t q_row0, float* scratch, size_t scratch_bytes,
                                 bool launch, const bf16_t* k2, const bf16_t* vt2, int64_t ldv2, int64_t n2,
                                 bool q_prescaled, hipStream_t s) {
+    if (hd == 128 && q_prescaled) {
+        const int n = launch_split_fwd64(q, k, vt, ldv, o, N, Hq, Hkv, q_row0, scratch, scratch_bytes, launch, k2, vt2, ldv2, n2, s);
+        if (n > 1) return n;
+    }
     if (hd == 128)
         return launch_split_t<128>(q, k, vt, ldv, o, N, Hq, Hkv, q_row0, scratch, scratch_bytes, launch, k2, vt2, ldv2, n2,
                                    q_prescaled, s);
