@@ -63,3 +63,16 @@ def test_scores_far_outside_the_exponent_range(total, cached):
     running maximum, from the cached and the fresh keys.  One rounding of a query value moves a score by up to 0.1 nats
     here, hence the wider bar."""
     _compare(_cfg(8, 2), total, cached, 30.0, 6e-2)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
+def test_value_transpose_aligned_and_unaligned(n):
+    """V at a 16-byte boundary and two bytes off it take different kernels to the same transposed copy."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(n, h, 128, generator=g, device="cuda").to(torch.bfloat16) for h in (4, 2, 2))
+    off = torch.empty(v.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(v.shape)
+    off.copy_(v)
+    assert off.data_ptr() % 16 == 2 and v.data_ptr() % 16 == 0
+    assert torch.equal(B.po_op_attention(q, k, off), B.po_op_attention(q, k, v))
