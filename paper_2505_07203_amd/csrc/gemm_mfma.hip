@@ -65,10 +65,14 @@ constexpr int NUNIT = 5;                           // ring of five units: the wh
 constexpr int SMEM_BYTES = NUNIT * UNIT_BYTES;
 constexpr int NT_BF16 = 512;                       // eight wavefronts
 
-template <int EPI>
+// MU = 16-row groups per wavefront patch: 8 (the form described above) or 6 (192-row block tile, phases of 12 MFMAs, the A
+// unit three quarters full): the bits are the same, and 3/4 of a tile's time in 3/4 of its rows lets a launch whose 256-row
+// tiles end in a nearly empty round come out with less of it.
+template <int EPI, int MU>
 __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int MU = 8;                          // 16-row groups per wavefront patch
+    constexpr int BM_ = 32 * MU, MH = MU / 2;      // block tile rows; 16-row groups per phase
+    constexpr int NA = MU / 2;                     // global->LDS loads per wavefront for an A unit (W: 4)
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
@@ -81,7 +85,7 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
     const int gm_this = min(GROUP_M, p.mt - g * GROUP_M);
     const int tn = within / gm_this;
     const int tm = g * GROUP_M + (within - tn * gm_this);
-    const int m0 = tm * BM, n0 = tn * BN;
+    const int m0 = tm * BM_, n0 = tn * BN;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -98,18 +102,17 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
         (void*)(p.W + (int64_t)n0 * p.ldw + k0), 0, (int)(uint32_t)(w_bytes > 0xffffffffull ? 0xffffffffull : w_bytes), 0x00020000);
     uint32_t voa[4], vow[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = (wave * 4 + i) * 8 + (lane >> 3);
-        const int lseg = (lane & 7) ^ ((row >> 1) & 7);
-        voa[i] = (uint32_t)row * (uint32_t)(p.lda * 2) + lseg * 16;
-        vow[i] = (uint32_t)row * (uint32_t)(p.ldw * 2) + lseg * 16;
+    for (int i = 0; i < 4; ++i) {                // (voa: NA entries used)
+        const int row = (wave * 4 + i) * 8 + (lane >> 3), rowa = (wave * NA + i) * 8 + (lane >> 3);
+        vow[i] = (uint32_t)row * (uint32_t)(p.ldw * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+        voa[i] = (uint32_t)rowa * (uint32_t)(p.lda * 2) + (((lane & 7) ^ ((rowa >> 1) & 7)) << 4);
     }
     const int KT = p.K / BK;
     // load i_ (0..3) of this wavefront's share of the A (is_w_ = 0) or W unit of slice slice_, into ring
     // position pos_
 #define PO_DMA(is_w_, slice_, pos_, i_)                                                                              \
     {                                                                                                                  \
-        unsigned char* d_ = smem + (pos_) * UNIT_BYTES + (wave * 4 + (i_)) * 1024;                    \
+        unsigned char* d_ = smem + (pos_) * UNIT_BYTES + (wave * ((is_w_) ? 4 : NA) + (i_)) * 1024;                    \
         __builtin_amdgcn_raw_ptr_buffer_load_lds((is_w_) ? rw : ra, (__attribute__((address_space(3))) void*)d_, 16,   \
                                                  (is_w_) ? vow[(i_)] : voa[(i_)],                    \
                                                  min((slice_), KT - 1) * (BK * 2), 0, 0);                              \
@@ -129,32 +132,32 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 #pragma unroll
     for (int u4 = 0; u4 < 4; ++u4)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) PO_DMA(u4 & 1, u4 >> 1, u4, i)
-    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");      // slice 0 has landed
-    bf16x8 A0[4], A1[4], W0[4], W1[4];
+        for (int i = 0; i < ((u4 & 1) ? 4 : NA); ++i) PO_DMA(u4 & 1, u4 >> 1, u4, i)
+    if (MU == 8) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");      // slice 0 has landed
+    else asm volatile("s_waitcnt vmcnt(7)\n\ts_barrier" ::: "memory");
+    bf16x8 A0[4], A1[4], W0[4], W1[4];           // (A: MH entries used)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        W0[j] = *(const bf16x8*)(smem + UNIT_BYTES + w_base + j * 2048 + f_off[0]);
-        A0[j] = *(const bf16x8*)(smem + a_base + j * 2048 + f_off[0]);
-    }
-    // One phase: 16 MFMAs, rows 64 uh_ .. +63 of the patch (A fragments AC, W fragments WC); behind MFMA m the
+    for (int j = 0; j < 4; ++j) W0[j] = *(const bf16x8*)(smem + UNIT_BYTES + w_base + j * 2048 + f_off[0]);
+#pragma unroll
+    for (int j = 0; j < MH; ++j) A0[j] = *(const bf16x8*)(smem + a_base + j * 2048 + f_off[0]);
+    // One phase: 4 MH MFMAs, rows 16 MH uh_ .. of the patch (A fragments AC, W fragments WC); behind MFMA m the
     // memory instruction number m of the phase, if it has one:
-    //   RA_: read the four A fragments (rows 64 rah_ .., k-step rak_) of the unit at ua_ into AN
+    //   RA_: read the MH A fragments (rows 16 MH rah_ .., k-step rak_) of the unit at ua_ into AN
     //   RW_: read the four W fragments (k-step rwk_) of the unit at uw_ into WN (behind the A reads)
-    //   DMA_: the four global->LDS loads of (dw_ ? W : A) unit of slice ds_ into position dp_ (behind the reads)
+    //   DMA_: the NA or 4 global->LDS loads of (dw_ ? W : A) unit of slice ds_ into position dp_ (behind the reads)
 #define PO_PHASE(AC, WC, uh_, RA_, AN, ua_, rah_, rak_, RW_, WN, uw_, rwk_, DMA_, dw_, ds_, dp_)                    \
-    _Pragma("unroll") for (int m = 0; m < 16; ++m) {                                                                  \
-        const int u_ = (uh_) * 4 + (m >> 2), t_ = m & 3;                                                              \
+    _Pragma("unroll") for (int m = 0; m < 4 * MH; ++m) {                                                                \
+        const int u_ = (uh_) * MH + (m >> 2), t_ = m & 3;                                                             \
         acc[u_][t_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WC[t_], AC[m >> 2], acc[u_][t_], 0, 0, 0);              \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
-        const int nra_ = (RA_) ? 4 : 0, nrw_ = (RW_) ? 4 : 0;                                                         \
+        const int nra_ = (RA_) ? MH : 0, nrw_ = (RW_) ? 4 : 0;                                                         \
         if (m < nra_) {                                                                                               \
-            AN[m & 3] = *(const bf16x8*)((ua_) + ((rah_) * 4 + (m & 3)) * 2048 + f_off[rak_]);     \
+            AN[m & 3] = *(const bf16x8*)((ua_) + ((rah_) * MH + (m & 3)) * 2048 + f_off[rak_]);     \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
         } else if (m < nra_ + nrw_) {                                                                                 \
             WN[(m - nra_) & 3] = *(const bf16x8*)((uw_) + ((m - nra_) & 3) * 2048 + f_off[rwk_]);  \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
-        } else if ((DMA_) && m < nra_ + nrw_ + 4) {                                                    \
+        } else if ((DMA_) && m < nra_ + nrw_ + ((dw_) ? 4 : NA)) {                                                  \
             PO_DMA(dw_, ds_, dp_, (m - nra_ - nrw_) & 3)                                         \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
         }                                                                                                             \
@@ -174,8 +177,9 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
         PO_PHASE(A1, W0, 1, 1, A0, ua, 0, 1, 0, W1, uw, 1, 1, 0, s + 2, (pa + 4 >= NUNIT ? pa + 4 - NUNIT : pa + 4))
         // phase 2: k-step 1, rows 0-63 | reads A(k1, rows 64-127)
         PO_PHASE(A0, W1, 0, 1, A1, ua, 1, 1, 0, W0, uw, 0, 0, 0, 0, 0)
-        // hand-over: slice s+1 has landed (all but the 4 youngest loads), every LDS read of slice s is done
-        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // hand-over: slice s+1 has landed (all but the NA youngest loads), every LDS read of slice s is done
+        if (MU == 8) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         // phase 3: k-step 1, rows 64-127 | reads W(k0) and A(k0, rows 0-63) of slice s+1; loads W(s+2) into A(s)'s position
         PO_PHASE(A1, W1, 1, 1, A0, ua1, 0, 0, 1, W0, uw1, 0, 1, 1, s + 2, pa)
         pa = pa1;
@@ -410,25 +414,28 @@ __global__ void __launch_bounds__(256) splitk_reduce_silu_kernel(const float* __
 }
 
 // Block tiles of the bf16 launches (see TileForm), fitted to 232 shapes: N, K of the 8B and 32B projections, 1 .. 8192
-// rows, weights from HBM; the pick is on average 0.6 % and at most 14 % off the fastest form.  Measured, 256-row tiles
+// rows, weights from HBM; the pick is on average 0.3 % and at most 9 % off the fastest form.  Measured, 256-row tiles
 // against the pick: down projection (N 4096, K 14336) 1 row 241 -> 76 us, 471 rows 247 -> 91, 1024 rows 245 -> 125; O
 // projection (4096 x 4096) 471 rows 72 -> 24, 2048 rows 78 -> 61; QKV 700 rows 76 -> 40; from about 2000 rows (gate/up:
-// 200) on the 256 x 256 tile, which moves half the bytes per flop.
+// 200) on the 256 x 256 tile, which moves half the bytes per flop, or the 192 x 256 one where that ends in a fuller
+// round: QKV of the 32B shape (N 7168) at 3072 rows 220 -> 195 us, O projection at 5000 rows 176 -> 148, the 8B shape's
+// QKV at 3500 rows 174 -> 148.
 constexpr TileForm FORMS[] = {{256, 256, 5.9, 0.99, 1.41}, {32, 128, 3.1, 0.29, 0.31}, {64, 128, 2.3, 0.34, 0.40},
                               {96, 128, 2.8, 0.35, 0.47},  {128, 128, 2.7, 0.41, 0.55}, {160, 128, 3.6, 0.46, 0.63},
-                              {192, 128, 3.6, 0.49, 0.70}, {256, 128, 1.0, 0.83, 0.97}};
+                              {192, 128, 3.6, 0.49, 0.70}, {256, 128, 1.0, 0.83, 0.97}, {192, 256, 3.3, 0.89, 1.15}};
 constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BK, 2};
 
-template <int EPI>
-void launch_256(const GemmParams& p, hipStream_t s, int splits) {
+template <int EPI, int MU>
+void launch_big(GemmParams p, hipStream_t s, int splits) {
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_mfma_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void*)gemm_bf16_mfma_kernel<EPI, MU>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   SMEM_BYTES);
         attr_set = true;
     }
+    p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     const int per_xcd = (p.mt * p.nt + 7) / 8;
-    hipLaunchKernelGGL((gemm_bf16_mfma_kernel<EPI>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NT_BF16),
+    hipLaunchKernelGGL((gemm_bf16_mfma_kernel<EPI, MU>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NT_BF16),
                        SMEM_BYTES, s, p);
 }
 
@@ -459,7 +466,8 @@ void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
         case 5: launch_small<EPI, 5, 3>(p, s, splits); break;
         case 6: launch_small<EPI, 6, 3>(p, s, splits); break;
         case 7: launch_small<EPI, 8, 2>(p, s, splits); break;
-        default: launch_256<EPI>(p, s, splits); break;
+        case 8: launch_big<EPI, 6>(p, s, splits); break;
+        default: launch_big<EPI, 8>(p, s, splits); break;
     }
 }
 
