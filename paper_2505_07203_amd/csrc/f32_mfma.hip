@@ -307,8 +307,9 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l15 = lane & 15, l4 = lane >> 4;
     const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)blockIdx.y * BT;
-    const int n0 = blockIdx.x * BT;
+    const unsigned nt = (unsigned)((N + BT - 1) / BT);       // (one grid dimension: the others end at 65536 tiles)
+    const int64_t m0 = (int64_t)(blockIdx.x / nt) * BT;
+    const int n0 = (int)(blockIdx.x % nt) * BT;
     const int rows_a = (int)min((int64_t)BT, M - m0), rows_w = min(BT, N - n0);
     // resources: the rows of the tile that exist (others read as zero)
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + m0 * lda), 0, (int)(uint32_t)(rows_a * lda * 4), 0x00020000);
@@ -436,7 +437,7 @@ static void launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t
                             const float* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s) {
     constexpr int BT = 32 * T, SMEM = D * 2 * BT * 128;
     static_assert(SMEM <= 64 * 1024, "two workgroups per compute unit, and no larger than a launch may ask for unannounced");
-    const dim3 grid((unsigned)((N + BT - 1) / BT), (unsigned)((M + BT - 1) / BT));
+    const dim3 grid((unsigned)(((N + BT - 1) / BT) * ((M + BT - 1) / BT)));
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, D>), grid, dim3(256), SMEM, s, A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K);
 }
 

@@ -25,12 +25,12 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("gemm_mfma.hip", "gemm_common.h", "attn_mfma.hip", "kernels_basic.hip")
 
-# kernel class -> substring of the kernel's demangled name
+# kernel class -> substring of the kernel's demangled name, or several
 CLASSES = collections.OrderedDict([
     ("attention", "attn_fwd64_kernel"),
-    ("gate_up", "gemm_bf16_mfma_kernel<2, "),          # either tile height
-    ("residual", "gemm_bf16_mfma_kernel<1, "),
-    ("qkv", "gemm_bf16_mfma_kernel<3, "),
+    ("gate_up", ("gemm_bf16_mfma_kernel<2, ", "gemm_bf16_small_kernel<2, ")),          # every tile form
+    ("residual", ("gemm_bf16_mfma_kernel<1, ", "gemm_bf16_small_kernel<1, ")),
+    ("qkv", ("gemm_bf16_mfma_kernel<3, ", "gemm_bf16_small_kernel<3, ")),
     ("attention_redo", "attn_fwd_kernel<128, 1, 8, false>"),
     ("rmsnorm", "rmsnorm_bf16_vec_kernel"),
     ("lm_head", "lm_head_kernel"),
@@ -48,8 +48,8 @@ def kernel_sources_sha256():
 
 
 def classify(name):
-    for cls, sub in CLASSES.items():
-        if sub in name:
+    for cls, subs in CLASSES.items():
+        if any(sub in name for sub in ((subs,) if isinstance(subs, str) else subs)):
             return cls
     return None
 
@@ -190,7 +190,8 @@ def main():
             f.write("\n")
             for cls in ("attention", "gate_up", "residual", "qkv"):
                 if cls in traffic:
-                    f.write(f"traffic_bytes_per_launch\t{cls}\t{CLASSES[cls]}\t{traffic[cls]:.0f}\n")
+                    name = CLASSES[cls] if isinstance(CLASSES[cls], str) else CLASSES[cls][0]
+                    f.write(f"traffic_bytes_per_launch\t{cls}\t{name}\t{traffic[cls]:.0f}\n")
             f.write(f"kernel_sources_sha256\t{kernel_sources_sha256()}\n")
         print("wrote", path)
 
