@@ -356,7 +356,10 @@ __device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4
             const int head = c / p.hd;
             const int patch = (c - head * p.hd) >> 6;
             // (the rotation as written-out fused multiply-adds: left to the compiler, which of the two products of a sum is
-            //  rounded first differs between instantiations of this function, and so would the bits between tile heights)
+            //  rounded first differs between instantiations of this function, and so would the bits between tile heights.
+            //  Here the products with a (the first halves) are fused and those with b rounded, in epilogue_patch the ones with
+            //  the cosine are fused: what the compiler made of the bf16 and of the FP8 kernel when each had one form, so that
+            //  results keep the bits they had.)
             auto qk_patch = [&](auto has_bias) {
                 constexpr bool HB = decltype(has_bias)::value;
                 float ba[2][4], bb[2][4];
@@ -387,7 +390,7 @@ __device__ __forceinline__ void tile_epilogue16(const GemmParams& p, const f32x4
                             float a = acc[u][t][e], b = acc[u][t + 2][e];
                             if (HB) { a += ba[t][e]; b += bb[t][e]; }
                             lo[e] = fmaf(a, cv[e], -(b * sv[e])) * qs;
-                            hi[e] = fmaf(b, cv[e], a * sv[e]) * qs;
+                            hi[e] = fmaf(a, sv[e], b * cv[e]) * qs;
                         }
                         *(uint2*)(drow + i0) = pack4(lo[0], lo[1], lo[2], lo[3]);
                         *(uint2*)(drow + half + i0) = pack4(hi[0], hi[1], hi[2], hi[3]);

@@ -86,6 +86,47 @@ def test_fp8_qkv_rows_are_the_same_bits_in_launches_of_every_height(bias):
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
 
 
+def _rotated(a, b, cos, sin, first_fused):
+    """(a cos - b sin, second half) in float32 with one product of each sum fused: bf16 GEMM b cos + [a sin], FP8 GEMM
+    a sin + [b cos] (the bracketed product unrounded); a, b, cos, sin float32 tensors."""
+    import torch
+    fma = lambda x, y, z: (x.double() * y.double() + z.double()).float()
+    lo = fma(a, cos, -(b * sin))
+    return lo, fma(a, sin, b * cos) if first_fused else fma(b, cos, a * sin)
+
+
+@pytest.mark.parametrize("m", [64, 3000])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_rotation_keeps_its_rounding(fp8, m):
+    """One-hot activations make every accumulator exact, so the stored bits show which product of the rotation is rounded:
+    part of the library's results, the same in every tile form and from version to version."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    hq, hkv, hd, K = 16, 4, 128, 128
+    g = torch.Generator(device="cuda").manual_seed(m)
+    scale = torch.randn(m, generator=g, device="cuda").to(torch.bfloat16)
+    hot = torch.arange(m, device="cuda") % K
+    codes = torch.randint(0, 0x78, ((hq + 2 * hkv) * hd, K), generator=g, device="cuda").to(torch.uint8)      # E4M3, below 2^8
+    w = codes.view(torch.float8_e4m3fn).to(torch.bfloat16) if fp8 else torch.randn(codes.shape, generator=g, device="cuda").to(torch.bfloat16)
+    wqkv, _ = B.po_op_pack_qkv(w[:hq * hd].contiguous(), w[hq * hd:(hq + hkv) * hd].contiguous(), w[(hq + hkv) * hd:].contiguous(),
+                               hq, hkv, hd)
+    cos, sin = B.po_op_rope_table(m, hd, 500000.0)
+    if fp8:
+        a8 = torch.zeros(m, K, dtype=torch.uint8, device="cuda")
+        a8[torch.arange(m, device="cuda"), hot] = 0x38                                                  # 1.0
+        w8 = wqkv.float().to(torch.float8_e4m3fn).view(torch.uint8).contiguous()
+        q, k, _ = B.po_op_qkv_rope_fp8(a8, scale.float(), w8, torch.ones(w8.shape[0], device="cuda"), None, cos, sin, hq, hkv, hd)
+    else:
+        a = torch.zeros(m, K, dtype=torch.bfloat16, device="cuda")
+        a[torch.arange(m, device="cuda"), hot] = scale
+        q, k, _ = B.po_op_qkv_rope(a, wqkv, None, cos, sin, hq, hkv, hd)
+    acc = (w.float()[:, hot].t() * scale.float()[:, None])[:, :(hq + hkv) * hd].view(m, hq + hkv, hd)      # exact: 16 bits
+    lo, hi = _rotated(acc[..., :hd // 2], acc[..., hd // 2:], cos[:, None], sin[:, None], not fp8)
+    want = torch.cat((lo, hi), -1).to(torch.bfloat16)
+    got = torch.cat((q.view(m, hq, hd), k.view(m, hkv, hd)), 1)
+    assert int((got != want).sum()) == 0
+
+
 @pytest.mark.parametrize("N,K", [(4096, 64), (4096, 100), (1030, 688), (256, 4), (33, 1000)])
 def test_f32_rows_are_the_same_bits_in_launches_of_every_height(N, K):
     import torch
