@@ -5,6 +5,7 @@
 // fixed order that depends on nothing but its own row and column; speed only has to be enough for whole
 // configurations (32 layers x 32768 tokens) to run in seconds.
 #include "po_internal.h"
+#include "slice_window.h"
 
 #include <algorithm>
 
@@ -311,9 +312,10 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
     const int64_t m0 = (int64_t)(blockIdx.x / nt) * BT;
     const int n0 = (int)(blockIdx.x % nt) * BT;
     const int rows_a = (int)min((int64_t)BT, M - m0), rows_w = min(BT, N - n0);
-    // resources: the rows of the tile that exist (others read as zero)
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + m0 * lda), 0, (int)(uint32_t)(rows_a * lda * 4), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (int64_t)n0 * ldw), 0, (int)(uint32_t)(rows_w * ldw * 4), 0x00020000);
+    // bounds: the rows of the tile that exist (others read as zero)
+    const int a_bytes = (int)(uint32_t)(rows_a * lda * 4), w_bytes = (int)(uint32_t)(rows_w * ldw * 4);
+    void* const pa_ = (void*)(A + m0 * lda);
+    void* const pw_ = (void*)(W + (int64_t)n0 * ldw);
     uint32_t voa[4], vow[4];                     // (T entries used: T loads of 8 rows per wavefront and operand)
     const int KT = (K + 31) / 32;
     uint32_t tail = 0;                           // bit i: load i of the last slice lies beyond K for this lane
@@ -325,15 +327,19 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
         vow[i] = (uint32_t)row * (uint32_t)(ldw * 4) + seg * 16;
         if ((KT - 1) * 32 + seg * 4 >= K) tail |= 1u << i;
     }
-    // byte offset of slice s_ along K; slices past the end, and columns of the last one past K, lie outside the resources:
-    // they read as zero without traffic
+    // Bounds are checked on the lane offset (not on the scalar offset along K): columns of the last slice past K get one
+    // outside, slices past the end an empty descriptor; both read as zero without traffic.
+#define PO_SLICE_RSRC(s_)                                                                                              \
+    const SliceWindow wa_ = slice_window((s_), KT, (unsigned)a_bytes, 128), ww_ = slice_window((s_), KT, (unsigned)w_bytes, 128); \
+    const int so = wa_.offset;                                                                                         \
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(pa_, 0, (int)wa_.bytes, 0x00020000);           \
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)ww_.bytes, 0x00020000);
 #define PO_DMA(s_, pos_, i_)                                                                                          \
     {                                                                                                                  \
-        const int so_ = (s_) < KT ? (s_) * 128 : 0x40000000;                                                           \
         const uint32_t past_ = ((s_) == KT - 1 && (tail >> (i_) & 1)) ? 0x40000000u : 0u;                              \
         unsigned char* d_ = smem + (pos_) * 2 * UNIT + (wave * T + (i_)) * 1024;                                       \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)d_, 16, voa[(i_)] + past_, so_, 0, 0); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(d_ + UNIT), 16, vow[(i_)] + past_, so_, 0, 0); \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)d_, 16, voa[(i_)] + past_, so, 0, 0); \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(d_ + UNIT), 16, vow[(i_)] + past_, so, 0, 0); \
     }
     int fo[2];                                   // the lane's 8 elements of a row: segments 2 g and 2 g + 1
 #pragma unroll
@@ -345,9 +351,11 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < D; ++s)
+    for (int s = 0; s < D; ++s) {
+        PO_SLICE_RSRC(s)
 #pragma unroll
         for (int i = 0; i < T; ++i) PO_DMA(s, s, i)
+    }
     PO_WAIT_BARRIER((D - 1) * 2 * T);            // slice 0 has landed
     f32x4 a0[2][T], w0[2][T], a1[2][T], w1[2][T];
 #pragma unroll
@@ -370,6 +378,7 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
                 acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(WC[h][t][e], AC[h][u][e], acc[u][t], 0, 0, 0);       \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
             if (h == 0 && e == 0) {                                                                                   \
+                PO_SLICE_RSRC(s + D)                                                                                  \
                 _Pragma("unroll") for (int i = 0; i < T; ++i) PO_DMA(s + D, ps, i)                                    \
             }                                                                                                         \
             if (h == 0 && e > 0 && e < 3) {                                                                           \
@@ -398,6 +407,7 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
     if (s < KT) PO_SLICE(a0, w0, a1, w1)
 #undef PO_SLICE
 #undef PO_DMA
+#undef PO_SLICE_RSRC
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // a lane holds token row l15 of a tile and four consecutive features
     const bool vec = (N % 4 == 0) && (ldc % 4 == 0) && (!R || ldr % 4 == 0);

@@ -1,6 +1,7 @@
 // Shared by the bf16 and the FP8 GEMM (gfx950): launch parameters and the epilogues.
 #pragma once
 #include "po_internal.h"
+#include "slice_window.h"
 
 #include <type_traits>
 

@@ -269,8 +269,8 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     const int64_t k0 = (EPI == EPI_PARTIAL) ? (int64_t)blockIdx.y * p.K : 0;
     const uint32_t a_bytes = (uint32_t)min(BM_, p.M - m0) * (uint32_t)p.lda - (uint32_t)k0;
     const uint32_t w_bytes = (uint32_t)min(BN_, p.N - n0) * (uint32_t)p.ldw - (uint32_t)k0;
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)p.A + (int64_t)m0 * p.lda + k0), 0, (int)a_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)p.W + (int64_t)n0 * p.ldw + k0), 0, (int)w_bytes, 0x00020000);
+    void* const pa_ = (void*)((const unsigned char*)p.A + (int64_t)m0 * p.lda + k0);
+    void* const pw_ = (void*)((const unsigned char*)p.W + (int64_t)n0 * p.ldw + k0);
     uint32_t voa[8], vow[4];                               // (voa: NA entries used)
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
@@ -283,14 +283,19 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
         vow[i] = (uint32_t)row * (uint32_t)p.ldw + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
     const int KT = p.K / BKB;
-    // byte offset of slice s_ along K; slices past the end lie outside both resources: they read as zero without traffic
-#define PO_SOFF(s_) ((s_) < KT ? (s_) * BKB : 0x40000000)
-#define PO_DMA_A(soff_, pos_, i_)                                                                                     \
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(smem + (pos_) * (AU + WU) + (wave * NA + (i_)) * 1024), \
-                                             16, voa[(i_)], (soff_), 0, 0);
-#define PO_DMA_W(soff_, pos_, i_)                                                                                     \
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(smem + (pos_) * (AU + WU) + AU + (wave * NW + (i_)) * 1024), \
-                                             16, vow[(i_)], (soff_), 0, 0);
+    // (descriptors empty past the end of K, as in the bf16 small kernel)
+#define PO_SLICE_RSRC(s_)                                                                                              \
+    const SliceWindow wa_ = slice_window((s_), KT, (unsigned)a_bytes, BKB), ww_ = slice_window((s_), KT, (unsigned)w_bytes, BKB); \
+    const int so = wa_.offset;                                                                                         \
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(pa_, 0, (int)wa_.bytes, 0x00020000);           \
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)ww_.bytes, 0x00020000);
+#define PO_DMA_A(pos_, i_)                                                                                               \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                            \
+        ra, (__attribute__((address_space(3))) void*)(smem + (pos_) * (AU + WU) + (wave * NA + (i_)) * 1024), 16, voa[(i_)], so, 0, 0);
+#define PO_DMA_W(pos_, i_)                                                                                               \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                            \
+        rw, (__attribute__((address_space(3))) void*)(smem + (pos_) * (AU + WU) + AU + (wave * NW + (i_)) * 1024), 16,     \
+        vow[(i_)], so, 0, 0);
     // a fragment: 32 rows from tile_ on, the 32 bytes of k-step kk_ a lane takes (two 16-byte segments, swizzled)
     int fo[2][2];
 #pragma unroll
@@ -310,11 +315,11 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
             for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 #pragma unroll
     for (int s = 0; s < D; ++s) {
-        const int so = PO_SOFF(s);
+        PO_SLICE_RSRC(s)
 #pragma unroll
-        for (int i = 0; i < NA; ++i) PO_DMA_A(so, s, i)
+        for (int i = 0; i < NA; ++i) PO_DMA_A(s, i)
 #pragma unroll
-        for (int i = 0; i < NW; ++i) PO_DMA_W(so, s, i)
+        for (int i = 0; i < NW; ++i) PO_DMA_W(s, i)
     }
     PO_WAIT_BARRIER((D - 1) * (NA + NW));                      // slice 0 has landed
     i32x8 A0[2][MR], W0[2][2], A1[2][MR], W1[2][2];            // fragments of a whole slice: [k-step][tile]
@@ -331,7 +336,7 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     {                                                                                                                 \
         PO_WAIT_BARRIER((D - 2) * (NA + NW));      /* slice s+1 has landed; all LDS reads of slice s are done */      \
         const int ps1 = ps + 1 >= D ? 0 : ps + 1;                                                                     \
-        const int so = PO_SOFF(s + D);                                                                                \
+        PO_SLICE_RSRC(s + D)                                                                                          \
         const unsigned char* u1 = smem + ps1 * (AU + WU);                                                             \
         _Pragma("unroll") for (int m = 0; m < 4 * MR; ++m) {                                                          \
             const int kk_ = m / (2 * MR), mi_ = (m >> 1) % MR, ni_ = m & 1;                                           \
@@ -344,8 +349,8 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
                     const int fk_ = x / (MR + 2) & 1, fj_ = x % (MR + 2);                                             \
                     if (x < F_ && fj_ < 2) WN[fk_][fj_ & 1] = PO_FRAG(u1 + w_base + fj_ * 4096, fk_);                 \
                     else if (x < F_) AN[fk_][fj_ >= 2 ? fj_ - 2 : 0] = PO_FRAG(u1 + a_base + (fj_ - 2) * 4096, fk_);  \
-                    else if (x < F_ + NA) PO_DMA_A(so, ps, ((x - F_) & 7))                                            \
-                    else PO_DMA_W(so, ps, ((x - F_ - NA) & 3))                                                        \
+                    else if (x < F_ + NA) PO_DMA_A(ps, ((x - F_) & 7))                                            \
+                    else PO_DMA_W(ps, ((x - F_ - NA) & 3))                                                        \
                     __builtin_amdgcn_sched_barrier(0);                                                                \
                 }                                                                                                     \
             }                                                                                                         \
@@ -364,7 +369,7 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
 #undef PO_FRAG
 #undef PO_DMA_A
 #undef PO_DMA_W
-#undef PO_SOFF
+#undef PO_SLICE_RSRC
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // codes -> values
 #pragma unroll

@@ -248,8 +248,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     const int64_t k0 = (EPI == EPI_PARTIAL) ? (int64_t)blockIdx.y * p.K : 0;
     const uint32_t a_bytes = (uint32_t)min(BM_, p.M - m0) * (uint32_t)(p.lda * 2) - (uint32_t)(k0 * 2);
     const uint32_t w_bytes = (uint32_t)min(BN_, p.N - n0) * (uint32_t)(p.ldw * 2) - (uint32_t)(k0 * 2);
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p.A + (int64_t)m0 * p.lda + k0), 0, (int)a_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(p.W + (int64_t)n0 * p.ldw + k0), 0, (int)w_bytes, 0x00020000);
+    void* const pa_ = (void*)(p.A + (int64_t)m0 * p.lda + k0);
+    void* const pw_ = (void*)(p.W + (int64_t)n0 * p.ldw + k0);
     uint32_t voa[8], vow[4];                               // (voa: NA entries used)
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
@@ -262,10 +262,20 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         vow[i] = (uint32_t)row * (uint32_t)(p.ldw * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
     const int KT = p.K / BK;
-    // byte offset of slice s_ along K; slices past the end lie outside both resources: they read as zero without traffic
-#define PO_SOFF(s_) ((s_) < KT ? (s_) * (BK * 2) : 0x40000000)
-#define PO_DMA_A(soff_, pos_, i_)                                                                                         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(smem + (pos_) * AU + (wave * NA + (i_)) * 1024),                                              16, voa[(i_)], (soff_), 0, 0);
-#define PO_DMA_W(soff_, pos_, i_)                                                                                         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(smem + (D + 1) * AU + (pos_) * WU + (wave * NW + (i_)) * 1024),                                              16, vow[(i_)], (soff_), 0, 0);
+    // Loads of slice s_ go through descriptors that are empty past the end of K: they read as zero without traffic, by
+    // the lane offset (bounds are checked on that, not on the scalar offset along K).
+#define PO_SLICE_RSRC(s_)                                                                                              \
+    const SliceWindow wa_ = slice_window((s_), KT, (unsigned)a_bytes, BK * 2), ww_ = slice_window((s_), KT, (unsigned)w_bytes, BK * 2); \
+    const int so = wa_.offset;                                                                                         \
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(pa_, 0, (int)wa_.bytes, 0x00020000);           \
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)ww_.bytes, 0x00020000);
+#define PO_DMA_A(pos_, i_)                                                                                               \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                            \
+        ra, (__attribute__((address_space(3))) void*)(smem + (pos_) * AU + (wave * NA + (i_)) * 1024), 16, voa[(i_)], so, 0, 0);
+#define PO_DMA_W(pos_, i_)                                                                                               \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                            \
+        rw, (__attribute__((address_space(3))) void*)(smem + (D + 1) * AU + (pos_) * WU + (wave * NW + (i_)) * 1024), 16,  \
+        vow[(i_)], so, 0, 0);
     int f_off[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) f_off[ks] = l15 * 128 + (((ks * 4 + l4) ^ ((l15 >> 1) & 7)) << 4);
@@ -279,11 +289,11 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
 
 #pragma unroll
     for (int s = 0; s < D; ++s) {
-        const int so = PO_SOFF(s);
+        PO_SLICE_RSRC(s)
 #pragma unroll
-        for (int i = 0; i < NA; ++i) PO_DMA_A(so, s, i)
+        for (int i = 0; i < NA; ++i) PO_DMA_A(s, i)
 #pragma unroll
-        for (int i = 0; i < NW; ++i) PO_DMA_W(so, s, i)
+        for (int i = 0; i < NW; ++i) PO_DMA_W(s, i)
     }
     PO_WAIT_BARRIER((D - 1) * (NA + NW));                      // slice 0 has landed
     bf16x8 A0[MU], A1[MU], W0[4], W1[4];
@@ -299,18 +309,18 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     for (int s = 0; s < KT; ++s) {
         const int pa1 = pa + 1 > D ? 0 : pa + 1, pw1 = pw + 1 >= D ? 0 : pw + 1;
         const int pa_free = pa == 0 ? D : pa - 1;              // position of A(s - 1)
-        const int so = PO_SOFF(s + D);
+        PO_SLICE_RSRC(s + D)
         const unsigned char* ua = smem + pa * AU + a_base;
         const unsigned char* uw = smem + pw * WU + w_base;
         const unsigned char* ua1 = smem + pa1 * AU + a_base;
         const unsigned char* uw1 = smem + pw1 * WU + w_base;
         // phase 0: k-step 0 | reads k-step 1; loads A(s + D) into the position A(s - 1) left
-#define PO_LA(i_) PO_DMA_A(so, pa_free, ((i_) < NA ? (i_) : 0))
+#define PO_LA(i_) PO_DMA_A(pa_free, ((i_) < NA ? (i_) : 0))
         PO_PHASE(A0, W0, A1, W1, ua, uw, 1, NA, PO_LA)
         // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1 and A(s+D)); all LDS reads of slice s are done
         PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA);
         // phase 1: k-step 1 | reads k-step 0 of slice s+1; loads W(s + D) into W(s)'s position
-#define PO_LW(i_) PO_DMA_W(so, pw, ((i_) < NW ? (i_) : 0))
+#define PO_LW(i_) PO_DMA_W(pw, ((i_) < NW ? (i_) : 0))
         PO_PHASE(A1, W1, A0, W0, ua1, uw1, 0, NW, PO_LW)
         pa = pa1;
         pw = pw1;
@@ -320,7 +330,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
 #undef PO_PHASE
 #undef PO_DMA_A
 #undef PO_DMA_W
-#undef PO_SOFF
+#undef PO_SLICE_RSRC
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (EPI == EPI_PARTIAL) {
         GemmParams q = p;

@@ -1,0 +1,19 @@
+// What the ring GEMMs may read of an operand tile for slice s along K (plain C++, host and device).
+#pragma once
+
+namespace po {
+
+// A tile is copied into LDS through a buffer descriptor of `bytes` bytes from the tile's first element, at (lane offset +
+// scalar offset); lanes beyond the descriptor read as zero without traffic.  The bounds check is made on the LANE offset
+// only: by contract the scalar offset is added behind it.  So a slice past the end of K must not be expressed by a
+// scalar offset outside the tile; it gets an empty descriptor instead.
+struct SliceWindow {
+    unsigned bytes;      // of the descriptor
+    int offset;          // scalar offset of the slice
+};
+
+constexpr SliceWindow slice_window(int s, int n_slices, unsigned tile_bytes, int slice_bytes) {
+    return s < n_slices ? SliceWindow{tile_bytes, s * slice_bytes} : SliceWindow{0u, 0};
+}
+
+}  // namespace po
