@@ -409,6 +409,15 @@ po_status po_op_attention_split(const void* dev_q, const void* dev_k, const void
                                 void* dev_scratch_vt, void* dev_scratch_part, size_t part_bytes, int64_t N,
                                 int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t q_row0,
                                 void* hip_stream, int32_t* splits_used);
+/* The same as the full path calls it in few-rows mode: q_prescaled as in po_op_attention, and the first n2 positions
+ * (a multiple of 64, at most q_row0; 0 = none) read from a second pair in the layout of a prefix-cache entry: dev_k2
+ * [n2, Hkv, hd] and dev_vt2 [Hkv*hd][ldv2] (V transposed; ldv2 >= n2 a multiple of 64; 16-byte aligned).  Rows below n2
+ * of dev_k and dev_v are not used then. */
+po_status po_op_attention_split_prefix(const void* dev_q, const void* dev_k, const void* dev_v, void* dev_o,
+                                       void* dev_scratch_vt, void* dev_scratch_part, size_t part_bytes, int64_t N,
+                                       int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t q_row0,
+                                       int32_t q_prescaled, const void* dev_k2, const void* dev_vt2, int64_t ldv2,
+                                       int64_t n2, void* hip_stream, int32_t* splits_used);
 
 /* Rotary embedding in place on x [N, H, hd] for positions 0..N-1 (angles formed in
  * double precision). */

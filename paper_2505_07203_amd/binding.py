@@ -39,6 +39,7 @@ EXPORTS = [
     "po_op_quantize_rows", "po_op_rmsnorm_quantize", "po_op_linear_fp8", "po_op_qkv_rope_fp8",
     "po_attach_kv_cache_slots", "po_kv_cache_match", "po_kv_cache_slot", "po_sched_pick_multi",
     "po_profile_jct", "po_engine_step", "po_set_few_rows_split", "po_set_storage_rounding", "po_op_linear_split", "po_sched_push_request", "po_op_attention_split",
+    "po_op_attention_split_prefix",
     "po_sched_create", "po_sched_destroy", "po_sched_set_jct_model", "po_sched_fit_jct_model", "po_sched_push",
     "po_sched_size", "po_sched_pick", "po_sched_remove", "po_op_rope_static", "po_op_mfma_peak", "po_op_stream_copy",
 ]
@@ -118,6 +119,8 @@ def lib() -> C.CDLL:
     L.po_op_rmsnorm.argtypes = [i32, vp, vp, vp, i64, i32, f32, vp]
     L.po_op_linear.argtypes = [i32, vp, vp, vp, vp, i64, i32, i32, vp]
     L.po_op_attention_split.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, vp, C.POINTER(i32)]
+    L.po_op_attention_split_prefix.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, i32, vp, vp, i64, i64, vp,
+                                               C.POINTER(i32)]
     L.po_op_linear_split.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_gate_up_silu.argtypes = [i32, vp, vp, vp, vp, i64, i32, i32, vp]
     L.po_op_pack_gate_up.argtypes = [i32, vp, vp, vp, i32, i32, vp]
@@ -544,15 +547,24 @@ def po_op_attention(q, k, v, out=None, q_prescaled: bool = False):
 
 def po_op_attention_split(q, k, v, q_row0: int, part_bytes: int = 1 << 28):
     """-> (o or None, splits): rows [q_row0, N) by the split-key kernel; None when nothing was split"""
+    return po_op_attention_split_prefix(q, k, v, q_row0, part_bytes=part_bytes)
+
+
+def po_op_attention_split_prefix(q, k, v, q_row0: int, q_prescaled: bool = False, k2=None, vt2=None, n2: int = 0, out=None,
+                                 part_bytes: int = 1 << 28):
+    """po_op_attention_split as the full path calls it: q_prescaled as in po_op_attention; the first n2 positions (a
+    multiple of 64) from k2 [>= n2, Hkv, hd] and the transposed vt2 [Hkv*hd, ldv2]; out may be q itself"""
     import torch
     N, Hq, hd = q.shape
     Hkv = k.shape[1]
-    o = torch.zeros_like(q)
+    o = torch.zeros_like(q) if out is None else out
     vt = torch.empty(Hkv * hd * ((N + 63) // 64 * 64), dtype=q.dtype, device=q.device)
-    part = torch.empty(part_bytes, dtype=torch.uint8, device=q.device)
+    part = torch.empty(max(part_bytes, 4), dtype=torch.uint8, device=q.device)
     n = C.c_int32(0)
-    check(lib().po_op_attention_split(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), vt.data_ptr(), part.data_ptr(),
-                                      part_bytes, N, Hq, Hkv, hd, q_row0, _stream(), C.byref(n)))
+    check(lib().po_op_attention_split_prefix(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), vt.data_ptr(),
+                                             part.data_ptr(), part_bytes, N, Hq, Hkv, hd, q_row0, 1 if q_prescaled else 0,
+                                             None if k2 is None else k2.data_ptr(), None if vt2 is None else vt2.data_ptr(),
+                                             0 if vt2 is None else vt2.shape[1], n2, _stream(), C.byref(n)))
     torch.cuda.synchronize()
     return (o if n.value > 1 else None), n.value
 

@@ -65,6 +65,106 @@ def test_scores_far_outside_the_exponent_range(total, cached):
     _compare(_cfg(8, 2), total, cached, 30.0, 6e-2)
 
 
+# ---- the operator by itself, every row and head against float64
+
+def _operands(n, hq, hkv, hd, seed, kind="ordinary", rows=None):
+    """Prescaled queries (scores in log2 units), keys, values.  Kinds that leave the range 2^-60 .. 2^100 of a row's sum of
+    exponentials: "shifted" moves whole rows of some heads up or down by 140 (softmax is invariant to it), "spread" makes
+    scores hundreds apart, "late" raises single late keys by 150."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v = (torch.randn(n, h, hd, generator=g, device="cuda") for h in (hq, hkv, hkv))
+    q *= 1.4 * 1.4427 * hd ** -0.5
+    rows = torch.arange(n, device="cuda")[:, None]
+    heads = torch.arange(hq, device="cuda")[None]
+    if kind == "shifted":
+        k[:, :, 0] = 8.0
+        q[:, :, 0] = torch.where((rows + heads) % 3 == 0, 17.5, 0.0) - torch.where((rows + heads) % 7 == 2, 17.5, 0.0)
+    elif kind == "spread":
+        q *= torch.where((rows + heads) % 2 == 0, 60.0, 1.0)[..., None]
+    elif kind == "late":
+        k[:, :, 0] = 0.0
+        k[n // 2::97, :, 0] = 8.0
+        q[:, :, 0] = torch.where(heads % 2 == 0, 18.75, 0.0).expand(n, hq)
+    return q.to(torch.bfloat16), k.to(torch.bfloat16), v.to(torch.bfloat16)
+
+
+def _reference(q, k, v, r0):
+    """Rows from r0 on in float64 -> outputs, sum p |v|, sqrt(sum p^2 v^2) (p normalised), log2 of the sums of 2^score"""
+    import torch
+    n, hq, hkv = q.shape[0], q.shape[1], k.shape[1]
+    outs = []
+    for h in range(hq):
+        c = h // (hq // hkv)
+        s = q[r0:, h].double() @ k[:, c].double().t()
+        future = torch.arange(n, device="cuda")[None] > torch.arange(r0, n, device="cuda")[:, None]
+        s = s.masked_fill(future, -float("inf")) * np.log(2.0)
+        lse = torch.logsumexp(s, -1)
+        p, vv = (s - lse[:, None]).exp(), v[:, c].double()
+        outs.append((p @ vv, p @ vv.abs(), ((p * p) @ (vv * vv)).sqrt(), lse / np.log(2.0)))
+    return [torch.stack(x, 1) for x in zip(*outs)]
+
+
+def _check_rows(o, ref, r0, extra=0.0):
+    """Probabilities are rounded to bf16 (2^-9 of each), the sum is one of such roundings, and the output is rounded once
+    more; float32 sums and the scores' own rounding stay below 2e-4.  Worst case per value; and the root mean square over a head's dimensions, where roundings are as
+    good as independent, at twice their size: a missing or doubled key tile shows there."""
+    want, a1, a2, _ = ref
+    err = (o[r0:].double() - want).abs()
+    assert float((err / a1).max()) <= 3 * 2.0 ** -9 + 2e-4 + extra
+    rms = lambda x: (x * x).mean(-1).sqrt()
+    assert float((rms(err) / (2.0 ** -9 * (rms(a2) + rms(want)) + (1e-5 + extra) * rms(a1))).max()) <= 2.0
+
+
+SHAPES = [(8, 2), (5, 1), (3, 3), (32, 8)]
+
+
+@pytest.mark.parametrize("hq,hkv", SHAPES)
+@pytest.mark.parametrize("n,r0,n2", [(257, 0, 0), (300, 299, 256), (641, 577, 576), (700, 511, 448), (1003, 100, 64), (1500, 500, 0),
+                                     (1411, 1408, 1408), (2200, 1500, 1472), (3137, 2987, 2944)])
+def test_every_row_against_float64(n, r0, n2, hq, hkv):
+    from paper_2505_07203_amd import binding as B
+    q, k, v = _operands(n, hq, hkv, 128, n + hq)
+    ref = _reference(q, k, v, r0)
+    for prescaled in (True, False):
+        x = q if prescaled else (q.float() / B.attention_q_scale(128)).to(q.dtype)
+        want = ref if prescaled else _reference(x.double() * B.attention_q_scale(128), k, v, r0)
+        o, pieces = _split(x, k, v, r0, n2, prescaled)
+        assert pieces > 1 and not o[:r0].any()
+        _check_rows(o, want, r0)
+
+
+def _split(q, k, v, r0, n2, prescaled=True, **kw):
+    """with the first n2 positions in a pair of their own, and poison in their place in k and v"""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    if not n2:
+        return B.po_op_attention_split_prefix(q, k, v, r0, prescaled, **kw)
+    n, hkv, hd = k.shape
+    k2 = k[:n2].clone()
+    vt2 = torch.full((hkv * hd, n2 + 128), float("nan"), dtype=v.dtype, device="cuda")
+    vt2[:, :n2] = v[:n2].reshape(n2, hkv * hd).t()
+    k, v = k.clone(), v.clone()
+    k[:n2] = float("nan")
+    v[:n2] = float("nan")
+    return B.po_op_attention_split_prefix(q, k, v, r0, prescaled, k2, vt2, n2, **kw)
+
+
+@pytest.mark.parametrize("kind", ["shifted", "spread", "late"])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1), (3, 3)])
+@pytest.mark.parametrize("n,r0,n2", [(300, 0, 0), (700, 511, 448), (2200, 2050, 2048)])
+def test_rows_far_outside_the_exponent_range_against_float64(n, r0, n2, hq, hkv, kind):
+    q, k, v = _operands(n, hq, hkv, 128, 7 * n + hq, kind)
+    ref = _reference(q, k, v, r0)
+    lse = ref[3]
+    assert float(lse.max()) > 100.0 and (kind != "shifted" or float(lse.min()) < -60.0)
+    assert ((lse > -60.0) & (lse < 100.0)).any()                       # and ordinary rows beside them
+    o, pieces = _split(q, k, v, r0, n2)
+    assert pieces > 1
+    # scores of several hundred: float32 holds them to about 2e-5, their sums over 128 products to a few times that
+    _check_rows(o, ref, r0, extra=2e-3 if kind == "spread" else 5e-4)
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
 def test_value_transpose_aligned_and_unaligned(n):
     """V at a 16-byte boundary and two bytes off it take different kernels to the same transposed copy."""
