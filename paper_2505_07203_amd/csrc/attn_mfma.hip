@@ -408,13 +408,18 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 // (scores far above or far below that) gives up and is recomputed by the running-maximum kernel, like an overflow
 // in the other form.
 //
-// SPLIT (with PRE; few query rows against many keys): rows q_row0 .. N-1 of ALL query heads of a KV head are the rows of
-// a workgroup, since they share its keys (a 150-row suffix of 4 heads per KV head is 600 rows: 3 workgroups that are
+// SPLIT (few query rows against many keys): rows q_row0 .. N-1 of ALL query heads of a KV head are the rows of a
+// workgroup, since they share its keys (a 150-row suffix of 4 heads per KV head is 600 rows: 3 workgroups that are
 // nearly full instead of 4 with 59 % of their rows), and the key tiles are divided into pieces of `per` tiles: pieces 0
 // .. n2 - 1 cover tiles [0, tiles2) of a second K / V^T pair (a prefix-cache entry read in place), the rest what follows
-// in the first.  A piece writes its unnormalised fp32 accumulators and row sums; without a reference exponent the sums of
-// the pieces simply add, in attn_combine_kernel, which also looks at the total.  Measured (32 heads on 8 KV heads, 150
-// rows behind 14 000 keys, per layer): 67 us with the 32-row kernel above, 45 us here; one row 43 us and 17.
+// in the first.  A piece writes its unnormalised fp32 accumulators, its reference exponents and its row sums, and
+// attn_combine_kernel merges the pieces.  Every piece takes its reference from its own first 32 keys (a zero reference,
+// as PRE has it, would make all pieces of a row flush or overflow together).  Nothing moves it afterwards: sums only grow,
+// so one look at the end finds a row sum past 2^100 or an accumulator that is not finite, and the workgroup then goes
+// through its piece a second time with the exact maxima, which a pass over K alone gives it: at most 2.5 times the time
+// of a piece, whatever the scores.  Measured (32 heads on 8 KV heads behind 14 000 keys, both kernels of a call): one row
+// 47 us with the 32-row kernel above, 26 here; 150 rows 67 and 50; 600 rows 201 and 141.  At 8000 keys 150 rows take 51 us
+// with ordinary scores and 84 with scores hundreds apart.
 struct SplitArgs {
     const bf16_t *k2, *vt2;
     int64_t ldv2;
@@ -427,7 +432,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                                                          int Hq, int Hkv, float sc_log2e, int nqt, int hpx, int* redo,
                                                          const SplitArgs sp) {
     constexpr int HD = 128, KS = 8, HT = 4;
-    constexpr int TILE_BYTES = 64 * HD * 2;
+    constexpr bool LATE = PRE || SPLIT;     // the row sums are looked at once, behind the last block
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     int qtile, head, kvh, piece = 0, tile0 = 0, piece_tiles = 0;
@@ -551,7 +556,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
     float mb[2], lrow[2] = {0.f, 0.f};      // reference exponents (log2 domain) and row sums per query tile
-    float lsum[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};       // PRE: the row sums as four partial sums each
+    float lsum[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};       // LATE: the row sums as four partial sums each
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     int gave_up = 0;                        // wavefront-uniform: a row sum left the range the reference scheme covers
     int* const lds_gave_up = (int*)(smem + 2 * A64_NSTAGE * A64_TILE);     // one word behind the ring
@@ -578,6 +583,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         out_ = half_swap_max(fmaxf(m0_, m1_));                                                   \
     }
 
+    float mtop[2] = {0.f, 0.f};             // SPLIT: the piece's exact maxima, for the second attempt
+    for (int attempt = 0;; ++attempt) {     // (one attempt unless SPLIT)
+    if (SPLIT) asm volatile("" : "+v"(vpos[0]), "+v"(vpos[1]));      // (keeps the masks of the first block from being formed, and spilled, in front of the loop)
     // ---- prologue: three tiles in flight, S(0), reference maxima
     _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(0, 0, jj);
     _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(1, 1, jj);
@@ -601,10 +609,14 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
             }
         }
         if (31 > (SPLIT ? pos_min : qw)) { PO_MASK(sa, 0, 0); PO_MASK(sa, 0, 1); }
-        float m0 = 0.f, m1 = 0.f;
-        if (!PRE) {
+        float m0 = mtop[0], m1 = mtop[1];
+        if (!PRE && attempt == 0) {
             PO_BLOCKMAX(sa, 0, m0);
             PO_BLOCKMAX(sa, 1, m1);
+        }
+        if (SPLIT) {                        // (a row all of whose keys so far are masked; its probabilities come out 0)
+            m0 = fmaxf(m0, -1.0e30f);
+            m1 = fmaxf(m1, -1.0e30f);
         }
         mb[0] = m0 * sc_log2e;
         mb[1] = m1 * sc_log2e;
@@ -705,16 +717,16 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                     const int c_ = (c - 8) * 2 + qt;             /* 0..15 */                                    \
                     if (c_ == 8 || c_ == 9) {                                                                   \
                         const int sq_ = c_ - 8;                                                                 \
-                        /* four independent chains: a dependent dot product waits about 6 cycles.  PRE: the     \
+                        /* four independent chains: a dependent dot product waits about 6 cycles.  LATE: the    \
                            four partial sums live across blocks (nothing looks at the row sum before the end) */\
                         float l_[4] = {lrow[sq_], 0.f, 0.f, 0.f};                                               \
                         _Pragma("unroll") for (int h2 = 0; h2 < 2; ++h2)                                        \
                         _Pragma("unroll") for (int e2 = 0; e2 < 4; ++e2) {                                      \
                             const bf16x2 pr2_ = {pf[sq_][h2][2 * e2], pf[sq_][h2][2 * e2 + 1]};                 \
-                            if (PRE) lsum[sq_][e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, lsum[sq_][e2], false); \
+                            if (LATE) lsum[sq_][e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, lsum[sq_][e2], false); \
                             else l_[e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, l_[e2], false);           \
                         }                                                                                       \
-                        if (!PRE) lrow[sq_] = (l_[0] + l_[1]) + (l_[2] + l_[3]);                                \
+                        if (!LATE) lrow[sq_] = (l_[0] + l_[1]) + (l_[2] + l_[3]);                               \
                     }                                                                                           \
                     if ((c_ & 3) == 3) { PO_DMA(DMA_T_, DMA_S_, (DMA_J0_) + (c_ >> 2)); }                       \
                 }                                                                                               \
@@ -722,8 +734,8 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
             }                                                                                                   \
         }                                                                                                       \
         /* ---- renormalise when a row sum has grown past 2^40 (rare; see the note on the reference) */         \
-        /* (PRE: nothing to watch.  The sums only grow, an overflow stays an overflow: one look at the end does) */ \
-        if (!PRE && __any(!(lrow[0] <= 0x1p40f) || !(lrow[1] <= 0x1p40f))) {                                    \
+        /* (LATE: the sums only grow, an overflow stays an overflow: one look at the end does) */              \
+        if (!LATE && __any(!(lrow[0] <= 0x1p40f) || !(lrow[1] <= 0x1p40f))) {                                   \
             const float t0_ = half_swap_sum(lrow[0]), t1_ = half_swap_sum(lrow[1]);                             \
             if (__any(!(t0_ < 0x1p100f) || !(t1_ < 0x1p100f))) gave_up = 1;                                     \
             int e0_ = ilogbf(t0_), e1_ = ilogbf(t1_);                                                           \
@@ -786,6 +798,65 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
         _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(j + 3, (j + 3) & 3, jj);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    PO_MFMA_DRAIN();
+    if (!SPLIT) break;
+    lrow[0] = (lsum[0][0] + lsum[0][1]) + (lsum[0][2] + lsum[0][3]);
+    lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
+    if (attempt) break;
+    // ---- SPLIT: did a row sum pass 2^100, or (large values) an accumulator the float range?
+    uint32_t top = 0;
+#pragma unroll
+    for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(oacc[ht][qt][r]) & 0x7fffffffu);
+    if (__any(top >= 0x7f800000u || !(lrow[0] < 0x1p100f) || !(lrow[1] < 0x1p100f)) && lane == 0) *(volatile int*)lds_gave_up = 1;
+    __syncthreads();
+    if (!*(volatile int*)lds_gave_up) break;
+    // the exact maxima: K tiles alone, one in flight
+    mtop[0] = mtop[1] = -INFINITY;
+    _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) PO_DMA(0, 0, jj);
+    for (int t = 0; t < n_tiles; ++t) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is there, the other stage free
+        if (t + 1 < n_tiles) {
+            _Pragma("unroll") for (int jj = 0; jj < 4; ++jj) PO_DMA(t + 1, (t + 1) & 1, jj);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 kf = *(const bf16x8*)(smem + (t & 1) * A64_TILE + b * 8192 + koff[ks]);
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt) {
+                    if (ks == 0) {
+                        const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                        sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], z, 0, 0, 0);
+                    } else {
+                        sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], sa[qt], 0, 0, 0);
+                    }
+                }
+            }
+            PO_MASK(sa, 2 * t + b, 0);
+            PO_MASK(sa, 2 * t + b, 1);
+            float m0, m1;
+            PO_BLOCKMAX(sa, 0, m0);
+            PO_BLOCKMAX(sa, 1, m1);
+            mtop[0] = fmaxf(mtop[0], m0);
+            mtop[1] = fmaxf(mtop[1], m1);
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) lsum[0][e] = lsum[1][e] = 0.f;
+    }   // attempt
 #undef PO_PAIR
 #undef PO_FRAG_ADDR
 #undef PO_WAIT_LGKM2
@@ -796,15 +867,13 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #undef PO_DMA
 #undef PO_MASK
 #undef PO_BLOCKMAX
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    PO_MFMA_DRAIN();
 #undef PO_MFMA_ACC
 #undef PO_MFMA_DRAIN
 
     if (SPLIT) {
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
-            const float ltot = half_swap_sum((lsum[qt][0] + lsum[qt][1]) + (lsum[qt][2] + lsum[qt][3]));
+            const float ltot = half_swap_sum(lrow[qt]);
             if (qw + qt * 32 + l31 >= n_virtual) continue;
             const int64_t slot = ((int64_t)piece * (N - sp.q_row0) + vrow[qt]) * Hq + vhead[qt];
             float* op = sp.opart + slot * HD + 4 * lhi;
@@ -816,7 +885,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                                       oacc[ht][qt][rg * 4 + 3]};
                     *(float4*)(op + ht * 32 + rg * 8) = v;
                 }
-            if (lhi == 0) *(float2*)(sp.mlpart + slot * 2) = make_float2(0.f, ltot);
+            if (lhi == 0) *(float2*)(sp.mlpart + slot * 2) = make_float2(mb[qt], ltot);
         }
         return;
     }
@@ -857,14 +926,10 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 }
 
 // o[row][head][:] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^((m_s - max m) sc_log2e); one thread per 4 values.
-// PRE64 (pieces of attn_fwd64_kernel: Q prescaled, every m_s 0, so every w_s 1): a total that left [2^-60, 2^100) means
-// probabilities near an end of the float range; the threads of that row and head then form it again with a running
-// maximum, key by key (q still holds the row: o may alias q, and nobody else writes it).
-template <int HD, bool PRE64>
+template <int HD>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ opart, const float* __restrict__ mlpart,
                                                            int n_split, int nq, int Hq, float sc_log2e, bf16_t* o,
-                                                           int q_row0, const bf16_t* q, const bf16_t* __restrict__ k,
-                                                           const bf16_t* __restrict__ vt, int64_t ldv, int Hkv, SplitArgs sp) {
+                                                           int q_row0) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     constexpr int PER = HD / 4;
     if (i >= (int64_t)nq * Hq * PER) return;
@@ -874,44 +939,16 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
     const int64_t row = q_row0 + rh / Hq;
     const int head = (int)(rh % Hq);
     float mx = -1.0e30f;
-    if (PRE64) mx = 0.f;
-    else
-        for (int sp = 0; sp < n_split; ++sp) mx = fmaxf(mx, mlpart[(sp * plane + rh) * 2]);
+    for (int sp = 0; sp < n_split; ++sp) mx = fmaxf(mx, mlpart[(sp * plane + rh) * 2]);
     float4 acc = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll 4
     for (int sp = 0; sp < n_split; ++sp) {
         const float2 ml = *(const float2*)(mlpart + (sp * plane + rh) * 2);
-        const float w = PRE64 ? 1.0f : __builtin_amdgcn_exp2f((ml.x - mx) * sc_log2e);
+        const float w = __builtin_amdgcn_exp2f((ml.x - mx) * sc_log2e);
         const float4 v = *(const float4*)(opart + (sp * plane + rh) * HD + f);
         acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
         l += w * ml.y;
-    }
-    if (PRE64 && (!(l >= 0x1p-60f) || !(l < 0x1p100f))) {
-        const int kvh = head / (Hq / Hkv);
-        const uint2 qv = *(const uint2*)(q + (row * Hq + head) * HD + f);
-        const float q0 = __uint_as_float(qv.x << 16), q1 = __uint_as_float(qv.x & 0xffff0000u),
-                    q2 = __uint_as_float(qv.y << 16), q3 = __uint_as_float(qv.y & 0xffff0000u);
-        float m = -1.0e30f;
-        acc = {0.f, 0.f, 0.f, 0.f};
-        l = 0.f;
-        for (int64_t key = 0; key <= row; ++key) {
-            const bool second = key < (int64_t)sp.tiles2 * 64;
-            const bf16_t* kr = (second ? sp.k2 : k) + (key * Hkv + kvh) * HD + f;
-            const bf16_t* vr = (second ? sp.vt2 : vt) + key;
-            const int64_t ld = second ? sp.ldv2 : ldv;
-            float d = q0 * bf2f(kr[0]) + q1 * bf2f(kr[1]) + q2 * bf2f(kr[2]) + q3 * bf2f(kr[3]);
-            for (int off = PER / 2; off > 0; off >>= 1) d += __shfl_xor(d, off);      // the PER threads of this row and head
-            const float mn = fmaxf(m, d);
-            const float a = __builtin_amdgcn_exp2f(m - mn), pv = __builtin_amdgcn_exp2f(d - mn);
-            const int64_t fr = (int64_t)kvh * HD + f;
-            acc.x = acc.x * a + pv * bf2f(vr[fr * ld]);
-            acc.y = acc.y * a + pv * bf2f(vr[(fr + 1) * ld]);
-            acc.z = acc.z * a + pv * bf2f(vr[(fr + 2) * ld]);
-            acc.w = acc.w * a + pv * bf2f(vr[(fr + 3) * ld]);
-            l = l * a + pv;
-            m = mn;
-        }
     }
     const float inv = 1.0f / l;
     uint2 w2;
@@ -999,17 +1036,17 @@ int launch_split_t(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t l
                        k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt, 0, (int)q_row0, n_split, opart, mlpart,
                        k2 ? k2 : k, vt2 ? vt2 : vt, vt2 ? ldv2 : ldv, (k2 && vt2) ? (int)(n2 / BNK) : 0, nullptr);
     const int64_t n = nq * Hq * (HD / 4);
-    hipLaunchKernelGGL((attn_combine_kernel<HD, false>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, opart, mlpart,
-                       n_split, (int)nq, Hq, sc_log2e, o, (int)q_row0, q, k, vt, ldv, Hkv, SplitArgs{});
+    hipLaunchKernelGGL(attn_combine_kernel<HD>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, opart, mlpart, n_split,
+                       (int)nq, Hq, sc_log2e, o, (int)q_row0);
     return n_split;
 }
 
-// The prescaled-Q form for head dimension 128: pieces of key tiles sized so that the workgroups (KV heads x blocks of
+// The form for head dimension 128: pieces of key tiles sized so that the workgroups (KV heads x blocks of
 // 256 rows of all a KV head's query heads x pieces) are one round of the 256 compute units, at least two tiles each.
 // 0 = nothing launched: too many rows for two pieces, fewer than four tiles, or the scratch too small.
 int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o, int64_t N, int Hq, int Hkv,
                        int64_t q_row0, float* scratch, size_t scratch_bytes, bool launch, const bf16_t* k2, const bf16_t* vt2,
-                       int64_t ldv2, int64_t n2, hipStream_t s) {
+                       int64_t ldv2, int64_t n2, bool q_prescaled, hipStream_t s) {
     constexpr int SMEM = 2 * A64_NSTAGE * A64_TILE + 16;
     const int64_t nq = N - q_row0;
     const int group = Hq / Hkv;
@@ -1029,7 +1066,7 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     if (!launch) return sp.n;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         attr_set = true;
     }
     sp.k2 = k2; sp.vt2 = vt2; sp.ldv2 = ldv2;
@@ -1037,11 +1074,12 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     sp.tiles2 = tiles2;
     sp.opart = scratch;
     sp.mlpart = scratch + (size_t)sp.n * (size_t)nq * (size_t)Hq * 128;
-    hipLaunchKernelGGL((attn_fwd64_kernel<true, true>), dim3((unsigned)(Hkv * sp.n * nqt)), dim3(256), SMEM, s, q, k, vt, ldv, o,
-                       (int)N, Hq, Hkv, 1.0f, nqt, 0, nullptr, sp);
+    hipLaunchKernelGGL((attn_fwd64_kernel<false, true>), dim3((unsigned)(Hkv * sp.n * nqt)), dim3(256), SMEM, s, q, k, vt, ldv, o,
+                       (int)N, Hq, Hkv, q_prescaled ? 1.0f : attention_q_scale(128), nqt, 0, nullptr, sp);
     const int64_t n = nq * Hq * 32;
-    hipLaunchKernelGGL((attn_combine_kernel<128, true>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sp.opart, sp.mlpart,
-                       sp.n, (int)nq, Hq, 1.0f, o, (int)q_row0, q, k, vt, ldv, Hkv, sp);
+    // (a piece's reference exponents are in log2 units)
+    hipLaunchKernelGGL(attn_combine_kernel<128>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sp.opart, sp.mlpart, sp.n,
+                       (int)nq, Hq, 1.0f, o, (int)q_row0);
     return sp.n;
 }
 
@@ -1055,8 +1093,9 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
                                 int Hq, int Hkv, int hd, int64_t q_row0, float* scratch, size_t scratch_bytes,
                                 bool launch, const bf16_t* k2, const bf16_t* vt2, int64_t ldv2, int64_t n2,
                                 bool q_prescaled, hipStream_t s) {
-    if (hd == 128 && q_prescaled) {
-        const int n = launch_split_fwd64(q, k, vt, ldv, o, N, Hq, Hkv, q_row0, scratch, scratch_bytes, launch, k2, vt2, ldv2, n2, s);
+    if (hd == 128) {
+        const int n = launch_split_fwd64(q, k, vt, ldv, o, N, Hq, Hkv, q_row0, scratch, scratch_bytes, launch, k2, vt2, ldv2, n2,
+                                         q_prescaled, s);
         if (n > 1) return n;
     }
     if (hd == 128)

@@ -165,6 +165,47 @@ def test_rows_far_outside_the_exponent_range_against_float64(n, r0, n2, hq, hkv,
     _check_rows(o, ref, r0, extra=2e-3 if kind == "spread" else 5e-4)
 
 
+def test_large_values_stay_finite():
+    """Scores 36 above the first key's and values near 2^95: sums of 2^score times value leave the float range (2^36 2^95),
+    the averages do not."""
+    q, k, v = _operands(900, 4, 1, 128, 3)
+    k[:, :, 0], q[:, :, 0] = 0.0, 4.5
+    k[5::7, :, 0] = 8.0
+    ref = _reference(q, k, v, 700)
+    o, pieces = _split(q, k, v * 2.0 ** 95, 700, 640)
+    assert pieces > 1
+    _check_rows(o.double() * 2.0 ** -95, ref, 700, extra=5e-4)
+
+
+@pytest.mark.parametrize("kind", ["shifted", "spread", "late"])
+def test_time_does_not_depend_on_the_scores(kind):
+    """A row outside the exponent range costs its workgroup another pass, not a walk over its keys one by one (which took
+    hundreds of times as long): 2.5 times the work at the most, 4 leaves room for the clock."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+
+    def seconds(q, k, v):
+        n, hq, hd = q.shape
+        vt = torch.empty(k.shape[1] * hd * ((n + 63) // 64 * 64), dtype=q.dtype, device="cuda")
+        part, o = torch.empty(1 << 27, dtype=torch.uint8, device="cuda"), torch.zeros_like(q)
+        splits, best = B.C.c_int32(0), 1e9
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.check(B.lib().po_op_attention_split_prefix(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), vt.data_ptr(),
+                                                         part.data_ptr(), part.numel(), n, hq, k.shape[1], hd, n - 150, 1, None,
+                                                         None, 0, 0, B._stream(), B.C.byref(splits)))
+            b.record()
+            b.synchronize()
+            assert splits.value > 1
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    ordinary, other = seconds(*_operands(8150, 32, 8, 128, 1)), seconds(*_operands(8150, 32, 8, 128, 1, kind))
+    print(f"150 rows behind 8000 keys: ordinary scores {ordinary * 1e3:.0f} us, {kind} {other * 1e3:.0f} us")
+    assert other <= 4 * ordinary
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
 def test_value_transpose_aligned_and_unaligned(n):
     """V at a 16-byte boundary and two bytes off it take different kernels to the same transposed copy."""
