@@ -556,7 +556,8 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
     float mb[2], lrow[2] = {0.f, 0.f};      // reference exponents (log2 domain) and row sums per query tile
-    float lsum[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};       // LATE: the row sums as four partial sums each
+    float lsum[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};       // LATE: the row sums as four partial sums each (SPLIT: of the
+                                                                           // probabilities in fp32, PRE: as rounded to bf16)
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     int gave_up = 0;                        // wavefront-uniform: a row sum left the range the reference scheme covers
     int* const lds_gave_up = (int*)(smem + 2 * A64_NSTAGE * A64_TILE);     // one word behind the ring
@@ -711,22 +712,26 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                         const int e_ = PO_JOB_E(nc_ & 15);                                                      \
                         pf[e_ >> 4][(e_ & 15) >> 3][e_ & 7] = (__bf16)ea_[nc_ & 15][0];                         \
                         pf[e_ >> 4][(e_ & 15) >> 3][(e_ & 7) + 1] = (__bf16)ea_[nc_ & 15][1];                   \
+                        if (SPLIT) {           /* (as they are, not as rounded: a piece has issue slots to spare) */ \
+                            lsum[e_ >> 4][e_ & 2] += ea_[nc_ & 15][0];                                          \
+                            lsum[e_ >> 4][(e_ & 2) + 1] += ea_[nc_ & 15][1];                                    \
+                        }                                                                                       \
                     }                                                                                           \
                 }                                                                                               \
                 if (c >= 8) {                                                                                   \
                     const int c_ = (c - 8) * 2 + qt;             /* 0..15 */                                    \
-                    if (c_ == 8 || c_ == 9) {                                                                   \
+                    if (!SPLIT && (c_ == 8 || c_ == 9)) {                                                       \
                         const int sq_ = c_ - 8;                                                                 \
-                        /* four independent chains: a dependent dot product waits about 6 cycles.  LATE: the    \
+                        /* four independent chains: a dependent dot product waits about 6 cycles.  PRE: the     \
                            four partial sums live across blocks (nothing looks at the row sum before the end) */\
                         float l_[4] = {lrow[sq_], 0.f, 0.f, 0.f};                                               \
                         _Pragma("unroll") for (int h2 = 0; h2 < 2; ++h2)                                        \
                         _Pragma("unroll") for (int e2 = 0; e2 < 4; ++e2) {                                      \
                             const bf16x2 pr2_ = {pf[sq_][h2][2 * e2], pf[sq_][h2][2 * e2 + 1]};                 \
-                            if (LATE) lsum[sq_][e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, lsum[sq_][e2], false); \
+                            if (PRE) lsum[sq_][e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, lsum[sq_][e2], false); \
                             else l_[e2] = __builtin_amdgcn_fdot2_f32_bf16(pr2_, ones, l_[e2], false);           \
                         }                                                                                       \
-                        if (!LATE) lrow[sq_] = (l_[0] + l_[1]) + (l_[2] + l_[3]);                               \
+                        if (!PRE) lrow[sq_] = (l_[0] + l_[1]) + (l_[2] + l_[3]);                                \
                     }                                                                                           \
                     if ((c_ & 3) == 3) { PO_DMA(DMA_T_, DMA_S_, (DMA_J0_) + (c_ >> 2)); }                       \
                 }                                                                                               \
