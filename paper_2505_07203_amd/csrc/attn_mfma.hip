@@ -410,9 +410,12 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 //
 // SPLIT (few query rows against many keys): rows q_row0 .. N-1 of ALL query heads of a KV head are the rows of a
 // workgroup, since they share its keys (a 150-row suffix of 4 heads per KV head is 600 rows: 3 workgroups that are
-// nearly full instead of 4 with 59 % of their rows), and the key tiles are divided into pieces of `per` tiles: pieces 0
-// .. n2 - 1 cover tiles [0, tiles2) of a second K / V^T pair (a prefix-cache entry read in place), the rest what follows
-// in the first.  A piece writes its unnormalised fp32 accumulators, its reference exponents and its row sums, and
+// nearly full instead of 4 with 59 % of their rows), and the key tiles are divided into pieces of `per` tiles.  Tiles [0,
+// tiles2) come from a second K / V^T pair (a prefix-cache entry read in place), the others from the first.  SPLIT 1: no piece
+// holds tiles of both (pieces 0 .. n2 - 1 are those of the second pair).  SPLIT 2: a piece may, and chooses the pair per
+// tile; with few pieces that is what keeps one of them from being the whole prefix (700 rows behind 14 000 cached positions,
+// two pieces: 260 us cut at the boundary, 162 so), with many the choice costs more than the cut (one row: 31.5 against
+// 29.5 us).  A piece writes its unnormalised fp32 accumulators, its reference exponents and its row sums, and
 // attn_combine_kernel merges the pieces.  Every piece takes its reference from its own first 32 keys (a zero reference,
 // as PRE has it, would make all pieces of a row flush or overflow together).  Nothing moves it afterwards: sums only grow,
 // so one look at the end finds a row sum past 2^100 or an accumulator that is not finite, and the workgroup then goes
@@ -426,16 +429,17 @@ struct SplitArgs {
     float *opart, *mlpart;        // [piece][row - q_row0][head][HD], [..][2]
     int q_row0, tiles2, n2, n, per;       // n: pieces
 };
-template <bool PRE, bool SPLIT>
+template <bool PRE, int SPLIT>
 __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ vt, int64_t ldv, bf16_t* o, int N,
                                                          int Hq, int Hkv, float sc_log2e, int nqt, int hpx, int* redo,
                                                          const SplitArgs sp) {
     constexpr int HD = 128, KS = 8, HT = 4;
-    constexpr bool LATE = PRE || SPLIT;     // the row sums are looked at once, behind the last block
+    constexpr bool LATE = PRE || SPLIT != 0;     // the row sums are looked at once, behind the last block
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     int qtile, head, kvh, piece = 0, tile0 = 0, piece_tiles = 0;
+    int tiles2 = 0, end = N;                // SPLIT: tiles of this piece in the second pair; positions from its first one on
     const int group = Hq / Hkv;
     if (SPLIT) {
         kvh = blockIdx.x % Hkv;
@@ -444,14 +448,16 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         qtile = rest / sp.n;
         head = kvh * group;
         const int n_all = (N + 63) / 64;
-        const bool second = piece < sp.n2;
-        tile0 = second ? piece * sp.per : sp.tiles2 + (piece - sp.n2) * sp.per;
+        const bool second = SPLIT == 1 && piece < sp.n2;       // (a piece of the second pair alone)
+        tile0 = (SPLIT == 2 || second) ? piece * sp.per : sp.tiles2 + (piece - sp.n2) * sp.per;
         piece_tiles = min(sp.per, (second ? sp.tiles2 : n_all) - tile0);
+        if (SPLIT == 2) tiles2 = max(0, min(sp.tiles2 - tile0, piece_tiles));
         if (second) {
             k = sp.k2;
             vt = sp.vt2;
             ldv = sp.ldv2;
         }
+        end = (second ? sp.tiles2 * 64 : N) - tile0 * 64;
         // everything below counts keys from this piece's first one
         k += (int64_t)tile0 * 64 * Hkv * HD;
         vt += tile0 * 64;
@@ -512,24 +518,35 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // beyond it read as zero (they are masked keys) instead of needing a clamp per load.
     const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(k + (int64_t)kvh * HD), 0,
-        (int)((SPLIT ? (uint32_t)((piece < sp.n2 ? sp.tiles2 * 64 : N) - tile0 * 64 - 1) : (uint32_t)(N - 1)) * krs2 + 256u), 0x00020000);
+        (int)((uint32_t)(end - 1) * krs2 + 256u), 0x00020000);
     // (V^T of this KV head: 128 rows of ldv positions; its columns are always inside the row)
     const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(vt + (int64_t)kvh * HD * ldv), 0, (int)((uint32_t)HD * (uint32_t)(ldv * 2) - (uint32_t)(tile0 * 128)), 0x00020000);
     const uint32_t vrow32 = (uint32_t)(32 * ldv * 2);
+    // SPLIT 2: the second pair, from this piece's first tile to its last one of the pair (empty without one)
+    const __amdgpu_buffer_rsrc_t krsrc2 = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(sp.k2 + ((int64_t)tile0 * 64 * Hkv + kvh) * HD), 0, tiles2 > 0 ? (int)((uint32_t)(tiles2 * 64 - 1) * krs2 + 256u) : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vrsrc2 = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(sp.vt2 + (int64_t)kvh * HD * sp.ldv2 + tile0 * 64), 0,
+        tiles2 > 0 ? (int)((uint32_t)HD * (uint32_t)(sp.ldv2 * 2) - (uint32_t)(tile0 * 128)) : 0, 0x00020000);
+    const uint32_t voff_v2 = (uint32_t)vrow_l * (uint32_t)(sp.ldv2 * 2) + (uint32_t)(((lane & 7) ^ swz8(vrow_l)) << 4);
     // load jj_ (0..3: K rows, 4..7: V^T rows) of tile tile_ into stage stg_
 #define PO_DMA(tile_, stg_, jj_)                                                                               \
     {                                                                                                          \
-        const int kv0_ = min((tile_), n_tiles - 1) * 64;                                                       \
+        const int t_ = min((tile_), n_tiles - 1), kv0_ = t_ * 64;                                              \
+        const bool second_ = SPLIT == 2 && t_ < tiles2;                                                        \
         if ((jj_) < 4) {                                                                                       \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                          \
-                krsrc, (__attribute__((address_space(3))) void*)(smem + (stg_) * A64_TILE + ((jj_) * 16 + wave * 4) * 256), \
+                second_ ? krsrc2 : krsrc,                                                                      \
+                (__attribute__((address_space(3))) void*)(smem + (stg_) * A64_TILE + ((jj_) * 16 + wave * 4) * 256), \
                 16, klane, (kv0_ + (jj_) * 16) * krs2, 0, 0);                                                  \
         } else {                                                                                               \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                          \
-                vrsrc, (__attribute__((address_space(3))) void*)(smem + A64_VBASE + (stg_) * A64_TILE +        \
-                                                                 (((jj_) - 4) * 32 + wave * 8) * 128),          \
-                16, voff_v, ((jj_) - 4) * vrow32 + kv0_ * 2, 0, 0);                                            \
+                second_ ? vrsrc2 : vrsrc,                                                                      \
+                (__attribute__((address_space(3))) void*)(smem + A64_VBASE + (stg_) * A64_TILE +               \
+                                                          (((jj_) - 4) * 32 + wave * 8) * 128),                 \
+                16, second_ ? voff_v2 : voff_v,                                                                \
+                ((jj_) - 4) * (second_ ? (uint32_t)(64 * sp.ldv2) : vrow32) + kv0_ * 2, 0, 0);                 \
         }                                                                                                      \
     }
 
@@ -968,8 +985,8 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     constexpr int SMEM_REDO = 2 * 2 * BNK * 128 * 2;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, false>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, false>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 0>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, 0>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         (void)hipFuncSetAttribute((const void*)attn_fwd_kernel<128, 1, 8, false>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, SMEM_REDO);
         attr_set = true;
@@ -980,10 +997,10 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     // workgroups enumerate query tiles from the last one down: fewer of them = only the last tiles
     const int nsel = nqt - (int)((q_row0 > 0 && q_row0 < N) ? q_row0 / 256 : 0);
     if (q_prescaled)
-        hipLaunchKernelGGL((attn_fwd64_kernel<true, false>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+        hipLaunchKernelGGL((attn_fwd64_kernel<true, 0>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
                            Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
     else
-        hipLaunchKernelGGL((attn_fwd64_kernel<false, false>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 0>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
                            Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
     // the (query tile, head) pairs given up above, by the running-maximum kernel with the same 256-row tiles
     // (8 wavefronts x 32 rows); item b = query tile * Hq + head
@@ -1060,18 +1077,28 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     const int tiles = (int)((N + 63) / 64), tiles2 = (k2 && vt2) ? (int)(n2 / 64) : 0;
     const int max_pieces = 256 / (nqt * Hkv);
     if (max_pieces < 2 || tiles < 4) return 0;
+    const size_t piece_bytes = (size_t)nq * (size_t)Hq * (128 + 2) * sizeof(float);
+    const int pieces = (int)std::min<size_t>(max_pieces, scratch_bytes / piece_bytes);
+    if (pieces < 2) return 0;
     SplitArgs sp{};
-    for (sp.per = std::max(2, (tiles + max_pieces - 1) / max_pieces);; ++sp.per) {
-        sp.n2 = (tiles2 + sp.per - 1) / sp.per;
-        sp.n = sp.n2 + (tiles - tiles2 + sp.per - 1) / sp.per;
-        if (sp.n < 2) return 0;
-        const size_t floats = (size_t)sp.n * (size_t)nq * (size_t)Hq * (128 + 2);
-        if (sp.n <= max_pieces && floats * sizeof(float) <= scratch_bytes) break;
+    sp.per = std::max(2, (tiles + pieces - 1) / pieces);
+    sp.n = (tiles + sp.per - 1) / sp.per;
+    // Cut at the end of the prefix (ends at the latest with two pieces) unless that makes the longest piece so much longer
+    // that it costs more than choosing the pair per tile does: a tile takes about 1.35 us, the choice 2 us and 4 % of them.
+    int per = sp.per;
+    auto cut = [&](int p) { return (tiles2 + p - 1) / p + (tiles - tiles2 + p - 1) / p; };
+    while (cut(per) > pieces) ++per;
+    const bool span = per - sp.per > 1.5 + 0.04 * sp.per;
+    if (!span) {
+        sp.per = per;
+        sp.n2 = (tiles2 + per - 1) / per;
+        sp.n = cut(per);
     }
     if (!launch) return sp.n;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         attr_set = true;
     }
     sp.k2 = k2; sp.vt2 = vt2; sp.ldv2 = ldv2;
@@ -1079,8 +1106,14 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     sp.tiles2 = tiles2;
     sp.opart = scratch;
     sp.mlpart = scratch + (size_t)sp.n * (size_t)nq * (size_t)Hq * 128;
-    hipLaunchKernelGGL((attn_fwd64_kernel<false, true>), dim3((unsigned)(Hkv * sp.n * nqt)), dim3(256), SMEM, s, q, k, vt, ldv, o,
-                       (int)N, Hq, Hkv, q_prescaled ? 1.0f : attention_q_scale(128), nqt, 0, nullptr, sp);
+    const dim3 grid((unsigned)(Hkv * sp.n * nqt));
+    const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(128);
+    if (span)
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 2>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
+                           nqt, 0, nullptr, sp);
+    else
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 1>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
+                           nqt, 0, nullptr, sp);
     const int64_t n = nq * Hq * 32;
     // (a piece's reference exponents are in log2 units)
     hipLaunchKernelGGL(attn_combine_kernel<128>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, sp.opart, sp.mlpart, sp.n,

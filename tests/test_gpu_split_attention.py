@@ -210,33 +210,59 @@ def test_large_values_stay_finite():
     _check_rows(o.double() * 2.0 ** -95, ref, 700, extra=5e-4)
 
 
+def _seconds(q, k, v, rows, k2=None, vt2=None, n2=0):
+    """fastest of eight calls for the last `rows` rows"""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    n, hq, hd = q.shape
+    vt = torch.empty(k.shape[1] * hd * ((n + 63) // 64 * 64), dtype=q.dtype, device="cuda")
+    part, o = torch.empty(1 << 28, dtype=torch.uint8, device="cuda"), torch.zeros_like(q)
+    splits, best = B.C.c_int32(0), 1e9
+    for _ in range(8):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        B.check(B.lib().po_op_attention_split_prefix(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), vt.data_ptr(),
+                                                     part.data_ptr(), part.numel(), n, hq, k.shape[1], hd, n - rows, 1,
+                                                     k2.data_ptr() if n2 else None, vt2.data_ptr() if n2 else None,
+                                                     vt2.shape[1] if n2 else 0, n2, B._stream(), B.C.byref(splits)))
+        b.record()
+        b.synchronize()
+        assert splits.value > 1
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
 @pytest.mark.parametrize("kind", ["shifted", "spread", "late"])
 def test_time_does_not_depend_on_the_scores(kind):
     """A row outside the exponent range costs its workgroup another pass, not a walk over its keys one by one (which took
     hundreds of times as long): 2.5 times the work at the most, 4 leaves room for the clock."""
-    import torch
-    from paper_2505_07203_amd import binding as B
-
-    def seconds(q, k, v):
-        n, hq, hd = q.shape
-        vt = torch.empty(k.shape[1] * hd * ((n + 63) // 64 * 64), dtype=q.dtype, device="cuda")
-        part, o = torch.empty(1 << 27, dtype=torch.uint8, device="cuda"), torch.zeros_like(q)
-        splits, best = B.C.c_int32(0), 1e9
-        for _ in range(8):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            B.check(B.lib().po_op_attention_split_prefix(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), vt.data_ptr(),
-                                                         part.data_ptr(), part.numel(), n, hq, k.shape[1], hd, n - 150, 1, None,
-                                                         None, 0, 0, B._stream(), B.C.byref(splits)))
-            b.record()
-            b.synchronize()
-            assert splits.value > 1
-            best = min(best, a.elapsed_time(b))
-        return best
-
-    ordinary, other = seconds(*_operands(8150, 32, 8, 128, 1)), seconds(*_operands(8150, 32, 8, 128, 1, kind))
+    ordinary, other = _seconds(*_operands(8150, 32, 8, 128, 1), 150), _seconds(*_operands(8150, 32, 8, 128, 1, kind), 150)
     print(f"150 rows behind 8000 keys: ordinary scores {ordinary * 1e3:.0f} us, {kind} {other * 1e3:.0f} us")
     assert other <= 4 * ordinary
+
+
+def test_time_does_not_depend_on_where_the_prefix_lies():
+    """700 rows behind 14 000 keys leave two pieces: cut at the end of the prefix one of them would be all of it."""
+    q, k, v = _operands(14700, 32, 8, 128, 1)
+    vt2 = v[:13952].reshape(13952, -1).t().contiguous()
+    whole, pair = _seconds(q, k, v, 700), _seconds(q, k, v, 700, k, vt2, 13952)
+    print(f"700 rows behind 14000 keys: {whole * 1e3:.0f} us, prefix in a pair of its own {pair * 1e3:.0f} us")
+    assert pair <= 1.25 * whole
+
+
+@pytest.mark.parametrize("n2", [0, 448])
+def test_scratch_for_fewer_pieces(n2):
+    """Scratch for two or three pieces is used as it is; for less than two nothing is computed (and the call returns)."""
+    q, k, v = _operands(700, 8, 2, 128, 5)
+    piece = 200 * 8 * (128 + 2) * 4
+    ref = _reference(q, k, v, 500)
+    for pieces in (2, 3):
+        o, n = _split(q, k, v, 500, n2, part_bytes=pieces * piece + 4)
+        assert n == pieces
+        _check_rows(o, ref, 500)
+    for part_bytes in (2 * piece - 4, piece, 64):
+        o, n = _split(q, k, v, 500, n2, part_bytes=part_bytes)
+        assert o is None and n <= 1
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
