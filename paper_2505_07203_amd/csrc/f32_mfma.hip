@@ -95,9 +95,12 @@ struct F32Rows {                  // a wavefront's 32 query rows: this lane's co
 #pragma unroll
         for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, p[r]);
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-        const float mn = fmaxf(m, tmax);                 // finite from the first tile a wavefront sees: its first key is never masked
+        const float mn = fmaxf(m, tmax);
+        // -inf while every score so far is (products that overflowed: a wavefront's first tile need not hold the row's first
+        // keys): the tile then adds nothing, instead of exp(-inf + inf)
+        const float ref = mn == -INFINITY ? 0.f : mn;
         if (__any(mn > m)) {                             // (else every factor is 1)
-            const float a = expf(m - mn);                // exp(-inf) = 0 on the first tile
+            const float a = expf(m - ref);               // exp(-inf) = 0 on the first tile
             l *= a;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -108,7 +111,7 @@ struct F32Rows {                  // a wavefront's 32 query rows: this lane's co
         float psum = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            p[r] = expf(p[r] - m);
+            p[r] = expf(p[r] - ref);
             psum += p[r];
         }
         l += psum;                                       // this lane's 16 keys; the partner's are added at the end

@@ -163,3 +163,25 @@ def test_f32_attention_rows_do_not_depend_on_the_length(Hq, Hkv, hd, n):
     for m in (1, 31, 32, 33, 127, 129, 1023, 1024, 1025, 1100, 1535, 1537, 1601):
         if m < n:
             assert torch.equal(B.po_op_attention(q[:m].contiguous(), k[:m].contiguous(), v[:m].contiguous()), o[:m]), m
+
+
+@pytest.mark.parametrize("hd,n", [(64, 200), (64, 1700), (128, 200), (128, 1200)])
+def test_f32_attention_with_whole_tiles_at_minus_infinity(hd, n):
+    """Scores whose product overflows to -inf have probability 0, also where they fill all the tiles that one of the four
+    wavefronts of an early row's workgroup sees, or its first ones."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(n, h, hd, generator=g, device="cuda") for h in (2, 1, 1))
+    q[:, :, 0], k[:, :, 0] = 1e20, 0.0
+    gone = torch.zeros(n, dtype=torch.bool, device="cuda")
+    for tile in (1, 3, 5, 6, 9, 13):
+        gone[32 * tile:32 * tile + 32] = True
+    k[gone, :, 0] = -1e20
+    o = B.po_op_attention(q, k, v)
+    assert torch.isfinite(o).all()
+    mask = torch.ones(n, n, dtype=torch.bool, device="cuda").tril() & ~gone[None]
+    for h in range(2):
+        s = (q[:, h, 1:].double() @ k[:, 0, 1:].double().t()) * hd ** -0.5
+        ref = s.masked_fill(~mask, -float("inf")).softmax(-1) @ v[:, 0].double()
+        assert (o[:, h].double() - ref).abs().max().item() <= 4e-6 * v.abs().max().item()
