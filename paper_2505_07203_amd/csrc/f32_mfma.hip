@@ -460,16 +460,18 @@ bool launch_gemm_f32_mfma(const float* A, int64_t lda, const float* W, int64_t l
     if (M <= 0 || N <= 0) return true;
     if (K <= 0 || K % 4 || lda % 4 || ldw % 4 || ((uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)bias | (uintptr_t)R) % 16)
         return false;
-    if (lda >= (1 << 20) || ldw >= (1 << 20)) return false;      // a tile is addressed with offsets below 2^30 bytes
+    const int64_t ld = std::max(lda, ldw);
+    if (ld > (1 << 23)) return false;        // a tile, of 32 rows at least, is addressed with offsets below 2^30 bytes
     // Tile by time: a round of 256 tiles, one per compute unit, costs this many microseconds per K slice of 32 (measured
     // on 256 .. 2048 tiles of each); where all three take one round the small tile has the shorter chain.
     constexpr double us[3] = {1.9, 0.54, 0.2};                     // tiles of 128, 64, 32
-    int best = 0;
-    double best_us = 0;
+    int best = 2;
+    double best_us = 1e300;
     for (int i = 0; i < 3; ++i) {
         const int64_t bt = 128 >> i, tiles = ((M + bt - 1) / bt) * ((N + bt - 1) / bt);
+        if (bt * ld > (1 << 28)) continue;
         const double t = us[i] * (double)((tiles + 255) / 256);
-        if (i == 0 || t < best_us) { best = i; best_us = t; }
+        if (t < best_us) { best = i; best_us = t; }
     }
     if (best == 0) launch_f32_tile<4, 2>(A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, s);
     else if (best == 1) launch_f32_tile<2, 4>(A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, s);

@@ -144,6 +144,29 @@ def test_f32_rows_are_the_same_bits_in_launches_of_every_height(N, K):
         assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole_r[:m]), m
 
 
+def test_f32_rows_of_more_than_a_million_elements():
+    """Above 2^20 elements per row only the tiles whose offsets still fit are taken, not the plain kernel: right, and no
+    step in time from one side of that size to the other."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a, w = (torch.randn(m, 2 ** 20 + 64, generator=g, device="cuda") for m in (70, 40))
+    us = {}
+    for K in (2 ** 20 - 32, 2 ** 20 + 60):
+        x, y = a[:, :K].contiguous(), w[:, :K].contiguous()
+        ref, size = x.double() @ y.double().t(), x.double().abs() @ y.double().abs().t()
+        # one running sum of K terms: its roundings add up like a walk of sqrt(K) steps (a fixed sum of K would allow 6 %)
+        assert float(((B.po_op_linear(x, y).double() - ref).abs() / size).max()) <= 8 * K ** 0.5 * 2.0 ** -24
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+        for e in ev:
+            B.po_op_linear(x, y)
+            e.record()
+        torch.cuda.synchronize()
+        us[K] = min(i.elapsed_time(j) for i, j in zip(ev, ev[1:])) * 1e3
+    print("70 x 40 outputs:", {k: round(v) for k, v in us.items()}, "us")
+    assert max(us.values()) <= 2 * min(us.values())
+
+
 @pytest.mark.parametrize("Hq,Hkv,hd,n", [(4, 2, 64, 1700), (4, 1, 128, 1200), (2, 2, 128, 33)])
 def test_f32_attention_rows_do_not_depend_on_the_length(Hq, Hkv, hd, n):
     """Rows below and above the change of work split: against float64, and the same bits in a shorter sequence."""
