@@ -419,6 +419,13 @@ po_status po_op_attention_split_prefix(const void* dev_q, const void* dev_k, con
                                        int32_t q_prescaled, const void* dev_k2, const void* dev_vt2, int64_t ldv2,
                                        int64_t n2, void* hip_stream, int32_t* splits_used);
 
+/* The block tile (rows x columns of the output) that a launch of po_op_linear, po_op_gate_up_silu (N = 2 F) or
+ * po_op_qkv_rope with contiguous operands takes, or of their FP8 forms with fp8 = 1.  *splits: 1 = a whole launch, more =
+ * one of that many K splits of few-rows mode, 0 = as many as that mode takes with enough scratch (written back).  Host
+ * only.  The tile changes no result (a split sum is rounded differently). */
+po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows,
+                       int32_t* tile_cols);
+
 /* Rotary embedding in place on x [N, H, hd] for positions 0..N-1 (angles formed in
  * double precision). */
 po_status po_op_rope(int32_t dtype, void* dev_x, int64_t N, int32_t n_heads, int32_t head_dim,
@@ -485,6 +492,12 @@ po_status po_op_rmsnorm_quantize(const void* dev_x, const void* dev_g, void* dev
 po_status po_op_linear_fp8(int32_t epilogue, const void* dev_a_codes, const float* dev_a_scales,
                            const void* dev_w_codes, const float* dev_w_scales, void* dev_c,
                            const void* dev_residual, int64_t M, int32_t N, int32_t K, void* hip_stream);
+/* The few-rows form of po_op_linear_fp8 with a residual, as po_op_linear_split is po_op_linear's (but 0 also where a split
+ * is not expected to pay). */
+po_status po_op_linear_fp8_split(const void* dev_a_codes, const float* dev_a_scales, const void* dev_w_codes,
+                                 const float* dev_w_scales, void* dev_c, const void* dev_residual, void* dev_scratch,
+                                 size_t scratch_bytes, int64_t M, int32_t N, int32_t K, void* hip_stream,
+                                 int32_t* splits_used);
 
 /* po_op_qkv_rope with FP8 operands: dev_w_codes / dev_w_scales hold the packed QKV weight rows
  * (the order po_op_pack_qkv produces), dev_bqkv (bf16, packed order) may be NULL. */

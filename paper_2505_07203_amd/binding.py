@@ -39,7 +39,7 @@ EXPORTS = [
     "po_op_quantize_rows", "po_op_rmsnorm_quantize", "po_op_linear_fp8", "po_op_qkv_rope_fp8",
     "po_attach_kv_cache_slots", "po_kv_cache_match", "po_kv_cache_slot", "po_sched_pick_multi",
     "po_profile_jct", "po_engine_step", "po_set_few_rows_split", "po_set_storage_rounding", "po_op_linear_split", "po_sched_push_request", "po_op_attention_split",
-    "po_op_attention_split_prefix",
+    "po_op_attention_split_prefix", "po_gemm_tile", "po_op_linear_fp8_split",
     "po_sched_create", "po_sched_destroy", "po_sched_set_jct_model", "po_sched_fit_jct_model", "po_sched_push",
     "po_sched_size", "po_sched_pick", "po_sched_remove", "po_op_rope_static", "po_op_mfma_peak", "po_op_stream_copy",
 ]
@@ -121,6 +121,8 @@ def lib() -> C.CDLL:
     L.po_op_attention_split.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, vp, C.POINTER(i32)]
     L.po_op_attention_split_prefix.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, i32, vp, vp, i64, i64, vp,
                                                C.POINTER(i32)]
+    L.po_gemm_tile.argtypes = [i32, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
+    L.po_op_linear_fp8_split.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_linear_split.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_gate_up_silu.argtypes = [i32, vp, vp, vp, vp, i64, i32, i32, vp]
     L.po_op_pack_gate_up.argtypes = [i32, vp, vp, vp, i32, i32, vp]
@@ -435,6 +437,14 @@ def po_op_linear(a, w, residual=None, out=None):
     return c
 
 
+def po_gemm_tile(M: int, N: int, K: int, splits: int = 1, fp8: bool = False):
+    """-> (rows, columns, K splits) of the block tile a launch of these sizes takes; splits = 0: in as many K splits as
+    few-rows mode makes; needs no GPU"""
+    r, c, n = C.c_int32(0), C.c_int32(0), C.c_int32(splits)
+    check(lib().po_gemm_tile(1 if fp8 else 0, M, N, K, C.byref(n), C.byref(r), C.byref(c)))
+    return r.value, c.value, n.value
+
+
 def po_op_linear_split(a, w, residual, scratch_bytes=1 << 28):
     """-> (C or None, splits): the split-K form of po_op_linear with a residual; None when nothing was split"""
     import torch
@@ -484,6 +494,20 @@ def po_op_linear_fp8(a_codes, a_scales, w_codes, w_scales, residual=None, out=No
     check(lib().po_op_linear_fp8(epi, a_codes.data_ptr(), a_scales.data_ptr(), w_codes.data_ptr(), w_scales.data_ptr(),
                                  c.data_ptr(), None if residual is None else residual.data_ptr(), M, N, K, _stream()))
     return c
+
+
+def po_op_linear_fp8_split(a_codes, a_scales, w_codes, w_scales, residual, scratch_bytes=1 << 28):
+    """-> (C or None, splits): the split-K form of po_op_linear_fp8 with a residual; None when nothing was split"""
+    import torch
+    M, K = a_codes.shape
+    N = w_codes.shape[0]
+    c = torch.empty((M, N), dtype=torch.bfloat16, device=a_codes.device)
+    scratch = torch.empty(scratch_bytes, dtype=torch.uint8, device=a_codes.device)
+    n = C.c_int32(0)
+    check(lib().po_op_linear_fp8_split(a_codes.data_ptr(), a_scales.data_ptr(), w_codes.data_ptr(), w_scales.data_ptr(), c.data_ptr(),
+                                       residual.data_ptr(), scratch.data_ptr(), scratch_bytes, M, N, K, _stream(), C.byref(n)))
+    torch.cuda.synchronize()
+    return (c if n.value > 1 else None), n.value
 
 
 def attention_q_scale(head_dim: int) -> float:

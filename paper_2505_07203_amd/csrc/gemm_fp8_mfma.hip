@@ -454,6 +454,16 @@ GemmParams base_params(const unsigned char* A, int64_t lda, const float* sa, con
 // K must be a multiple of 128 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_fp8_supported(int N, int K) { return K > 0 && K % 128 == 0 && N > 0 && N % 64 == 0; }
 
+int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols) {
+    GemmParams p = base_params(nullptr, K, nullptr, nullptr, K, nullptr, M, N, K);
+    if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
+    p.K = K / splits;
+    const TileForm& t = FORMS[pick_form(TILES, p, splits)];
+    *rows = t.bm;
+    *cols = t.bn;
+    return splits;
+}
+
 void launch_gemm_fp8(int epi, const unsigned char* A, int64_t lda, const float* sa, const unsigned char* W, int64_t ldw,
                      const float* sw, bf16_t* C, int64_t ldc, const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M,
                      int N, int K, hipStream_t s) {

@@ -500,6 +500,16 @@ GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ld
 // K must be a multiple of 64 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_mfma_supported(int N, int K) { return K > 0 && K % 64 == 0 && N > 0 && N % 64 == 0; }
 
+int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols) {
+    GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
+    if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
+    p.K = K / splits;
+    const TileForm& t = FORMS[pick_form(TILES, p, splits)];
+    *rows = t.bm;
+    *cols = t.bn;
+    return splits;
+}
+
 double gemm_mfma_launch_cost(int64_t M, int N) { return (double)((form_tiles(FORMS[0], M, N) + 255) / 256); }
 
 void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C, int64_t ldc,

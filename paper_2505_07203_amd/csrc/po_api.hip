@@ -1319,6 +1319,14 @@ po_status po_op_linear(int32_t dtype, const void* a, const void* w, void* cc, co
     return PO_OK;
 }
 
+po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows, int32_t* tile_cols) {
+    if ((fp8 != 0 && fp8 != 1) || M <= 0 || !splits || *splits < 0 || *splits > 8 || !tile_rows || !tile_cols) return PO_ERR_INVALID_ARG;
+    const int32_t parts = *splits > 1 ? *splits : 1;
+    if (K <= 0 || K % parts || !(fp8 ? gemm_fp8_supported(N, K / parts) : gemm_mfma_supported(N, K / parts))) return PO_ERR_BAD_CONFIG;
+    *splits = (fp8 ? gemm_fp8_tile : gemm_mfma_tile)(M, N, K, *splits, tile_rows, tile_cols);
+    return PO_OK;
+}
+
 po_status po_op_linear_split(const void* a, const void* w, void* cc, const void* residual, void* scratch,
                              size_t scratch_bytes, int64_t M, int32_t N, int32_t K, void* stream, int32_t* splits_used) {
     if (!a || !w || !cc || !residual || !scratch || !splits_used || M <= 0 || N <= 0 || K <= 0) return PO_ERR_INVALID_ARG;
@@ -1540,6 +1548,19 @@ po_status po_op_linear_fp8(int32_t epilogue, const void* a_codes, const float* a
     const int64_t ldc = epilogue == EPI_SILU_MUL ? N / 2 : N;
     launch_gemm_fp8(epilogue, (const unsigned char*)a_codes, K, a_scales, (const unsigned char*)w_codes, K, w_scales,
                     (bf16_t*)cc, ldc, nullptr, (const bf16_t*)residual, N, M, N, K, (hipStream_t)stream);
+    PO_HIP(hipGetLastError());
+    return PO_OK;
+}
+
+po_status po_op_linear_fp8_split(const void* a_codes, const float* a_scales, const void* w_codes, const float* w_scales, void* cc,
+                                 const void* residual, void* scratch, size_t scratch_bytes, int64_t M, int32_t N, int32_t K,
+                                 void* stream, int32_t* splits_used) {
+    if (!a_codes || !a_scales || !w_codes || !w_scales || !cc || !residual || !scratch || !splits_used || M <= 0 || N <= 0 || K <= 0)
+        return PO_ERR_INVALID_ARG;
+    if (!gemm_fp8_supported(N, K)) return PO_ERR_BAD_CONFIG;
+    *splits_used = launch_gemm_fp8_splitk(EPI_RESIDUAL, (const unsigned char*)a_codes, K, a_scales, (const unsigned char*)w_codes, K,
+                                          w_scales, (bf16_t*)cc, N, (const bf16_t*)residual, N, M, N, K, (float*)scratch,
+                                          scratch_bytes, (hipStream_t)stream);
     PO_HIP(hipGetLastError());
     return PO_OK;
 }

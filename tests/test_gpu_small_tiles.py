@@ -6,54 +6,62 @@ from paper_2505_07203_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# heights at which the tiles of 32 .. 256 rows x 128 columns and 192 or 256 x 256 come in, one row off whole tiles among them
-ROWS = (1, 31, 33, 191, 193, 200, 257, 471, 640, 901, 1025, 1281, 1537, 1931)
+# heights at which the tiles of 32 .. 256 rows x 128 columns and 192 or 256 x 256 come in, one row off whole tiles among
+# them; test_tile_forms_cpu.py holds them to taking every tile with the sizes below
+ROWS = (1, 31, 33, 191, 193, 200, 257, 471, 640, 700, 901, 1025, 1281, 1537, 1931, 2300, 2700, 3500)
+TOP = 4300
+BF16_SHAPES = [(4096, 64), (4096, 448), (4096, 1024), (320, 128), (64, 832), (6144, 512)]
+BF16_QKV = [(I.LLAMA8B, 512, True), (I.LLAMA8B, 4096, False), (I.TINY, 192, False)]
+FP8_SHAPES = [(4096, 128), (4096, 896), (6144, 2048), (320, 640), (64, 1024)]
+FP8_QKV_K = 4096
+BF16_SPLIT = [(m, 4096, 14336) for m in (1, 65, 129, 161, 165, 193, 245, 321, 385)]
+FP8_SPLIT = [(m, 4096, 14336) for m in (1, 65, 129, 385)] + [(577, 5120, 27648)]
 
 
-@pytest.mark.parametrize("N,K", [(4096, 64), (4096, 448), (4096, 1024), (320, 128), (64, 832), (6144, 512)])
+@pytest.mark.parametrize("N,K", BF16_SHAPES)
 def test_rows_are_the_same_bits_in_launches_of_every_height(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
     g = torch.Generator(device="cuda").manual_seed(N + K)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
-    top = 4300
+    top = TOP
     a, r, w = rnd(top, K), rnd(top, N), rnd(N, K) * 0.05
     whole = {"store": B.po_op_linear(a, w), "residual": B.po_op_linear(a, w, residual=r), "silu": B.po_op_gate_up_silu(a, w)}
     # fp32 sums of K products of size |a||w|, then one bf16 rounding
     ref = (a.double() @ w.double().t()).cpu().numpy()
     tol = 2.0 ** -8 * np.abs(ref) + K * 2.0 ** -22 * (a.double().abs() @ w.double().abs().t()).cpu().numpy()
     assert np.all(np.abs(whole["store"].double().cpu().numpy() - ref) <= tol)
-    for m in ROWS + (2300, 2700, 3500):
+    for m in ROWS:
         x = a[:m].contiguous()
         assert torch.equal(B.po_op_linear(x, w), whole["store"][:m]), m
         assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole["residual"][:m]), m
         assert torch.equal(B.po_op_gate_up_silu(x, w), whole["silu"][:m]), m
 
 
-@pytest.mark.parametrize("cfg,K,bias", [(I.LLAMA8B, 512, True), (I.LLAMA8B, 1024, False), (I.TINY, 192, False)])
+@pytest.mark.parametrize("cfg,K,bias", BF16_QKV)
 def test_qkv_rows_are_the_same_bits_in_launches_of_every_height(cfg, K, bias):
     import torch
     from paper_2505_07203_amd import binding as B
     hq, hkv, hd = cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim
     g = torch.Generator(device="cuda").manual_seed(K)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
-    top = 4300
+    top = TOP
     a, w = rnd(top, K), rnd((hq + 2 * hkv) * hd, K) * 0.05
     b = rnd((hq + 2 * hkv) * hd) if bias else None
     cos, sin = B.po_op_rope_table(top, hd, cfg.rope_theta)
     q, k, vt = B.po_op_qkv_rope(a, w, b, cos, sin, hq, hkv, hd)
-    for m in ROWS + (2300, 2700, 3500):
+    for m in ROWS:
         q1, k1, vt1 = B.po_op_qkv_rope(a[:m].contiguous(), w, b, cos, sin, hq, hkv, hd)
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
 
 
-@pytest.mark.parametrize("N,K", [(4096, 128), (4096, 896), (6144, 2048), (320, 640), (64, 1024)])
+@pytest.mark.parametrize("N,K", FP8_SHAPES)
 def test_fp8_rows_are_the_same_bits_in_launches_of_every_height(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
     g = torch.Generator(device="cuda").manual_seed(N + K)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
-    top = 4300
+    top = TOP
     r = rnd(top, N)
     (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(top, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
     whole = {"store": B.po_op_linear_fp8(qa, sa, qw, sw), "residual": B.po_op_linear_fp8(qa, sa, qw, sw, residual=r),
@@ -62,7 +70,7 @@ def test_fp8_rows_are_the_same_bits_in_launches_of_every_height(N, K):
     ref = (val(qa, sa) @ val(qw, sw).t()).cpu().numpy()
     tol = 2.0 ** -8 * np.abs(ref) + K * 2.0 ** -22 * (val(qa, sa).abs() @ val(qw, sw).abs().t()).cpu().numpy()
     assert np.all(np.abs(whole["store"].double().cpu().numpy() - ref) <= tol)
-    for m in ROWS + (2100,):
+    for m in ROWS:
         x, s = qa[:m].contiguous(), sa[:m].contiguous()
         assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw), whole["store"][:m]), m
         assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole["residual"][:m]), m
@@ -73,17 +81,39 @@ def test_fp8_rows_are_the_same_bits_in_launches_of_every_height(N, K):
 def test_fp8_qkv_rows_are_the_same_bits_in_launches_of_every_height(bias):
     import torch
     from paper_2505_07203_amd import binding as B
-    hq, hkv, hd, K = 32, 8, 128, 1024
+    hq, hkv, hd, K = 32, 8, 128, FP8_QKV_K
     g = torch.Generator(device="cuda").manual_seed(7)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
-    top = 4300
+    top = TOP
     (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(top, K)), B.po_op_quantize_rows(rnd((hq + 2 * hkv) * hd, K) * 0.05)
     b = rnd((hq + 2 * hkv) * hd) if bias else None
     cos, sin = B.po_op_rope_table(top, hd, 500000.0)
     q, k, vt = B.po_op_qkv_rope_fp8(qa, sa, qw, sw, b, cos, sin, hq, hkv, hd)
-    for m in ROWS + (2100,):
+    for m in ROWS:
         q1, k1, vt1 = B.po_op_qkv_rope_fp8(qa[:m].contiguous(), sa[:m].contiguous(), qw, sw, b, cos, sin, hq, hkv, hd)
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("M,N,K,fp8", [(*x, False) for x in BF16_SPLIT] + [(*x, True) for x in FP8_SPLIT])
+def test_split_sums_in_every_tile_against_float64(M, N, K, fp8):
+    """Partial sums of few-rows mode, tile by tile: against float64, and the splits and the tile the planner names."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    a, w, r = rnd(M, K), rnd(N, K) * 0.05, rnd(M, N)
+    if fp8:
+        qa, qw = B.po_op_quantize_rows(a), B.po_op_quantize_rows(w)
+        c, splits = B.po_op_linear_fp8_split(*qa, *qw, r)
+        a, w = (x.view(torch.float8_e4m3fn).double() * y.double()[:, None] for x, y in (qa, qw))
+    else:
+        c, splits = B.po_op_linear_split(a, w, r)
+        a, w = a.double(), w.double()
+    assert splits == B.po_gemm_tile(M, N, K, 0, fp8)[2] > 1
+    ref = a @ w.t() + r.double()
+    # fp32 sums of K products of size |a||w|, then one bf16 rounding
+    tol = 2.0 ** -8 * ref.abs() + K * 2.0 ** -22 * (a.abs() @ w.abs().t())
+    assert bool(((c.double() - ref).abs() <= tol).all())
 
 
 def _rotated(a, b, cos, sin, first_fused):
@@ -132,13 +162,13 @@ def test_f32_rows_are_the_same_bits_in_launches_of_every_height(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
     g = torch.Generator(device="cuda").manual_seed(N + K)
-    top = 4300
+    top = TOP
     a, r, w = (torch.randn(*s, generator=g, device="cuda") for s in ((top, K), (top, N), (N, K)))
     whole, whole_r = B.po_op_linear(a, w), B.po_op_linear(a, w, residual=r)
     ref = (a.double() @ w.double().t()).cpu().numpy()
     tol = K * 2.0 ** -24 * (a.double().abs() @ w.double().abs().t()).cpu().numpy()      # K sequential float32 additions
     assert np.all(np.abs(whole.double().cpu().numpy() - ref) <= tol + 2.0 ** -24 * np.abs(ref))
-    for m in ROWS + (2100,):
+    for m in ROWS:
         x = a[:m].contiguous()
         assert torch.equal(B.po_op_linear(x, w), whole[:m]), m
         assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole_r[:m]), m

@@ -1,0 +1,52 @@
+"""The sizes of the GPU tests of the GEMM block tiles reach every tile that launches take (the choice is a host function of
+sizes): a refit of its constants that moved a tile out of the tests' sizes fails here."""
+import pytest
+
+import test_gpu_small_tiles as T
+from paper_2505_07203_amd import binding as B
+from paper_2505_07203_amd import inputs as I
+
+BF16 = {(r, 128) for r in (32, 64, 96, 128, 160, 192, 256)} | {(192, 256), (256, 256)}
+FP8 = {(r, 128) for r in (64, 128, 192, 256)} | {(256, 256)}
+
+
+def qkv_columns(cfg):
+    return cfg.q_dim + 2 * cfg.kv_dim
+
+
+def tiles(shapes, fp8=False):
+    return {B.po_gemm_tile(m, N, K, 1, fp8)[:2] for N, K in shapes for m in T.ROWS + (T.TOP,)}
+
+
+def test_whole_launches():
+    assert tiles(T.BF16_SHAPES) == BF16
+    assert tiles([(qkv_columns(cfg), K) for cfg, K, _ in T.BF16_QKV]) == BF16
+    assert tiles(T.FP8_SHAPES, True) == FP8
+    assert tiles([(qkv_columns(I.LLAMA8B), T.FP8_QKV_K)], True) == FP8
+
+
+def test_split_launches():
+    for shapes, fp8, every in ((T.BF16_SPLIT, False, BF16), (T.FP8_SPLIT, True, FP8)):
+        got = [B.po_gemm_tile(M, N, K, 0, fp8) for M, N, K in shapes]
+        assert all(s > 1 for _, _, s in got)
+        assert {(r, c) for r, c, _ in got} == every
+
+
+@pytest.mark.parametrize("cfg", [I.LLAMA8B, I.QWEN32B])
+def test_no_launch_of_the_models_takes_another_tile(cfg):
+    d, F = cfg.d_model, cfg.ffn_dim
+    for N, K in ((qkv_columns(cfg), d), (d, cfg.q_dim), (2 * F, d), (d, F)):
+        for splits in (0, 1):
+            assert {B.po_gemm_tile(m, N, K, splits)[:2] for m in range(1, 4400, 7)} <= BF16
+            assert {B.po_gemm_tile(m, N, K, splits, True)[:2] for m in range(1, 4400, 7)} <= FP8
+
+
+def test_arguments():
+    L, n, r, c = B.lib(), B.C.c_int32(1), B.C.c_int32(0), B.C.c_int32(0)
+    ask = lambda *a: L.po_gemm_tile(*a, B.C.byref(n), B.C.byref(r), B.C.byref(c))
+    assert ask(2, 1, 64, 64) == ask(0, 0, 64, 64) == B.PO_ERR_INVALID_ARG
+    assert ask(0, 1, 65, 64) == ask(0, 1, 64, 96) == ask(1, 1, 64, 64) == B.PO_ERR_BAD_CONFIG
+    n.value = 9
+    assert ask(0, 1, 64, 1024) == B.PO_ERR_INVALID_ARG
+    n.value = 2
+    assert ask(0, 1, 64, 64) == B.PO_ERR_BAD_CONFIG
