@@ -294,12 +294,6 @@ bool launch_attention_f32_mfma(const float* q, const float* k, const float* v, f
 // one row of K 14336 1034 -> 84 us.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-#ifdef __HIP_DEVICE_COMPILE__
-#define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
-#else
-#define PO_WAIT_BARRIER(n_)
-#endif
-
 template <int T, int D>
 __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __restrict__ A, int64_t lda,
                                                                const float* __restrict__ W, int64_t ldw, float* C,

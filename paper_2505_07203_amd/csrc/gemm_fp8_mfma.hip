@@ -211,14 +211,6 @@ __global__ void __launch_bounds__(NTHREADS) gemm_fp8_mfma_kernel(const GemmParam
     }
 }
 
-// all but the n_ youngest global->LDS loads and every LDS read done, then the workgroup barrier (n_ a constant
-// expression of template parameters, which the host pass would not take as an asm operand)
-#ifdef __HIP_DEVICE_COMPILE__
-#define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
-#else
-#define PO_WAIT_BARRIER(n_)
-#endif
-
 // The same GEMM in small block tiles for launches of few 256 x 256 tiles (see the bf16 small kernel for what bounds
 // them): 128 columns, four wavefronts 2 x 2, patches of 32 MR rows x 64 columns, a ring of D whole slices (as many as LDS
 // holds).  With one workgroup per compute unit a wavefront has 512 registers, enough for the fragments of TWO whole

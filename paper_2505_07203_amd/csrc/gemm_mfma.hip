@@ -197,14 +197,6 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
     }
 }
 
-// all but the n_ youngest global->LDS loads and every LDS read done, then the workgroup barrier (n_ a constant
-// expression of template parameters, which the host pass would not take as an asm operand)
-#ifdef __HIP_DEVICE_COMPILE__
-#define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
-#else
-#define PO_WAIT_BARRIER(n_)
-#endif
-
 // The same GEMM in small block tiles, for launches whose 256-column tiles would leave compute units idle (requests of up
 // to about 2000 rows, the last layer's single row, split-K launches).  What bounds those launches is the latency of a
 // slice, not the matrix pipe: a 256-row tile of the kernel above takes 1.05 us per slice in a launch of 16 tiles, and the
@@ -304,7 +296,20 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
 
     // One phase: the 4 MU MFMAs of one k-step; spread behind them the MU + 4 fragment reads of the next k-step (A unit
     // at ua_, W unit at uw_, k-step kn_) and then ND_ global->LDS loads
-#define PO_PHASE(AC, WC, AN, WN, ua_, uw_, kn_, ND_, LOAD_)                                                              _Pragma("unroll") for (int m = 0; m < 4 * MU; ++m) {                                                                      acc[m >> 2][m & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WC[m & 3], AC[m >> 2], acc[m >> 2][m & 3], 0, 0, 0);         __builtin_amdgcn_sched_barrier(0);                                                                                    constexpr int T_ = MU + 4 + (ND_);                                                                                    _Pragma("unroll") for (int x = 0; x < T_; ++x) {                                                                          if (x >= m * T_ / (4 * MU) && x < (m + 1) * T_ / (4 * MU)) {                                                              if (x < MU) AN[x < MU ? x : 0] = *(const bf16x8*)((ua_) + x * 2048 + f_off[kn_]);                                     else if (x < MU + 4) WN[(x - MU) & 3] = *(const bf16x8*)((uw_) + (x - MU) * 2048 + f_off[kn_]);                       else { LOAD_(x - MU - 4) }                                                                                            __builtin_amdgcn_sched_barrier(0);                                                                                }                                                                                                                 }                                                                                                                 }
+#define PO_PHASE(AC, WC, AN, WN, ua_, uw_, kn_, ND_, LOAD_)                                                            \
+    _Pragma("unroll") for (int m = 0; m < 4 * MU; ++m) {                                                               \
+        acc[m >> 2][m & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WC[m & 3], AC[m >> 2], acc[m >> 2][m & 3], 0, 0, 0); \
+        __builtin_amdgcn_sched_barrier(0);                                                                             \
+        constexpr int T_ = MU + 4 + (ND_);                                                                             \
+        _Pragma("unroll") for (int x = 0; x < T_; ++x) {                                                               \
+            if (x >= m * T_ / (4 * MU) && x < (m + 1) * T_ / (4 * MU)) {                                               \
+                if (x < MU) AN[x < MU ? x : 0] = *(const bf16x8*)((ua_) + x * 2048 + f_off[kn_]);                      \
+                else if (x < MU + 4) WN[(x - MU) & 3] = *(const bf16x8*)((uw_) + (x - MU) * 2048 + f_off[kn_]);        \
+                else { LOAD_(x - MU - 4) }                                                                             \
+                __builtin_amdgcn_sched_barrier(0);                                                                     \
+            }                                                                                                          \
+        }                                                                                                              \
+    }
     int pa = 0, pw = 0;                          // ring positions of slice s: A in D + 1 positions, W in D
     for (int s = 0; s < KT; ++s) {
         const int pa1 = pa + 1 > D ? 0 : pa + 1, pw1 = pw + 1 >= D ? 0 : pw + 1;

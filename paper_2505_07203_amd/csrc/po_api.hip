@@ -231,10 +231,10 @@ struct PhaseTimer {
     }
 };
 
-// Rows per launch of a chunk loop.  The MFMA GEMM works in tiles of 256 (or 128) rows x 256 columns, one per CU at a
-// time, so a launch costs whole rounds of tiles over the 256 CUs (gemm_mfma_launch_cost): among max_rows and the
-// multiples of 256 rows below it this picks the one with the least such cost per row, summed over the GEMMs of the loop (ties:
-// the larger).  Results do not depend on the choice (row results are independent of the other rows of a launch);
+// Rows per launch of a chunk loop.  Launches of thousands of rows run in tiles of 256 rows x 256 columns, one per CU at a
+// time, and cost whole rounds of them over the 256 CUs (gemm_mfma_launch_cost): among max_rows and the multiples of 256
+// rows below it this picks the one with the least such cost per row, summed over the GEMMs of the loop (ties: the larger).
+// (The launcher may take another tile for such a launch, 192 x 256 above all; this choice does not look at that.)  Results do not depend on the choice (row results are independent of the other rows of a launch);
 // only the buffers' capacity (max_rows) binds it.
 struct GemmCols {
     int64_t n_cols, k;

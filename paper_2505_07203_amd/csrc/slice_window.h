@@ -1,4 +1,5 @@
-// What the ring GEMMs may read of an operand tile for slice s along K (plain C++, host and device).
+// Shared by the GEMMs that copy slices along K into a ring in LDS: what a copy may read, and how a slice is handed over
+// (the first is plain C++, host and device).
 #pragma once
 
 namespace po {
@@ -17,3 +18,11 @@ constexpr SliceWindow slice_window(int s, int n_slices, unsigned tile_bytes, int
 }
 
 }  // namespace po
+
+// all but the n_ youngest global->LDS loads and every LDS read done, then the workgroup barrier (n_ a constant
+// expression of template parameters, which the host pass would not take as an asm operand)
+#ifdef __HIP_DEVICE_COMPILE__
+#define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
+#else
+#define PO_WAIT_BARRIER(n_)
+#endif
