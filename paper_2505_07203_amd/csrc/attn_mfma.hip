@@ -511,21 +511,23 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     const int krow_l = wave * 4 + (lane >> 4);
     const uint32_t kcol = (uint32_t)(((lane & 15) ^ (krow_l & 15)) << 4);
     const uint32_t krs2 = (uint32_t)(Hkv * HD * 2);
-    const uint32_t klane = (uint32_t)krow_l * krs2 + kcol;
+    uint32_t klane[4];                                           // of round jj, from the tile's first key
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) klane[jj] = (uint32_t)(jj * 16 + krow_l) * krs2 + kcol;
     const int vrow_l = wave * 8 + (lane >> 3);
     const uint32_t voff_v = (uint32_t)vrow_l * (uint32_t)(ldv * 2) + (uint32_t)(((lane & 7) ^ swz8(vrow_l)) << 4);
-    // K goes through a buffer resource that ends with the last position: rows of the last, ragged tile
-    // beyond it read as zero (they are masked keys) instead of needing a clamp per load.
-    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(k + (int64_t)kvh * HD), 0,
-        (int)((uint32_t)(end - 1) * krs2 + 256u), 0x00020000);
+    // K goes through a buffer resource per tile, from its first key to the last position: rows of the last, ragged tile
+    // beyond it read as zero (they are masked keys) instead of needing a clamp per load.  The whole offset sits in the
+    // lane part, on which the bounds are checked.
+    const bf16_t* const kbase = k + (int64_t)kvh * HD;
+    const uint32_t kbytes = (uint32_t)(end - 1) * krs2 + 256u;
     // (V^T of this KV head: 128 rows of ldv positions; its columns are always inside the row)
     const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(vt + (int64_t)kvh * HD * ldv), 0, (int)((uint32_t)HD * (uint32_t)(ldv * 2) - (uint32_t)(tile0 * 128)), 0x00020000);
     const uint32_t vrow32 = (uint32_t)(32 * ldv * 2);
     // SPLIT 2: the second pair, from this piece's first tile to its last one of the pair (empty without one)
-    const __amdgpu_buffer_rsrc_t krsrc2 = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(sp.k2 + ((int64_t)tile0 * 64 * Hkv + kvh) * HD), 0, tiles2 > 0 ? (int)((uint32_t)(tiles2 * 64 - 1) * krs2 + 256u) : 0, 0x00020000);
+    const bf16_t* const kbase2 = sp.k2 + ((int64_t)tile0 * 64 * Hkv + kvh) * HD;
+    const uint32_t kbytes2 = tiles2 > 0 ? (uint32_t)(tiles2 * 64 - 1) * krs2 + 256u : 0u;
     const __amdgpu_buffer_rsrc_t vrsrc2 = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(sp.vt2 + (int64_t)kvh * HD * sp.ldv2 + tile0 * 64), 0,
         tiles2 > 0 ? (int)((uint32_t)HD * (uint32_t)(sp.ldv2 * 2) - (uint32_t)(tile0 * 128)) : 0, 0x00020000);
@@ -536,10 +538,13 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         const int t_ = min((tile_), n_tiles - 1), kv0_ = t_ * 64;                                              \
         const bool second_ = SPLIT == 2 && t_ < tiles2;                                                        \
         if ((jj_) < 4) {                                                                                       \
+            const uint32_t ko_ = (uint32_t)t_ * (64 * krs2);                                                   \
+            const __amdgpu_buffer_rsrc_t kr_ = __builtin_amdgcn_make_buffer_rsrc(                              \
+                (void*)((const char*)(second_ ? kbase2 : kbase) + ko_), 0,                                     \
+                (int)((second_ ? kbytes2 : kbytes) - ko_), 0x00020000);                                        \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                          \
-                second_ ? krsrc2 : krsrc,                                                                      \
-                (__attribute__((address_space(3))) void*)(smem + (stg_) * A64_TILE + ((jj_) * 16 + wave * 4) * 256), \
-                16, klane, (kv0_ + (jj_) * 16) * krs2, 0, 0);                                                  \
+                kr_, (__attribute__((address_space(3))) void*)(smem + (stg_) * A64_TILE + ((jj_) * 16 + wave * 4) * 256), \
+                16, klane[(jj_) & 3], 0, 0, 0);                                                                \
         } else {                                                                                               \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                          \
                 second_ ? vrsrc2 : vrsrc,                                                                      \
