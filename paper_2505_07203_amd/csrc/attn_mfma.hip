@@ -1001,14 +1001,12 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
                   int Hkv, int64_t q_row0, int* redo, bool q_prescaled, hipStream_t s) {
     constexpr int SMEM = 2 * A64_NSTAGE * A64_TILE + 16;             // the ring and the give-up word
     constexpr int SMEM_REDO = 2 * 2 * BNK * 128 * 2;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 0>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<true, 0>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        (void)hipFuncSetAttribute((const void*)attn_fwd_kernel<128, 1, 8, false>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM_REDO);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 0>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<true, 0>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd_kernel<128, 1, 8, false>), SMEM_REDO);
+    });
     const int nqt = (int)((N + 255) / 256);
     const int hpx = (Hq % 8 == 0) ? Hq / 8 : 0;
     const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(128);
@@ -1031,12 +1029,10 @@ void launch_t(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, b
               int Hkv, int64_t q_row0, bool q_prescaled, hipStream_t s) {
     constexpr int BMQ = NW * QT * 32;
     constexpr int SMEM = 2 * 2 * BNK * HD * 2;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, QT, NW, false>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(attn_fwd_kernel<HD, QT, NW, false>), SMEM);
+    });
     const int nqt = (int)((N + BMQ - 1) / BMQ);
     const int hpx = (Hq % 8 == 0) ? Hq / 8 : 0;
     const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(HD);
@@ -1063,12 +1059,10 @@ int launch_split_t(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t l
     const size_t o_bytes = (size_t)n_split * nq * Hq * HD * sizeof(float), ml_bytes = (size_t)n_split * nq * Hq * 2 * sizeof(float);
     if (n_split < 2 || o_bytes + ml_bytes > scratch_bytes) return 0;
     if (!launch) return n_split;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, 1, NW, true>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(attn_fwd_kernel<HD, 1, NW, true>), SMEM);
+    });
     float* opart = scratch;
     float* mlpart = scratch + o_bytes / sizeof(float);
     const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(HD);
@@ -1113,12 +1107,11 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
         sp.n = cut(per);
     }
     if (!launch) return sp.n;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        (void)hipFuncSetAttribute((const void*)(attn_fwd64_kernel<false, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 1>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 2>), SMEM);
+    });
     sp.k2 = k2; sp.vt2 = vt2; sp.ldv2 = ldv2;
     sp.q_row0 = (int)q_row0;
     sp.tiles2 = tiles2;

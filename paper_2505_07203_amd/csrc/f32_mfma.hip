@@ -252,11 +252,10 @@ static void launch_attention_f32(const float* q, const float* k, const float* v,
                                  int64_t q_row0, hipStream_t s) {
     constexpr int SMEM_MAIN = 2 * 2 * 32 * HD * 4, SMEM_SPLIT = 4 * HD * 32 * 4 + 2 * 128 * 4;
     constexpr int SMEM = SMEM_MAIN > SMEM_SPLIT ? SMEM_MAIN : SMEM_SPLIT;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)attention_f32_mfma_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(attention_f32_mfma_kernel<HD>), SMEM);
+    });
     const int64_t row0 = (q_row0 > 0 && q_row0 < N) ? q_row0 : 0, split_rows = f32_split_rows(HD);
     const int64_t blk_main = std::max<int64_t>(row0, split_rows) / 128, end_main = (N + 127) / 128;
     const int64_t blk_split = row0 / 32, end_split = (std::min<int64_t>(N, split_rows) + 31) / 32;

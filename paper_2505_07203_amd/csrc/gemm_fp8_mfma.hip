@@ -390,11 +390,10 @@ constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BKB, 1};
 
 template <int EPI>
 void launch_256(const GemmParams& p, hipStream_t s, int splits) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_fp8_mfma_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM_BYTES);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(gemm_fp8_mfma_kernel<EPI>), SMEM_BYTES);
+    });
     const int per_xcd = (p.mt * p.nt + 7) / 8;
     hipLaunchKernelGGL(gemm_fp8_mfma_kernel<EPI>, dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NTHREADS), SMEM_BYTES, s, p);
 }
@@ -403,11 +402,10 @@ template <int EPI, int MR, int D>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     constexpr int SMEM = D * (64 * MR + 128) * BKB;
     static_assert(SMEM <= 160 * 1024 && SMEM >= 4 * 8192, "LDS of a compute unit; staging of four wavefronts");
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_fp8_small_kernel<EPI, MR, D>, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(gemm_fp8_small_kernel<EPI, MR, D>), SMEM);
+    });
     p.mt = (p.M + 64 * MR - 1) / (64 * MR);
     p.nt = (p.N + 127) / 128;
     const int per_xcd = (p.mt * p.nt + 7) / 8;

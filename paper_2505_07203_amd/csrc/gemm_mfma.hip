@@ -442,12 +442,10 @@ constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BK, 2};
 
 template <int EPI, int MU>
 void launch_big(GemmParams p, hipStream_t s, int splits) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_mfma_kernel<EPI, MU>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  SMEM_BYTES);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(gemm_bf16_mfma_kernel<EPI, MU>), SMEM_BYTES);
+    });
     p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     const int per_xcd = (p.mt * p.nt + 7) / 8;
     hipLaunchKernelGGL((gemm_bf16_mfma_kernel<EPI, MU>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NT_BF16),
@@ -458,12 +456,10 @@ template <int EPI, int MU, int D>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     constexpr int SMEM = ((D + 1) * 32 * MU + D * 128) * 128;
     static_assert(SMEM <= 160 * 1024 && SMEM >= 4 * 4096, "LDS of a compute unit; staging of four wavefronts");
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_small_kernel<EPI, MU, D>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(gemm_bf16_small_kernel<EPI, MU, D>), SMEM);
+    });
     p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     p.nt = (p.N + 127) / 128;
     const int per_xcd = (p.mt * p.nt + 7) / 8;

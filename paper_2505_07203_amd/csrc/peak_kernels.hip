@@ -80,14 +80,13 @@ double launch_mfma_peak(int kind, int waves_per_simd, int iters, const void* ope
     // 96 KiB of (unused) dynamic LDS per workgroup: one workgroup per compute unit at a time, so that the number of
     // wavefronts per SIMD is what the caller asked for
     constexpr int LDS = 96 * 1024;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)mfma_peak_kernel<256, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        (void)hipFuncSetAttribute((const void*)mfma_peak_kernel<512, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        (void)hipFuncSetAttribute((const void*)mfma_peak_kernel<256, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        (void)hipFuncSetAttribute((const void*)mfma_peak_kernel<512, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(mfma_peak_kernel<256, 0>), LDS);
+        allow_dynamic_lds((const void*)(mfma_peak_kernel<512, 0>), LDS);
+        allow_dynamic_lds((const void*)(mfma_peak_kernel<256, 1>), LDS);
+        allow_dynamic_lds((const void*)(mfma_peak_kernel<512, 1>), LDS);
+    });
     if (kind == 0 && nt == 256) hipLaunchKernelGGL((mfma_peak_kernel<256, 0>), dim3(blocks), dim3(256), LDS, s, op, sink, iters);
     if (kind == 0 && nt == 512) hipLaunchKernelGGL((mfma_peak_kernel<512, 0>), dim3(blocks), dim3(512), LDS, s, op, sink, iters);
     if (kind == 1 && nt == 256) hipLaunchKernelGGL((mfma_peak_kernel<256, 1>), dim3(blocks), dim3(256), LDS, s, op, sink, iters);

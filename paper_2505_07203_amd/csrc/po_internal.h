@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "once_per_device.h"
+
 namespace po {
 
 typedef uint16_t bf16_t;   // bf16 bit pattern as stored in HBM
@@ -21,6 +23,16 @@ __device__ __forceinline__ float to_f32(bf16_t v) { return bf2f(v); }
 template <typename T> __device__ __forceinline__ T from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return f2bf(v); }
+
+// more than 64 KiB of dynamic LDS for a kernel on the current device (see OncePerDevice)
+static inline void allow_dynamic_lds(const void* kernel, int bytes) {
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+static inline int current_device() {
+    int device = 0;
+    (void)hipGetDevice(&device);
+    return device;
+}
 
 static inline int64_t round_up64(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
