@@ -238,3 +238,15 @@ def test_f32_attention_with_whole_tiles_at_minus_infinity(hd, n):
         s = (q[:, h, 1:].double() @ k[:, 0, 1:].double().t()) * hd ** -0.5
         ref = s.masked_fill(~mask, -float("inf")).softmax(-1) @ v[:, 0].double()
         assert (o[:, h].double() - ref).abs().max().item() <= 4e-6 * v.abs().max().item()
+
+
+@pytest.mark.parametrize("hd,n", [(64, 100), (128, 1200)])
+def test_f32_attention_four_bytes_off_a_16_byte_boundary(hd, n):
+    """Keys and values are copied to LDS 16 bytes at a time from wherever they start."""
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = [torch.randn(n, h, hd, generator=g, device="cuda") for h in (4, 2, 2)]
+    off = [torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape).copy_(t) for t in x]
+    assert all(t.data_ptr() % 16 == 4 for t in off)
+    assert torch.equal(B.po_op_attention(*off), B.po_op_attention(*x))
