@@ -418,10 +418,10 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 // 29.5 us).  A piece writes its unnormalised fp32 accumulators, its reference exponents and its row sums, and
 // attn_combine_kernel merges the pieces.  Every piece takes its reference from its own first 32 keys (a zero reference,
 // as PRE has it, would make all pieces of a row flush or overflow together).  Nothing moves it afterwards: sums only grow,
-// so one look at the end finds a row sum past 2^100 or an accumulator that is not finite, and the workgroup then goes
+// so one look at the end finds a row sum or an accumulator near the end of the float range, and the workgroup then goes
 // through its piece a second time with the exact maxima, which a pass over K alone gives it: at most 2.5 times the time
 // of a piece, whatever the scores.  Measured (32 heads on 8 KV heads behind 14 000 keys, both kernels of a call): one row
-// 47 us with the 32-row kernel above, 26 here; 150 rows 67 and 50; 600 rows 201 and 141.  At 8000 keys 150 rows take 51 us
+// 47 us with the 32-row kernel above, 22 here; 150 rows 67 and 50; 600 rows 205 and 137.  At 8000 keys 150 rows take 51 us
 // with ordinary scores and 84 with scores hundreds apart.
 struct SplitArgs {
     const bf16_t *k2, *vt2;
@@ -607,8 +607,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     }
 
     float mtop[2] = {0.f, 0.f};             // SPLIT: the piece's exact maxima, for the second attempt
-    for (int attempt = 0;; ++attempt) {     // (one attempt unless SPLIT)
-    if (SPLIT) asm volatile("" : "+v"(vpos[0]), "+v"(vpos[1]));      // (keeps the masks of the first block from being formed, and spilled, in front of the loop)
+    for (int attempt = 0;; ++attempt) {     // (one attempt unless SPLIT; the body is not indented for it)
+    // (keeps the masks of the first block from being formed, and spilled, in front of the loop)
+    if (SPLIT) asm volatile("" : "+v"(vpos[0]), "+v"(vpos[1]));
     // ---- prologue: three tiles in flight, S(0), reference maxima
     _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(0, 0, jj);
     _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(1, 1, jj);
@@ -831,7 +832,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     lrow[0] = (lsum[0][0] + lsum[0][1]) + (lsum[0][2] + lsum[0][3]);
     lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
     if (attempt) break;
-    // ---- SPLIT: did a row sum pass 2^100, or (large values) an accumulator the float range?
+    // ---- SPLIT: did a row sum pass 2^100, or (large values) an accumulator 2^119, which 256 pieces could add up to infinity?
     uint32_t top = 0;
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
@@ -839,7 +840,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(oacc[ht][qt][r]) & 0x7fffffffu);
-    if (__any(top >= 0x7f800000u || !(lrow[0] < 0x1p100f) || !(lrow[1] < 0x1p100f)) && lane == 0) *(volatile int*)lds_gave_up = 1;
+    if (__any(top >= 0x7b000000u || !(lrow[0] < 0x1p100f) || !(lrow[1] < 0x1p100f)) && lane == 0) *(volatile int*)lds_gave_up = 1;
     __syncthreads();
     if (!*(volatile int*)lds_gave_up) break;
     // the exact maxima: K tiles alone, one in flight
