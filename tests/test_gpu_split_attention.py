@@ -1,5 +1,6 @@
-"""Few-rows attention with prescaled queries (head dimension 128): pieces of the keys, all query heads of a KV head in one
-workgroup, cached prefix read in place.  Against the default path on the same tokens, which other tests hold to the oracle."""
+"""Few-rows attention at head dimension 128: pieces of the keys, all query heads of a KV head in one workgroup, cached prefix
+read in place.  Through whole calls against the default path on the same tokens, which other tests hold to the oracle, and
+as an operator of its own, every row and head against float64."""
 import numpy as np
 import pytest
 
@@ -59,9 +60,9 @@ def test_split_attention_agrees_with_the_default_path(hq, hkv, total, cached):
 
 @pytest.mark.parametrize("total,cached", [(300, 0), (1500, 1400)])
 def test_scores_far_outside_the_exponent_range(total, cached):
-    """A norm gain that puts scores hundreds of nats apart: rows whose sums leave the float range are formed again with a
-    running maximum, from the cached and the fresh keys.  One rounding of a query value moves a score by up to 0.1 nats
-    here, hence the wider bar."""
+    """A norm gain that puts scores hundreds of nats apart: pieces whose sums come near the end of the float range go through
+    their cached and fresh keys a second time.  One rounding of a query value moves a score by up to 0.1 nats here, hence
+    the wider bar."""
     _compare(_cfg(8, 2), total, cached, 30.0, 6e-2)
 
 
