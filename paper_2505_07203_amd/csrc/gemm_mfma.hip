@@ -198,23 +198,36 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 }
 
 // The same GEMM in small block tiles, for launches whose 256-column tiles would leave compute units idle (requests of up
-// to about 2000 rows, the last layer's single row, split-K launches).  What bounds those launches is the latency of a
-// slice, not the matrix pipe: a 256-row tile of the kernel above takes 1.05 us per slice in a launch of 16 tiles, and the
-// same 128 x 128 tile 0.8 us with two slices in flight and 0.41 with four.  So a tile has 128 columns, four wavefronts
-// (2 x 2 patches of 16 MU rows x 64 columns) and as many slices in flight as the LDS of a whole compute unit holds
+// to about 2000 rows, the last layer's single row, split-K launches).  What bounds those launches is the way of an operand
+// slice into LDS, not the matrix pipe: a 256-row tile of the kernel above takes 1.05 us per slice in a launch of 16 tiles,
+// and the same 128 x 128 tile 0.8 us with two slices in flight and 0.41 with four.  So a tile has 128 columns, four
+// wavefronts (2 x 2 patches of 16 MU rows x 64 columns) and as many slices in flight as the LDS of a whole compute unit holds
 // (D = 7 at 32 rows .. 2 at 256; two workgroups per compute unit with half the depth each were 1.9 x slower at one round
 // of tiles and no faster at two).  A and W have rings of their own, D + 1 and D slices: A(s + D) is loaded during phase 0
 // of slice s into what A(s - 1) left, W(s + D) behind the hand-over barrier into W(s)'s place.  A slice is two phases,
 // one per k-step of 32, with the next k-step's fragments read behind this one's MFMAs; swizzle, tile order and epilogues
 // are those of the kernel above, and so are the bits (one fp32 accumulator per output, K in steps of 32, in order).
-// Measured: down projection (N 4096, K 14336) at 471 rows 225 -> 92 us, 1 row 240 -> 76; O projection at 471 rows 48 ->
-// 24; at one round of 128 x 128 tiles 0.89 PFLOP/s, with 14 TB/s from L2 into LDS.
-template <int EPI, int MU, int D>
+// Weights on their way from HBM.  A compute unit's loads return in order and about 32 KiB of them are in flight, whatever
+// the depth of the ring, so a slice whose weight rows come from HBM paces everything behind it: a tile streams at 36-60
+// GB/s per compute unit from HBM, at 95 from the memory-side cache and at 130 from L2.  The row tiles of a group sit on one
+// XCD and multiply with the same weights; without help all of them wait for the same lines.  So they take turns: every 2 R
+// slices one of R row tiles touches the weights of two slices a few slices ahead of the ring (one dword per line and lane,
+// into LDS that nobody reads), waits for HBM that once, and all others find them in L2.  (Every tile touching its share of
+// every slice helps nobody: then each of them waits for HBM every slice.)
+// Measured: down projection (N 4096, K 14336) at 300 rows 97 -> 80 us with the turns, 471 rows 92 -> 79 (225 on 256-row
+// tiles), 1000 rows 133 -> 117, 1 row 240 -> 76; O projection at 300 rows 30 -> 26, QKV at 1000 rows 67 -> 57.  Not kept, with and
+// without turns: one ring and one barrier per slice, whole slices of fragments in registers (no faster up to 192 rows), all
+// loads of a slice behind the hand-over (2-8 % slower); turns in the 256 x 256 kernel (2-3 % slower).
+template <int EPI, int MU, int D, bool TURNS>
 __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int BM_ = 32 * MU, BN_ = 128;
     constexpr int AU = BM_ * 128, WU = BN_ * 128;          // bytes of a slice of A / W
     constexpr int NA = MU, NW = 4;                         // global->LDS loads per wavefront and slice
+    // how far ahead of the multiplied slice weights are touched: with D - 2 touches or more behind the first D slices' loads,
+    // the hand-over's count of younger loads holds from the first slice on
+    constexpr int AHEAD = D + (D > 6 ? D - 2 : 4);
+    static_assert(AHEAD - D >= D - 2, "");
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
@@ -271,6 +284,19 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     int f_off[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) f_off[ks] = l15 * 128 + (((ks * 4 + l4) ^ ((l15 >> 1) & 7)) << 4);
+    // this wavefront's 32 weight rows of slices s_ and s_ + 1, one dword per line, when it is this row tile's turn (an empty
+    // descriptor otherwise, and where slice s_ + 1 lies past the end of K)
+    unsigned char* const touched = smem + (D + 1) * AU + D * WU + wave * 256;
+    const uint32_t vot = (uint32_t)(wave * 32 + (lane & 31)) * (uint32_t)(p.ldw * 2) + (lane >> 5) * 128;
+    int turn = gm_this > 1 ? (tm - g * GM) * 2 : 1 << 30;
+#define PO_TOUCH(s_)                                                                                                   \
+    if (TURNS) {                                                                                                         \
+        const SliceWindow wt_ = slice_window((s_) + 1, KT, (unsigned)w_bytes, BK * 2);                                 \
+        const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)(turn == 0 ? wt_.bytes : 0), 0x00020000); \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot,         \
+                                                 wt_.bytes ? wt_.offset - BK * 2 : 0, 0, 0);                           \
+        turn = turn == 0 ? 2 * gm_this - 1 : turn - 1;                                                                 \
+    }
     const int a_base = wm * (MU * 16) * 128, w_base = (D + 1) * AU + wn * 64 * 128;
 
     f32x4 acc[MU][4];
@@ -288,6 +314,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         for (int i = 0; i < NW; ++i) PO_DMA_W(s, i)
     }
     PO_WAIT_BARRIER((D - 1) * (NA + NW));                      // slice 0 has landed
+#pragma unroll 1
+    for (int s = D; s < AHEAD; ++s) { PO_TOUCH(s) }
     bf16x8 A0[MU], A1[MU], W0[4], W1[4];
 #pragma unroll
     for (int j = 0; j < MU; ++j) A0[j] = *(const bf16x8*)(smem + a_base + j * 2048 + f_off[0]);
@@ -315,6 +343,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         const int pa1 = pa + 1 > D ? 0 : pa + 1, pw1 = pw + 1 >= D ? 0 : pw + 1;
         const int pa_free = pa == 0 ? D : pa - 1;              // position of A(s - 1)
         PO_SLICE_RSRC(s + D)
+        PO_TOUCH(s + AHEAD)
         const unsigned char* ua = smem + pa * AU + a_base;
         const unsigned char* uw = smem + pw * WU + w_base;
         const unsigned char* ua1 = smem + pa1 * AU + a_base;
@@ -322,8 +351,9 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         // phase 0: k-step 0 | reads k-step 1; loads A(s + D) into the position A(s - 1) left
 #define PO_LA(i_) PO_DMA_A(pa_free, ((i_) < NA ? (i_) : 0))
         PO_PHASE(A0, W0, A1, W1, ua, uw, 1, NA, PO_LA)
-        // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1 and A(s+D)); all LDS reads of slice s are done
-        PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA);
+        // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1, A(s+D) and, with turns, a touch each); all LDS
+        // reads of slice s are done
+        PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA + (TURNS ? D - 1 : 0));
         // phase 1: k-step 1 | reads k-step 0 of slice s+1; loads W(s + D) into W(s)'s position
 #define PO_LW(i_) PO_DMA_W(pw, ((i_) < NW ? (i_) : 0))
         PO_PHASE(A1, W1, A0, W0, ua1, uw1, 0, NW, PO_LW)
@@ -331,6 +361,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         pw = pw1;
     }
 #undef PO_LA
+#undef PO_TOUCH
 #undef PO_LW
 #undef PO_PHASE
 #undef PO_DMA_A
@@ -452,19 +483,37 @@ void launch_big(GemmParams p, hipStream_t s, int splits) {
                        SMEM_BYTES, s, p);
 }
 
-template <int EPI, int MU, int D>
-void launch_small(GemmParams p, hipStream_t s, int splits) {
-    constexpr int SMEM = ((D + 1) * 32 * MU + D * 128) * 128;
+template <int EPI, int MU, int D, bool TURNS>
+void launch_small_t(const GemmParams& p, hipStream_t s, int splits) {
+    constexpr int SMEM = ((D + 1) * 32 * MU + D * 128) * 128 + 1024;           // the rings; where touches go
     static_assert(SMEM <= 160 * 1024 && SMEM >= 4 * 4096, "LDS of a compute unit; staging of four wavefronts");
     static OncePerDevice lds;
     lds.run(current_device(), [] {
-        allow_dynamic_lds((const void*)(gemm_bf16_small_kernel<EPI, MU, D>), SMEM);
+        allow_dynamic_lds((const void*)(gemm_bf16_small_kernel<EPI, MU, D, TURNS>), SMEM);
     });
+    const int per_xcd = (p.mt * p.nt + 7) / 8;
+    hipLaunchKernelGGL((gemm_bf16_small_kernel<EPI, MU, D, TURNS>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(256),
+                       SMEM, s, p);
+}
+
+template <int EPI, int MU, int D>
+void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     p.nt = (p.N + 127) / 128;
-    const int per_xcd = (p.mt * p.nt + 7) / 8;
-    hipLaunchKernelGGL((gemm_bf16_small_kernel<EPI, MU, D>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(256), SMEM,
-                       s, p);
+    // Turns pay where the weights are what a tile waits for (us without / with, 40 .. 1931 rows of five projections alone and
+    // of down projections behind their gate/up).  A row tile that is nearly empty does without them what they do: its
+    // workgroup, short of activations to load, runs ahead of the others (900 rows of the down projection 106 / 118, 1000
+    // rows 135 / 117), and with two or three row tiles in all there is hardly anyone to take turns with.  So: up to 64 rows per
+    // tile from five row tiles on, 10-18 % (150 rows 84 / 70; two, the second a quarter full, 80 / 90); 96 rows with the last one
+    // a third full, 4-15 %; 128 rows with six of them, the last half full, 2-14 %; 160 rows with the last three quarters full, 6 % (1100 rows
+    // 153 / 144; half full 137 / 170); 192 rows never (1500 rows behind their gate/up 164 / 169); 256 rows, with the
+    // shallowest ring, 4-15 %.
+    const int last = p.M - (p.mt - 1) * 32 * MU;                       // rows of the last row tile
+    const bool third = 3 * last >= 32 * MU, half = 2 * last >= 32 * MU;
+    const bool turns = p.mt > 1 && (MU <= 2 ? p.mt >= 5 || half : MU == 3 ? third : MU == 4 ? half && p.mt >= 6
+                                    : MU == 5 ? 4 * last >= 3 * 160 : MU == 8 && (p.mt > 2 || half));
+    if (MU != 6 && turns) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
+    else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
 template <int EPI>
