@@ -422,8 +422,9 @@ po_status po_op_attention_split_prefix(const void* dev_q, const void* dev_k, con
 
 /* The block tile (rows x columns of the output) that a launch of po_op_linear, po_op_gate_up_silu (N = 2 F) or
  * po_op_qkv_rope with contiguous operands takes, or of their FP8 forms with fp8 = 1.  *splits: 1 = a whole launch, more =
- * one of that many K splits of few-rows mode, 0 = as many as that mode takes with enough scratch (written back).  Host
- * only.  The tile changes no result (a split sum is rounded differently). */
+ * one of that many K splits, 0 = as many as the split entry points take with enough scratch (written back; few-rows mode takes
+ * the same, except that it runs bf16 launches of up to 16 rows and 16384 columns whole).  Host only.  The tile changes no result
+ * (a split sum is rounded differently). */
 po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows,
                        int32_t* tile_cols);
 

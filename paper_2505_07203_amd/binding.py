@@ -439,7 +439,7 @@ def po_op_linear(a, w, residual=None, out=None):
 
 def po_gemm_tile(M: int, N: int, K: int, splits: int = 1, fp8: bool = False):
     """-> (rows, columns, K splits) of the block tile a launch of these sizes takes; splits = 0: in as many K splits as
-    few-rows mode makes; needs no GPU"""
+    the split entry points make; needs no GPU"""
     r, c, n = C.c_int32(0), C.c_int32(0), C.c_int32(splits)
     check(lib().po_gemm_tile(1 if fp8 else 0, M, N, K, C.byref(n), C.byref(r), C.byref(c)))
     return r.value, c.value, n.value

@@ -377,6 +377,147 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     }
 }
 
+// The 32 x 128 tile of a launch of at most 16 rows (the last layer's single row above all), worked on in strips of 16
+// columns (16 gate and the 16 up columns behind them, a rotary pair of 16: two strips of W rows) by a wavefront of its own.
+// What bounds it: the weights' way from HBM, and a compute unit streams 128 rows of them at 36-50 GB/s (see above): with 4096
+// columns in 32 tiles that is 1.6 TB/s.  Strips put a wavefront on every compute unit (256 for 4096 columns, 896 pairs for
+// 28672), and 5.3-6 TB/s is what they stream.  One wavefront needs no barrier; K goes by in blocks of 256, so that a visit to
+// a row is 512 bytes, straight into a ring of D blocks in LDS.  (16-byte segments XOR-swizzled with the row on the global
+// side: the 16 rows of a fragment read lie 512 bytes apart.)  One accumulator per output, K in steps of 32, in order: the bits
+// of every other tile.  Measured at one row: down projection (N 4096, K 14336) 76 -> 24 us, O projection 23 -> 8.4, QKV 24 ->
+// 11; the 32B shape's (N 5120, K 27648) 140 -> 57, 31 -> 13, 32 -> 15; at 16 rows 83 -> 25, 25 -> 9, 26 -> 13.
+// NA: loads of two activation rows per block (rows past the last one loaded hold anything: they meet no other row's sums).
+template <int EPI, int NA, int D>
+__global__ void __launch_bounds__(64, 2) gemm_bf16_strip_kernel(const GemmParams p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int NS = (EPI == EPI_SILU_MUL || EPI == EPI_QKV_ROPE) ? 2 : 1;
+    constexpr int BKS = 256, ROWB = BKS * 2;               // K per block; bytes of a row of it
+    constexpr int BLOCK = (16 * NS + 2 * NA) * ROWB, NL = 8 * NS + NA;
+    const int lane = threadIdx.x, l15 = lane & 15, l4 = lane >> 4;
+    // first column of the strip(s): 16 t of a 64-column patch, its pair 32 behind
+    const int c0 = NS == 2 ? (blockIdx.x >> 1) * 64 + (blockIdx.x & 1) * 16 : blockIdx.x * 16;
+
+    // Offsets of the lane in a load of two rows; a descriptor per block, from its first column to the end of the last row
+    const uint32_t lda2 = (uint32_t)(p.lda * 2), ldw2 = (uint32_t)(p.ldw * 2);
+    const int row2 = lane >> 5, seg = lane & 31;           // row of the pair, physical segment
+    uint32_t voa[8], vow[8];                               // (voa: NA entries used)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = 2 * i + row2;
+        voa[i] = (uint32_t)row * lda2 + (uint32_t)((seg ^ row) << 4);
+        vow[i] = (uint32_t)row * ldw2 + (uint32_t)((seg ^ row) << 4);
+    }
+    const uint32_t a_bytes = (uint32_t)(p.M - 1) * lda2 + (uint32_t)p.K * 2, w_bytes = 15u * ldw2 + (uint32_t)p.K * 2;
+    const unsigned char* const wbase = (const unsigned char*)(p.W + (int64_t)c0 * p.ldw);
+    const int NB = (p.K + BKS - 1) / BKS;
+#define PO_LOAD_BLOCK(b_, pos_)                                                                                        \
+    {                                                                                                                  \
+        const uint32_t o_ = (b_) < NB ? (uint32_t)(b_) * ROWB : 0u;                                                    \
+        const __amdgpu_buffer_rsrc_t ra_ = __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)p.A + o_), 0, (int)((b_) < NB ? a_bytes - o_ : 0u), 0x00020000); \
+        unsigned char* const d_ = smem + (pos_) * BLOCK;                                                               \
+        _Pragma("unroll") for (int t = 0; t < NS; ++t) {                                                               \
+            const __amdgpu_buffer_rsrc_t rw_ = __builtin_amdgcn_make_buffer_rsrc((void*)(wbase + (int64_t)(32 * t) * ldw2 + o_), 0, (int)((b_) < NB ? w_bytes - o_ : 0u), 0x00020000); \
+            _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                              \
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rw_, (__attribute__((address_space(3))) void*)(d_ + (t * 8 + i) * 1024), 16, vow[i], 0, 0, 0); \
+        }                                                                                                              \
+        _Pragma("unroll") for (int i = 0; i < NA; ++i)                                                                 \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra_, (__attribute__((address_space(3))) void*)(d_ + (NS * 8 + i) * 1024), 16, voa[i], 0, 0, 0); \
+    }
+    static_assert((D - 1) * NL < 64, "what the counter of loads holds");
+    f32x4 acc[NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < D; ++b) PO_LOAD_BLOCK(b, b)
+    const int arow = l15 < 2 * NA ? l15 : 0;               // (a lane without an activation row multiplies row 0 again)
+#define PO_W(ks_, t_) (*(const bf16x8*)(u + (t_) * 8192 + l15 * ROWB + ((((ks_) * 4 + l4) ^ l15) << 4)))
+#define PO_A(ks_) (*(const bf16x8*)(u + NS * 8192 + arow * ROWB + ((((ks_) * 4 + l4) ^ arow) << 4)))
+    int pos = 0, b = 0;
+    for (; b < p.K / BKS; ++b) {
+        PO_WAIT_LOADS((D - 1) * NL);                       // block b has landed
+        const unsigned char* u = smem + pos * BLOCK;
+        bf16x8 wf[8][NS], af[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+#pragma unroll
+            for (int t = 0; t < NS; ++t) wf[ks][t] = PO_W(ks, t);
+            af[ks] = PO_A(ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+            for (int t = 0; t < NS; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][t], af[ks], acc[t], 0, 0, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // (every fragment is in registers: the position is free)
+        PO_LOAD_BLOCK(b + D, pos)
+        pos = pos + 1 == D ? 0 : pos + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (b < NB) {                                          // the last block has fewer than 8 k-steps of K
+        const unsigned char* u = smem + pos * BLOCK;
+        for (int ks = 0; ks < (p.K - b * BKS) >> 5; ++ks)
+#pragma unroll
+            for (int t = 0; t < NS; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(PO_W(ks, t), PO_A(ks), acc[t], 0, 0, 0);
+    }
+#undef PO_A
+#undef PO_W
+#undef PO_LOAD_BLOCK
+
+    // a lane holds token row l15 and features 4 l4 .. + 3 of a strip
+    if (l15 >= p.M) return;
+    const int row = l15, col = c0 + 4 * l4;
+    if (EPI == EPI_SILU_MUL) {
+        const f32x4 &g = acc[0], &up = acc[NS - 1];
+        *(uint2*)(p.dst + (int64_t)row * p.ld + (c0 >> 6) * 32 + (c0 & 63) + 4 * l4) =
+            pack4(silu_f(g[0]) * up[0], silu_f(g[1]) * up[1], silu_f(g[2]) * up[2], silu_f(g[3]) * up[3]);
+    } else if (EPI == EPI_QKV_ROPE) {
+        float a[4], b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = acc[0][e];
+            b[e] = acc[NS - 1][e];
+            if (p.bias) {
+                a[e] += bf2f(p.bias[col + e]);
+                b[e] += bf2f(p.bias[col + 32 + e]);
+            }
+        }
+        if (c0 < p.qd + p.kvd) {
+            const bool is_q = c0 < p.qd;
+            const float qs = is_q ? p.q_scale : 1.0f;
+            const int half = p.hd >> 1, c = is_q ? c0 : c0 - p.qd;
+            const int head = c / p.hd, in = c - head * p.hd;
+            const int i0 = (in >> 6) * 32 + (in & 63) + 4 * l4;               // rotary index of register 0
+            const int64_t pos_ = p.row_pos ? (int64_t)p.row_pos[p.pos0 + row] : p.pos0 + row;
+            bf16_t* drow = (is_q ? p.dst + (int64_t)row * p.qd : p.dst_k + (int64_t)row * p.kvd) + head * p.hd;
+            const float4 cs = *(const float4*)(p.rope_cos + pos_ * half + i0), sn = *(const float4*)(p.rope_sin + pos_ * half + i0);
+            const float cv[4] = {cs.x, cs.y, cs.z, cs.w}, sv[4] = {sn.x, sn.y, sn.z, sn.w};
+            float lo[4], hi[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {                  // (roundings as in tile_epilogue16)
+                lo[e] = fmaf(a[e], cv[e], -(b[e] * sv[e])) * qs;
+                hi[e] = fmaf(a[e], sv[e], b[e] * cv[e]) * qs;
+            }
+            *(uint2*)(drow + i0) = pack4(lo[0], lo[1], lo[2], lo[3]);
+            *(uint2*)(drow + half + i0) = pack4(hi[0], hi[1], hi[2], hi[3]);
+        } else {
+            bf16_t* dcol = p.dst_vt + p.pos0 + row + (int64_t)(col - p.qd - p.kvd) * p.ldv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dcol[(int64_t)e * p.ldv] = f2bf(a[e]);
+                dcol[(int64_t)(e + 32) * p.ldv] = f2bf(b[e]);
+            }
+        }
+    } else {
+        float v[4] = {acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+        const bf16_t* add = EPI == EPI_RESIDUAL ? p.R + (int64_t)row * p.ldr + col : p.bias ? p.bias + col : nullptr;
+        if (add) {
+            const uint2 r = *(const uint2*)add;
+            v[0] += __uint_as_float(r.x << 16); v[1] += __uint_as_float(r.x & 0xffff0000u);
+            v[2] += __uint_as_float(r.y << 16); v[3] += __uint_as_float(r.y & 0xffff0000u);
+        }
+        *(uint2*)(p.dst + (int64_t)row * p.ld + col) = pack4(v[0], v[1], v[2], v[3]);
+    }
+}
+
 // C[row][col .. col+7] = bf16(sum over splits of part[s][row][col ..] + R[row][col ..]); one thread per 8 features.
 __global__ void __launch_bounds__(256) splitk_reduce_residual_kernel(const float* __restrict__ part, int64_t plane,
                                                                      int splits, const bf16_t* R, int64_t ldr,
@@ -516,8 +657,33 @@ void launch_small(GemmParams p, hipStream_t s, int splits) {
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
+// 32 x 128 tiles on at most half the compute units: in strips, also where other tiles would be faster than whole ones of 32
+// rows.  (gate/up of the 8B shape, 224 tiles, streams its weights at 4.9 TB/s as it is, 4.5 in strips: 48 and 52 us.)  In
+// few-rows mode too (one row of the 8B shape, us in K splits / in strips: O projection 14 / 8, down 36 / 24).
+bool takes_strips(const GemmParams& p) {
+    return p.M <= 16 && p.N <= 128 * 128 && p.lda < (1 << 20) && p.ldw < (1 << 20);      // (offsets of 16 rows below 2^26 bytes)
+}
+
+template <int EPI, int NA>
+void launch_strips(const GemmParams& p, hipStream_t s) {
+    constexpr int NS = (EPI == EPI_SILU_MUL || EPI == EPI_QKV_ROPE) ? 2 : 1, D = NS == 2 ? 3 : NA == 1 ? 5 : 4;
+    constexpr int SMEM = D * (16 * NS + 2 * NA) * 512;
+    static_assert(SMEM <= 80 * 1024, "two workgroups on a compute unit at least");
+    static OncePerDevice lds;
+    lds.run(current_device(), [] {
+        allow_dynamic_lds((const void*)(gemm_bf16_strip_kernel<EPI, NA, D>), SMEM);
+    });
+    hipLaunchKernelGGL((gemm_bf16_strip_kernel<EPI, NA, D>), dim3((unsigned)(p.N / (16 * NS))), dim3(64), SMEM, s, p);
+}
+
 template <int EPI>
 void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
+    if (EPI != EPI_PARTIAL && form == 1 && takes_strips(p)) {
+        constexpr int E = EPI == EPI_PARTIAL ? EPI_STORE : EPI;
+        if (p.M <= 2) launch_strips<E, 1>(p, s);
+        else launch_strips<E, 8>(p, s);
+        return;
+    }
     switch (form) {
         case 1: launch_small<EPI, 1, 7>(p, s, splits); break;
         case 2: launch_small<EPI, 2, 6>(p, s, splits); break;
@@ -531,8 +697,10 @@ void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
     }
 }
 
+int whole_form(const GemmParams& p) { return takes_strips(p) ? 1 : pick_form(TILES, p, 1); }
+
 template <int EPI>
-void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(pick_form(TILES, p, 1), p, s); }
+void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(whole_form(p), p, s); }
 
 GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, int64_t M, int N, int K) {
     GemmParams p;
@@ -554,7 +722,7 @@ int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols) {
     GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
-    const TileForm& t = FORMS[pick_form(TILES, p, splits)];
+    const TileForm& t = FORMS[splits == 1 ? whole_form(p) : pick_form(TILES, p, splits)];
     *rows = t.bm;
     *cols = t.bn;
     return splits;
@@ -649,6 +817,7 @@ int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv
     const int N = qd + 2 * kvd;
     if (M <= 0 || !gemm_mfma_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
     GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K);
+    if (takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -668,6 +837,7 @@ int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, 
                                  int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s) {
     if (M <= 0 || !gemm_mfma_supported(N, K)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    if (takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -684,6 +854,7 @@ int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t*
                                      float* part, size_t part_bytes, bool must, hipStream_t s) {
     if (M <= 0 || N <= 0 || !gemm_mfma_supported(N, K) || (N & 7) || (ldc & 7) || (ldr & 7)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    if (!must && takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, must);
     if (splits < 2) return 0;
     p.K = K / splits;

@@ -23,6 +23,9 @@ constexpr SliceWindow slice_window(int s, int n_slices, unsigned tile_bytes, int
 // expression of template parameters, which the host pass would not take as an asm operand)
 #ifdef __HIP_DEVICE_COMPILE__
 #define PO_WAIT_BARRIER(n_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n_) : "memory")
+// the wait alone, for a workgroup of one wavefront
+#define PO_WAIT_LOADS(n_) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n_) : "memory")
 #else
 #define PO_WAIT_BARRIER(n_)
+#define PO_WAIT_LOADS(n_)
 #endif
