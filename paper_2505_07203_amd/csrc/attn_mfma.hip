@@ -405,8 +405,13 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 // does, in fp32: Q is rounded once, as before).  K Q^T then IS the exponent's argument, and no reference exponent is
 // subtracted at all: p = exp2(s) as it comes out of the matrix pipe, no multiply-add per score.  fp32 and bf16 hold
 // 2^-126 .. 2^127, attention scores of ordinary size are within +-40, and a row whose sum of p leaves 2^-60 .. 2^100
-// (scores far above or far below that) gives up and is recomputed by the running-maximum kernel, like an overflow
-// in the other form.
+// (scores far above or far below that) gives up and is recomputed with a running maximum: by the running-maximum kernel, like
+// an overflow in the other form, or, with redo null, by this workgroup in place (see redoes_in_place).
+//
+// QT: query tiles of 32 rows per wavefront.  2 is the form described above; 1 (PRE only) halves the rows of a workgroup, for
+// launches that do not fill the chip (see takes_128_rows).  It reads a fragment per MFMA, which bounds it by LDS (5-12 % more
+// time per row), so fragments are read seven steps ahead instead of three.  Row by row the same MFMAs, roundings and sums in
+// the same order: the same bits.
 //
 // SPLIT (few query rows against many keys): rows q_row0 .. N-1 of ALL query heads of a KV head are the rows of a
 // workgroup, since they share its keys (a 150-row suffix of 4 heads per KV head is 600 rows: 3 workgroups that are
@@ -429,13 +434,16 @@ struct SplitArgs {
     float *opart, *mlpart;        // [piece][row - q_row0][head][HD], [..][2]
     int q_row0, tiles2, n2, n, per;       // n: pieces
 };
-template <bool PRE, int SPLIT>
+template <bool PRE, int SPLIT, int QT>
 __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ vt, int64_t ldv, bf16_t* o, int N,
                                                          int Hq, int Hkv, float sc_log2e, int nqt, int hpx, int* redo,
                                                          const SplitArgs sp) {
     constexpr int HD = 128, KS = 8, HT = 4;
     constexpr bool LATE = PRE || SPLIT != 0;     // the row sums are looked at once, behind the last block
+    constexpr int ROWS = 128 * QT;               // query rows of a workgroup
+    constexpr int FD = QT == 2 ? 3 : 7;          // steps that a fragment is read ahead: about 200 cycles of MFMAs
+    static_assert(QT == 2 || (PRE && !SPLIT), "");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     int qtile, head, kvh, piece = 0, tile0 = 0, piece_tiles = 0;
@@ -473,11 +481,11 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l31 = lane & 31, lhi = lane >> 5;
-    const int qb = qtile * 256;
-    const int qw = qb + wave * 64;
-    const int blk_last = min(N, qb + 256) - 1;
+    const int qb = qtile * ROWS;
+    const int qw = qb + wave * (32 * QT);
+    const int blk_last = min(N, qb + ROWS) - 1;
     const int n_tiles = SPLIT ? piece_tiles : blk_last / 64 + 1;       // 64-key tiles the workgroup streams
-    const int nkb_w = (qw < N) ? (min(N, qw + 64) - 1) / 32 + 1 : 0;   // 32-key blocks this wavefront needs
+    const int nkb_w = (qw < N) ? (min(N, qw + 32 * QT) - 1) / 32 + 1 : 0;   // 32-key blocks this wavefront needs
     // SPLIT: this lane's query rows (position and head), clamped to the last one, and their positions in keys of this piece
     const int n_virtual = SPLIT ? (N - sp.q_row0) * group : 0;
     int vrow[2], vhead[2], vpos[2];
@@ -492,9 +500,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     }
 
     // ---- Q fragments (B operand: lane = query column, 8 consecutive head-dim values)
-    bf16x8 qf[2][KS];
+    bf16x8 qf[QT][KS];
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
+    for (int qt = 0; qt < QT; ++qt) {
         const int qrow = SPLIT ? sp.q_row0 + vrow[qt] : min(qw + qt * 32 + l31, N - 1);
         const bf16_t* qp = q + ((int64_t)qrow * Hq + (SPLIT ? vhead[qt] : head)) * HD + lhi * 8;
 #pragma unroll
@@ -570,11 +578,11 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // the lowest position among this wavefront's rows (rows ascend with the lane and the tile)
     const int pos_min = SPLIT ? __builtin_amdgcn_readfirstlane(vpos[0]) : 0;
 
-    f32x16 oacc[HT][2];
+    f32x16 oacc[HT][QT];
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
     float mb[2], lrow[2] = {0.f, 0.f};      // reference exponents (log2 domain) and row sums per query tile
@@ -616,14 +624,14 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(2, 2, jj);
     asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");      // Q fragments and tile 0 have landed
 
-    f32x16 sa[2], sb[2];
-    bf16x8 pf[2][2], fr[4];
+    f32x16 sa[QT], sb[QT];
+    bf16x8 pf[QT][2], fr[FD + 1];
     {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const bf16x8 kf = *(const bf16x8*)(smem + koff[ks]);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt) {
+            for (int qt = 0; qt < QT; ++qt) {
                 if (ks == 0) {
                     const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                     sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], z, 0, 0, 0);
@@ -632,11 +640,11 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                 }
             }
         }
-        if (31 > (SPLIT ? pos_min : qw)) { PO_MASK(sa, 0, 0); PO_MASK(sa, 0, 1); }
+        if (31 > (SPLIT ? pos_min : qw)) { PO_MASK(sa, 0, 0); if (QT == 2) PO_MASK(sa, 0, QT - 1); }
         float m0 = mtop[0], m1 = mtop[1];
         if (!PRE && attempt == 0) {
             PO_BLOCKMAX(sa, 0, m0);
-            PO_BLOCKMAX(sa, 1, m1);
+            PO_BLOCKMAX(sa, QT - 1, m1);
         }
         if (SPLIT) {                        // (a row all of whose keys so far are masked; its probabilities come out 0)
             m0 = fmaxf(m0, -1.0e30f);
@@ -655,27 +663,39 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // by hand; MFMA-to-MFMA accumulation on the same registers needs no software wait.
 #define PO_MFMA_ACC(ACC, A_, B_) \
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(A_), "v"(B_))
+    // behind a vector instruction that writes an operand there must be two wait states, which the compiler does not know an
+    // MFMA written as an instruction to need: QT 1 has no other MFMA between the last conversion of a P fragment and its use
+#define PO_MFMA_ACC_FRESH(ACC, A_, B_) \
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(A_), "v"(B_))
 #define PO_MFMA_DRAIN() asm volatile("s_nop 15\n\ts_nop 15" ::: "memory")
+    // behind the last block (the empty statements keep every read of an accumulator behind the wait)
+#define PO_MFMA_END()                                                                                                  \
+    {                                                                                                                  \
+        PO_MFMA_DRAIN();                                                                                               \
+        _Pragma("unroll") for (int ht_ = 0; ht_ < HT; ++ht_)                                                           \
+            _Pragma("unroll") for (int qt_ = 0; qt_ < QT; ++qt_) asm volatile("" : "+a"(oacc[ht_][qt_]));              \
+    }
     // One iteration over key block i_: SC holds S(i_), SN receives S(i_+1).  It is a chain of 16 steps,
-    // each one LDS fragment feeding two MFMAs (steps 0..7: K rows of block i_+1 at KST_/KA_; steps 8..15:
-    // V^T of block i_ at VST_/VA_, 16-key half outermost); the fragment of step c+3 is requested right
-    // after the first MFMA of step c, into the register step c-1 has just finished with (steps 13..15
-    // request the first three K fragments of the next iteration, at NKST_/NKA_).
+    // each one LDS fragment feeding QT MFMAs (steps 0..7: K rows of block i_+1 at KST_/KA_; steps 8..15:
+    // V^T of block i_ at VST_/VA_, 16-key half outermost); the fragment of step c + FD is requested right
+    // after the first MFMA of step c, into the register step c-1 has just finished with (the last FD steps
+    // request the first FD K fragments of the next iteration, at NKST_/NKA_).
     //   BAR_: the hand-over barrier sits between the two halves of this iteration.
     //   DMA_T_/DMA_J0_: four global->LDS loads ride on steps 9, 11, 13, 15.
     // The compiler waits for ALL LDS reads in flight before an MFMA written as an instruction (it does
-    // not work out which read feeds it).  Three fragment reads are in flight at the first MFMA of a step
-    // and LDS reads return in order, so an explicit wait for "all but the two youngest" in front of it
+    // not work out which read feeds it).  FD fragment reads are in flight at the first MFMA of a step
+    // and LDS reads return in order, so an explicit wait for "all but the FD - 1 youngest" in front of it
     // is exact, and the compiler, which does account for explicit waits, then adds none.
 #define PO_FRAG_ADDR(c_, KST_, KA_, VST_, VA_, NKST_, NKA_)                                                     \
     ((c_) < 8 ? (KST_) + (KA_) * 8192 + koff[(c_) & 7]                                                          \
               : (c_) < 16 ? (VST_) + (((c_) - 8) & 3) * 4096 + vofs[VA_][((c_) - 8) >> 2]                       \
                           : (NKST_) + (NKA_) * 8192 + koff[(c_) & 7])
-#define PO_WAIT_LGKM2() __builtin_amdgcn_s_waitcnt(0xC27F)     /* lgkmcnt(2), other counters untouched */
+#define PO_WAIT_FRAG() __builtin_amdgcn_s_waitcnt(0xC07F | (FD - 1) << 8)     /* lgkmcnt(FD - 1), other counters untouched */
     // job whose exponentials are issued in MFMA slot s_ (-1: none), and the first of its two values
-#define PO_JOB_AT(s_) ((s_) < 0 ? -1 : (s_) < 8 ? (s_) : (s_) < 16 ? (((s_) & 1) ? -1 : 8 + ((s_) - 8) / 2) \
+#define PO_JOB_AT(s_) (QT == 1 ? ((s_) < 0 || (s_) > 10 ? -1 : (s_) < 7 ? ((s_) & 1 ? -1 : (s_) / 2) : (s_) - 3) \
+                       : (s_) < 0 ? -1 : (s_) < 8 ? (s_) : (s_) < 16 ? (((s_) & 1) ? -1 : 8 + ((s_) - 8) / 2) \
                        : (((s_) < 24 && !((s_) & 1)) ? 12 + ((s_) - 16) / 2 : -1))
-#define PO_JOB_E(n_) ((n_) < 4 ? 2 * (n_) : (n_) < 8 ? 16 + 2 * ((n_) - 4) : (n_) < 12 ? 8 + 2 * ((n_) - 8) : 24 + 2 * ((n_) - 12))
+#define PO_JOB_E(n_) (QT == 1 ? 2 * ((n_) & 7) : (n_) < 4 ? 2 * (n_) : (n_) < 8 ? 16 + 2 * ((n_) - 4) : (n_) < 12 ? 8 + 2 * ((n_) - 8) : 24 + 2 * ((n_) - 12))
 #define PO_EXP_ARG(n_, SC, mb0_, mb1_)                                                             \
     {                                                                                              \
         const int e_ = PO_JOB_E((n_) & 15);                                                        \
@@ -691,36 +711,38 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
             if (c == 8) {                                                                                       \
                 if (MASK_) {                                                                                    \
                     PO_MASK(SN, (i_) + 1, 0);                                                                   \
-                    PO_MASK(SN, (i_) + 1, 1);                                                                   \
+                    if (QT == 2) PO_MASK(SN, (i_) + 1, QT - 1);                                                 \
                 }                                                                                               \
                 if (BAR_) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");                         \
                 __builtin_amdgcn_sched_barrier(0);                                                              \
             }                                                                                                   \
-            PO_WAIT_LGKM2();                                                                                    \
+            PO_WAIT_FRAG();                                                                                        \
             __builtin_amdgcn_sched_barrier(0);                                                                  \
-            _Pragma("unroll") for (int qt = 0; qt < 2; ++qt) {                                                  \
+            _Pragma("unroll") for (int qt = 0; qt < QT; ++qt) {                                                 \
                 if (c < 8) {                                                                                    \
                     if (c == 0) {                                                                               \
                         const f32x16 z_ = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; \
-                        SN[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c & 3], qf[qt][c & 7], z_, 0, 0, 0); \
+                        SN[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c & FD], qf[qt][c & 7], z_, 0, 0, 0); \
                     } else {                                                                                    \
-                        SN[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c & 3], qf[qt][c & 7], SN[qt], 0, 0, 0); \
+                        SN[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c & FD], qf[qt][c & 7], SN[qt], 0, 0, 0); \
                     }                                                                                           \
+                } else if (QT == 1 && (c == 8 || c == 12)) {                                                    \
+                    PO_MFMA_ACC_FRESH(oacc[(c - 8) & 3][qt], fr[c & FD], pf[qt][(c - 8) >> 2]);                 \
                 } else {                                                                                        \
-                    PO_MFMA_ACC(oacc[(c - 8) & 3][qt], fr[c & 3], pf[qt][(c - 8) >> 2]);                        \
+                    PO_MFMA_ACC(oacc[(c - 8) & 3][qt], fr[c & FD], pf[qt][(c - 8) >> 2]);                       \
                 }                                                                                               \
                 __builtin_amdgcn_sched_barrier(0);                                                              \
                 if (qt == 0) {                                                                                  \
-                    fr[(c + 3) & 3] = *(const bf16x8*)PO_FRAG_ADDR(c + 3, KST_, KA_, VST_, VA_, NKST_, NKA_);   \
+                    fr[(c + FD) & FD] = *(const bf16x8*)PO_FRAG_ADDR(c + FD, KST_, KA_, VST_, VA_, NKST_, NKA_); \
                     __builtin_amdgcn_sched_barrier(0);                                                          \
                 }                                                                                               \
                 /* Probabilities of S(i): 16 jobs of two values (one packed conversion each).  The            \
                    exponential is a quarter-rate instruction, so 12 jobs go into the first half (slots 0..7:    \
                    the 16 values the first four V^T steps need; slots 8, 10, 12, 14: query tile 0, registers    \
                    8..15) and 4 (query tile 1, registers 8..15, needed from V^T step 4 on) into slots 16, 18,   \
-                   20, 22.  Each job is spread over three MFMA slots (exponent arguments | exponentials |       \
+                   20, 22 (QT 1: 8 jobs, slots 0, 2, 4, 6 and 7..10).  Each job is spread over three MFMA slots (exponent arguments | exponentials |       \
                    conversion) so that no instruction waits for the one issued just before it. */               \
-                const int slot_ = 2 * c + qt;                    /* 0..31 over the iteration */                 \
+                const int slot_ = QT * c + qt;                   /* 0..31 (0..15) over the iteration */         \
                 {                                                                                               \
                     const int na_ = PO_JOB_AT(slot_ + 1), nb_ = PO_JOB_AT(slot_), nc_ = PO_JOB_AT(slot_ - 1);   \
                     if (!PRE && slot_ == 0) { PO_EXP_ARG(0, SC, mb0_, mb1_); }                                  \
@@ -742,9 +764,9 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                     }                                                                                           \
                 }                                                                                               \
                 if (c >= 8) {                                                                                   \
-                    const int c_ = (c - 8) * 2 + qt;             /* 0..15 */                                    \
-                    if (!SPLIT && (c_ == 8 || c_ == 9)) {                                                       \
-                        const int sq_ = c_ - 8;                                                                 \
+                    const int c_ = (c - 8) * QT + qt;            /* 0..15 (0..7) */                             \
+                    if (!SPLIT && (QT == 2 ? c_ == 8 || c_ == 9 : c_ == 5)) {                                   \
+                        const int sq_ = QT == 2 ? c_ - 8 : 0;                                                   \
                         /* four independent chains: a dependent dot product waits about 6 cycles.  PRE: the     \
                            four partial sums live across blocks (nothing looks at the row sum before the end) */\
                         float l_[4] = {lrow[sq_], 0.f, 0.f, 0.f};                                               \
@@ -756,7 +778,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                         }                                                                                       \
                         if (!PRE) lrow[sq_] = (l_[0] + l_[1]) + (l_[2] + l_[3]);                                \
                     }                                                                                           \
-                    if ((c_ & 3) == 3) { PO_DMA(DMA_T_, DMA_S_, (DMA_J0_) + (c_ >> 2)); }                       \
+                    if ((c_ & (2 * QT - 1)) == 2 * QT - 1) { PO_DMA(DMA_T_, DMA_S_, (DMA_J0_) + c_ / (2 * QT)); } \
                 }                                                                                               \
                 __builtin_amdgcn_sched_barrier(0);                                                              \
             }                                                                                                   \
@@ -775,7 +797,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
             lrow[0] *= a0_;                                                                                     \
             lrow[1] *= a1_;                                                                                     \
             _Pragma("unroll") for (int ht = 0; ht < HT; ++ht)                                                   \
-            _Pragma("unroll") for (int r = 0; r < 16; ++r) { oacc[ht][0][r] *= a0_; oacc[ht][1][r] *= a1_; }    \
+            _Pragma("unroll") for (int r = 0; r < 16; ++r) { oacc[ht][0][r] *= a0_; oacc[ht][QT - 1][r] *= a1_; }    \
         }                                                                                                       \
     }
 
@@ -801,9 +823,8 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
     // last pair with work.  SPLIT: pairs j with 64 j + 95 <= pos_min touch no masked key, all others take both masks
     const int j_free = pos_min < 95 ? 0 : min((pos_min - 95) / 64 + 1, n_tiles);
     const int j_last = SPLIT ? j_free + 1 : (nkb_w > 0) ? wt : -1;
-    fr[0] = *(const bf16x8*)(smem + 8192 + koff[0]);      // K fragments 0, 1, 2 of block 1
-    fr[1] = *(const bf16x8*)(smem + 8192 + koff[1]);
-    fr[2] = *(const bf16x8*)(smem + 8192 + koff[2]);
+#pragma unroll
+    for (int c = 0; c < FD; ++c) fr[c] = *(const bf16x8*)(smem + 8192 + koff[c]);      // the first K fragments of block 1
     int j = 0;
     for (; j + 4 <= j_last - 1; j += 4) {
         PO_PAIR(0, 0, 0);
@@ -827,7 +848,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(j + 3, (j + 3) & 3, jj);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    PO_MFMA_DRAIN();
+    PO_MFMA_END();
     if (!SPLIT) break;
     lrow[0] = (lsum[0][0] + lsum[0][1]) + (lsum[0][2] + lsum[0][3]);
     lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
@@ -837,7 +858,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(oacc[ht][qt][r]) & 0x7fffffffu);
     if (__any(top >= 0x7b000000u || !(lrow[0] < 0x1p100f) || !(lrow[1] < 0x1p100f)) && lane == 0) *(volatile int*)lds_gave_up = 1;
@@ -857,7 +878,7 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
             for (int ks = 0; ks < KS; ++ks) {
                 const bf16x8 kf = *(const bf16x8*)(smem + (t & 1) * A64_TILE + b * 8192 + koff[ks]);
 #pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
+                for (int qt = 0; qt < QT; ++qt) {
                     if (ks == 0) {
                         const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                         sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], z, 0, 0, 0);
@@ -867,10 +888,10 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
                 }
             }
             PO_MASK(sa, 2 * t + b, 0);
-            PO_MASK(sa, 2 * t + b, 1);
+            PO_MASK(sa, 2 * t + b, QT - 1);
             float m0, m1;
             PO_BLOCKMAX(sa, 0, m0);
-            PO_BLOCKMAX(sa, 1, m1);
+            PO_BLOCKMAX(sa, QT - 1, m1);
             mtop[0] = fmaxf(mtop[0], m0);
             mtop[1] = fmaxf(mtop[1], m1);
         }
@@ -879,28 +900,15 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) lsum[0][e] = lsum[1][e] = 0.f;
     }   // attempt
-#undef PO_PAIR
-#undef PO_FRAG_ADDR
-#undef PO_WAIT_LGKM2
-#undef PO_ITER
-#undef PO_JOB_AT
-#undef PO_JOB_E
-#undef PO_EXP_ARG
-#undef PO_DMA
-#undef PO_MASK
-#undef PO_BLOCKMAX
-#undef PO_MFMA_ACC
-#undef PO_MFMA_DRAIN
-
     if (SPLIT) {
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
+        for (int qt = 0; qt < QT; ++qt) {
             const float ltot = half_swap_sum(lrow[qt]);
             if (qw + qt * 32 + l31 >= n_virtual) continue;
             const int64_t slot = ((int64_t)piece * (N - sp.q_row0) + vrow[qt]) * Hq + vhead[qt];
@@ -922,20 +930,94 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
         // a row sum of 2^100 or more (or infinite) means probabilities near or past the top of the float range; one
         // below 2^-60 that the row's scores sit so far below zero that terms were flushed away
-        const float t0 = half_swap_sum(lrow[0]), t1 = half_swap_sum(lrow[1]);
+        const float t0 = half_swap_sum(lrow[0]), t1 = half_swap_sum(lrow[QT - 1]);
         if (nkb_w > 0 && __any(!(t0 >= 0x1p-60f) || !(t0 < 0x1p100f) || !(t1 >= 0x1p-60f) || !(t1 < 0x1p100f))) gave_up = 1;
     }
     // ---- did any wavefront give up?  (every wavefront has met the same number of barriers and arrives here)
     if (gave_up && lane == 0) *(volatile int*)lds_gave_up = 1;
     __syncthreads();
     if (*(volatile int*)lds_gave_up) {
-        if (tid == 0) redo[qtile * Hq + head] = 1;
-        return;
+        if (!PRE || redo) {
+            if (tid == 0) redo[qtile * Hq + head] = 1;
+            return;
+        }
+        // Once more with a running maximum, tile by tile, one in flight: total on finite inputs.  (Rare, so short code instead
+        // of a pipeline, but in one pass: with the exact maxima from a pass over K first it took a third longer.)
+        float m[2] = {-1.0e30f, -1.0e30f};
+        lrow[0] = lrow[1] = 0.f;
+#pragma unroll
+        for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
+        _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(0, 0, jj);
+        for (int t = 0; t < n_tiles; ++t) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is there, the other stage free
+            if (t + 1 < n_tiles) {
+                _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(t + 1, (t + 1) & 1, jj);
+            }
+            const unsigned char* st = smem + (t & 1) * A64_TILE;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                f32x16 S[QT];
+                bf16x8 pr[QT][2];
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) S[qt][r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 kf = *(const bf16x8*)(st + b * 8192 + koff[ks]);
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt) S[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], S[qt], 0, 0, 0);
+                }
+                if (t * 64 + b * 32 + 31 > qw) {
+                    PO_MASK(S, 2 * t + b, 0);
+                    if (QT == 2) PO_MASK(S, 2 * t + b, QT - 1);
+                }
+                float n[2];
+                PO_BLOCKMAX(S, 0, n[0]);
+                PO_BLOCKMAX(S, QT - 1, n[1]);
+                n[0] = fmaxf(n[0], m[0]);
+                n[1] = fmaxf(n[1], m[1]);
+                if (__any(n[0] > m[0] || n[1] > m[1])) {
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt) {
+                        const float a = __builtin_amdgcn_exp2f(m[qt] - n[qt]);
+                        lrow[qt] *= a;
+#pragma unroll
+                        for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) oacc[ht][qt][r] *= a;
+                    }
+                    m[0] = n[0];
+                    m[1] = n[1];
+                }
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float e = __builtin_amdgcn_exp2f(S[qt][r] - m[qt]);
+                        lrow[qt] += e;
+                        pr[qt][r >> 3][r & 7] = (__bf16)e;
+                    }
+#pragma unroll
+                for (int j2 = 0; j2 < 2; ++j2)
+#pragma unroll
+                    for (int ht = 0; ht < HT; ++ht) {
+                        const bf16x8 vf = *(const bf16x8*)(st + ht * 4096 + vofs[b][j2]);
+#pragma unroll
+                        for (int qt = 0; qt < QT; ++qt) PO_MFMA_ACC_FRESH(oacc[ht][qt], vf, pr[qt][j2]);
+                    }
+                PO_MFMA_END();
+            }
+        }
     }
 
     // ---- normalise and store: lane = query row, registers = head-dim rows
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
+    for (int qt = 0; qt < QT; ++qt) {
         const float inv = 1.0f / half_swap_sum(lrow[qt]);
         const int qrow = qw + qt * 32 + l31;
         if (qrow < N) {
@@ -952,6 +1034,21 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         }
     }
 }
+
+#undef PO_PAIR
+#undef PO_FRAG_ADDR
+#undef PO_WAIT_FRAG
+#undef PO_ITER
+#undef PO_JOB_AT
+#undef PO_JOB_E
+#undef PO_EXP_ARG
+#undef PO_DMA
+#undef PO_MASK
+#undef PO_BLOCKMAX
+#undef PO_MFMA_ACC
+#undef PO_MFMA_ACC_FRESH
+#undef PO_MFMA_DRAIN
+#undef PO_MFMA_END
 
 // o[row][head][:] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^((m_s - max m) sc_log2e); one thread per 4 values.
 template <int HD>
@@ -998,27 +1095,48 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
     *(uint2*)(o + (row * Hq + head) * HD + f) = w2;
 }
 
+// Workgroups of 256 rows and of 128 rows (QT 1): a launch of one round is as long as its longest tile, which half the rows halve;
+// with more, the 256-row form does the same in 5-12 % less time.  Measured, prescaled queries, 32 heads on 8, whole call
+// before / now (us, the redo launch gone as well): 300 rows 21 / 12, 700 rows 27 / 16, 1500 rows 44 / 30, 1931 rows 51 / 41; 128-row
+// tiles at 2500 rows (320 workgroups) would take as long as 256-row ones, at 8000 rows 10 % longer.
+bool takes_128_rows(int64_t n_tiles256, int Hq) { return n_tiles256 * Hq <= 256; }
+
+// The tiles that gave up are recomputed by a second launch, or in place by the workgroup that gave up.  In place spares every
+// call the second launch (4 us: 5-7 % at 2300 rows), but takes up to a third longer when tiles do give up in numbers, since a
+// workgroup has one wavefront per SIMD for it and the other kernel two: so up to two rounds of workgroups.
+bool redoes_in_place(int64_t n_tiles256, int Hq) { return n_tiles256 * Hq <= 512; }
+
 void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o, int64_t N, int Hq,
                   int Hkv, int64_t q_row0, int* redo, bool q_prescaled, hipStream_t s) {
     constexpr int SMEM = 2 * A64_NSTAGE * A64_TILE + 16;             // the ring and the give-up word
     constexpr int SMEM_REDO = 2 * 2 * BNK * 128 * 2;
     static OncePerDevice lds;
     lds.run(current_device(), [] {
-        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 0>), SMEM);
-        allow_dynamic_lds((const void*)(attn_fwd64_kernel<true, 0>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 0, 2>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<true, 0, 2>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<true, 0, 1>), SMEM);
         allow_dynamic_lds((const void*)(attn_fwd_kernel<128, 1, 8, false>), SMEM_REDO);
     });
     const int nqt = (int)((N + 255) / 256);
     const int hpx = (Hq % 8 == 0) ? Hq / 8 : 0;
     const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(128);
     // workgroups enumerate query tiles from the last one down: fewer of them = only the last tiles
-    const int nsel = nqt - (int)((q_row0 > 0 && q_row0 < N) ? q_row0 / 256 : 0);
+    const int64_t first = (q_row0 > 0 && q_row0 < N) ? q_row0 : 0;
+    const int nsel = nqt - (int)(first / 256);
+    if (q_prescaled && takes_128_rows(nsel, Hq)) {
+        const int nqt128 = (int)((N + 127) / 128);
+        hipLaunchKernelGGL((attn_fwd64_kernel<true, 0, 1>), dim3((unsigned)((nqt128 - (int)(first / 128)) * Hq)), dim3(256), SMEM, s,
+                           q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt128, hpx, nullptr, SplitArgs{});
+        return;
+    }
+    const bool in_place = q_prescaled && redoes_in_place(nsel, Hq);
     if (q_prescaled)
-        hipLaunchKernelGGL((attn_fwd64_kernel<true, 0>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
-                           Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
+        hipLaunchKernelGGL((attn_fwd64_kernel<true, 0, 2>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+                           Hq, Hkv, sc_log2e, nqt, hpx, in_place ? nullptr : redo, SplitArgs{});
     else
-        hipLaunchKernelGGL((attn_fwd64_kernel<false, 0>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 0, 2>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
                            Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
+    if (in_place) return;
     // the (query tile, head) pairs given up above, by the running-maximum kernel with the same 256-row tiles
     // (8 wavefronts x 32 rows); item b = query tile * Hq + head
     hipLaunchKernelGGL((attn_fwd_kernel<128, 1, 8, false>), dim3((unsigned)std::min(nqt * Hq, 256)), dim3(512), SMEM_REDO, s, q, k, vt, ldv,
@@ -1110,8 +1228,8 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     if (!launch) return sp.n;
     static OncePerDevice lds;
     lds.run(current_device(), [] {
-        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 1>), SMEM);
-        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 2>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 1, 2>), SMEM);
+        allow_dynamic_lds((const void*)(attn_fwd64_kernel<false, 2, 2>), SMEM);
     });
     sp.k2 = k2; sp.vt2 = vt2; sp.ldv2 = ldv2;
     sp.q_row0 = (int)q_row0;
@@ -1121,10 +1239,10 @@ int launch_split_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64
     const dim3 grid((unsigned)(Hkv * sp.n * nqt));
     const float sc_log2e = q_prescaled ? 1.0f : attention_q_scale(128);
     if (span)
-        hipLaunchKernelGGL((attn_fwd64_kernel<false, 2>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 2, 2>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
                            nqt, 0, nullptr, sp);
     else
-        hipLaunchKernelGGL((attn_fwd64_kernel<false, 1>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
+        hipLaunchKernelGGL((attn_fwd64_kernel<false, 1, 2>), grid, dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e,
                            nqt, 0, nullptr, sp);
     const int64_t n = nq * Hq * 32;
     // (a piece's reference exponents are in log2 units)
@@ -1155,6 +1273,10 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
         return launch_split_t<64>(q, k, vt, ldv, o, N, Hq, Hkv, q_row0, scratch, scratch_bytes, launch, k2, vt2, ldv2, n2,
                                   q_prescaled, s);
     return 0;
+}
+
+bool attention_mfma_uses_redo(int64_t N, int Hq, int hd, bool q_prescaled) {
+    return hd == 128 && !(q_prescaled && redoes_in_place((N + 255) / 256, Hq));
 }
 
 size_t attention_mfma_redo_bytes(int64_t N, int Hq) { return (size_t)((N + 255) / 256) * (size_t)Hq * sizeof(int); }

@@ -327,12 +327,11 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
         PO_HIP(hipMemcpyAsync(d_tok, row_pos.data(), (size_t)total * 4, hipMemcpyHostToDevice, s));
         d_row_pos = d_tok;
     }
-    // the last key tile of the attention reads V^T up to the next multiple of 64 positions
-    if (dt == PO_BF16) launch_vt_pad_zero((bf16_t*)(ws + L.Vt), kvd, L.ldv, total, s);
-    // the attention's give-up words start every request at zero (its second launch leaves them so)
+    // the last key tile of the attention reads V^T up to the next multiple of 64 positions; its give-up words start every
+    // request at zero (its second launch leaves them so)
     int* attn_redo = (int*)(ws + L.attn_redo);
-    if (dt == PO_BF16) launch_fill_zero32(attn_redo, attention_mfma_redo_bytes(c->max_len, m.n_q_heads) / 4, s);
-
+    if (dt == PO_BF16)
+        launch_vt_pad_zero((bf16_t*)(ws + L.Vt), kvd, L.ldv, total, attn_redo, attention_mfma_redo_bytes(c->max_len, m.n_q_heads) / 4, s);
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerOff& o = L.layers[l];
         const unsigned char* wqkv = c->w + o.wqkv;
@@ -1375,7 +1374,8 @@ po_status po_op_attention(int32_t dtype, const void* q, const void* k, const voi
         const int64_t ldv = round_up64(N, 64);
         // scratch: V^T, then (256-byte aligned) the give-up words of the attention kernel
         int* redo = (int*)((unsigned char*)scratch + align_up((size_t)Hkv * hd * (size_t)ldv * 2));
-        launch_fill_zero32(redo, attention_mfma_redo_bytes(N, Hq) / 4, (hipStream_t)stream);
+        if (attention_mfma_uses_redo(N, Hq, hd, q_prescaled != 0))
+            launch_fill_zero32(redo, attention_mfma_redo_bytes(N, Hq) / 4, (hipStream_t)stream);
         launch_v_transpose((const bf16_t*)v, (bf16_t*)scratch, N, Hkv * hd, ldv, (hipStream_t)stream);
         launch_attention_mfma((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)scratch, ldv, (bf16_t*)o, N, Hq, Hkv,
                               hd, 0, redo, q_prescaled != 0, (hipStream_t)stream);
