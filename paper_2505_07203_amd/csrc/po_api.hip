@@ -370,6 +370,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                 PO_HIP(hipMemcpyAsync(V, kc_l + c->kv_v_off, (size_t)p_reuse * kvd * esz, hipMemcpyDeviceToDevice, s));
             }
         }
+        bool f32_rotated = false;           // float32 path: the projection rotated Q and K already
         for (int64_t c0 = p_reuse; c0 < total; c0 += Cq) {
             const int64_t rows = (total - c0 < Cq) ? total - c0 : Cq;
             unsigned char* Xn = Xq;     // (shadows the MLP-phase buffer inside this loop)
@@ -408,6 +409,12 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                     launch_gemm_qkv_rope((const bf16_t*)Xn, d, (const bf16_t*)wqkv, d, (const bf16_t*)bqkv,
                                          (bf16_t*)(Q + (size_t)c0 * qd * esz), (bf16_t*)(K + (size_t)c0 * kvd * esz),
                                          (bf16_t*)(ws + L.Vt), L.ldv, rc, rs, c0, d_row_pos, rows, qd, kvd, hd, d, q_scale, s);
+            } else if (launch_gemm_f32_qkv_rope((const float*)Xn, d, (const float*)wqkv, d, (const float*)bqkv, rows, d,
+                                                F32QkvRope{(float*)(Q + (size_t)c0 * qd * esz), (float*)(K + (size_t)c0 * kvd * esz),
+                                                           (float*)(V + (size_t)c0 * kvd * esz), rc, rs, c0, d_row_pos, qd, kvd, hd},
+                                                s)) {
+                f32_rotated = true;
+                if (sr) launch_round_bf16_f32((float*)(V + (size_t)c0 * kvd * esz), rows * kvd, s);
             } else {
                 launch_gemm_basic(dt, Xn, d, wqkv, d, Q + (size_t)c0 * qd * esz, qd, bqkv, nullptr, 0, rows, qd, d, s);
                 launch_gemm_basic(dt, Xn, d, wqkv + (size_t)qd * d * esz, d, K + (size_t)c0 * kvd * esz, kvd,
@@ -422,8 +429,10 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
             for (const Seg& g : segs) {
                 const int64_t r0 = g.start + p_reuse, nr = g.len - p_reuse;
                 const size_t t0 = (size_t)p_reuse * (hd / 2);
-                launch_rope(dt, Q + (size_t)r0 * qd * esz, qd, rc + t0, rs + t0, nr, m.n_q_heads, hd, s);
-                launch_rope(dt, K + (size_t)r0 * kvd * esz, kvd, rc + t0, rs + t0, nr, m.n_kv_heads, hd, s);
+                if (!f32_rotated) {
+                    launch_rope(dt, Q + (size_t)r0 * qd * esz, qd, rc + t0, rs + t0, nr, m.n_q_heads, hd, s);
+                    launch_rope(dt, K + (size_t)r0 * kvd * esz, kvd, rc + t0, rs + t0, nr, m.n_kv_heads, hd, s);
+                }
                 if (sr) {
                     launch_round_bf16_f32((float*)(Q + (size_t)r0 * qd * esz), nr * qd, s);
                     launch_round_bf16_f32((float*)(K + (size_t)r0 * kvd * esz), nr * kvd, s);
@@ -595,8 +604,10 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                 if (sr) launch_round_bf16_f32((float*)Xn, rows * d, s);
                 {
                     PhaseTimer pt(c, PO_K_GATE_UP);
-                    launch_gemm_basic(dt, Xn, d, c->w + o.wgu, d, GU, 2 * F, nullptr, nullptr, 0, rows, 2 * F, d, s);
-                    launch_silu_mul(dt, GU, H, rows, F, s);
+                    if (!launch_gemm_f32_silu((const float*)Xn, d, (const float*)(c->w + o.wgu), d, (float*)H, F, rows, F, d, s)) {
+                        launch_gemm_basic(dt, Xn, d, c->w + o.wgu, d, GU, 2 * F, nullptr, nullptr, 0, rows, 2 * F, d, s);
+                        launch_silu_mul(dt, GU, H, rows, F, s);
+                    }
                     if (sr) launch_round_bf16_f32((float*)H, rows * F, s);
                 }
                 PhaseTimer pt(c, PO_K_RESIDUAL);
@@ -1346,6 +1357,10 @@ po_status po_op_gate_up_silu(int32_t dtype, const void* a, const void* wgu, void
                          2 * F, K, (hipStream_t)stream);
     } else {
         if (!scratch) return PO_ERR_INVALID_ARG;
+        if (launch_gemm_f32_silu((const float*)a, K, (const float*)wgu, K, (float*)h, F, M, F, K, (hipStream_t)stream)) {
+            PO_HIP(hipGetLastError());
+            return PO_OK;
+        }
         launch_gemm_basic(dtype, a, K, wgu, K, scratch, 2 * F, nullptr, nullptr, 0, M, 2 * F, K, (hipStream_t)stream);
         launch_silu_mul(dtype, scratch, h, M, F, (hipStream_t)stream);
     }

@@ -116,6 +116,19 @@ void launch_fill_zero32(void* dst, size_t n_words, hipStream_t s);
 void launch_round_bf16_f32(float* x, int64_t n, hipStream_t s);
 // float32 GEMM on the float32 matrix instruction; false (nothing launched) when K, the leading dimensions or the
 // pointers do not allow 16-byte loads
+// destinations and rotary table (cos / sin [positions, hd / 2]) of launch_gemm_f32_qkv_rope; row m of a launch is buffer row
+// pos0 + m: its position, or row_pos[pos0 + m] of it where requests are packed; q, k, v point at the launch's first row
+struct F32QkvRope {
+    float *q, *k, *v;
+    const float *cos_t, *sin_t;
+    int64_t pos0;
+    const int32_t* row_pos;
+    int qd, kvd, hd;
+};
+bool launch_gemm_f32_qkv_rope(const float* A, int64_t lda, const float* W, int64_t ldw, const float* bias, int64_t M, int K,
+                              const F32QkvRope& qkv, hipStream_t s);
+bool launch_gemm_f32_silu(const float* A, int64_t lda, const float* W, int64_t ldw, float* H, int64_t ldh, int64_t M, int F, int K,
+                          hipStream_t s);
 bool launch_gemm_f32_mfma(const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc, const float* bias,
                           const float* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s);
 // float32 attention on the float32 matrix instruction; false (nothing launched) when hd is neither 64 nor 128

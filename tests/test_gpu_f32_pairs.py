@@ -1,0 +1,42 @@
+"""Float32 projections that finish their pairs themselves: gate/up with the SiLU-multiply, QKV with bias and rotation, in every
+tile (32, 64, 128 columns) and with columns that end inside one."""
+import numpy as np
+import pytest
+
+import helpers as H
+from paper_2505_07203_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# F: less than half a tile, ends inside half a tile, whole ones; the last sizes take tiles of 64 and of 128
+@pytest.mark.parametrize("M,F,K", [(1, 4, 64), (33, 36, 104), (257, 688, 256), (70, 88, 72), (500, 2052, 128), (1500, 6148, 96)])
+def test_gate_up_against_float64(M, F, K):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(M + F)
+    a, wg, wu = (torch.randn(*s, generator=g, device="cuda") * 0.3 for s in ((M, K), (F, K), (F, K)))
+    h = B.po_op_gate_up_silu(a, B.po_op_pack_gate_up(wg, wu)).double()
+    x, y = a.double() @ wg.double().t(), a.double() @ wu.double().t()
+    ref = x * torch.sigmoid(x) * y
+    # K sequential float32 additions each; d(silu)/dx is at most 1.1, silu(x) at most |x|; a few roundings of the result
+    ex, ey = (K * 2.0 ** -24 * (a.double().abs() @ w.double().abs().t()) for w in (wg, wu))
+    assert bool(((h - ref).abs() <= 1.1 * ex * (y.abs() + ey) + x.abs() * ey + 2.0 ** -20 * ref.abs() + 1e-12).all())
+
+
+@pytest.mark.parametrize("hd,hq,hkv,d,n", [(64, 4, 2, 256, 150), (128, 3, 1, 256, 100), (64, 3, 3, 192, 1), (128, 8, 2, 512, 700)])
+def test_whole_path_with_bias_against_oracle(hd, hq, hkv, d, n):
+    from paper_2505_07203_amd import binding as B
+    cfg = I.ModelConfig(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, ffn_dim=344, vocab_size=512,
+                        rms_eps=1e-5, rope_theta=10000.0, dtype=I.F32, qkv_bias=1)
+    tokens = I.make_tokens(cfg, 7, n)
+    z_ref, _ = H.oracle_prefill(cfg, 1001, tokens, cand=I.label_ids(cfg))
+    ctx = B.Context(cfg, 2 * n + 70, 64, device="cuda:0")
+    try:
+        ctx.load_synthetic(1001, threads=2)
+        z, _ = ctx.po_prefill(tokens, I.label_ids(cfg))
+        assert np.max(np.abs(z - z_ref)) <= 1e-4
+        packed = ctx.po_prefill_packed([tokens, tokens], I.label_ids(cfg), want_logits=True)[0]
+        assert np.array_equal(packed[0], z) and np.array_equal(packed[1], z)
+    finally:
+        ctx.po_destroy()
