@@ -219,12 +219,14 @@ __global__ void __launch_bounds__(NTHREADS) gemm_fp8_mfma_kernel(const GemmParam
 // on 16x16x128 MFMAs was up to 1.6 x slower: half as much work per fragment read.)  k-steps of 64 in order, as above: the
 // same bits.  Measured: down projection (N 4096, K 14336) 471 rows 143 -> 47 us, 2048 rows (256-row tiles) 143 -> 99,
 // 2.4 PFLOP/s.
-template <int EPI, int MR, int D>
+template <int EPI, int MR, int D, bool TURNS>
 __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int BM_ = 64 * MR, BN_ = 128;
     constexpr int AU = BM_ * BKB, WU = BN_ * BKB;          // bytes of a slice of A / W
     constexpr int NA = 2 * MR, NW = 4;                     // global->LDS loads per wavefront and slice
+    constexpr int AHEAD = D + 4;                           // how far ahead of the multiplied slice weights are touched
+    static_assert(AHEAD - D >= D - 2, "the hand-over's count of younger loads holds from the first slice on");
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
@@ -296,6 +298,18 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
         for (int h2 = 0; h2 < 2; ++h2) fo[kk][h2] = l31 * 128 + (((kk * 4 + lhi * 2 + h2) ^ ((l31 >> 1) & 7)) << 4);
 #define PO_FRAG(tile_, kk_)                                                                                           \
     __builtin_shufflevector(*(const i32x4*)((tile_) + fo[kk_][0]), *(const i32x4*)((tile_) + fo[kk_][1]), 0, 1, 2, 3, 4, 5, 6, 7)
+    // (turns: as in the bf16 small kernel)
+    unsigned char* const touched = smem + D * (AU + WU) + wave * 256;
+    const uint32_t vot = (uint32_t)(wave * 32 + (lane & 31)) * (uint32_t)p.ldw + (lane >> 5) * BKB;
+    int turn = gm_this > 1 ? (tm - g * GM) * 2 : 1 << 30;
+#define PO_TOUCH(s_)                                                                                                   \
+    if (TURNS) {                                                                                                       \
+        const SliceWindow wt_ = slice_window((s_) + 1, KT, (unsigned)w_bytes, BKB);                                    \
+        const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)(turn == 0 ? wt_.bytes : 0), 0x00020000); \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot,         \
+                                                 wt_.bytes ? wt_.offset - BKB : 0, 0, 0);                              \
+        turn = turn == 0 ? 2 * gm_this - 1 : turn - 1;                                                                 \
+    }
     const int a_base = wm * (MR * 32) * 128, w_base = AU + wn * 64 * 128;
 
     f32x16 acc[MR][2];
@@ -314,6 +328,8 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
         for (int i = 0; i < NW; ++i) PO_DMA_W(s, i)
     }
     PO_WAIT_BARRIER((D - 1) * (NA + NW));                      // slice 0 has landed
+#pragma unroll 1
+    for (int s = D; s < AHEAD; ++s) { PO_TOUCH(s) }
     i32x8 A0[2][MR], W0[2][2], A1[2][MR], W1[2][2];            // fragments of a whole slice: [k-step][tile]
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
@@ -326,9 +342,10 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     // s + D into the position of slice s, whose fragments every wavefront holds in registers by the barrier in front
 #define PO_SLICE(AC, WC, AN, WN)                                                                                     \
     {                                                                                                                 \
-        PO_WAIT_BARRIER((D - 2) * (NA + NW));      /* slice s+1 has landed; all LDS reads of slice s are done */      \
+        PO_WAIT_BARRIER((D - 2) * (NA + NW + (TURNS ? 1 : 0)));  /* slice s+1 has landed; all LDS reads of slice s are done */ \
         const int ps1 = ps + 1 >= D ? 0 : ps + 1;                                                                     \
         PO_SLICE_RSRC(s + D)                                                                                          \
+        PO_TOUCH(s + AHEAD)                                                                                           \
         const unsigned char* u1 = smem + ps1 * (AU + WU);                                                             \
         _Pragma("unroll") for (int m = 0; m < 4 * MR; ++m) {                                                          \
             const int kk_ = m / (2 * MR), mi_ = (m >> 1) % MR, ni_ = m & 1;                                           \
@@ -358,6 +375,7 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     }
     if (s < KT) PO_SLICE(A0, W0, A1, W1)
 #undef PO_SLICE
+#undef PO_TOUCH
 #undef PO_FRAG
 #undef PO_DMA_A
 #undef PO_DMA_W
@@ -398,27 +416,41 @@ void launch_256(const GemmParams& p, hipStream_t s, int splits) {
     hipLaunchKernelGGL(gemm_fp8_mfma_kernel<EPI>, dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(NTHREADS), SMEM_BYTES, s, p);
 }
 
-template <int EPI, int MR, int D>
-void launch_small(GemmParams p, hipStream_t s, int splits) {
-    constexpr int SMEM = D * (64 * MR + 128) * BKB;
+template <int EPI, int MR, int D, bool TURNS>
+void launch_small_t(const GemmParams& p, hipStream_t s, int splits) {
+    constexpr int SMEM = D * (64 * MR + 128) * BKB + (TURNS ? 1024 : 0);       // the ring; where touches go
     static_assert(SMEM <= 160 * 1024 && SMEM >= 4 * 8192, "LDS of a compute unit; staging of four wavefronts");
     static OncePerDevice lds;
     lds.run(current_device(), [] {
-        allow_dynamic_lds((const void*)(gemm_fp8_small_kernel<EPI, MR, D>), SMEM);
+        allow_dynamic_lds((const void*)(gemm_fp8_small_kernel<EPI, MR, D, TURNS>), SMEM);
     });
+    const int per_xcd = (p.mt * p.nt + 7) / 8;
+    hipLaunchKernelGGL((gemm_fp8_small_kernel<EPI, MR, D, TURNS>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(256), SMEM,
+                       s, p);
+}
+
+// DT: ring depth with turns (a ring that fills the LDS leaves no room for where touches go)
+template <int EPI, int MR, int D, int DT>
+void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 64 * MR - 1) / (64 * MR);
     p.nt = (p.N + 127) / 128;
-    const int per_xcd = (p.mt * p.nt + 7) / 8;
-    hipLaunchKernelGGL((gemm_fp8_small_kernel<EPI, MR, D>), dim3((unsigned)(per_xcd * 8), (unsigned)splits), dim3(256), SMEM, s, p);
+    // Turns (see the bf16 small kernel; us without / with, 70 .. 2000 rows): 64 rows per tile from five row tiles on (down
+    // projection of the 8B shape, 471 rows 49 / 44; two tiles 45 / 54), 128 rows with four, the last nearly half full (600 rows 66 /
+    // 57; O projection of the 32B shape 33 / 28; last tile 3 % full 56 / 59).  192 rows gain or lose by the size (1100 rows 78 /
+    // 72, 1500 rows 87 / 94), 256 rows lose 3-8 %, and K 27648 loses 4-8 % in every tile.
+    const int last = p.M - (p.mt - 1) * 64 * MR;                       // rows of the last row tile
+    const bool turns = p.K <= 16384 && (MR == 1 ? p.mt >= 5 : MR == 2 && p.mt >= 4 && 9 * last >= 4 * 128);
+    if (MR <= 2 && turns) launch_small_t<EPI, MR, MR <= 2 ? DT : D, MR <= 2>(p, s, splits);
+    else launch_small_t<EPI, MR, D, false>(p, s, splits);
 }
 
 template <int EPI>
 void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
     switch (form) {
-        case 1: launch_small<EPI, 1, 6>(p, s, splits); break;
-        case 2: launch_small<EPI, 2, 5>(p, s, splits); break;
-        case 3: launch_small<EPI, 3, 4>(p, s, splits); break;
-        case 4: launch_small<EPI, 4, 3>(p, s, splits); break;
+        case 1: launch_small<EPI, 1, 6, 6>(p, s, splits); break;
+        case 2: launch_small<EPI, 2, 5, 4>(p, s, splits); break;
+        case 3: launch_small<EPI, 3, 4, 4>(p, s, splits); break;
+        case 4: launch_small<EPI, 4, 3, 3>(p, s, splits); break;
         default: launch_256<EPI>(p, s, splits); break;
     }
 }

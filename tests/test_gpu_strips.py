@@ -59,3 +59,16 @@ def test_turns_are_the_bits_of_a_launch_without(N, K):
     assert bool(((whole.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + K * 2.0 ** -22 * size).all())
     for m in (64, 129, 160, 300, 471, 540, 1000, 1024, 1100, 1280, 1800, 2000):
         assert torch.equal(B.po_op_linear(a[:m].contiguous(), w, residual=r[:m].contiguous()), whole[:m]), m
+
+
+@pytest.mark.parametrize("N,K", [(4096, 128), (4096, 384), (4096, 1152), (2112, 4096)])
+def test_fp8_turns_are_the_bits_of_a_launch_without(N, K):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    rnd = _rnd(N * K + 1)
+    r = rnd(8192, N)
+    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(8192, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
+    whole = B.po_op_linear_fp8(qa, sa, qw, sw, residual=r)
+    for m in (64, 200, 300, 400, 471, 512, 600, 768, 1000, 1024):
+        x, s = qa[:m].contiguous(), sa[:m].contiguous()
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole[:m]), m
