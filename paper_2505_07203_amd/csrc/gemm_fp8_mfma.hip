@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(NTHREADS) gemm_fp8_mfma_kernel(const GemmParam
 // slices beside the accumulators: a slice is multiplied from registers while the next one's fragments are read, so by
 // the one barrier of a slice nobody needs its LDS position any more and slice s + D is loaded there.  (The same kernel
 // on 16x16x128 MFMAs was up to 1.6 x slower: half as much work per fragment read.)  k-steps of 64 in order, as above: the
-// same bits.  Measured: down projection (N 4096, K 14336) 471 rows 143 -> 47 us, 2048 rows (256-row tiles) 143 -> 99,
+// same bits.  Measured: down projection (N 4096, K 14336) 471 rows 143 -> 47 us (44 with turns), 2048 rows (256-row tiles) 143 -> 99,
 // 2.4 PFLOP/s.
 template <int EPI, int MR, int D, bool TURNS>
 __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams p) {
@@ -226,7 +226,6 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     constexpr int AU = BM_ * BKB, WU = BN_ * BKB;          // bytes of a slice of A / W
     constexpr int NA = 2 * MR, NW = 4;                     // global->LDS loads per wavefront and slice
     constexpr int AHEAD = D + 4;                           // how far ahead of the multiplied slice weights are touched
-    static_assert(AHEAD - D >= D - 2, "the hand-over's count of younger loads holds from the first slice on");
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
@@ -304,10 +303,10 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     int turn = gm_this > 1 ? (tm - g * GM) * 2 : 1 << 30;
 #define PO_TOUCH(s_)                                                                                                   \
     if (TURNS) {                                                                                                       \
-        const SliceWindow wt_ = slice_window((s_) + 1, KT, (unsigned)w_bytes, BKB);                                    \
-        const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)(turn == 0 ? wt_.bytes : 0), 0x00020000); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot,         \
-                                                 wt_.bytes ? wt_.offset - BKB : 0, 0, 0);                              \
+        if (turn == 0 && (s_) + 1 < KT) {                                                                              \
+            const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)w_bytes, 0x00020000);    \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot, (s_) * (BKB), 0, 0); \
+        }                                                                                                              \
         turn = turn == 0 ? 2 * gm_this - 1 : turn - 1;                                                                 \
     }
     const int a_base = wm * (MR * 32) * 128, w_base = AU + wn * 64 * 128;
@@ -342,7 +341,7 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     // s + D into the position of slice s, whose fragments every wavefront holds in registers by the barrier in front
 #define PO_SLICE(AC, WC, AN, WN)                                                                                     \
     {                                                                                                                 \
-        PO_WAIT_BARRIER((D - 2) * (NA + NW + (TURNS ? 1 : 0)));  /* slice s+1 has landed; all LDS reads of slice s are done */ \
+        PO_WAIT_BARRIER((D - 2) * (NA + NW));      /* slice s+1 has landed; all LDS reads of slice s are done */      \
         const int ps1 = ps + 1 >= D ? 0 : ps + 1;                                                                     \
         PO_SLICE_RSRC(s + D)                                                                                          \
         PO_TOUCH(s + AHEAD)                                                                                           \

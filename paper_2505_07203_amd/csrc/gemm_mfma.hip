@@ -214,6 +214,9 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 // slices one of R row tiles touches the weights of two slices a few slices ahead of the ring (one dword per line and lane,
 // into LDS that nobody reads), waits for HBM that once, and all others find them in L2.  (Every tile touching its share of
 // every slice helps nobody: then each of them waits for HBM every slice.)
+// A touch out of turn is skipped by a branch (as an instruction with nothing to load it cost every slice 2-6 %).  Weights
+// that a program multiplies with over and over, without 200 MB of others between, are in the memory-side cache, and there
+// turns cost up to 20 % (down projection alone at 150 rows); a model's layers never find theirs there.
 // Measured: down projection (N 4096, K 14336) at 300 rows 97 -> 80 us with the turns, 471 rows 92 -> 79 (225 on 256-row
 // tiles), 1000 rows 133 -> 117, 1 row 240 -> 76; O projection at 300 rows 30 -> 26, QKV at 1000 rows 67 -> 57.  Not kept, with and
 // without turns: one ring and one barrier per slice, whole slices of fragments in registers (no faster up to 192 rows), all
@@ -224,10 +227,7 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     constexpr int BM_ = 32 * MU, BN_ = 128;
     constexpr int AU = BM_ * 128, WU = BN_ * 128;          // bytes of a slice of A / W
     constexpr int NA = MU, NW = 4;                         // global->LDS loads per wavefront and slice
-    // how far ahead of the multiplied slice weights are touched: with D - 2 touches or more behind the first D slices' loads,
-    // the hand-over's count of younger loads holds from the first slice on
-    constexpr int AHEAD = D + (D > 6 ? D - 2 : 4);
-    static_assert(AHEAD - D >= D - 2, "");
+    constexpr int AHEAD = D + 4;                           // how far ahead of the multiplied slice weights are touched
 
     const int total = p.mt * p.nt;
     const int per_xcd = (total + 7) >> 3;
@@ -284,17 +284,18 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
     int f_off[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) f_off[ks] = l15 * 128 + (((ks * 4 + l4) ^ ((l15 >> 1) & 7)) << 4);
-    // this wavefront's 32 weight rows of slices s_ and s_ + 1, one dword per line, when it is this row tile's turn (an empty
-    // descriptor otherwise, and where slice s_ + 1 lies past the end of K)
+    // this wavefront's 32 weight rows of slices s_ and s_ + 1, one dword per line, when it is this row tile's turn.  (A load
+    // of 64 lines keeps the address unit busy for 64 cycles even where it is masked off, hence the branch.  The hand-over's
+    // count of younger loads leaves a touch out: it then waits for one load more, of the slice after.)
     unsigned char* const touched = smem + (D + 1) * AU + D * WU + wave * 256;
     const uint32_t vot = (uint32_t)(wave * 32 + (lane & 31)) * (uint32_t)(p.ldw * 2) + (lane >> 5) * 128;
     int turn = gm_this > 1 ? (tm - g * GM) * 2 : 1 << 30;
 #define PO_TOUCH(s_)                                                                                                   \
-    if (TURNS) {                                                                                                         \
-        const SliceWindow wt_ = slice_window((s_) + 1, KT, (unsigned)w_bytes, BK * 2);                                 \
-        const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)(turn == 0 ? wt_.bytes : 0), 0x00020000); \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot,         \
-                                                 wt_.bytes ? wt_.offset - BK * 2 : 0, 0, 0);                           \
+    if (TURNS) {                                                                                                       \
+        if (turn == 0 && (s_) + 1 < KT) {                                                                              \
+            const __amdgpu_buffer_rsrc_t rt_ = __builtin_amdgcn_make_buffer_rsrc(pw_, 0, (int)w_bytes, 0x00020000);    \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rt_, (__attribute__((address_space(3))) void*)touched, 4, vot, (s_) * (BK * 2), 0, 0); \
+        }                                                                                                              \
         turn = turn == 0 ? 2 * gm_this - 1 : turn - 1;                                                                 \
     }
     const int a_base = wm * (MU * 16) * 128, w_base = (D + 1) * AU + wn * 64 * 128;
@@ -351,9 +352,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
         // phase 0: k-step 0 | reads k-step 1; loads A(s + D) into the position A(s - 1) left
 #define PO_LA(i_) PO_DMA_A(pa_free, ((i_) < NA ? (i_) : 0))
         PO_PHASE(A0, W0, A1, W1, ua, uw, 1, NA, PO_LA)
-        // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1, A(s+D) and, with turns, a touch each); all LDS
-        // reads of slice s are done
-        PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA + (TURNS ? D - 1 : 0));
+        // hand-over: slice s+1 has landed (everything but slices s+2 .. s+D-1 and A(s+D)); all LDS reads of slice s are done
+        PO_WAIT_BARRIER((D - 2) * (NA + NW) + NA);
         // phase 1: k-step 1 | reads k-step 0 of slice s+1; loads W(s + D) into W(s)'s position
 #define PO_LW(i_) PO_DMA_W(pw, ((i_) < NW ? (i_) : 0))
         PO_PHASE(A1, W1, A0, W0, ua1, uw1, 0, NW, PO_LW)
@@ -646,12 +646,15 @@ void launch_small(GemmParams p, hipStream_t s, int splits) {
     // workgroup, short of activations to load, runs ahead of the others (900 rows of the down projection 106 / 118, 1000
     // rows 135 / 117), and with two or three row tiles in all there is hardly anyone to take turns with.  So: up to 64 rows per
     // tile from five row tiles on, 10-18 % (150 rows 84 / 70; two, the second a quarter full, 80 / 90); 96 rows with the last one
-    // a third full, 4-15 %; 128 rows with six of them, the last half full, 2-14 %; 160 rows with the last three quarters full, 6 % (1100 rows
+    // two thirds full, 3-15 %, and for short K only with weight rows a multiple of 4 KiB apart (QKV + O projection, weights from
+    // the memory-side cache: 8B shape, 8 KiB, 460 rows 65 / 61; 32B shape, 10 KiB, 450 rows 96.0 / 97.6, 350 rows 87.1 / 87.6,
+    // though from HBM its O projection gains as well); 128 rows with six of them, the last half full, 2-14 %; 160 rows with the last three quarters full, 6 % (1100 rows
     // 153 / 144; half full 137 / 170); 192 rows never (1500 rows behind their gate/up 164 / 169); 256 rows, with the
     // shallowest ring, 4-15 %.
     const int last = p.M - (p.mt - 1) * 32 * MU;                       // rows of the last row tile
-    const bool third = 3 * last >= 32 * MU, half = 2 * last >= 32 * MU;
-    const bool turns = p.mt > 1 && (MU <= 2 ? p.mt >= 5 || half : MU == 3 ? third : MU == 4 ? half && p.mt >= 6
+    const bool most = 3 * last >= 64 * MU, half = 2 * last >= 32 * MU;
+    const bool apart = MU > 3 || p.K > 8192 || p.ldw % 2048 == 0;
+    const bool turns = p.mt > 1 && apart && (MU <= 2 ? p.mt >= 5 || half : MU == 3 ? most : MU == 4 ? half && p.mt >= 6
                                     : MU == 5 ? 4 * last >= 3 * 160 : MU == 8 && (p.mt > 2 || half));
     if (MU != 6 && turns) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
