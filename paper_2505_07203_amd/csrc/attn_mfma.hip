@@ -366,7 +366,8 @@ next_redo_item:
 // that gave up stores NOTHING (its query rows, which the output overwrites, stay intact) and sets its word in
 // `redo`, and a second launch right behind this one recomputes exactly those (query tile, head) pairs with the
 // running-maximum kernel above, which is total on finite inputs.  With `redo` all zero, as it is for attention
-// inputs of ordinary size, that launch is a few thousand workgroups that read one word and exit.
+// inputs of ordinary size, that launch is at most 256 workgroups that read a few words and exit.  (That is the form for plain
+// queries.  Prescaled ones, which the full path has, decide and recompute row by row in the same launch, see PRE.)
 //
 // Two wavefronts per SIMD do not help here.  A copy of this kernel with eight wavefronts of 32 query rows (each K /
 // V^T fragment then feeds one MFMA) was built and is exact, but 7 % slower: vector instructions of one wavefront do
@@ -405,8 +406,8 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 // does, in fp32: Q is rounded once, as before).  K Q^T then IS the exponent's argument, and no reference exponent is
 // subtracted at all: p = exp2(s) as it comes out of the matrix pipe, no multiply-add per score.  fp32 and bf16 hold
 // 2^-126 .. 2^127, attention scores of ordinary size are within +-40, and a row whose sum of p leaves 2^-60 .. 2^100
-// (scores far above or far below that) gives up and is recomputed with a running maximum: by the running-maximum kernel, like
-// an overflow in the other form, or, with redo null, by this workgroup in place (see redoes_in_place).
+// (scores far above or far below that) is recomputed with a running maximum by its own workgroup: that row alone, so that
+// its bits and its neighbours' do not depend on each other.
 //
 // QT: query tiles of 32 rows per wavefront.  2 is the form described above; 1 (PRE only) halves the rows of a workgroup, for
 // launches that do not fill the chip (see takes_128_rows).  It reads a fragment per MFMA, which bounds it by LDS (5-12 % more
@@ -925,116 +926,157 @@ __global__ void __launch_bounds__(256) attn_fwd64_kernel(const bf16_t* q, const 
         }
         return;
     }
+    // PRE: this lane's rows whose sum left the range: 2^100 or more (or infinite) means probabilities near or past the top of the
+    // float range, below 2^-60 that the row's scores sit so far below zero that terms were flushed away.  (Rows below
+    // q_row0 hold anything.)
+    bool again[2] = {false, false};
     if (PRE) {
         lrow[0] = (lsum[0][0] + lsum[0][1]) + (lsum[0][2] + lsum[0][3]);
         lrow[1] = (lsum[1][0] + lsum[1][1]) + (lsum[1][2] + lsum[1][3]);
-        // a row sum of 2^100 or more (or infinite) means probabilities near or past the top of the float range; one
-        // below 2^-60 that the row's scores sit so far below zero that terms were flushed away
-        const float t0 = half_swap_sum(lrow[0]), t1 = half_swap_sum(lrow[QT - 1]);
-        if (nkb_w > 0 && __any(!(t0 >= 0x1p-60f) || !(t0 < 0x1p100f) || !(t1 >= 0x1p-60f) || !(t1 < 0x1p100f))) gave_up = 1;
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            const float t = half_swap_sum(lrow[qt]);
+            const int row = qw + qt * 32 + l31;
+            again[qt] = row >= sp.q_row0 && row < N && (!(t >= 0x1p-60f) || !(t < 0x1p100f));
+        }
+        gave_up = __any(again[0] || again[QT - 1]);
     }
     // ---- did any wavefront give up?  (every wavefront has met the same number of barriers and arrives here)
     if (gave_up && lane == 0) *(volatile int*)lds_gave_up = 1;
     __syncthreads();
-    if (*(volatile int*)lds_gave_up) {
-        if (!PRE || redo) {
-            if (tid == 0) redo[qtile * Hq + head] = 1;
-            return;
-        }
-        // Once more with a running maximum, tile by tile, one in flight: total on finite inputs.  (Rare, so short code instead
-        // of a pipeline, but in one pass: with the exact maxima from a pass over K first it took a third longer.)
-        float m[2] = {-1.0e30f, -1.0e30f};
-        lrow[0] = lrow[1] = 0.f;
-#pragma unroll
-        for (int ht = 0; ht < HT; ++ht)
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
-        _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(0, 0, jj);
-        for (int t = 0; t < n_tiles; ++t) {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is there, the other stage free
-            if (t + 1 < n_tiles) {
-                _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(t + 1, (t + 1) & 1, jj);
-            }
-            const unsigned char* st = smem + (t & 1) * A64_TILE;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                f32x16 S[QT];
-                bf16x8 pr[QT][2];
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) S[qt][r] = 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const bf16x8 kf = *(const bf16x8*)(st + b * 8192 + koff[ks]);
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt) S[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], S[qt], 0, 0, 0);
-                }
-                if (t * 64 + b * 32 + 31 > qw) {
-                    PO_MASK(S, 2 * t + b, 0);
-                    if (QT == 2) PO_MASK(S, 2 * t + b, QT - 1);
-                }
-                float n[2];
-                PO_BLOCKMAX(S, 0, n[0]);
-                PO_BLOCKMAX(S, QT - 1, n[1]);
-                n[0] = fmaxf(n[0], m[0]);
-                n[1] = fmaxf(n[1], m[1]);
-                if (__any(n[0] > m[0] || n[1] > m[1])) {
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt) {
-                        const float a = __builtin_amdgcn_exp2f(m[qt] - n[qt]);
-                        lrow[qt] *= a;
-#pragma unroll
-                        for (int ht = 0; ht < HT; ++ht)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) oacc[ht][qt][r] *= a;
-                    }
-                    m[0] = n[0];
-                    m[1] = n[1];
-                }
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float e = __builtin_amdgcn_exp2f(S[qt][r] - m[qt]);
-                        lrow[qt] += e;
-                        pr[qt][r >> 3][r & 7] = (__bf16)e;
-                    }
-#pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2)
-#pragma unroll
-                    for (int ht = 0; ht < HT; ++ht) {
-                        const bf16x8 vf = *(const bf16x8*)(st + ht * 4096 + vofs[b][j2]);
-#pragma unroll
-                        for (int qt = 0; qt < QT; ++qt) PO_MFMA_ACC_FRESH(oacc[ht][qt], vf, pr[qt][j2]);
-                    }
-                PO_MFMA_END();
-            }
-        }
+    const bool any_again = *(volatile int*)lds_gave_up != 0;
+    if (!PRE && any_again) {
+        if (tid == 0) redo[qtile * Hq + head] = 1;
+        return;
     }
 
-    // ---- normalise and store: lane = query row, registers = head-dim rows
+    // ---- normalise and store the rows for which again[] is AGAIN_: lane = query row, registers = head-dim rows
+#define PO_STORE_ROWS(AGAIN_)                                                                                          \
+    _Pragma("unroll") for (int qt = 0; qt < QT; ++qt) {                                                                \
+        const float inv = 1.0f / half_swap_sum(lrow[qt]);                                                              \
+        const int qrow = qw + qt * 32 + l31;                                                                           \
+        if (qrow < N && again[qt] == (AGAIN_)) {                                                                       \
+            bf16_t* op = o + ((int64_t)qrow * Hq + head) * HD + 4 * lhi;                                               \
+            _Pragma("unroll") for (int ht = 0; ht < HT; ++ht)                                                          \
+                _Pragma("unroll") for (int rg = 0; rg < 4; ++rg) {                                                     \
+                    uint2 w;                                                                                           \
+                    w.x = (uint32_t)f2bf(oacc[ht][qt][rg * 4 + 0] * inv) | ((uint32_t)f2bf(oacc[ht][qt][rg * 4 + 1] * inv) << 16); \
+                    w.y = (uint32_t)f2bf(oacc[ht][qt][rg * 4 + 2] * inv) | ((uint32_t)f2bf(oacc[ht][qt][rg * 4 + 3] * inv) << 16); \
+                    *(uint2*)(op + ht * 32 + rg * 8) = w;                                                              \
+                }                                                                                                      \
+        }                                                                                                              \
+    }
+    PO_STORE_ROWS(false)
+    if (!PRE || !any_again) return;
+
+    // ---- The rows that are left, once more with a running maximum, total on finite inputs; wavefronts without such a row only
+    // copy.  Maximum, sum and roundings go by 64-key tiles from key 0 on, as in the running-maximum kernel above, and rows do
+    // not meet: a row's bits depend on the row and its keys alone, not on the tile's height or on where a launch starts.  (A
+    // second launch cannot know which rows of a tile are meant, since the output of the others overwrites their queries.)
+    // Three tiles in flight; V^T fragments are asked for in front of the softmax, which hides the read.  Measured against the
+    // fast kernel and a second launch of whole tiles behind it (32 heads on 8 KV heads, us): every row out of range 1931 rows
+    // 113 / 97, 2300 157 / 162, 4700 415 / 445, 16000 3640 / 3810; one row in 997 out 4700 rows 355 / 285, 32768 rows 10190 / 8110; none
+    // 32768 rows equal, 300 rows 24 / 15 (the 128-row tiles' gain included).
+    {
+        const int n_w = gave_up ? (min(N, qw + 32 * QT) - 1) / 64 + 1 : 0;
+        float m[QT];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const float inv = 1.0f / half_swap_sum(lrow[qt]);
-        const int qrow = qw + qt * 32 + l31;
-        if (qrow < N) {
-            bf16_t* op = o + ((int64_t)qrow * Hq + head) * HD + 4 * lhi;
+        for (int qt = 0; qt < QT; ++qt) {
+            m[qt] = -1.0e30f;
+            lrow[qt] = 0.f;
 #pragma unroll
             for (int ht = 0; ht < HT; ++ht)
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    uint2 w;
-                    w.x = (uint32_t)f2bf(oacc[ht][qt][rg * 4 + 0] * inv) | ((uint32_t)f2bf(oacc[ht][qt][rg * 4 + 1] * inv) << 16);
-                    w.y = (uint32_t)f2bf(oacc[ht][qt][rg * 4 + 2] * inv) | ((uint32_t)f2bf(oacc[ht][qt][rg * 4 + 3] * inv) << 16);
-                    *(uint2*)(op + ht * 32 + rg * 8) = w;
+                for (int r = 0; r < 16; ++r) oacc[ht][qt][r] = 0.f;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (the stores above are counted too)
+        _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(0, 0, jj);
+        _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(1, 1, jj);
+        _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(2, 2, jj);
+        for (int t = 0; t < n_tiles; ++t) {
+            asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");    // tile t is there, stage of t - 1 free
+            _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) PO_DMA(t + 3, (t + 3) & 3, jj);
+            if (t >= n_w) continue;
+            const unsigned char* st = smem + (t & 3) * A64_TILE;
+            f32x16 S[2][QT];
+            bf16x8 pr[QT][4], vf[2][HT];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) S[b][qt][r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const bf16x8 kf = *(const bf16x8*)(st + b * 8192 + koff[ks]);
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt) S[b][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qt][ks], S[b][qt], 0, 0, 0);
                 }
+#pragma unroll
+            for (int j2 = 0; j2 < 2; ++j2)
+#pragma unroll
+                for (int ht = 0; ht < HT; ++ht) vf[j2][ht] = *(const bf16x8*)(st + ht * 4096 + vofs[0][j2]);
+            if (t * 64 + 63 > qw) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    PO_MASK(S[b], 2 * t + b, 0);
+                    if (QT == 2) PO_MASK(S[b], 2 * t + b, QT - 1);
+                }
+            }
+            float top[QT];
+            bool grew = false;
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+                float m0, m1;
+                PO_BLOCKMAX(S[0], qt, m0);
+                PO_BLOCKMAX(S[1], qt, m1);
+                top[qt] = fmaxf(m[qt], fmaxf(m0, m1));
+                grew |= top[qt] > m[qt];
+            }
+            if (__any(grew)) {
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt) {
+                    const float a = __builtin_amdgcn_exp2f(m[qt] - top[qt]);
+                    lrow[qt] *= a;
+                    m[qt] = top[qt];
+#pragma unroll
+                    for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) oacc[ht][qt][r] *= a;
+                }
+            }
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+                float rs = 0.f;
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float e = __builtin_amdgcn_exp2f(S[b][qt][r] - m[qt]);
+                        rs += e;
+                        pr[qt][2 * b + (r >> 3)][r & 7] = (__bf16)e;
+                    }
+                lrow[qt] += rs;
+            }
+#pragma unroll
+            for (int j2 = 0; j2 < 4; ++j2)
+#pragma unroll
+                for (int ht = 0; ht < HT; ++ht) {
+                    const bf16x8 v = vf[j2 & 1][ht];
+                    if (j2 < 2) vf[j2][ht] = *(const bf16x8*)(st + ht * 4096 + vofs[1][j2]);
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt) PO_MFMA_ACC_FRESH(oacc[ht][qt], v, pr[qt][j2]);
+                }
+            PO_MFMA_END();
         }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    PO_STORE_ROWS(true)
 }
 
+#undef PO_STORE_ROWS
 #undef PO_PAIR
 #undef PO_FRAG_ADDR
 #undef PO_WAIT_FRAG
@@ -1097,14 +1139,9 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
 
 // Workgroups of 256 rows and of 128 rows (QT 1): a launch of one round is as long as its longest tile, which half the rows halve;
 // with more, the 256-row form does the same in 5-12 % less time.  Measured, prescaled queries, 32 heads on 8, whole call
-// before / now (us, the redo launch gone as well): 300 rows 21 / 12, 700 rows 27 / 16, 1500 rows 44 / 30, 1931 rows 51 / 41; 128-row
+// before / now (us, a redo launch gone as well): 300 rows 21 / 12, 700 rows 27 / 16, 1500 rows 44 / 30, 1931 rows 51 / 41; 128-row
 // tiles at 2500 rows (320 workgroups) would take as long as 256-row ones, at 8000 rows 10 % longer.
 bool takes_128_rows(int64_t n_tiles256, int Hq) { return n_tiles256 * Hq <= 256; }
-
-// The tiles that gave up are recomputed by a second launch, or in place by the workgroup that gave up.  In place spares every
-// call the second launch (4 us: 5-7 % at 2300 rows), but takes up to a third longer when tiles do give up in numbers, since a
-// workgroup has one wavefront per SIMD for it and the other kernel two: so up to two rounds of workgroups.
-bool redoes_in_place(int64_t n_tiles256, int Hq) { return n_tiles256 * Hq <= 512; }
 
 void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o, int64_t N, int Hq,
                   int Hkv, int64_t q_row0, int* redo, bool q_prescaled, hipStream_t s) {
@@ -1123,20 +1160,21 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     // workgroups enumerate query tiles from the last one down: fewer of them = only the last tiles
     const int64_t first = (q_row0 > 0 && q_row0 < N) ? q_row0 : 0;
     const int nsel = nqt - (int)(first / 256);
+    SplitArgs rows{};
+    rows.q_row0 = (int)first;
     if (q_prescaled && takes_128_rows(nsel, Hq)) {
         const int nqt128 = (int)((N + 127) / 128);
         hipLaunchKernelGGL((attn_fwd64_kernel<true, 0, 1>), dim3((unsigned)((nqt128 - (int)(first / 128)) * Hq)), dim3(256), SMEM, s,
-                           q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt128, hpx, nullptr, SplitArgs{});
+                           q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt128, hpx, nullptr, rows);
         return;
     }
-    const bool in_place = q_prescaled && redoes_in_place(nsel, Hq);
-    if (q_prescaled)
+    if (q_prescaled) {
         hipLaunchKernelGGL((attn_fwd64_kernel<true, 0, 2>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
-                           Hq, Hkv, sc_log2e, nqt, hpx, in_place ? nullptr : redo, SplitArgs{});
-    else
-        hipLaunchKernelGGL((attn_fwd64_kernel<false, 0, 2>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
-                           Hq, Hkv, sc_log2e, nqt, hpx, redo, SplitArgs{});
-    if (in_place) return;
+                           Hq, Hkv, sc_log2e, nqt, hpx, nullptr, rows);
+        return;
+    }
+    hipLaunchKernelGGL((attn_fwd64_kernel<false, 0, 2>), dim3((unsigned)(nsel * Hq)), dim3(256), SMEM, s, q, k, vt, ldv, o, (int)N,
+                       Hq, Hkv, sc_log2e, nqt, hpx, redo, rows);
     // the (query tile, head) pairs given up above, by the running-maximum kernel with the same 256-row tiles
     // (8 wavefronts x 32 rows); item b = query tile * Hq + head
     hipLaunchKernelGGL((attn_fwd_kernel<128, 1, 8, false>), dim3((unsigned)std::min(nqt * Hq, 256)), dim3(512), SMEM_REDO, s, q, k, vt, ldv,
@@ -1275,9 +1313,7 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
     return 0;
 }
 
-bool attention_mfma_uses_redo(int64_t N, int Hq, int hd, bool q_prescaled) {
-    return hd == 128 && !(q_prescaled && redoes_in_place((N + 255) / 256, Hq));
-}
+bool attention_mfma_uses_redo(int hd, bool q_prescaled) { return hd == 128 && !q_prescaled; }
 
 size_t attention_mfma_redo_bytes(int64_t N, int Hq) { return (size_t)((N + 255) / 256) * (size_t)Hq * sizeof(int); }
 

@@ -6,8 +6,6 @@
 // float32 matrix-instruction kernels (f32_mfma.hip) do not cover.
 #include "po_internal.h"
 
-#include <algorithm>
-
 namespace po {
 
 // ------------------------------------------------------------------ embedding gather
@@ -499,12 +497,8 @@ void launch_pack_rope_rows(bf16_t* W, int n_heads, int hd, int64_t row_elems, hi
     hipLaunchKernelGGL(pack_rope_rows_kernel, dim3(32, (unsigned)n_heads), dim3(256), 0, s, W, row_elems);
 }
 
-// columns n .. n + pad - 1 of `rows` rows of V^T, and n_words words, in one launch
-__global__ void __launch_bounds__(64) vt_pad_zero_kernel(bf16_t* Vt, int rows, int64_t ldv, int64_t n, int pad, uint32_t* words,
-                                                         size_t n_words) {
-    if ((int)blockIdx.x < rows && (int)threadIdx.x < pad) Vt[(int64_t)blockIdx.x * ldv + n + threadIdx.x] = 0;
-    const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
-    if (i < n_words) words[i] = 0u;
+__global__ void __launch_bounds__(64) vt_pad_zero_kernel(bf16_t* Vt, int64_t ldv, int64_t n, int pad) {
+    if ((int)threadIdx.x < pad) Vt[(int64_t)blockIdx.x * ldv + n + threadIdx.x] = 0;
 }
 
 __global__ void __launch_bounds__(256) fill_zero32_kernel(uint32_t* dst, size_t n) {
@@ -528,11 +522,10 @@ void launch_round_bf16_f32(float* x, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(round_bf16_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, n);
 }
 
-void launch_vt_pad_zero(bf16_t* Vt, int rows, int64_t ldv, int64_t n, void* words, size_t n_words, hipStream_t s) {
+void launch_vt_pad_zero(bf16_t* Vt, int rows, int64_t ldv, int64_t n, hipStream_t s) {
     const int pad = (int)(round_up64(n, 64) - n);
-    const int64_t blocks = std::max<int64_t>(pad > 0 ? rows : 0, (int64_t)((n_words + 63) / 64));
-    if (blocks <= 0) return;
-    hipLaunchKernelGGL(vt_pad_zero_kernel, dim3((unsigned)blocks), dim3(64), 0, s, Vt, rows, ldv, n, pad, (uint32_t*)words, n_words);
+    if (pad <= 0 || rows <= 0) return;
+    hipLaunchKernelGGL(vt_pad_zero_kernel, dim3((unsigned)rows), dim3(64), 0, s, Vt, ldv, n, pad);
 }
 
 // Highest 32-bit word of an arena that differs from a fill pattern: per-thread strided scan,

@@ -48,7 +48,6 @@ struct Layout {
     size_t weights_bytes;
     // workspace arena
     size_t tokens, X, Q, K, V, Vt, Xn, H, GU, rope_cos, rope_sin, logits, xn_last, cand, cand_lp;
-    size_t attn_redo;   // bf16: one word per 256-row query tile and head (see launch_attention_mfma)
     size_t profile_mark;  // the last 256 bytes: where po_profile's scan leaves its result (not part of what it scans)
     size_t sx;          // PO_BF16_FP8: float32 scale per row of the activation being multiplied
     size_t workspace_bytes;
@@ -135,6 +134,8 @@ po_status make_layout(const po_model_config* c, int64_t max_len, int32_t mlp_chu
     L->K = take(N * kvd * esz);
     L->V = c->dtype == PO_F32 ? take(N * kvd * esz) : 0;   // bf16: V lives only as V^T
     L->Vt = is_bf16(c->dtype) ? take(kvd * (size_t)L->ldv * esz) : 0;
+    // (part of the arena's published size; nothing uses it: with prescaled queries the attention marks no tiles)
+    if (is_bf16(c->dtype)) take(attention_mfma_redo_bytes(max_len, c->n_q_heads));
     L->Xn = take(C * d * esz);
     L->H = take(C * F * esz);
     L->GU = c->dtype == PO_F32 ? take(C * 2 * F * esz) : 0;
@@ -144,7 +145,6 @@ po_status make_layout(const po_model_config* c, int64_t max_len, int32_t mlp_chu
     L->xn_last = take(d * esz);
     L->cand = take(MAX_CAND * 4);
     L->cand_lp = take(MAX_CAND * 4);
-    L->attn_redo = is_bf16(c->dtype) ? take(attention_mfma_redo_bytes(max_len, c->n_q_heads)) : 0;
     // one scale per row of a launch: at most the rows of d values the MLP chunk buffer holds
     L->sx = fp8 ? take(std::max(C, C * F / d) * 4) : 0;
     L->profile_mark = take(sizeof(unsigned long long));
@@ -327,11 +327,8 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
         PO_HIP(hipMemcpyAsync(d_tok, row_pos.data(), (size_t)total * 4, hipMemcpyHostToDevice, s));
         d_row_pos = d_tok;
     }
-    // the last key tile of the attention reads V^T up to the next multiple of 64 positions; its give-up words start every
-    // request at zero (its second launch leaves them so)
-    int* attn_redo = (int*)(ws + L.attn_redo);
-    if (dt == PO_BF16)
-        launch_vt_pad_zero((bf16_t*)(ws + L.Vt), kvd, L.ldv, total, attn_redo, attention_mfma_redo_bytes(c->max_len, m.n_q_heads) / 4, s);
+    // the last key tile of the attention reads V^T up to the next multiple of 64 positions
+    if (dt == PO_BF16) launch_vt_pad_zero((bf16_t*)(ws + L.Vt), kvd, L.ldv, total, s);
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerOff& o = L.layers[l];
         const unsigned char* wqkv = c->w + o.wqkv;
@@ -478,7 +475,7 @@ po_status run_rows(po_ctx* c, const int32_t* tokens, int64_t total, const std::v
                 else
                     launch_attention_mfma((const bf16_t*)Qg, (const bf16_t*)(K + (size_t)g.start * kvd * esz),
                                           (const bf16_t*)(ws + L.Vt) + g.start, L.ldv, (bf16_t*)Qg, g.len, m.n_q_heads,
-                                          m.n_kv_heads, hd, q_row0, attn_redo, true, s);
+                                          m.n_kv_heads, hd, q_row0, nullptr, true, s);
             } else {
                 launch_attention_basic(dt, Qg, K + (size_t)g.start * kvd * esz, V + (size_t)g.start * kvd * esz, Qg,
                                        g.len, m.n_q_heads, m.n_kv_heads, hd, q_row0, s);
@@ -1389,7 +1386,7 @@ po_status po_op_attention(int32_t dtype, const void* q, const void* k, const voi
         const int64_t ldv = round_up64(N, 64);
         // scratch: V^T, then (256-byte aligned) the give-up words of the attention kernel
         int* redo = (int*)((unsigned char*)scratch + align_up((size_t)Hkv * hd * (size_t)ldv * 2));
-        if (attention_mfma_uses_redo(N, Hq, hd, q_prescaled != 0))
+        if (attention_mfma_uses_redo(hd, q_prescaled != 0))
             launch_fill_zero32(redo, attention_mfma_redo_bytes(N, Hq) / 4, (hipStream_t)stream);
         launch_v_transpose((const bf16_t*)v, (bf16_t*)scratch, N, Hkv * hd, ldv, (hipStream_t)stream);
         launch_attention_mfma((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)scratch, ldv, (bf16_t*)o, N, Hq, Hkv,

@@ -92,7 +92,7 @@ static inline float attention_q_scale(int hd) { return (float)(1.442695040888963
 // apart inside one 64-row group.  row_elems = elements per row (1 for a bias vector).
 void launch_pack_rope_rows(bf16_t* W, int n_heads, int hd, int64_t row_elems, hipStream_t s);
 // zero columns [n, round_up(n,64)) of V^T [rows][ldv]
-void launch_vt_pad_zero(bf16_t* Vt, int rows, int64_t ldv, int64_t n, void* words, size_t n_words, hipStream_t s);
+void launch_vt_pad_zero(bf16_t* Vt, int rows, int64_t ldv, int64_t n, hipStream_t s);
 void launch_high_water(const void* ws, size_t bytes, uint32_t pattern, unsigned long long* out, hipStream_t s);
 // Vt[Hkv*hd][ldv] = transpose of V[n, Hkv*hd]; columns n..round_up(n,64)-1 are zero-filled
 // K rows (k_bytes contiguous bytes) and v_rows rows of V^T (v_bytes each, pitches in bytes) between the one-layer
@@ -101,14 +101,15 @@ void launch_kv_copy(void* dk, const void* sk, size_t k_bytes, void* dv, size_t d
                     size_t v_bytes, int v_rows, hipStream_t s);
 void launch_v_transpose(const bf16_t* V, bf16_t* Vt, int64_t n, int kv_dim, int64_t ldv, hipStream_t s);
 // causal GQA flash attention; q [N,Hq,hd], k [N,Hkv,hd], vt [Hkv*hd][ldv]; o may alias q.
-// redo: attention_mfma_redo_bytes(N, Hq) bytes of device memory, all zero on entry and left all zero (one word
-// per 256-row query tile and head: the tiles whose scores leave the range of the fast kernel's fixed reference
-// exponent are marked there and recomputed by the running-maximum kernel in a second launch)
+// redo (may be null where attention_mfma_uses_redo is false: plain queries of head dimension 128 use it):
+// attention_mfma_redo_bytes(N, Hq) bytes of device memory, all zero on entry and left all zero (one word per 256-row query
+// tile and head: the tiles whose scores leave the range of the fast kernel's fixed reference exponent are marked there and
+// recomputed by the running-maximum kernel in a second launch)
 size_t attention_mfma_redo_bytes(int64_t N, int Hq);
-// whether a launch over N positions, or over the last rows of them, may touch those words (where not: they may hold anything)
-bool attention_mfma_uses_redo(int64_t N, int Hq, int hd, bool q_prescaled);
+bool attention_mfma_uses_redo(int hd, bool q_prescaled);
 // q_prescaled: q holds the rotated queries times attention_q_scale(hd) (launch_gemm_qkv_rope's q_scale); the
-// kernels then exponentiate K Q^T as it is.
+// kernels then exponentiate K Q^T as it is, and recompute rows whose scores leave the range that way by themselves, each row
+// with the same bits whichever other rows the launch has.
 void launch_attention_mfma(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o,
                            int64_t N, int Hq, int Hkv, int hd, int64_t q_row0, int* redo, bool q_prescaled, hipStream_t s);
 // n 32-bit words of zeros (a kernel, not a memset node, so that it can be captured into a graph)
