@@ -401,6 +401,11 @@ po_status po_op_pack_gate_up(int32_t dtype, const void* dev_wg, const void* dev_
 po_status po_op_attention(int32_t dtype, const void* dev_q, const void* dev_k, const void* dev_v,
                           void* dev_o, void* dev_scratch, int64_t N, int32_t n_q_heads,
                           int32_t n_kv_heads, int32_t head_dim, int32_t q_prescaled, void* hip_stream);
+/* The number of query rows per workgroup with which bf16 attention runs over rows [q_row0, N) (q_row0 = 0 in
+ * po_op_attention; the full path's launches start behind a cached prefix or at the last row).  Host only.  Changes no
+ * result. */
+po_status po_attention_tile(int64_t N, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t q_row0,
+                            int32_t q_prescaled, int32_t* tile_rows);
 /* The few-rows form of po_op_attention (bf16 only; see po_set_few_rows_split): rows [q_row0, N) of the causal
  * attention, each query tile's keys divided between workgroups and merged by a second kernel.  dev_scratch_vt as
  * dev_scratch there; dev_scratch_part (part_bytes, 256-byte aligned) takes the fp32 partial results.  Rows below

@@ -39,7 +39,7 @@ EXPORTS = [
     "po_op_quantize_rows", "po_op_rmsnorm_quantize", "po_op_linear_fp8", "po_op_qkv_rope_fp8",
     "po_attach_kv_cache_slots", "po_kv_cache_match", "po_kv_cache_slot", "po_sched_pick_multi",
     "po_profile_jct", "po_engine_step", "po_set_few_rows_split", "po_set_storage_rounding", "po_op_linear_split", "po_sched_push_request", "po_op_attention_split",
-    "po_op_attention_split_prefix", "po_gemm_tile", "po_op_linear_fp8_split",
+    "po_op_attention_split_prefix", "po_attention_tile", "po_gemm_tile", "po_op_linear_fp8_split",
     "po_sched_create", "po_sched_destroy", "po_sched_set_jct_model", "po_sched_fit_jct_model", "po_sched_push",
     "po_sched_size", "po_sched_pick", "po_sched_remove", "po_op_rope_static", "po_op_mfma_peak", "po_op_stream_copy",
 ]
@@ -121,6 +121,7 @@ def lib() -> C.CDLL:
     L.po_op_attention_split.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, vp, C.POINTER(i32)]
     L.po_op_attention_split_prefix.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, i32, i64, i32, vp, vp, i64, i64, vp,
                                                C.POINTER(i32)]
+    L.po_attention_tile.argtypes = [i64, i32, i32, i32, i64, i32, C.POINTER(i32)]
     L.po_gemm_tile.argtypes = [i32, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     L.po_op_linear_fp8_split.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_linear_split.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
@@ -435,6 +436,13 @@ def po_op_linear(a, w, residual=None, out=None):
     check(lib().po_op_linear(_dt(a), a.data_ptr(), w.data_ptr(), c.data_ptr(),
                              None if residual is None else residual.data_ptr(), M, N, K, _stream()))
     return c
+
+
+def po_attention_tile(N: int, n_q_heads: int, n_kv_heads: int, head_dim: int = 128, q_row0: int = 0, q_prescaled: bool = True):
+    """query rows per workgroup of a bf16 attention launch; needs no GPU"""
+    r = C.c_int32(0)
+    check(lib().po_attention_tile(N, n_q_heads, n_kv_heads, head_dim, q_row0, 1 if q_prescaled else 0, C.byref(r)))
+    return r.value
 
 
 def po_gemm_tile(M: int, N: int, K: int, splits: int = 1, fp8: bool = False):

@@ -1137,11 +1137,26 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
     *(uint2*)(o + (row * Hq + head) * HD + f) = w2;
 }
 
-// Workgroups of 256 rows and of 128 rows (QT 1): a launch of one round is as long as its longest tile, which half the rows halve;
-// with more, the 256-row form does the same in 5-12 % less time.  Measured, prescaled queries, 32 heads on 8, whole call
-// before / now (us, a redo launch gone as well): 300 rows 21 / 12, 700 rows 27 / 16, 1500 rows 44 / 30, 1931 rows 51 / 41; 128-row
-// tiles at 2500 rows (320 workgroups) would take as long as 256-row ones, at 8000 rows 10 % longer.
-bool takes_128_rows(int64_t n_tiles256, int Hq) { return n_tiles256 * Hq <= 256; }
+// Workgroups of 256 rows or of 128 (QT 1) for query rows q_row0 .. N-1 of Hq heads, one workgroup per compute unit at a time.
+// A causal launch of one round is as long as its longest tile, which half the rows halve; behind a cached prefix all tiles are
+// about as long, and half the rows help until they take a second round.  So where 256-row tiles are one round, the
+// heights are compared by the time each takes: key tiles of the longest workgroup, or of a workgroup of the second round (they
+// start longest first, so workgroup 256 + k follows workgroup 255 - k) and the one it follows, each with 5 more for its
+// beginning and end; a key tile of 128 rows takes 0.6 of one of 256 rows (0.56-0.59 measured, which leaves ties to 256).  With
+// more 256-row tiles than a round, 128 rows would gain behind a prefix as well, but not in causal launches (2500 rows as long, 8000
+// rows 10 % longer).  Measured, prescaled queries, 32 heads on 8, 256-row / 128-row tiles (us): whole causal calls of 300 rows 21 /
+// 12, 700 rows 27 / 16, 1500 rows 44 / 30, 1931 rows 51 / 41; a layer behind 14000 cached positions, 900 rows (256 workgroups)
+// 245 / 198, 1000 rows (288) 259 / 320, 1800 rows (480) 375 / 398; behind 4000, 900 rows 92 / 70, 1100 rows 104 / 111.
+bool takes_128_rows(int64_t N, int64_t q_row0, int Hq) {
+    if (((N + 255) / 256 - q_row0 / 256) * Hq > 256) return false;
+    constexpr int64_t ENDS = 5;
+    const int64_t last = (N - 1) / 128, n = (last + 1 - q_row0 / 128) * Hq;        // n <= 512 workgroups
+    auto keys = [&](int64_t tile) { return (std::min(N, (tile + 1) * 128) - 1) / 64 + 1 + ENDS; };
+    int64_t longest = keys(last);
+    for (int64_t b = 256; b < n; b += std::min(Hq - b % Hq, (511 - b) % Hq + 1))   // (every pair of tiles that follow each other)
+        longest = std::max(longest, keys(last - b / Hq) + keys(last - (511 - b) / Hq));
+    return 6 * longest < 10 * keys(last);
+}
 
 void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ldv, bf16_t* o, int64_t N, int Hq,
                   int Hkv, int64_t q_row0, int* redo, bool q_prescaled, hipStream_t s) {
@@ -1162,7 +1177,7 @@ void launch_fwd64(const bf16_t* q, const bf16_t* k, const bf16_t* vt, int64_t ld
     const int nsel = nqt - (int)(first / 256);
     SplitArgs rows{};
     rows.q_row0 = (int)first;
-    if (q_prescaled && takes_128_rows(nsel, Hq)) {
+    if (q_prescaled && takes_128_rows(N, first, Hq)) {
         const int nqt128 = (int)((N + 127) / 128);
         hipLaunchKernelGGL((attn_fwd64_kernel<true, 0, 1>), dim3((unsigned)((nqt128 - (int)(first / 128)) * Hq)), dim3(256), SMEM, s,
                            q, k, vt, ldv, o, (int)N, Hq, Hkv, sc_log2e, nqt128, hpx, nullptr, rows);
@@ -1314,6 +1329,10 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
 }
 
 bool attention_mfma_uses_redo(int hd, bool q_prescaled) { return hd == 128 && !q_prescaled; }
+
+int attention_mfma_tile_rows(int64_t N, int64_t q_row0, int Hq, int hd, bool q_prescaled) {
+    return hd == 128 && q_prescaled && takes_128_rows(N, q_row0, Hq) ? 128 : 256;
+}
 
 size_t attention_mfma_redo_bytes(int64_t N, int Hq) { return (size_t)((N + 255) / 256) * (size_t)Hq * sizeof(int); }
 

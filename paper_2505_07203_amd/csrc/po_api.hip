@@ -1399,6 +1399,13 @@ po_status po_op_attention(int32_t dtype, const void* q, const void* k, const voi
     return PO_OK;
 }
 
+po_status po_attention_tile(int64_t N, int32_t Hq, int32_t Hkv, int32_t hd, int64_t q_row0, int32_t q_prescaled, int32_t* rows) {
+    if (N <= 0 || N > (int64_t)1 << 24 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || q_row0 < 0 || q_row0 >= N || !rows) return PO_ERR_INVALID_ARG;
+    if (!attention_mfma_supported(Hq, Hkv, hd)) return PO_ERR_BAD_CONFIG;
+    *rows = attention_mfma_tile_rows(N, q_row0, Hq, hd, q_prescaled != 0);
+    return PO_OK;
+}
+
 po_status po_op_attention_split(const void* q, const void* k, const void* v, void* o, void* scratch_vt, void* scratch_part,
                                 size_t part_bytes, int64_t N, int32_t Hq, int32_t Hkv, int32_t hd, int64_t q_row0,
                                 void* stream, int32_t* splits_used) {

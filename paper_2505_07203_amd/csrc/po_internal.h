@@ -107,6 +107,8 @@ void launch_v_transpose(const bf16_t* V, bf16_t* Vt, int64_t n, int kv_dim, int6
 // recomputed by the running-maximum kernel in a second launch)
 size_t attention_mfma_redo_bytes(int64_t N, int Hq);
 bool attention_mfma_uses_redo(int hd, bool q_prescaled);
+// query rows of a workgroup of launch_attention_mfma
+int attention_mfma_tile_rows(int64_t N, int64_t q_row0, int Hq, int hd, bool q_prescaled);
 // q_prescaled: q holds the rotated queries times attention_q_scale(hd) (launch_gemm_qkv_rope's q_scale); the
 // kernels then exponentiate K Q^T as it is, and recompute rows whose scores leave the range that way by themselves, each row
 // with the same bits whichever other rows the launch has.
