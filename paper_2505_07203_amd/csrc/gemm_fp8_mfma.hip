@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(NTHREADS) gemm_fp8_mfma_kernel(const GemmParam
 // slices beside the accumulators: a slice is multiplied from registers while the next one's fragments are read, so by
 // the one barrier of a slice nobody needs its LDS position any more and slice s + D is loaded there.  (The same kernel
 // on 16x16x128 MFMAs was up to 1.6 x slower: half as much work per fragment read.)  k-steps of 64 in order, as above: the
-// same bits.  Measured: down projection (N 4096, K 14336) 471 rows 143 -> 47 us (44 with turns), 2048 rows (256-row tiles) 143 -> 99,
+// same bits.  Measured: down projection (N 4096, K 14336) 471 rows 143 -> 48 us (46 with turns), 2048 rows (256-row tiles) 143 -> 99,
 // 2.4 PFLOP/s.
 template <int EPI, int MR, int D, bool TURNS>
 __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams p) {
@@ -428,18 +428,24 @@ void launch_small_t(const GemmParams& p, hipStream_t s, int splits) {
                        s, p);
 }
 
+// Turns (see takes_turns of the bf16 kernels), for a launch of M rows in tiles of 64 mr rows, K per split.  Measured like those,
+// on 355 launches, weights from HBM, time with turns against without: 64 rows per tile from five row tiles on, the last a quarter
+// full, -13 to 0 %, but -4 to +8 with fewer than 40 slices, which end before a lead of ten pays; two to four row tiles -9 to +26;
+// 128 rows with the last tile two fifths full -21 to 0, emptier -6 to +7; 192 rows, whose ring would be a slice shorter with turns,
+// -10 to +4 with the last tile two thirds full, emptier -1 to +16, never taken; 256 rows -1 to +11, never.  K splits are no
+// different (128 rows where taken -9 and -7).  Weights in the memory-side cache: 64 rows +10 to +30 where taken, 128 rows -5 to +10.
+bool takes_turns(int mr, int64_t M, int K) {
+    const int64_t rows = 64 * mr, mt = (M + rows - 1) / rows, last = M - (mt - 1) * rows;
+    if (mr == 1) return mt >= 5 && 4 * last >= rows && K >= 40 * BKB;
+    return mr == 2 && mt >= 3 && 5 * last >= 2 * rows;
+}
+
 // DT: ring depth with turns (a ring that fills the LDS leaves no room for where touches go)
 template <int EPI, int MR, int D, int DT>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 64 * MR - 1) / (64 * MR);
     p.nt = (p.N + 127) / 128;
-    // Turns (see the bf16 small kernel; us without / with, 70 .. 2000 rows): 64 rows per tile from five row tiles on (down
-    // projection of the 8B shape, 471 rows 49 / 44; two tiles 45 / 54), 128 rows with four, the last nearly half full (600 rows 66 /
-    // 57; O projection of the 32B shape 33 / 28; last tile 3 % full 56 / 59).  192 rows gain or lose by the size (1100 rows 78 /
-    // 72, 1500 rows 87 / 94), 256 rows lose 3-8 %, and K 27648 loses 4-8 % in every tile.
-    const int last = p.M - (p.mt - 1) * 64 * MR;                       // rows of the last row tile
-    const bool turns = p.K <= 16384 && (MR == 1 ? p.mt >= 5 : MR == 2 && p.mt >= 4 && 9 * last >= 4 * 128);
-    if (MR <= 2 && turns) launch_small_t<EPI, MR, MR <= 2 ? DT : D, MR <= 2>(p, s, splits);
+    if (MR <= 2 && takes_turns(MR, p.M, p.K)) launch_small_t<EPI, MR, MR <= 2 ? DT : D, MR <= 2>(p, s, splits);
     else launch_small_t<EPI, MR, D, false>(p, s, splits);
 }
 
@@ -475,13 +481,14 @@ GemmParams base_params(const unsigned char* A, int64_t lda, const float* sa, con
 // K must be a multiple of 128 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_fp8_supported(int N, int K) { return K > 0 && K % 128 == 0 && N > 0 && N % 64 == 0; }
 
-int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols) {
+int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns) {
     GemmParams p = base_params(nullptr, K, nullptr, nullptr, K, nullptr, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
     const TileForm& t = FORMS[pick_form(TILES, p, splits)];
     *rows = t.bm;
     *cols = t.bn;
+    *turns = t.bn == 128 && takes_turns(t.bm / 64, M, p.K);
     return splits;
 }
 

@@ -215,8 +215,7 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 // into LDS that nobody reads), waits for HBM that once, and all others find them in L2.  (Every tile touching its share of
 // every slice helps nobody: then each of them waits for HBM every slice.)
 // A touch out of turn is skipped by a branch (as an instruction with nothing to load it cost every slice 2-6 %).  Weights
-// that a program multiplies with over and over, without 200 MB of others between, are in the memory-side cache, and there
-// turns cost up to 20 % (down projection alone at 150 rows); a model's layers never find theirs there.
+// in the memory-side cache need no turns (see takes_turns).
 // Measured: down projection (N 4096, K 14336) at 300 rows 97 -> 80 us with the turns, 471 rows 92 -> 79 (225 on 256-row
 // tiles), 1000 rows 133 -> 117, 1 row 240 -> 76; O projection at 300 rows 30 -> 26, QKV at 1000 rows 67 -> 57.  Not kept, with and
 // without turns: one ring and one barrier per slice, whole slices of fragments in registers (no faster up to 192 rows), all
@@ -637,26 +636,35 @@ void launch_small_t(const GemmParams& p, hipStream_t s, int splits) {
                        SMEM, s, p);
 }
 
+// Turns, for a launch of M rows in tiles of 32 mu rows.  They pay where row tiles wait for weights from HBM, and how many do is a
+// matter of the last row tile's rows: a workgroup that is nearly empty, short of activations to load, runs ahead of the others
+// and fetches their weights for them (down projection of the 8B shape in 128-row tiles, us without / with turns: last tile 3 %
+// full 110 / 118, 81 % full 134 / 115).  With two row tiles the one that is not on turn has nothing left to wait for.
+// Measured on 393 launches, weights from HBM, eleven pairs of N and K between 2048 and 28672, 33 .. 2000 rows, time with turns
+// against without:
+//   up to 64 rows per tile: five row tiles and more -23 to 0 %, three or four with the last half full -15 to -4, emptier -9 to
+//     +13, two +1 to +19;
+//   96 rows: last tile half full or more -17 to +2, emptier -7 to +9;
+//   128 rows: half full or more -14 to +2, emptier -3 to +13;
+//   160 rows: three quarters full -13 to +4, emptier -4 to +12;  192 rows: -4 to +9, never taken;
+//   256 rows, with the shallowest ring: -13 to 0 whatever the rows.
+// (The +2 and +4 are launches of exactly 256 tiles.)  K splits, by the row tiles they have, are no different: two row tiles +3
+// to +17 %, 256-row tiles -3 to -8.  Weights that sit in the memory-side cache come fast enough for all, and there turns cost 2
+// to 25 %.
+bool takes_turns(int mu, int64_t M) {
+    const int64_t rows = 32 * mu, mt = (M + rows - 1) / rows, last = M - (mt - 1) * rows;
+    const bool half = 2 * last >= rows;
+    if (mu == 8) return mt > 2 || (mt == 2 && half);
+    if (mu == 6 || mt < 3) return false;
+    if (mu == 5) return 4 * last >= 3 * rows;
+    return half || (mu <= 2 && mt >= 5);
+}
+
 template <int EPI, int MU, int D>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     p.nt = (p.N + 127) / 128;
-    // Turns pay where the weights are what a tile waits for (us without / with, 40 .. 1931 rows of five projections alone and
-    // of down projections behind their gate/up).  A row tile that is nearly empty does without them what they do: its
-    // workgroup, short of activations to load, runs ahead of the others (900 rows of the down projection 106 / 118, 1000
-    // rows 135 / 117), and with two or three row tiles in all there is hardly anyone to take turns with.  So: up to 64 rows per
-    // tile from five row tiles on, 10-18 % (150 rows 84 / 70; two, the second a quarter full, 80 / 90); 96 rows with the last one
-    // two thirds full, 3-15 %, and for short K only with weight rows a multiple of 4 KiB apart (QKV + O projection, weights from
-    // the memory-side cache: 8B shape, 8 KiB, 460 rows 65 / 61; 32B shape, 10 KiB, 450 rows 96.0 / 97.6, 350 rows 87.1 / 87.6,
-    // though from HBM its O projection gains as well); 128 rows with six of them, the last half full, 2-14 %; 160 rows with the last three quarters full, 6 % (1100 rows
-    // 153 / 144; half full 137 / 170); 192 rows never (1500 rows behind their gate/up 164 / 169); 256 rows, with the
-    // shallowest ring, 4-15 %.
-    const int last = p.M - (p.mt - 1) * 32 * MU;                       // rows of the last row tile
-    const bool most = 3 * last >= 64 * MU, half = 2 * last >= 32 * MU;
-    const bool apart = MU > 3 || p.K > 8192 || p.ldw % 2048 == 0;
-    const bool turns = p.mt > 1 && apart && (MU <= 2 ? p.mt >= 5 || half : MU == 3 ? most : MU == 4 ? half && p.mt >= 6
-                                    : MU == 5 ? 4 * last >= 3 * 160 : MU == 8 && (p.mt > 2 || half));
-    if (MU != 6 && turns) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
+    if (MU != 6 && takes_turns(MU, p.M)) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
@@ -721,13 +729,14 @@ GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ld
 // K must be a multiple of 64 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_mfma_supported(int N, int K) { return K > 0 && K % 64 == 0 && N > 0 && N % 64 == 0; }
 
-int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols) {
+int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns) {
     GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
     const TileForm& t = FORMS[splits == 1 ? whole_form(p) : pick_form(TILES, p, splits)];
     *rows = t.bm;
     *cols = t.bn;
+    *turns = t.bn == 128 && !(splits == 1 && takes_strips(p)) && takes_turns(t.bm / 32, M);
     return splits;
 }
 

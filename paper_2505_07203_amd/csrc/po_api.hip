@@ -1326,12 +1326,27 @@ po_status po_op_linear(int32_t dtype, const void* a, const void* w, void* cc, co
     return PO_OK;
 }
 
-po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows, int32_t* tile_cols) {
-    if ((fp8 != 0 && fp8 != 1) || M <= 0 || !splits || *splits < 0 || *splits > 8 || !tile_rows || !tile_cols) return PO_ERR_INVALID_ARG;
+static po_status gemm_launch(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* rows, int32_t* cols, bool* turns) {
+    if ((fp8 != 0 && fp8 != 1) || M <= 0 || *splits < 0 || *splits > 8) return PO_ERR_INVALID_ARG;
     const int32_t parts = *splits > 1 ? *splits : 1;
     if (K <= 0 || K % parts || !(fp8 ? gemm_fp8_supported(N, K / parts) : gemm_mfma_supported(N, K / parts))) return PO_ERR_BAD_CONFIG;
-    *splits = (fp8 ? gemm_fp8_tile : gemm_mfma_tile)(M, N, K, *splits, tile_rows, tile_cols);
+    *splits = (fp8 ? gemm_fp8_tile : gemm_mfma_tile)(M, N, K, *splits, rows, cols, turns);
     return PO_OK;
+}
+
+po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows, int32_t* tile_cols) {
+    bool turns;
+    if (!splits || !tile_rows || !tile_cols) return PO_ERR_INVALID_ARG;
+    return gemm_launch(fp8, M, N, K, splits, tile_rows, tile_cols, &turns);
+}
+
+po_status po_gemm_turns(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t splits, int32_t* turns) {
+    int32_t rows, cols;
+    bool t = false;
+    if (!turns) return PO_ERR_INVALID_ARG;
+    const po_status st = gemm_launch(fp8, M, N, K, &splits, &rows, &cols, &t);
+    if (st == PO_OK) *turns = t;
+    return st;
 }
 
 po_status po_op_linear_split(const void* a, const void* w, void* cc, const void* residual, void* scratch,

@@ -149,9 +149,9 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
                                 int64_t n2, bool q_prescaled, hipStream_t s);
 bool gemm_mfma_supported(int N, int K);
 // block tile of a launch of `splits` K splits (0: as planned for few rows) with contiguous operands, -> splits
-// (gemm_fp8_tile: of the FP8 GEMM)
-int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols);
-int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols);
+// (gemm_fp8_tile: of the FP8 GEMM); turns: whether its row tiles take turns at fetching weights
+int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns);
+int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns);
 // Time of one bf16 GEMM launch of M rows x N columns on 256 x 256 tiles, in units of one such tile's K loop: rounds of
 // tiles over the compute units.
 double gemm_mfma_launch_cost(int64_t M, int N);

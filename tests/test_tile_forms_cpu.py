@@ -50,3 +50,21 @@ def test_arguments():
     assert ask(0, 1, 64, 1024) == B.PO_ERR_INVALID_ARG
     n.value = 2
     assert ask(0, 1, 64, 64) == B.PO_ERR_BAD_CONFIG
+    assert L.po_gemm_turns(2, 1, 64, 64, 1, B.C.byref(r)) == L.po_gemm_turns(0, 1, 64, 64, 1, None) == B.PO_ERR_INVALID_ARG
+    assert L.po_gemm_turns(0, 1, 64, 64, 2, B.C.byref(r)) == B.PO_ERR_BAD_CONFIG
+
+
+def test_turns_where_row_tiles_wait_for_weights():
+    turns = B.po_gemm_turns
+    # two row tiles, whole or as K splits, have nobody to take turns with
+    for M, N, K, splits in ((50, 4096, 4096, 1), (48, 4096, 4096, 0), (100, 4096, 14336, 0), (100, 8192, 8192, 0)):
+        assert not turns(M, N, K, splits), (M, N, K)
+    assert not any(turns(M, N, K, 0, True) for M, N, K in ((70, 5120, 5120), (100, 4096, 14336), (130, 4096, 4096)))
+    # a last row tile with few rows runs ahead of the others by itself
+    assert [turns(m, 4096, 14336) for m in (900, 1000)] == [False, True]
+    assert [turns(m, 5120, 27648, fp8=True) for m in (400, 471)] == [False, True]
+    # whatever the pitch of the weight rows and the length of K
+    for N, K in ((4096, 4096), (5120, 5120), (3072, 3072), (5120, 27648)):
+        assert all(turns(m, N, K) for m in (150, 300, 471, 540)), (N, K)
+    # FP8 tiles of 64 rows: from 40 slices on
+    assert [turns(300, K, K, fp8=True) for K in (3072, 4096, 5120)] == [False, False, True]
