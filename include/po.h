@@ -432,9 +432,12 @@ po_status po_op_attention_split_prefix(const void* dev_q, const void* dev_k, con
  * (a split sum is rounded differently). */
 po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows,
                        int32_t* tile_cols);
-/* Whether the row tiles of that launch take turns at fetching weights from memory ahead of their use (1) or not (0).  Host
- * only.  Changes no result. */
-po_status po_gemm_turns(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t splits, int32_t* turns);
+/* Whether the row tiles of that launch take turns at fetching weights from memory ahead of their use (1) or not (0): as an
+ * operator (model null), or as part of a request to the model.  Turns are for weights in HBM: a model whose weights stay in the
+ * 256 MiB memory-side cache from one request to the next takes none.  An operator cannot know and expects its weights in
+ * HBM; a program that multiplies with the same few matrices over and over waits up to a quarter longer for them than
+ * without turns, where weights from HBM come up to a fifth sooner.  Host only.  Changes no result. */
+po_status po_gemm_turns(const po_model_config* model, int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t splits, int32_t* turns);
 
 /* Rotary embedding in place on x [N, H, hd] for positions 0..N-1 (angles formed in
  * double precision). */

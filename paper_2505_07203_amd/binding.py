@@ -123,7 +123,7 @@ def lib() -> C.CDLL:
                                                C.POINTER(i32)]
     L.po_attention_tile.argtypes = [i64, i32, i32, i32, i64, i32, C.POINTER(i32)]
     L.po_gemm_tile.argtypes = [i32, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
-    L.po_gemm_turns.argtypes = [i32, i64, i32, i32, i32, C.POINTER(i32)]
+    L.po_gemm_turns.argtypes = [C.POINTER(ModelConfigC), i32, i64, i32, i32, i32, C.POINTER(i32)]
     L.po_op_linear_fp8_split.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_linear_split.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_gate_up_silu.argtypes = [i32, vp, vp, vp, vp, i64, i32, i32, vp]
@@ -454,10 +454,12 @@ def po_gemm_tile(M: int, N: int, K: int, splits: int = 1, fp8: bool = False):
     return r.value, c.value, n.value
 
 
-def po_gemm_turns(M: int, N: int, K: int, splits: int = 1, fp8: bool = False):
-    """whether the row tiles of that launch take turns at fetching weights; needs no GPU"""
+def po_gemm_turns(M: int, N: int, K: int, splits: int = 1, fp8: bool = False, model=None):
+    """whether the row tiles of that launch, as an operator or in a request to a model, take turns at fetching weights;
+    needs no GPU"""
     t = C.c_int32(0)
-    check(lib().po_gemm_turns(1 if fp8 else 0, M, N, K, splits, C.byref(t)))
+    cc = None if model is None else C.byref(config_c(model))
+    check(lib().po_gemm_turns(cc, 1 if fp8 else 0, M, N, K, splits, C.byref(t)))
     return bool(t.value)
 
 

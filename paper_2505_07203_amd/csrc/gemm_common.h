@@ -37,6 +37,7 @@ struct GemmParams {
     const float* sw;
     float q_scale;       // EPI_QKV_ROPE: factor on the rotated Q values before they are rounded (1, or the softmax
                          // scale in log2 units when the attention kernel expects Q scaled; K and V are never scaled)
+    bool w_cached;       // (launchers) the weights are expected in the memory-side cache
 };
 
 // g * sigmoid(g).  The reciprocal is the hardware's (v_rcp_f32, 1 ulp) instead of an IEEE division: the division expands

@@ -445,7 +445,7 @@ template <int EPI, int MR, int D, int DT>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 64 * MR - 1) / (64 * MR);
     p.nt = (p.N + 127) / 128;
-    if (MR <= 2 && takes_turns(MR, p.M, p.K)) launch_small_t<EPI, MR, MR <= 2 ? DT : D, MR <= 2>(p, s, splits);
+    if (MR <= 2 && !p.w_cached && takes_turns(MR, p.M, p.K)) launch_small_t<EPI, MR, MR <= 2 ? DT : D, MR <= 2>(p, s, splits);
     else launch_small_t<EPI, MR, D, false>(p, s, splits);
 }
 
@@ -481,22 +481,23 @@ GemmParams base_params(const unsigned char* A, int64_t lda, const float* sa, con
 // K must be a multiple of 128 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_fp8_supported(int N, int K) { return K > 0 && K % 128 == 0 && N > 0 && N % 64 == 0; }
 
-int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns) {
+int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool w_cached, bool* turns) {
     GemmParams p = base_params(nullptr, K, nullptr, nullptr, K, nullptr, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
     const TileForm& t = FORMS[pick_form(TILES, p, splits)];
     *rows = t.bm;
     *cols = t.bn;
-    *turns = t.bn == 128 && takes_turns(t.bm / 64, M, p.K);
+    *turns = t.bn == 128 && !w_cached && takes_turns(t.bm / 64, M, p.K);
     return splits;
 }
 
 void launch_gemm_fp8(int epi, const unsigned char* A, int64_t lda, const float* sa, const unsigned char* W, int64_t ldw,
                      const float* sw, bf16_t* C, int64_t ldc, const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M,
-                     int N, int K, hipStream_t s) {
+                     int N, int K, hipStream_t s, bool w_cached) {
     if (M <= 0 || N <= 0) return;
     GemmParams p = base_params(A, lda, sa, W, ldw, sw, M, N, K);
+    p.w_cached = w_cached;
     p.bias = bias; p.R = R; p.ldr = ldr; p.dst = C; p.ld = ldc;
     switch (epi) {
         case EPI_STORE: launch_t<EPI_STORE>(p, s); break;
@@ -510,10 +511,11 @@ void launch_gemm_fp8(int epi, const unsigned char* A, int64_t lda, const float* 
 // of the bf16 GEMM finish them.  epi: EPI_RESIDUAL (C = sum + R) or EPI_SILU_MUL (C = H [M, N / 2]).
 int launch_gemm_fp8_splitk(int epi, const unsigned char* A, int64_t lda, const float* sa, const unsigned char* W,
                            int64_t ldw, const float* sw, bf16_t* C, int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M,
-                           int N, int K, float* part, size_t part_bytes, hipStream_t s) {
+                           int N, int K, float* part, size_t part_bytes, hipStream_t s, bool w_cached) {
     if (M <= 0 || !gemm_fp8_supported(N, K) || (epi != EPI_RESIDUAL && epi != EPI_SILU_MUL)) return 0;
     if (epi == EPI_RESIDUAL && ((N & 7) || (ldc & 7) || (ldr & 7))) return 0;
     GemmParams p = base_params(A, lda, sa, W, ldw, sw, M, N, K);
+    p.w_cached = w_cached;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -530,10 +532,11 @@ int launch_gemm_fp8_qkv_rope_splitk(const unsigned char* A, int64_t lda, const f
                                     int64_t ldw, const float* sw, const bf16_t* bias, bf16_t* Q, bf16_t* Kd, bf16_t* Vt,
                                     int64_t ldv, const float* rope_cos, const float* rope_sin, int64_t pos0,
                                     const int32_t* row_pos, int64_t M, int qd, int kvd, int hd, int K, float q_scale,
-                                    float* part, size_t part_bytes, hipStream_t s) {
+                                    float* part, size_t part_bytes, hipStream_t s, bool w_cached) {
     const int N = qd + 2 * kvd;
     if (M <= 0 || !gemm_fp8_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
     GemmParams p = base_params(A, lda, sa, Wqkv, ldw, sw, M, N, K);
+    p.w_cached = w_cached;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -552,9 +555,10 @@ int launch_gemm_fp8_qkv_rope_splitk(const unsigned char* A, int64_t lda, const f
 void launch_gemm_fp8_qkv_rope(const unsigned char* A, int64_t lda, const float* sa, const unsigned char* Wqkv, int64_t ldw,
                               const float* sw, const bf16_t* bias, bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv,
                               const float* rope_cos, const float* rope_sin, int64_t pos0, const int32_t* row_pos,
-                              int64_t M, int qd, int kvd, int hd, int K, float q_scale, hipStream_t s) {
+                              int64_t M, int qd, int kvd, int hd, int K, float q_scale, hipStream_t s, bool w_cached) {
     if (M <= 0) return;
     GemmParams p = base_params(A, lda, sa, Wqkv, ldw, sw, M, qd + 2 * kvd, K);
+    p.w_cached = w_cached;
     p.q_scale = q_scale;
     p.bias = bias; p.dst = Q; p.dst_k = Kd; p.dst_vt = Vt; p.ldv = ldv;
     p.rope_cos = rope_cos; p.rope_sin = rope_sin; p.pos0 = pos0; p.row_pos = row_pos;

@@ -650,7 +650,7 @@ void launch_small_t(const GemmParams& p, hipStream_t s, int splits) {
 //   256 rows, with the shallowest ring: -13 to 0 whatever the rows.
 // (The +2 and +4 are launches of exactly 256 tiles.)  K splits, by the row tiles they have, are no different: two row tiles +3
 // to +17 %, 256-row tiles -3 to -8.  Weights that sit in the memory-side cache come fast enough for all, and there turns cost 2
-// to 25 %.
+// to 25 %: a model that stays in it takes none (w_cached); an operator by itself does not know and goes by weights from HBM.
 bool takes_turns(int mu, int64_t M) {
     const int64_t rows = 32 * mu, mt = (M + rows - 1) / rows, last = M - (mt - 1) * rows;
     const bool half = 2 * last >= rows;
@@ -664,7 +664,7 @@ template <int EPI, int MU, int D>
 void launch_small(GemmParams p, hipStream_t s, int splits) {
     p.mt = (p.M + 32 * MU - 1) / (32 * MU);
     p.nt = (p.N + 127) / 128;
-    if (MU != 6 && takes_turns(MU, p.M)) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
+    if (MU != 6 && !p.w_cached && takes_turns(MU, p.M)) launch_small_t<EPI, MU, D, MU != 6>(p, s, splits);
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
@@ -729,23 +729,24 @@ GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ld
 // K must be a multiple of 64 (whole slices), N of 64 (the epilogues work on 64-column patches).
 bool gemm_mfma_supported(int N, int K) { return K > 0 && K % 64 == 0 && N > 0 && N % 64 == 0; }
 
-int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns) {
+int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool w_cached, bool* turns) {
     GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
     const TileForm& t = FORMS[splits == 1 ? whole_form(p) : pick_form(TILES, p, splits)];
     *rows = t.bm;
     *cols = t.bn;
-    *turns = t.bn == 128 && !(splits == 1 && takes_strips(p)) && takes_turns(t.bm / 32, M);
+    *turns = t.bn == 128 && !w_cached && !(splits == 1 && takes_strips(p)) && takes_turns(t.bm / 32, M);
     return splits;
 }
 
 double gemm_mfma_launch_cost(int64_t M, int N) { return (double)((form_tiles(FORMS[0], M, N) + 255) / 256); }
 
 void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C, int64_t ldc,
-                      const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s) {
+                      const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s, bool w_cached) {
     if (M <= 0 || N <= 0) return;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    p.w_cached = w_cached;
     p.bias = bias; p.R = R; p.ldr = ldr; p.dst = C; p.ld = ldc;
     switch (epi) {
         case EPI_STORE: launch_t<EPI_STORE>(p, s); break;
@@ -825,10 +826,11 @@ void launch_splitk_reduce_qkv(const float* part, int splits, const GemmParams& r
 int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                                 bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                                 const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd, int kvd,
-                                int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s) {
+                                int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s, bool w_cached) {
     const int N = qd + 2 * kvd;
     if (M <= 0 || !gemm_mfma_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
     GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K);
+    p.w_cached = w_cached;
     if (takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
@@ -846,9 +848,10 @@ int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv
 }
 
 int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* H, int64_t ldh,
-                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s) {
+                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s, bool w_cached) {
     if (M <= 0 || !gemm_mfma_supported(N, K)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    p.w_cached = w_cached;
     if (takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
@@ -863,9 +866,10 @@ int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, 
 
 int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C,
                                      int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M, int N, int K,
-                                     float* part, size_t part_bytes, bool must, hipStream_t s) {
+                                     float* part, size_t part_bytes, bool must, hipStream_t s, bool w_cached) {
     if (M <= 0 || N <= 0 || !gemm_mfma_supported(N, K) || (N & 7) || (ldc & 7) || (ldr & 7)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
+    p.w_cached = w_cached;
     if (!must && takes_strips(p)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, must);
     if (splits < 2) return 0;
@@ -881,9 +885,10 @@ int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t*
 void launch_gemm_qkv_rope(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                           bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                           const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd, int kvd,
-                          int hd, int K, float q_scale, hipStream_t s) {
+                          int hd, int K, float q_scale, hipStream_t s, bool w_cached) {
     if (M <= 0) return;
     GemmParams p = base_params(A, lda, Wqkv, ldw, M, qd + 2 * kvd, K);
+    p.w_cached = w_cached;
     p.q_scale = q_scale;
     p.bias = bias; p.dst = Q; p.dst_k = Kd; p.dst_vt = Vt; p.ldv = ldv;
     p.rope_cos = rope_cos; p.rope_sin = rope_sin; p.pos0 = pos0; p.row_pos = row_pos;

@@ -71,8 +71,9 @@ enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SILU_MUL = 2, EPI_QKV_ROPE = 3, EPI_
 //   EPI_STORE    : C = acc (+ bias[N], bf16)
 //   EPI_RESIDUAL : C = acc + R  (added in fp32; R may alias C)
 //   EPI_SILU_MUL : W rows interleaved gate/up in blocks of 32; C[M, N/2] = silu(gate) * up
+// w_cached (here and below): the weights are expected in the memory-side cache, not in HBM.  Changes no result.
 void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C, int64_t ldc,
-                      const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s);
+                      const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s, bool w_cached = false);
 // Fused QKV projection: [Q|K|V] = A Wqkv^T (+bias), rotary embedding applied to Q and K in
 // the fp32 epilogue, V written transposed.  Wqkv (and bias) rows must be in the packed order
 // of launch_pack_rope_rows.  Q, K point at the first row of this call (row stride qd / kvd);
@@ -84,7 +85,7 @@ void launch_gemm_mfma(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, in
 void launch_gemm_qkv_rope(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                           bf16_t* Q, bf16_t* K, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                           const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd, int kvd,
-                          int hd, int Kdim, float q_scale, hipStream_t s);
+                          int hd, int Kdim, float q_scale, hipStream_t s, bool w_cached = false);
 // the softmax scale in log2 units: p = exp2(q_scaled . k) = exp(q . k / sqrt(hd))
 static inline float attention_q_scale(int hd) { return (float)(1.4426950408889634 / sqrt((double)hd)); }
 // In place: within every head of `hd` rows (hd == 128 only; hd == 64 is already in order)
@@ -150,8 +151,8 @@ int launch_attention_mfma_split(const bf16_t* q, const bf16_t* k, const bf16_t* 
 bool gemm_mfma_supported(int N, int K);
 // block tile of a launch of `splits` K splits (0: as planned for few rows) with contiguous operands, -> splits
 // (gemm_fp8_tile: of the FP8 GEMM); turns: whether its row tiles take turns at fetching weights
-int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns);
-int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool* turns);
+int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool w_cached, bool* turns);
+int gemm_fp8_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bool w_cached, bool* turns);
 // Time of one bf16 GEMM launch of M rows x N columns on 256 x 256 tiles, in units of one such tile's K loop: rounds of
 // tiles over the compute units.
 double gemm_mfma_launch_cost(int64_t M, int N);
@@ -167,13 +168,13 @@ double gemm_mfma_launch_cost(int64_t M, int N);
 int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv, int64_t ldw, const bf16_t* bias,
                                 bf16_t* Q, bf16_t* Kd, bf16_t* Vt, int64_t ldv, const float* rope_cos,
                                 const float* rope_sin, int64_t pos0, const int32_t* row_pos, int64_t M, int qd,
-                                int kvd, int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s);
+                                int kvd, int hd, int K, float q_scale, float* part, size_t part_bytes, hipStream_t s, bool w_cached = false);
 // launch_gemm_mfma(EPI_SILU_MUL) the same way; part must not overlap H's rows [0, M)
 int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* H, int64_t ldh,
-                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s);
+                                 int64_t M, int N, int K, float* part, size_t part_bytes, hipStream_t s, bool w_cached = false);
 int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, bf16_t* C,
                                      int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M, int N, int K,
-                                     float* part, size_t part_bytes, bool must, hipStream_t s);
+                                     float* part, size_t part_bytes, bool must, hipStream_t s, bool w_cached = false);
 
 // ---- FP8-dynamic linear layers (OCP E4M3 codes + float32 scales) -----------------------------------
 // rows of bf16 -> codes + one scale per row; source row r goes to destination row
@@ -186,21 +187,21 @@ void launch_quant_rows(const bf16_t* x, int64_t ldx, unsigned char* q, int64_t l
 bool gemm_fp8_supported(int N, int K);
 void launch_gemm_fp8(int epi, const unsigned char* A, int64_t lda, const float* sa, const unsigned char* W, int64_t ldw,
                      const float* sw, bf16_t* C, int64_t ldc, const bf16_t* bias, const bf16_t* R, int64_t ldr, int64_t M,
-                     int N, int K, hipStream_t s);
+                     int N, int K, hipStream_t s, bool w_cached = false);
 void launch_gemm_fp8_qkv_rope(const unsigned char* A, int64_t lda, const float* sa, const unsigned char* Wqkv, int64_t ldw,
                               const float* sw, const bf16_t* bias, bf16_t* Q, bf16_t* K, bf16_t* Vt, int64_t ldv,
                               const float* rope_cos, const float* rope_sin, int64_t pos0, const int32_t* row_pos,
-                              int64_t M, int qd, int kvd, int hd, int Kdim, float q_scale, hipStream_t s);
+                              int64_t M, int qd, int kvd, int hd, int Kdim, float q_scale, hipStream_t s, bool w_cached = false);
 // split-K forms of the two above for launches with few rows (see launch_gemm_mfma_splitk_residual): return the
 // number of splits used, 0 = nothing launched (not worth it, or part_bytes of scratch too small)
 int launch_gemm_fp8_splitk(int epi, const unsigned char* A, int64_t lda, const float* sa, const unsigned char* W,
                            int64_t ldw, const float* sw, bf16_t* C, int64_t ldc, const bf16_t* R, int64_t ldr, int64_t M,
-                           int N, int K, float* part, size_t part_bytes, hipStream_t s);
+                           int N, int K, float* part, size_t part_bytes, hipStream_t s, bool w_cached = false);
 int launch_gemm_fp8_qkv_rope_splitk(const unsigned char* A, int64_t lda, const float* sa, const unsigned char* Wqkv,
                                     int64_t ldw, const float* sw, const bf16_t* bias, bf16_t* Q, bf16_t* Kd, bf16_t* Vt,
                                     int64_t ldv, const float* rope_cos, const float* rope_sin, int64_t pos0,
                                     const int32_t* row_pos, int64_t M, int qd, int kvd, int hd, int K, float q_scale,
-                                    float* part, size_t part_bytes, hipStream_t s);
+                                    float* part, size_t part_bytes, hipStream_t s, bool w_cached = false);
 // q, scales = quantise(bf16(rmsnorm(x; g)))   (d % 8 == 0, d <= 8192)
 void launch_rmsnorm_quant(const bf16_t* x, const bf16_t* g, unsigned char* q, float* scales, int64_t rows, int d,
                           float eps, hipStream_t s);

@@ -50,8 +50,8 @@ def test_arguments():
     assert ask(0, 1, 64, 1024) == B.PO_ERR_INVALID_ARG
     n.value = 2
     assert ask(0, 1, 64, 64) == B.PO_ERR_BAD_CONFIG
-    assert L.po_gemm_turns(2, 1, 64, 64, 1, B.C.byref(r)) == L.po_gemm_turns(0, 1, 64, 64, 1, None) == B.PO_ERR_INVALID_ARG
-    assert L.po_gemm_turns(0, 1, 64, 64, 2, B.C.byref(r)) == B.PO_ERR_BAD_CONFIG
+    assert L.po_gemm_turns(None, 2, 1, 64, 64, 1, B.C.byref(r)) == L.po_gemm_turns(None, 0, 1, 64, 64, 1, None) == B.PO_ERR_INVALID_ARG
+    assert L.po_gemm_turns(None, 0, 1, 64, 64, 2, B.C.byref(r)) == B.PO_ERR_BAD_CONFIG
 
 
 def test_turns_where_row_tiles_wait_for_weights():
@@ -68,3 +68,14 @@ def test_turns_where_row_tiles_wait_for_weights():
         assert all(turns(m, N, K) for m in (150, 300, 471, 540)), (N, K)
     # FP8 tiles of 64 rows: from 40 slices on
     assert [turns(300, K, K, fp8=True) for K in (3072, 4096, 5120)] == [False, False, True]
+
+
+def test_no_turns_in_a_model_whose_weights_stay_in_the_memory_side_cache():
+    at = lambda **k: I.LLAMA8B.replace(dtype=k.pop("dtype", I.BF16), **k)
+    turns = lambda cfg: B.po_gemm_turns(300, 4096, 4096, model=cfg)
+    small = dict(d_model=1024, n_q_heads=8, n_kv_heads=2, ffn_dim=4096)           # 31.5 MB a layer
+    assert B.po_gemm_turns(300, 4096, 4096) and turns(at())
+    for vocab, layers, cached in ((4096, 7, True), (4096, 8, False), (100000, 2, False), (100000, 0, True)):
+        assert turns(at(n_layers=layers, vocab_size=vocab, **small)) != cached
+    fp8 = at(n_layers=12, vocab_size=4096, dtype=I.BF16_FP8, **small)
+    assert not B.po_gemm_turns(471, 5120, 5120, fp8=True, model=fp8) and B.po_gemm_turns(471, 5120, 5120, fp8=True)
