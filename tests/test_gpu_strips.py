@@ -2,6 +2,7 @@
 weights: the bits of every other launch."""
 import pytest
 
+import test_gpu_small_tiles as T
 from paper_2505_07203_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -47,28 +48,75 @@ def test_few_qkv_rows_are_the_bits_of_a_larger_launch(cfg, K, bias):
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
 
 
-@pytest.mark.parametrize("N,K", [(4096, 128), (4096, 192), (4096, 1088), (2112, 4096)])
+# Launches whose row tiles take turns: odd numbers of slices, of which the short ones (11 and 17 of 64, 9 of 128) end within
+# the first turns; a last column tile of 64.  test_tile_forms_cpu.py holds them to reaching every tile that takes turns.
+TURNS_TOP = 8192                # rows of the launch they are compared with, which takes none
+TURNS_ROWS = (81, 150, 170, 250, 300, 384, 471, 512, 540, 620, 780, 840, 1000, 1100, 1240, 1400, 1600, 1800, 2000, 2200)
+TURNS_BF16 = [(4096, 704), (4096, 1088), (2112, 4160)]
+TURNS_QKV = [(I.LLAMA8B, 704), (I.LLAMA8B, 4160)]
+TURNS_FP8 = [(4096, 1152), (4096, 5248), (2112, 5248)]
+TURNS_FP8_QKV = (I.LLAMA8B, 5248)
+TURNS_SPLIT = [(81, 320, 4224), (162, 320, 1408), (465, 2112, 4224), (381, 2112, 2816), (450, 2112, 14336), (771, 1024, 14336)]
+TURNS_FP8_SPLIT = [(273, 320, 10496), (705, 1024, 14336)]
+
+
+@pytest.mark.parametrize("N,K", TURNS_BF16)
 def test_turns_are_the_bits_of_a_launch_without(N, K):
-    """Heights whose row tiles take turns: fewer slices than a turn is ahead, odd numbers of slices, a last column tile of 64."""
     import torch
     from paper_2505_07203_amd import binding as B
     rnd = _rnd(N * K)
-    a, r, w = rnd(8192, K), rnd(8192, N), rnd(N, K) * 0.05
-    whole = B.po_op_linear(a, w, residual=r)
+    a, r, w = rnd(TURNS_TOP, K), rnd(TURNS_TOP, N), rnd(N, K) * 0.05
+    whole = B.po_op_linear(a, w, residual=r), B.po_op_gate_up_silu(a, w)
     ref, size = a.double() @ w.double().t() + r.double(), a.double().abs() @ w.double().abs().t()
-    assert bool(((whole.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + K * 2.0 ** -22 * size).all())
-    for m in (64, 129, 160, 300, 471, 540, 1000, 1024, 1100, 1280, 1800, 2000):
-        assert torch.equal(B.po_op_linear(a[:m].contiguous(), w, residual=r[:m].contiguous()), whole[:m]), m
+    assert bool(((whole[0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + K * 2.0 ** -22 * size).all())
+    for m in TURNS_ROWS:
+        x = a[:m].contiguous()
+        assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole[0][:m]), m
+        assert torch.equal(B.po_op_gate_up_silu(x, w), whole[1][:m]), m
 
 
-@pytest.mark.parametrize("N,K", [(4096, 128), (4096, 384), (4096, 1152), (2112, 4096)])
+@pytest.mark.parametrize("cfg,K", TURNS_QKV)
+def test_qkv_turns_are_the_bits_of_a_launch_without(cfg, K):
+    import torch
+    from paper_2505_07203_amd import binding as B
+    hq, hkv, hd = cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim
+    rnd = _rnd(K + 1)
+    a, w, b = rnd(TURNS_TOP, K), rnd((hq + 2 * hkv) * hd, K) * 0.05, rnd((hq + 2 * hkv) * hd)
+    cos, sin = B.po_op_rope_table(TURNS_TOP, hd, cfg.rope_theta)
+    q, k, vt = B.po_op_qkv_rope(a, w, b, cos, sin, hq, hkv, hd)
+    for m in TURNS_ROWS:
+        q1, k1, vt1 = B.po_op_qkv_rope(a[:m].contiguous(), w, b, cos, sin, hq, hkv, hd)
+        assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("N,K", TURNS_FP8)
 def test_fp8_turns_are_the_bits_of_a_launch_without(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
     rnd = _rnd(N * K + 1)
-    r = rnd(8192, N)
-    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(8192, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
-    whole = B.po_op_linear_fp8(qa, sa, qw, sw, residual=r)
-    for m in (64, 200, 300, 400, 471, 512, 600, 768, 1000, 1024):
+    r = rnd(TURNS_TOP, N)
+    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(TURNS_TOP, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
+    whole = B.po_op_linear_fp8(qa, sa, qw, sw, residual=r), B.po_op_linear_fp8(qa, sa, qw, sw, silu_mul=True)
+    for m in TURNS_ROWS:
         x, s = qa[:m].contiguous(), sa[:m].contiguous()
-        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole[:m]), m
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole[0][:m]), m
+        assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, silu_mul=True), whole[1][:m]), m
+
+
+def test_fp8_qkv_turns_are_the_bits_of_a_launch_without():
+    import torch
+    from paper_2505_07203_amd import binding as B
+    cfg, K = TURNS_FP8_QKV
+    hq, hkv, hd = cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim
+    rnd = _rnd(K + 2)
+    (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(TURNS_TOP, K)), B.po_op_quantize_rows(rnd((hq + 2 * hkv) * hd, K) * 0.05)
+    cos, sin = B.po_op_rope_table(TURNS_TOP, hd, cfg.rope_theta)
+    q, k, vt = B.po_op_qkv_rope_fp8(qa, sa, qw, sw, None, cos, sin, hq, hkv, hd)
+    for m in TURNS_ROWS:
+        q1, k1, vt1 = B.po_op_qkv_rope_fp8(qa[:m].contiguous(), sa[:m].contiguous(), qw, sw, None, cos, sin, hq, hkv, hd)
+        assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("M,N,K,fp8", [(*x, False) for x in TURNS_SPLIT] + [(*x, True) for x in TURNS_FP8_SPLIT])
+def test_split_sums_with_turns_against_float64(M, N, K, fp8):
+    T.test_split_sums_in_every_tile_against_float64(M, N, K, fp8)

@@ -3,6 +3,7 @@ sizes): a refit of its constants that moved a tile out of the tests' sizes fails
 import pytest
 
 import test_gpu_small_tiles as T
+import test_gpu_strips as S
 from paper_2505_07203_amd import binding as B
 from paper_2505_07203_amd import inputs as I
 
@@ -79,3 +80,21 @@ def test_no_turns_in_a_model_whose_weights_stay_in_the_memory_side_cache():
         assert turns(at(n_layers=layers, vocab_size=vocab, **small)) != cached
     fp8 = at(n_layers=12, vocab_size=4096, dtype=I.BF16_FP8, **small)
     assert not B.po_gemm_turns(471, 5120, 5120, fp8=True, model=fp8) and B.po_gemm_turns(471, 5120, 5120, fp8=True)
+
+
+def test_launches_of_the_gpu_tests_take_turns_in_every_tile():
+    """... and are compared with launches that do not"""
+    def reached(shapes, fp8=False):
+        assert not any(B.po_gemm_turns(S.TURNS_TOP, N, K, 1, fp8) for N, K in shapes)
+        return {B.po_gemm_tile(m, N, K, 1, fp8)[0] for N, K in shapes for m in S.TURNS_ROWS if B.po_gemm_turns(m, N, K, 1, fp8)}
+
+    def split(launches, fp8=False):
+        assert all(B.po_gemm_turns(*x, 0, fp8) and B.po_gemm_tile(*x, 0, fp8)[2] > 1 for x in launches)
+        return {B.po_gemm_tile(*x, 0, fp8)[0] for x in launches}
+
+    low = {32, 64, 96, 128, 160, 256}
+    assert reached(S.TURNS_BF16[1:2]) == reached(S.TURNS_BF16[2:] + S.TURNS_BF16[:1]) == low
+    assert reached([(qkv_columns(c), K) for c, K in S.TURNS_QKV]) == split(S.TURNS_SPLIT) == low
+    cfg, K = S.TURNS_FP8_QKV
+    assert reached(S.TURNS_FP8, True) == reached([(qkv_columns(cfg), K)], True) == split(S.TURNS_FP8_SPLIT, True) == {64, 128}
+    assert all(K // 64 % 2 for _, K in S.TURNS_BF16 + S.TURNS_QKV) and all(K // 128 % 2 for _, K in S.TURNS_FP8)
