@@ -439,6 +439,11 @@ po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* sp
  * without turns, where weights from HBM come up to a fifth sooner.  Host only.  Changes no result. */
 po_status po_gemm_turns(const po_model_config* model, int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t splits, int32_t* turns);
 
+/* The rows, and columns, of the block tile that a float32 launch on the matrix instruction takes, with contiguous operands
+ * on 16-byte boundaries and K a multiple of 4: of po_op_linear or po_op_gate_up_silu (N = 2 F; rope_head_dim 0), or of a
+ * request's QKV projection with rotation (64 or 128).  Host only.  The tile changes no result. */
+po_status po_gemm_f32_tile(int64_t M, int32_t N, int32_t K, int32_t rope_head_dim, int32_t* tile);
+
 /* Rotary embedding in place on x [N, H, hd] for positions 0..N-1 (angles formed in
  * double precision). */
 po_status po_op_rope(int32_t dtype, void* dev_x, int64_t N, int32_t n_heads, int32_t head_dim,

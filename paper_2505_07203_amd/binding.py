@@ -39,7 +39,7 @@ EXPORTS = [
     "po_op_quantize_rows", "po_op_rmsnorm_quantize", "po_op_linear_fp8", "po_op_qkv_rope_fp8",
     "po_attach_kv_cache_slots", "po_kv_cache_match", "po_kv_cache_slot", "po_sched_pick_multi",
     "po_profile_jct", "po_engine_step", "po_set_few_rows_split", "po_set_storage_rounding", "po_op_linear_split", "po_sched_push_request", "po_op_attention_split",
-    "po_op_attention_split_prefix", "po_attention_tile", "po_gemm_tile", "po_gemm_turns", "po_op_linear_fp8_split",
+    "po_op_attention_split_prefix", "po_attention_tile", "po_gemm_tile", "po_gemm_turns", "po_gemm_f32_tile", "po_op_linear_fp8_split",
     "po_sched_create", "po_sched_destroy", "po_sched_set_jct_model", "po_sched_fit_jct_model", "po_sched_push",
     "po_sched_size", "po_sched_pick", "po_sched_remove", "po_op_rope_static", "po_op_mfma_peak", "po_op_stream_copy",
 ]
@@ -123,6 +123,7 @@ def lib() -> C.CDLL:
                                                C.POINTER(i32)]
     L.po_attention_tile.argtypes = [i64, i32, i32, i32, i64, i32, C.POINTER(i32)]
     L.po_gemm_tile.argtypes = [i32, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
+    L.po_gemm_f32_tile.argtypes = [i64, i32, i32, i32, C.POINTER(i32)]
     L.po_gemm_turns.argtypes = [C.POINTER(ModelConfigC), i32, i64, i32, i32, i32, C.POINTER(i32)]
     L.po_op_linear_fp8_split.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
     L.po_op_linear_split.argtypes = [vp, vp, vp, vp, vp, sz, i64, i32, i32, vp, C.POINTER(i32)]
@@ -461,6 +462,13 @@ def po_gemm_turns(M: int, N: int, K: int, splits: int = 1, fp8: bool = False, mo
     cc = None if model is None else C.byref(config_c(model))
     check(lib().po_gemm_turns(cc, 1 if fp8 else 0, M, N, K, splits, C.byref(t)))
     return bool(t.value)
+
+
+def po_gemm_f32_tile(M: int, N: int, K: int, rope_head_dim: int = 0):
+    """rows, and columns, of the block tile of a float32 launch; needs no GPU"""
+    t = C.c_int32(0)
+    check(lib().po_gemm_f32_tile(M, N, K, rope_head_dim, C.byref(t)))
+    return t.value
 
 
 def po_op_linear_split(a, w, residual, scratch_bytes=1 << 28):

@@ -514,18 +514,11 @@ static void launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, D, PAIR>), grid, dim3(256), SMEM, s, A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, qkv);
 }
 
-// false (nothing launched) when the operands do not allow 16-byte loads along K; largest: of tiles of 128, 64, 32 (0, 1, 2)
-template <int PAIR>
-static bool launch_f32(const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc, const float* bias,
-                       const float* R, int64_t ldr, int64_t M, int N, int K, const F32QkvRope& qkv, int largest, hipStream_t s) {
-    if (M <= 0 || N <= 0) return true;
-    if (K <= 0 || K % 4 || lda % 4 || ldw % 4 || ((uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)bias | (uintptr_t)R) % 16)
-        return false;
-    const int64_t ld = std::max(lda, ldw);
-    if (ld > (1 << 23)) return false;        // a tile, of 32 rows at least, is addressed with offsets below 2^30 bytes
+// Tile of a launch: 0, 1, 2 = 128, 64, 32 rows and columns; largest: the first of them that is allowed; ld: of either operand
+static int f32_tile(int64_t M, int N, int64_t ld, int largest) {
     // Tile by time: a round of 256 tiles, one per compute unit, costs this many microseconds per K slice of 32 (measured
     // on 256 .. 2048 tiles of each); where all three take one round the small tile has the shorter chain.
-    constexpr double us[3] = {1.9, 0.54, 0.2};                     // tiles of 128, 64, 32
+    constexpr double us[3] = {1.9, 0.54, 0.2};
     int best = 2;
     double best_us = 1e300;
     for (int i = largest; i < 3; ++i) {
@@ -534,6 +527,24 @@ static bool launch_f32(const float* A, int64_t lda, const float* W, int64_t ldw,
         const double t = us[i] * (double)((tiles + 255) / 256);
         if (t < best_us) { best = i; best_us = t; }
     }
+    return best;
+}
+
+// the largest tile of a launch with rotation: pairs stay within a head
+static int f32_rope_largest(int hd) { return hd == 128 ? 0 : 1; }
+
+int gemm_f32_tile(int64_t M, int N, int K, int rope_hd) { return 128 >> f32_tile(M, N, K, rope_hd ? f32_rope_largest(rope_hd) : 0); }
+
+// false (nothing launched) when the operands do not allow 16-byte loads along K; largest: of f32_tile
+template <int PAIR>
+static bool launch_f32(const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc, const float* bias,
+                       const float* R, int64_t ldr, int64_t M, int N, int K, const F32QkvRope& qkv, int largest, hipStream_t s) {
+    if (M <= 0 || N <= 0) return true;
+    if (K <= 0 || K % 4 || lda % 4 || ldw % 4 || ((uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)bias | (uintptr_t)R) % 16)
+        return false;
+    const int64_t ld = std::max(lda, ldw);
+    if (ld > (1 << 23)) return false;        // a tile, of 32 rows at least, is addressed with offsets below 2^30 bytes
+    const int best = f32_tile(M, N, ld, largest);
     if (best == 0) launch_f32_tile<4, 2, PAIR>(A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, qkv, s);
     else if (best == 1) launch_f32_tile<2, 4, PAIR>(A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, qkv, s);
     else launch_f32_tile<1, 8, PAIR>(A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, qkv, s);
@@ -560,7 +571,7 @@ bool launch_gemm_f32_qkv_rope(const float* A, int64_t lda, const float* W, int64
     if ((qkv.hd != 64 && qkv.hd != 128) || qkv.qd % qkv.hd || qkv.kvd % qkv.hd || ((int64_t)N + 128) * ldw * 4 > ((int64_t)1 << 31) ||
         ((uintptr_t)qkv.q | (uintptr_t)qkv.k | (uintptr_t)qkv.v) % 16)
         return false;
-    return launch_f32<PAIR_ROPE>(A, lda, W, ldw, nullptr, 0, bias, nullptr, 0, M, N, K, qkv, qkv.hd == 128 ? 0 : 1, s);
+    return launch_f32<PAIR_ROPE>(A, lda, W, ldw, nullptr, 0, bias, nullptr, 0, M, N, K, qkv, f32_rope_largest(qkv.hd), s);
 }
 
 }  // namespace po

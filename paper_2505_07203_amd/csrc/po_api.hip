@@ -1357,6 +1357,13 @@ po_status po_gemm_turns(const po_model_config* model, int32_t fp8, int64_t M, in
     return st;
 }
 
+po_status po_gemm_f32_tile(int64_t M, int32_t N, int32_t K, int32_t rope_head_dim, int32_t* tile) {
+    if (M <= 0 || N <= 0 || !tile || (rope_head_dim != 0 && rope_head_dim != 64 && rope_head_dim != 128)) return PO_ERR_INVALID_ARG;
+    if (K <= 0 || K % 4 || K > 1 << 23) return PO_ERR_BAD_CONFIG;
+    *tile = gemm_f32_tile(M, N, K, rope_head_dim);
+    return PO_OK;
+}
+
 po_status po_op_linear_split(const void* a, const void* w, void* cc, const void* residual, void* scratch,
                              size_t scratch_bytes, int64_t M, int32_t N, int32_t K, void* stream, int32_t* splits_used) {
     if (!a || !w || !cc || !residual || !scratch || !splits_used || M <= 0 || N <= 0 || K <= 0) return PO_ERR_INVALID_ARG;

@@ -135,6 +135,8 @@ bool launch_gemm_f32_silu(const float* A, int64_t lda, const float* W, int64_t l
                           hipStream_t s);
 bool launch_gemm_f32_mfma(const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc, const float* bias,
                           const float* R, int64_t ldr, int64_t M, int N, int K, hipStream_t s);
+// rows and columns of the tile of such a launch with contiguous operands; rope_hd: head dimension of launch_gemm_f32_qkv_rope, else 0
+int gemm_f32_tile(int64_t M, int N, int K, int rope_hd);
 // float32 attention on the float32 matrix instruction; false (nothing launched) when hd is neither 64 nor 128
 bool launch_attention_f32_mfma(const float* q, const float* k, const float* v, float* o, int64_t N, int Hq, int Hkv, int hd,
                                int64_t q_row0, hipStream_t s);

@@ -2,6 +2,7 @@
 sizes): a refit of its constants that moved a tile out of the tests' sizes fails here."""
 import pytest
 
+import test_gpu_f32_pairs as P
 import test_gpu_small_tiles as T
 import test_gpu_strips as S
 from paper_2505_07203_amd import binding as B
@@ -98,3 +99,14 @@ def test_launches_of_the_gpu_tests_take_turns_in_every_tile():
     cfg, K = S.TURNS_FP8_QKV
     assert reached(S.TURNS_FP8, True) == reached([(qkv_columns(cfg), K)], True) == split(S.TURNS_FP8_SPLIT, True) == {64, 128}
     assert all(K // 64 % 2 for _, K in S.TURNS_BF16 + S.TURNS_QKV) and all(K // 128 % 2 for _, K in S.TURNS_FP8)
+
+
+def test_float32_launches_of_the_gpu_tests_take_every_tile():
+    tile = B.po_gemm_f32_tile
+    assert [tile(M, 2 * F, K) for M, F, K in P.GATE_UP] == [32, 32, 32, 32, 64, 128]
+    of = lambda rows: [tile(rows(n), (hq + 2 * hkv) * hd, d, hd) for hd, hq, hkv, d, n in P.QKV]
+    assert of(lambda n: P.QKV_CHUNK) == [32, 32, 32]
+    assert of(lambda n: n) == [64, 64, 32] and of(lambda n: 2 * n) == [64, 128, 64]
+    f, t = B.lib().po_gemm_f32_tile, B.C.c_int32(0)
+    assert f(0, 4, 4, 0, B.C.byref(t)) == f(1, 4, 4, 32, B.C.byref(t)) == f(1, 4, 4, 0, None) == B.PO_ERR_INVALID_ARG
+    assert f(1, 4, 6, 0, B.C.byref(t)) == B.PO_ERR_BAD_CONFIG
