@@ -610,6 +610,7 @@ constexpr TileForm FORMS[] = {{256, 256, 5.9, 0.99, 1.41}, {32, 128, 3.1, 0.29, 
                               {96, 128, 2.8, 0.35, 0.47},  {128, 128, 2.7, 0.41, 0.55}, {160, 128, 3.6, 0.46, 0.63},
                               {192, 128, 3.6, 0.49, 0.70}, {256, 128, 1.0, 0.83, 0.97}, {192, 256, 3.3, 0.89, 1.15}};
 constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BK, 2};
+constexpr int STRIPS = sizeof(FORMS) / sizeof(FORMS[0]);       // not by time, see takes_strips
 
 template <int EPI, int MU>
 void launch_big(GemmParams p, hipStream_t s, int splits) {
@@ -668,7 +669,7 @@ void launch_small(GemmParams p, hipStream_t s, int splits) {
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
-// 32 x 128 tiles on at most half the compute units: in strips, also where other tiles would be faster than whole ones of 32
+// Launches of up to 16 rows that would be 32 x 128 tiles on at most half the compute units: in strips, also where other tiles would be faster than whole ones of 32
 // rows.  (gate/up of the 8B shape, 224 tiles, streams its weights at 4.9 TB/s as it is, 4.5 in strips: 48 and 52 us.)  In
 // few-rows mode too (one row of the 8B shape, us in K splits / in strips: O projection 14 / 8, down 36 / 24).
 bool takes_strips(const GemmParams& p) {
@@ -689,7 +690,7 @@ void launch_strips(const GemmParams& p, hipStream_t s) {
 
 template <int EPI>
 void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
-    if (EPI != EPI_PARTIAL && form == 1 && takes_strips(p)) {
+    if (EPI != EPI_PARTIAL && form == STRIPS) {
         constexpr int E = EPI == EPI_PARTIAL ? EPI_STORE : EPI;
         if (p.M <= 2) launch_strips<E, 1>(p, s);
         else launch_strips<E, 8>(p, s);
@@ -708,7 +709,7 @@ void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
     }
 }
 
-int whole_form(const GemmParams& p) { return takes_strips(p) ? 1 : pick_form(TILES, p, 1); }
+int whole_form(const GemmParams& p) { return takes_strips(p) ? STRIPS : pick_form(TILES, p, 1); }
 
 template <int EPI>
 void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(whole_form(p), p, s); }
@@ -733,10 +734,11 @@ int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bo
     GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
-    const TileForm& t = FORMS[splits == 1 ? whole_form(p) : pick_form(TILES, p, splits)];
-    *rows = t.bm;
-    *cols = t.bn;
-    *turns = t.bn == 128 && !w_cached && !(splits == 1 && takes_strips(p)) && takes_turns(t.bm / 32, M);
+    const int form = splits == 1 ? whole_form(p) : pick_form(TILES, p, splits);
+    const bool strips = form == STRIPS;
+    *rows = strips ? 16 : FORMS[form].bm;
+    *cols = strips ? 16 : FORMS[form].bn;
+    *turns = *cols == 128 && !w_cached && takes_turns(*rows / 32, M);
     return splits;
 }
 

@@ -9,6 +9,7 @@ from paper_2505_07203_amd import binding as B
 from paper_2505_07203_amd import inputs as I
 
 BF16 = {(r, 128) for r in (32, 64, 96, 128, 160, 192, 256)} | {(192, 256), (256, 256)}
+STRIPS = (16, 16)
 FP8 = {(r, 128) for r in (64, 128, 192, 256)} | {(256, 256)}
 
 
@@ -21,8 +22,8 @@ def tiles(shapes, fp8=False):
 
 
 def test_whole_launches():
-    assert tiles(T.BF16_SHAPES) == BF16
-    assert tiles([(qkv_columns(cfg), K) for cfg, K, _ in T.BF16_QKV]) == BF16
+    assert tiles(T.BF16_SHAPES) == BF16 | {STRIPS}
+    assert tiles([(qkv_columns(cfg), K) for cfg, K, _ in T.BF16_QKV]) == BF16 | {STRIPS}
     assert tiles(T.FP8_SHAPES, True) == FP8
     assert tiles([(qkv_columns(I.LLAMA8B), T.FP8_QKV_K)], True) == FP8
 
@@ -39,8 +40,14 @@ def test_no_launch_of_the_models_takes_another_tile(cfg):
     d, F = cfg.d_model, cfg.ffn_dim
     for N, K in ((qkv_columns(cfg), d), (d, cfg.q_dim), (2 * F, d), (d, F)):
         for splits in (0, 1):
-            assert {B.po_gemm_tile(m, N, K, splits)[:2] for m in range(1, 4400, 7)} <= BF16
+            assert {B.po_gemm_tile(m, N, K, splits)[:2] for m in range(1, 4400, 7)} <= BF16 | {STRIPS}
             assert {B.po_gemm_tile(m, N, K, splits, True)[:2] for m in range(1, 4400, 7)} <= FP8
+
+
+def test_strips():
+    tile = lambda m, N: B.po_gemm_tile(m, N, 4096)[:2]
+    assert {tile(m, N) for m in (1, 2, 3, 16) for N in (64, 4096, 16384)} == {STRIPS}
+    assert STRIPS not in {tile(17, 4096), tile(16, 16448), B.po_gemm_tile(1, 4096, 4096, 2)[:2], B.po_gemm_tile(1, 4096, 4096, 1, True)[:2]}
 
 
 def test_arguments():
