@@ -317,7 +317,8 @@ po_status po_set_lazy_last_layer(po_ctx* ctx, int32_t on);
  * few output tiles, and attention too few query tiles, to occupy the chip.  With the mode on,
  * launches of those GEMMs whose 256 x 256 tiles would fill at most half the compute units split
  * their reduction over K between workgroups where that is expected to take less time (always
- * where their tiles would fill at most a quarter of the units), and
+ * where their tiles would fill at most a quarter of the units; never bf16 launches of up to 16 rows and 16384
+ * columns, which fill the chip in strips of 16 columns), and
  * attention over at most 1024 query rows splits each query tile's keys between workgroups (fp32
  * partial results in the free part of the chunk buffer, merged in a fixed order by a second
  * kernel: deterministic; the footprint

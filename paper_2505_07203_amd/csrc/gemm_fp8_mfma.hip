@@ -397,9 +397,9 @@ __global__ void __launch_bounds__(256, 1) gemm_fp8_small_kernel(const GemmParams
     if (col_base < p.N) tile_epilogue<EPI, MR, 2>(q, acc, smem + wave * 8192, row_base, col_base, lane);
 }
 
-// Block tiles of the FP8 launches (see TileForm), fitted to 208 shapes like the bf16 ones; the pick is on average 0.2 %
-// and at most 10 % off the fastest form.  Measured, 256-row tiles against the pick: down projection (N 4096, K 14336) 1
-// row 136 -> 41 us, 471 rows 143 -> 47, 1024 rows 141 -> 72, 2048 rows 143 -> 99; gate/up 150 rows 50 -> 34.
+// Block tiles of the FP8 launches (see TileForm), fitted to 208 shapes like the bf16 ones; on 255 others, with turns, the pick
+// is on average 0.1 % and at most 5 % off the fastest form.  Measured, 256-row tiles against the pick: down projection (N 4096, K 14336) 1
+// row 136 -> 41 us, 471 rows 143 -> 46, 1000 rows 141 -> 61, 2048 rows 143 -> 99; gate/up 150 rows 50 -> 34.
 constexpr TileForm FORMS[] = {{256, 256, 10.0, 1.02, 1.54}, {64, 128, 3.0, 0.31, 0.41}, {128, 128, 4.6, 0.36, 0.59},
                               {192, 128, 6.3, 0.43, 0.73},  {256, 128, 7.7, 0.55, 0.90}};
 constexpr TileForms TILES = {FORMS, sizeof(FORMS) / sizeof(FORMS[0]), BKB, 1};

@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 // A touch out of turn is skipped by a branch (as an instruction with nothing to load it cost every slice 2-6 %).  Weights
 // in the memory-side cache need no turns (see takes_turns).
 // Measured: down projection (N 4096, K 14336) at 300 rows 97 -> 80 us with the turns, 471 rows 92 -> 79 (225 on 256-row
-// tiles), 1000 rows 133 -> 117, 1 row 240 -> 76; O projection at 300 rows 30 -> 26, QKV at 1000 rows 67 -> 57.  Not kept, with and
+// tiles), 1000 rows 133 -> 117; O projection at 300 rows 30 -> 26, QKV at 1000 rows 67 -> 57.  Not kept, with and
 // without turns: one ring and one barrier per slice, whole slices of fragments in registers (no faster up to 192 rows), all
 // loads of a slice behind the hand-over (2-8 % slower); turns in the 256 x 256 kernel (2-3 % slower).
 template <int EPI, int MU, int D, bool TURNS>
@@ -599,10 +599,11 @@ __global__ void __launch_bounds__(256) splitk_reduce_silu_kernel(const float* __
     H[(int64_t)row * ldh + f] = f2bf(silu_f(g) * u);
 }
 
-// Block tiles of the bf16 launches (see TileForm), fitted to 232 shapes: N, K of the 8B and 32B projections, 1 .. 8192
-// rows, weights from HBM; the pick is on average 0.3 % and at most 9 % off the fastest form.  Measured, 256-row tiles
-// against the pick: down projection (N 4096, K 14336) 1 row 241 -> 76 us, 471 rows 247 -> 91, 1024 rows 245 -> 125; O
-// projection (4096 x 4096) 471 rows 72 -> 24, 2048 rows 78 -> 61; QKV 700 rows 76 -> 40; from about 2000 rows (gate/up:
+// Block tiles of the bf16 launches (see TileForm), fitted without turns to 232 shapes: N, K of the 8B and 32B projections, 1 ..
+// 8192 rows, weights from HBM.  On 254 other launches (ten pairs of N and K, 20 .. 4096 rows), with turns as takes_turns has
+// them, the pick is on average 0.1 % and at most 5 % off the fastest form.  Measured, 256-row tiles against the pick: down
+// projection (N 4096, K 14336) 70 rows 244 -> 78 us, 471 rows 247 -> 80, 1000 rows 245 -> 115; O projection (4096 x 4096) 471 rows
+// 72 -> 27, 845 rows 74 -> 36; from about 2000 rows (gate/up:
 // 200) on the 256 x 256 tile, which moves half the bytes per flop, or the 192 x 256 one where that ends in a fuller
 // round: QKV of the 32B shape (N 7168) at 3072 rows 220 -> 195 us, O projection at 5000 rows 176 -> 148, the 8B shape's
 // QKV at 3500 rows 174 -> 148.
@@ -784,7 +785,8 @@ int pick_form(const TileForms& f, const GemmParams& p, int splits) {
 // second launch (3 us) and the partial sums written and read at 6 TB/s (fitted to 40 bf16 shapes, 1 .. 1000 rows: on
 // average 3.6 % off the fastest of all forms and splits).  Measured at 150 rows of the 8B shape, 256-row tiles with their
 // splits -> now: O 24 -> 17 us, down 49 -> 36, QKV 28 -> 22, gate/up 75 -> 60 (unsplit).  Launches of up to 64 tiles
-// always split where they can: nearly the whole chip is idle without.
+// always split where they can: nearly the whole chip is idle without.  (bf16 launches that go in strips fill it whole, and
+// few-rows mode does not ask here for them.)
 int plan_splits(const TileForms& f, const GemmParams& p, size_t part_bytes, bool must) {
     const int kt = p.K / f.slice;
     auto allowed = [&](int splits) {
