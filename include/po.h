@@ -317,8 +317,8 @@ po_status po_set_lazy_last_layer(po_ctx* ctx, int32_t on);
  * few output tiles, and attention too few query tiles, to occupy the chip.  With the mode on,
  * launches of those GEMMs whose 256 x 256 tiles would fill at most half the compute units split
  * their reduction over K between workgroups where that is expected to take less time (always
- * where their tiles would fill at most a quarter of the units; never bf16 launches of up to 16 rows and 16384
- * columns, which fill the chip in strips of 16 columns), and
+ * where their tiles would fill at most a quarter of the units; bf16 launches of up to 16 rows
+ * mostly run whole instead, in strips of 16 columns), and
  * attention over at most 1024 query rows splits each query tile's keys between workgroups (fp32
  * partial results in the free part of the chunk buffer, merged in a fixed order by a second
  * kernel: deterministic; the footprint
@@ -429,9 +429,10 @@ po_status po_op_attention_split_prefix(const void* dev_q, const void* dev_k, con
 /* The block tile (rows x columns of the output) that a launch of po_op_linear, po_op_gate_up_silu (N = 2 F) or
  * po_op_qkv_rope with contiguous operands takes, or of their FP8 forms with fp8 = 1.  *splits: 1 = a whole launch, more =
  * one of that many K splits, 0 = as many as the split entry points take with enough scratch (written back; few-rows mode takes
- * the same, except that it runs bf16 launches of up to 16 rows and 16384 columns whole).  16 x 16: those launches, whole, in
- * strips of 16 columns by a wavefront each (po_op_gate_up_silu and po_op_qkv_rope: a pair of strips 32 columns apart).  Host
- * only.  The tile changes no result (a split sum is rounded differently). */
+ * the same, except for bf16 launches of up to 16 rows that are faster whole, in strips).  16 x 16: a launch of up to 16 rows in
+ * strips of 16 columns by a wavefront each (reported as for po_op_linear; po_op_gate_up_silu and po_op_qkv_rope, in pairs of
+ * strips, draw the line between 8192 and 16384 columns elsewhere).  Host only.  The tile changes no result (a split sum is
+ * rounded differently). */
 po_status po_gemm_tile(int32_t fp8, int64_t M, int32_t N, int32_t K, int32_t* splits, int32_t* tile_rows,
                        int32_t* tile_cols);
 /* Whether the row tiles of that launch take turns at fetching weights from memory ahead of their use (1) or not (0): as an

@@ -670,16 +670,34 @@ void launch_small(GemmParams p, hipStream_t s, int splits) {
     else launch_small_t<EPI, MU, D, false>(p, s, splits);
 }
 
-// Launches of up to 16 rows that would be 32 x 128 tiles on at most half the compute units: in strips, also where other tiles would be faster than whole ones of 32
-// rows.  (gate/up of the 8B shape, 224 tiles, streams its weights at 4.9 TB/s as it is, 4.5 in strips: 48 and 52 us.)  In
-// few-rows mode too (one row of the 8B shape, us in K splits / in strips: O projection 14 / 8, down 36 / 24).
-bool takes_strips(const GemmParams& p) {
-    return p.M <= 16 && p.N <= 128 * 128 && p.lda < (1 << 20) && p.ldw < (1 << 20);      // (offsets of 16 rows below 2^26 bytes)
+constexpr bool strip_pairs(int epi) { return epi == EPI_SILU_MUL || epi == EPI_QKV_ROPE; }
+
+// Launches of up to 16 rows go in strips instead of 32 x 128 or 64 x 128 tiles, also where other tiles would be faster than those.
+// Measured, weights from HBM, 1 .. 16 rows, us strips / the faster of the two tiles (silu: pairs of strips): up to 8192 columns
+// 3.7 / 4.4 (N 4096, K 256), 8.5 / 22 (4096 x 4096), 15 / 26 (8192 x 4096), 47 / 89 (8192 x 14336), silu 20 / 26 (8192 x 4096).
+// A compute unit holds three strips or pairs of up to two rows at once (their rings' LDS), two of more rows; past one round of
+// them, 8192 columns and pairs of 16384, or 12288 with up to two rows, short K loses up to 0.8 us (12288 x 256 5.6 / 5.1, 16384 x
+// 1024 10.7 / 10.2) and K 4096 wins 2-17 % (10240 24 / 29, 16384 28 / 34).  Pairs at the far end lose in between (16384 columns,
+// K 2048 15.7 / 17.0, 4096 34.4 / 32.1, 14336 92 / 111; 14336 x 4096 27.5 / 30).  Wider launches (gate/up of the 8B shape, 224 tiles) stream their weights at 4.9
+// TB/s as they are, 4.5 in strips.  (Weights from the memory-side cache, K 4096: pairs 9 / 16 at 4096 columns, 18 / 16 at 8192, 34 / 21
+// at 16384; K 1024 wins there as well.)
+bool takes_strips(const GemmParams& p, bool pairs) {
+    if (p.M > 16 || p.N > 16384 || p.lda >= (1 << 20) || p.ldw >= (1 << 20)) return false;       // (offsets of 16 rows below 2^26 bytes)
+    if (pairs) return p.N <= 14336 || p.K <= 2048 || p.K >= 8192;
+    return p.N <= (p.M <= 2 ? 12288 : 8192) || p.K >= 4096;
+}
+
+// In few-rows mode the other choice is K splits.  Up to 16 rows, us strips / splits, weights from HBM: 3072 to 8192 columns always
+// strips (4096 x 4096 8.6 / 12.6, 4096 x 14336 24 / 28, 8192 x 27648 76 / 91); fewer leave compute units without a strip (2048 x
+// 4096 7.8 / 10.3, 2048 x 14336 20.2 / 20.1, 512 x 14336 18 / 16, 2048 x 27648 33 / 28), and more are a second round that ends with most
+// of them idle (10240 x 4096 24 / 24, 12288 x 14336 82 / 64, 16384 x 14336 97 / 81).
+bool takes_strips_in_few_rows_mode(const GemmParams& p, bool pairs) {
+    return takes_strips(p, pairs) && (p.N <= 2048 ? p.K <= 8192 : p.N <= 8192 || p.K <= 4096);
 }
 
 template <int EPI, int NA>
 void launch_strips(const GemmParams& p, hipStream_t s) {
-    constexpr int NS = (EPI == EPI_SILU_MUL || EPI == EPI_QKV_ROPE) ? 2 : 1, D = NS == 2 ? 3 : NA == 1 ? 5 : 4;
+    constexpr int NS = strip_pairs(EPI) ? 2 : 1, D = NS == 2 ? 3 : NA == 1 ? 5 : 4;
     constexpr int SMEM = D * (16 * NS + 2 * NA) * 512;
     static_assert(SMEM <= 80 * 1024, "two workgroups on a compute unit at least");
     static OncePerDevice lds;
@@ -710,10 +728,10 @@ void launch_form(int form, const GemmParams& p, hipStream_t s, int splits = 1) {
     }
 }
 
-int whole_form(const GemmParams& p) { return takes_strips(p) ? STRIPS : pick_form(TILES, p, 1); }
+int whole_form(const GemmParams& p, bool pairs) { return takes_strips(p, pairs) ? STRIPS : pick_form(TILES, p, 1); }
 
 template <int EPI>
-void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(whole_form(p), p, s); }
+void launch_t(const GemmParams& p, hipStream_t s) { launch_form<EPI>(whole_form(p, strip_pairs(EPI)), p, s); }
 
 GemmParams base_params(const bf16_t* A, int64_t lda, const bf16_t* W, int64_t ldw, int64_t M, int N, int K) {
     GemmParams p;
@@ -735,7 +753,7 @@ int gemm_mfma_tile(int64_t M, int N, int K, int splits, int* rows, int* cols, bo
     GemmParams p = base_params(nullptr, K, nullptr, K, M, N, K);
     if (splits == 0) splits = plan_splits(TILES, p, SIZE_MAX, false);
     p.K = K / splits;
-    const int form = splits == 1 ? whole_form(p) : pick_form(TILES, p, splits);
+    const int form = splits == 1 ? whole_form(p, false) : pick_form(TILES, p, splits);
     const bool strips = form == STRIPS;
     *rows = strips ? 16 : FORMS[form].bm;
     *cols = strips ? 16 : FORMS[form].bn;
@@ -785,8 +803,8 @@ int pick_form(const TileForms& f, const GemmParams& p, int splits) {
 // second launch (3 us) and the partial sums written and read at 6 TB/s (fitted to 40 bf16 shapes, 1 .. 1000 rows: on
 // average 3.6 % off the fastest of all forms and splits).  Measured at 150 rows of the 8B shape, 256-row tiles with their
 // splits -> now: O 24 -> 17 us, down 49 -> 36, QKV 28 -> 22, gate/up 75 -> 60 (unsplit).  Launches of up to 64 tiles
-// always split where they can: nearly the whole chip is idle without.  (bf16 launches that go in strips fill it whole, and
-// few-rows mode does not ask here for them.)
+// always split where they can: nearly the whole chip is idle without.  (For bf16 launches that take strips few-rows mode does not
+// ask here.)
 int plan_splits(const TileForms& f, const GemmParams& p, size_t part_bytes, bool must) {
     const int kt = p.K / f.slice;
     auto allowed = [&](int splits) {
@@ -835,7 +853,7 @@ int launch_gemm_qkv_rope_splitk(const bf16_t* A, int64_t lda, const bf16_t* Wqkv
     if (M <= 0 || !gemm_mfma_supported(N, K) || (qd & 63) || (kvd & 63) || (hd & 63)) return 0;
     GemmParams p = base_params(A, lda, Wqkv, ldw, M, N, K);
     p.w_cached = w_cached;
-    if (takes_strips(p)) return 0;
+    if (takes_strips_in_few_rows_mode(p, true)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -856,7 +874,7 @@ int launch_gemm_mfma_splitk_silu(const bf16_t* A, int64_t lda, const bf16_t* W, 
     if (M <= 0 || !gemm_mfma_supported(N, K)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
     p.w_cached = w_cached;
-    if (takes_strips(p)) return 0;
+    if (takes_strips_in_few_rows_mode(p, true)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, false);
     if (splits < 2) return 0;
     p.K = K / splits;
@@ -874,7 +892,7 @@ int launch_gemm_mfma_splitk_residual(const bf16_t* A, int64_t lda, const bf16_t*
     if (M <= 0 || N <= 0 || !gemm_mfma_supported(N, K) || (N & 7) || (ldc & 7) || (ldr & 7)) return 0;
     GemmParams p = base_params(A, lda, W, ldw, M, N, K);
     p.w_cached = w_cached;
-    if (!must && takes_strips(p)) return 0;
+    if (!must && takes_strips_in_few_rows_mode(p, false)) return 0;
     const int splits = plan_splits(TILES, p, part_bytes, must);
     if (splits < 2) return 0;
     p.K = K / splits;

@@ -14,8 +14,9 @@ def _rnd(seed):
     return lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
 
 
-# K: less than a block of 256, whole blocks, a block and a remainder of 1 .. 3 slices; more blocks than the ring holds
-@pytest.mark.parametrize("N,K", [(64, 64), (320, 256), (4096, 448), (128, 832), (16384, 1344), (16448, 128), (4096, 2752)])
+# K: less than a block of 256, whole blocks, a block and a remainder of 1 .. 3 slices; more blocks than the ring holds; more strips
+# than the compute units hold at once
+@pytest.mark.parametrize("N,K", [(64, 64), (320, 256), (4096, 448), (128, 832), (16384, 1344), (16448, 128), (4096, 2752), (14336, 4160)])
 def test_few_rows_are_the_bits_of_a_larger_launch(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
@@ -46,6 +47,24 @@ def test_few_qkv_rows_are_the_bits_of_a_larger_launch(cfg, K, bias):
     for m in (1, 2, 3, 16):
         q1, k1, vt1 = B.po_op_qkv_rope(a[:m].contiguous(), w, b, cos, sin, hq, hkv, hd, q_scale=scale)
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
+
+
+@pytest.mark.parametrize("ffn,splits", [(4096, False), (8192, False), (16384, True)])
+def test_few_rows_mode_splits_where_strips_leave_compute_units_idle(ffn, splits):
+    import numpy as np
+    from paper_2505_07203_amd import binding as B
+    cfg = I.LLAMA8B.replace(dtype=I.BF16, d_model=512, n_q_heads=4, n_kv_heads=2, ffn_dim=ffn, n_layers=2, vocab_size=512)
+    ctx = B.Context(cfg, 64, 64, device="cuda:0")
+    try:
+        ctx.load_synthetic(3, threads=2)
+        tokens, cand = I.make_tokens(cfg, 5, 12), I.label_ids(cfg)
+        whole = ctx.po_prefill(tokens, cand)[0]
+        ctx.po_set_few_rows_split(True)
+        z = ctx.po_prefill(tokens, cand)[0]
+        assert (ctx.po_get_stats()["split_launches"] > 0) == splits
+        assert np.array_equal(z, whole) or splits and np.max(np.abs(z - whole)) <= 1e-2 * np.max(np.abs(whole))
+    finally:
+        ctx.po_destroy()
 
 
 # Launches whose row tiles take turns: odd numbers of slices, of which the short ones (11 and 17 of 64, 9 of 128) end within

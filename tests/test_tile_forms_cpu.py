@@ -45,8 +45,11 @@ def test_no_launch_of_the_models_takes_another_tile(cfg):
 
 
 def test_strips():
-    tile = lambda m, N: B.po_gemm_tile(m, N, 4096)[:2]
-    assert {tile(m, N) for m in (1, 2, 3, 16) for N in (64, 4096, 16384)} == {STRIPS}
+    tile = lambda m, N, K=4096: B.po_gemm_tile(m, N, K)[:2]
+    assert {tile(m, N, K) for m in (1, 2, 3, 16) for N in (64, 4096, 8192) for K in (64, 4096)} == {STRIPS}
+    # more than a round of them: only with long K
+    assert {tile(16, 16384), tile(16, 8256), tile(1, 12288, 1024)} == {STRIPS}
+    assert STRIPS not in {tile(3, 8256, 4032), tile(1, 12352, 1024)}
     assert STRIPS not in {tile(17, 4096), tile(16, 16448), B.po_gemm_tile(1, 4096, 4096, 2)[:2], B.po_gemm_tile(1, 4096, 4096, 1, True)[:2]}
 
 
