@@ -514,8 +514,9 @@ static void launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<T, D, PAIR>), grid, dim3(256), SMEM, s, A, lda, W, ldw, C, ldc, bias, R, ldr, M, N, K, qkv);
 }
 
-// Tile of a launch: 0, 1, 2 = 128, 64, 32 rows and columns; largest: the first of them that is allowed; ld: of either operand
-static int f32_tile(int64_t M, int N, int64_t ld, int largest) {
+// Tile of a launch: 0, 1, 2 = 128, 64, 32 rows and columns; largest: the first of them that is allowed; ld: of either operand;
+// slice_us: where its time per K slice goes
+static int f32_tile(int64_t M, int N, int64_t ld, int largest, double* slice_us = nullptr) {
     // Tile by time: a round of 256 tiles, one per compute unit, costs this many microseconds per K slice of 32 (measured
     // on 256 .. 2048 tiles of each); where all three take one round the small tile has the shorter chain.
     constexpr double us[3] = {1.9, 0.54, 0.2};
@@ -527,6 +528,7 @@ static int f32_tile(int64_t M, int N, int64_t ld, int largest) {
         const double t = us[i] * (double)((tiles + 255) / 256);
         if (t < best_us) { best = i; best_us = t; }
     }
+    if (slice_us) *slice_us = best_us;
     return best;
 }
 
@@ -571,7 +573,21 @@ bool launch_gemm_f32_qkv_rope(const float* A, int64_t lda, const float* W, int64
     if ((qkv.hd != 64 && qkv.hd != 128) || qkv.qd % qkv.hd || qkv.kvd % qkv.hd || ((int64_t)N + 128) * ldw * 4 > ((int64_t)1 << 31) ||
         ((uintptr_t)qkv.q | (uintptr_t)qkv.k | (uintptr_t)qkv.v) % 16)
         return false;
-    return launch_f32<PAIR_ROPE>(A, lda, W, ldw, nullptr, 0, bias, nullptr, 0, M, N, K, qkv, f32_rope_largest(qkv.hd), s);
+    // One launch, or where its tiles end in a round that is mostly empty, Q by itself: a second launch takes 4 us and more (M 256,
+    // N 4096 + 2048, K 4096: two rounds of 64-row tiles, 384 in all, against one of them and two of 32-row tiles, 2048 rows of a
+    // 4096-wide layer, hidden width 4096, in chunks of 256 1629 -> 1493 us)
+    const int largest = f32_rope_largest(qkv.hd);
+    double whole, q, kv;
+    f32_tile(M, N, std::max(lda, ldw), largest, &whole);
+    f32_tile(M, qkv.qd, std::max(lda, ldw), largest, &q);
+    f32_tile(M, 2 * qkv.kvd, std::max(lda, ldw), largest, &kv);
+    if ((whole - q - kv) * ((K + 31) / 32) <= 5.0)
+        return launch_f32<PAIR_ROPE>(A, lda, W, ldw, nullptr, 0, bias, nullptr, 0, M, N, K, qkv, largest, s);
+    F32QkvRope rest = qkv;
+    rest.qd = 0;
+    return launch_f32<PAIR_ROPE>(A, lda, W, ldw, nullptr, 0, bias, nullptr, 0, M, qkv.qd, K, qkv, largest, s) &&
+           launch_f32<PAIR_ROPE>(A, lda, W + (int64_t)qkv.qd * ldw, ldw, nullptr, 0, bias ? bias + qkv.qd : nullptr, nullptr, 0, M,
+                                 2 * qkv.kvd, K, rest, largest, s);
 }
 
 }  // namespace po

@@ -71,3 +71,19 @@ def test_qkv_in_large_tiles_is_the_bits_of_small_ones(hd, hq, hkv, d, n):
         finally:
             ctx.po_destroy()
     assert all(np.isfinite(a).all() and np.array_equal(a, b) for a, b in zip(z[QKV_CHUNK], z[2 * n]))
+
+
+def test_qkv_in_two_launches_is_the_bits_of_one():
+    """256 rows of 3072 columns fill one round of 32-row tiles and half of a second, with K long enough to make Q a launch by itself"""
+    from paper_2505_07203_amd import binding as B
+    cfg = _config(128, 32, 8, 2048)
+    tokens = I.make_tokens(cfg, 7, 256)
+    z = []
+    for chunk in (QKV_CHUNK, 256):
+        ctx = B.Context(cfg, 256, chunk, device="cuda:0")
+        try:
+            ctx.load_synthetic(1001, threads=4)
+            z.append(ctx.po_prefill(tokens, I.label_ids(cfg))[0])
+        finally:
+            ctx.po_destroy()
+    assert np.isfinite(z[0]).all() and np.array_equal(z[0], z[1])
