@@ -28,9 +28,10 @@ KERNEL_SOURCES = ("gemm_mfma.hip", "gemm_common.h", "attn_mfma.hip", "kernels_ba
 # kernel class -> substring of the kernel's demangled name, or several
 CLASSES = collections.OrderedDict([
     ("attention", "attn_fwd64_kernel"),
-    ("gate_up", ("gemm_bf16_mfma_kernel<2, ", "gemm_bf16_small_kernel<2, ")),          # every tile form
-    ("residual", ("gemm_bf16_mfma_kernel<1, ", "gemm_bf16_small_kernel<1, ")),
-    ("qkv", ("gemm_bf16_mfma_kernel<3, ", "gemm_bf16_small_kernel<3, ")),
+    # every tile form, and strips
+    ("gate_up", ("gemm_bf16_mfma_kernel<2, ", "gemm_bf16_small_kernel<2, ", "gemm_bf16_strip_kernel<2, ")),
+    ("residual", ("gemm_bf16_mfma_kernel<1, ", "gemm_bf16_small_kernel<1, ", "gemm_bf16_strip_kernel<1, ")),
+    ("qkv", ("gemm_bf16_mfma_kernel<3, ", "gemm_bf16_small_kernel<3, ", "gemm_bf16_strip_kernel<3, ")),
     ("attention_redo", "attn_fwd_kernel<128, 1, 8, false>"),
     ("rmsnorm", "rmsnorm_bf16_vec_kernel"),
     ("lm_head", "lm_head_kernel"),
