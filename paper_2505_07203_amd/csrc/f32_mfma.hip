@@ -292,7 +292,7 @@ bool launch_attention_f32_mfma(const float* q, const float* k, const float* v, f
 // columns of one kind and half of the other, `apart` weight rows away, arranged so that a lane finds a pair in tiles t and
 // t + T / 2 of its wavefront (T 1: in the other wavefront of its rows, through LDS), and the SiLU-multiply or the rotation
 // is done on the accumulators.  Neither the [M, 2F] product nor unrotated queries and keys go through memory, and a layer is
-// five launches shorter: the small configuration's whole call 203 -> 181 us, 1000 rows of the 8B MLP 2657 -> 2611.
+// five launches shorter: the small configuration's whole call 203-215 -> 180 us, 1000 rows of the 8B MLP 2657 -> 2611.
 // Measured (kernel before: 128 x 128 tiles of 32x32x2, slices staged through registers, two barriers each): 1000 rows of
 // the 8B shape, down projection 1060 -> 866 us (136 TFLOP/s), gate/up 1990 -> 1726; 256 x 256 outputs of K 256 26 -> 9 us;
 // one row of K 14336 1034 -> 84 us.

@@ -47,6 +47,13 @@ def test_causal_launches_of_one_round_and_suffixes():
     assert B.po_attention_tile(100, 32, 8, 128, 0, False) == B.po_attention_tile(100, 32, 8, 64) == 256
 
 
+def test_launches_of_the_gpu_tests_start_inside_tiles_of_both_heights():
+    """suffixes behind a cached prefix and the last layer's single row, as in test_gpu_out_of_range.py"""
+    at = {(B.po_attention_tile(n, 32, 8, 128, q0), q0 % 128 != 0) for n in (2000, 2300, 4500)
+          for q0 in (0, 1000, n - 1100, n - 300, n - 70, n - 1)}
+    assert at >= {(128, True), (256, True), (256, False)}
+
+
 def test_arguments():
     L, r = B.lib(), B.C.c_int32(0)
     ask = lambda *a: L.po_attention_tile(*a, B.C.byref(r))
