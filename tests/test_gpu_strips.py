@@ -75,11 +75,14 @@ TURNS_BF16 = [(4096, 704), (4096, 1088), (2112, 4160)]
 TURNS_QKV = [(I.LLAMA8B, 704), (I.LLAMA8B, 4160)]
 TURNS_FP8 = [(4096, 1152), (4096, 5248), (2112, 5248)]
 TURNS_FP8_QKV = (I.LLAMA8B, 5248)
+# ... and launches that end before the first touch, or of an even number of slices; whole numbers of tiles
+TURNS_BF16_SHORT, TURNS_FP8_SHORT = [(4096, 128), (4096, 192), (2112, 4096)], [(4096, 128), (4096, 384), (2112, 4096)]
+TURNS_WHOLE_ROWS = (64, 129, 160, 200, 400, 600, 768, 1024, 1280)
 TURNS_SPLIT = [(81, 320, 4224), (162, 320, 1408), (465, 2112, 4224), (381, 2112, 2816), (450, 2112, 14336), (771, 1024, 14336)]
 TURNS_FP8_SPLIT = [(273, 320, 10496), (705, 1024, 14336)]
 
 
-@pytest.mark.parametrize("N,K", TURNS_BF16)
+@pytest.mark.parametrize("N,K", TURNS_BF16 + TURNS_BF16_SHORT)
 def test_turns_are_the_bits_of_a_launch_without(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
@@ -88,7 +91,7 @@ def test_turns_are_the_bits_of_a_launch_without(N, K):
     whole = B.po_op_linear(a, w, residual=r), B.po_op_gate_up_silu(a, w)
     ref, size = a.double() @ w.double().t() + r.double(), a.double().abs() @ w.double().abs().t()
     assert bool(((whole[0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + K * 2.0 ** -22 * size).all())
-    for m in TURNS_ROWS:
+    for m in TURNS_ROWS + TURNS_WHOLE_ROWS:
         x = a[:m].contiguous()
         assert torch.equal(B.po_op_linear(x, w, residual=r[:m].contiguous()), whole[0][:m]), m
         assert torch.equal(B.po_op_gate_up_silu(x, w), whole[1][:m]), m
@@ -108,7 +111,7 @@ def test_qkv_turns_are_the_bits_of_a_launch_without(cfg, K):
         assert torch.equal(q1, q[:m]) and torch.equal(k1, k[:m]) and torch.equal(vt1[:, :m], vt[:, :m]), m
 
 
-@pytest.mark.parametrize("N,K", TURNS_FP8)
+@pytest.mark.parametrize("N,K", TURNS_FP8 + TURNS_FP8_SHORT)
 def test_fp8_turns_are_the_bits_of_a_launch_without(N, K):
     import torch
     from paper_2505_07203_amd import binding as B
@@ -116,7 +119,7 @@ def test_fp8_turns_are_the_bits_of_a_launch_without(N, K):
     r = rnd(TURNS_TOP, N)
     (qa, sa), (qw, sw) = B.po_op_quantize_rows(rnd(TURNS_TOP, K)), B.po_op_quantize_rows(rnd(N, K) * 0.05)
     whole = B.po_op_linear_fp8(qa, sa, qw, sw, residual=r), B.po_op_linear_fp8(qa, sa, qw, sw, silu_mul=True)
-    for m in TURNS_ROWS:
+    for m in TURNS_ROWS + TURNS_WHOLE_ROWS:
         x, s = qa[:m].contiguous(), sa[:m].contiguous()
         assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, residual=r[:m].contiguous()), whole[0][:m]), m
         assert torch.equal(B.po_op_linear_fp8(x, s, qw, sw, silu_mul=True), whole[1][:m]), m
