@@ -207,9 +207,9 @@ __global__ void __launch_bounds__(NT_BF16) gemm_bf16_mfma_kernel(const GemmParam
 // of slice s into what A(s - 1) left, W(s + D) behind the hand-over barrier into W(s)'s place.  A slice is two phases,
 // one per k-step of 32, with the next k-step's fragments read behind this one's MFMAs; swizzle, tile order and epilogues
 // are those of the kernel above, and so are the bits (one fp32 accumulator per output, K in steps of 32, in order).
-// Weights on their way from HBM.  A compute unit's loads return in order and about 32 KiB of them are in flight, whatever
-// the depth of the ring, so a slice whose weight rows come from HBM paces everything behind it: a tile streams at 36-60
-// GB/s per compute unit from HBM, at 95 from the memory-side cache and at 130 from L2.  The row tiles of a group sit on one
+// Weights on their way from HBM.  A wavefront's loads return in order, so a slice whose weight rows come from HBM paces
+// everything behind it: one round of 32-row tiles (N 128 or 4096, K 4096 .. 14336, 32 or 64 rows) streams its weights at 39-47
+// GB/s per compute unit from HBM and at 62-76 from the memory-side cache.  The row tiles of a group sit on one
 // XCD and multiply with the same weights; without help all of them wait for the same lines.  So they take turns: every 2 R
 // slices one of R row tiles touches the weights of two slices a few slices ahead of the ring (one dword per line and lane,
 // into LDS that nobody reads), waits for HBM that once, and all others find them in L2.  (Every tile touching its share of
@@ -378,8 +378,8 @@ __global__ void __launch_bounds__(256, 2) gemm_bf16_small_kernel(const GemmParam
 
 // The 32 x 128 tile of a launch of at most 16 rows (the last layer's single row above all), worked on in strips of 16
 // columns (16 gate and the 16 up columns behind them, a rotary pair of 16: two strips of W rows) by a wavefront of its own.
-// What bounds it: the weights' way from HBM, and a compute unit streams 128 rows of them at 36-50 GB/s (see above): with 4096
-// columns in 32 tiles that is 1.6 TB/s.  Strips put a wavefront on every compute unit (256 for 4096 columns, 896 pairs for
+// What bounds it: the weights' way from HBM, and a compute unit streams 128 rows of them at 39-47 GB/s (see above): with 4096
+// columns in 32 tiles that is 1.5 TB/s.  Strips put a wavefront on every compute unit (256 for 4096 columns, 896 pairs for
 // 28672), and 5.3-6 TB/s is what they stream.  One wavefront needs no barrier; K goes by in blocks of 256, so that a visit to
 // a row is 512 bytes, straight into a ring of D blocks in LDS.  (16-byte segments XOR-swizzled with the row on the global
 // side: the 16 rows of a fragment read lie 512 bytes apart.)  One accumulator per output, K in steps of 32, in order: the bits
